@@ -106,26 +106,40 @@ def _activations(n: int, d: int, g, rng) -> torch.Tensor:
     return x
 
 
-def _plan(d: int, family: str, rng) -> harp.Plan:
+def _processor(d: int, family: str, rng) -> tuple:
+    """(d, radices, blocks, signs) of one processor."""
     radices = schedule(d, family)
-    return harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    return d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
+
+
+def _inputs(case: dict, seed: int) -> dict:
+    """Processors as numpy arrays, the matrices on the device; the same for every caller."""
+    rng, g, dt = np.random.default_rng(seed), _generator(seed), _dtype(case)
+    if case["op"] in ("rotate", "unrotate"):
+        out = {"U": _processor(case["d_out"], case["family"], rng),
+               "V": _processor(case["d_in"], case["family"], rng)}
+        w = torch.randn(case["d_out"], case["d_in"], device="cuda", generator=g)
+        out["W"] = w.mul_(0.02).to(dt)
+        return out
+    n, d = case["n"], case["d"]
+    out = {"processor": _processor(d, case["family"], rng)}
+    out["X"] = _activations(n, d, g, rng).to(dt)
+    if case["op"] == "grad":
+        out["G"] = (torch.randn(n, d, device="cuda", generator=g) * 0.05).to(dt)
+    return out
 
 
 def prepare(case: dict, seed: int) -> dict:
-    rng, g, dt = np.random.default_rng(seed), _generator(seed), _dtype(case)
+    inp = _inputs(case, seed)
     state = {"op": case["op"]}
     if case["op"] in ("rotate", "unrotate"):
-        state["plan_U"] = _plan(case["d_out"], case["family"], rng)
-        state["plan_V"] = _plan(case["d_in"], case["family"], rng)
-        w = torch.randn(case["d_out"], case["d_in"], device="cuda", generator=g)
-        state["W"] = w.mul_(0.02).to(dt)
+        state["plan_U"], state["plan_V"] = harp.Plan(*inp["U"]), harp.Plan(*inp["V"])
+        state["W"] = inp["W"]
         return state
-    n, d = case["n"], case["d"]
-    state["plan"] = _plan(d, case["family"], rng)
-    state["X"] = _activations(n, d, g, rng).to(dt)
+    state["plan"], state["X"] = harp.Plan(*inp["processor"]), inp["X"]
     if case["op"] == "grad":
-        state["G"] = (torch.randn(n, d, device="cuda", generator=g) * 0.05).to(dt)
-    elif n <= 64:
+        state["G"] = inp["G"]
+    elif case["n"] <= 64:
         state["Y"] = torch.empty_like(state["X"])      # a serving loop keeps its output buffer
     return state
 
@@ -171,3 +185,57 @@ def tolerance(case: dict) -> dict:
     if case["dtype"] == "bf16":
         return {"rel": 7e-3, "max": 2e-2}
     return {"rel": 1e-6, "max": 2e-5}
+
+
+def _stage(x: torch.Tensor, K: torch.Tensor, b: int, s: int, transpose: bool) -> torch.Tensor:
+    """One stride stage on the rows of x: y[r'] = sum_r x[r] K[c][r][r'] over every digit group."""
+    n, d = x.shape
+    v, k = x.view(n, d // (b * s), b, s), K.view(d // (b * s), s, b, b)
+    if transpose:
+        k = k.transpose(2, 3)
+    y = torch.zeros_like(v)
+    for r in range(b):
+        for q in range(b):
+            y[:, :, q, :].addcmul_(v[:, :, r, :], k[:, :, r, q])
+    return y.view(n, d)
+
+
+def _on_device(processor) -> tuple:
+    """(blocks, radices, strides, signs) in float64 on the device."""
+    d, radices, blocks, signs = processor
+    K = [torch.from_numpy(np.asarray(k, dtype=np.float64)).cuda() for k in blocks]
+    strides = [math.prod(radices[:t]) for t in range(len(radices))]
+    return K, radices, strides, torch.from_numpy(signs.astype(np.float64)).cuda()
+
+
+def _rows_times_U(x: torch.Tensor, processor, transpose: bool) -> torch.Tensor:
+    K, rad, st, sg = _on_device(processor)
+    order = range(len(rad) - 1, -1, -1) if transpose else range(len(rad))
+    x = x if transpose else x * sg
+    for t in order:
+        x = _stage(x, K[t], rad[t], st[t], transpose)
+    return x * sg if transpose else x
+
+
+def exact(case: dict, seed: int):
+    """The outputs of ``run`` in float64 from the definition, stage by stage."""
+    inp, op = _inputs(case, seed), case["op"]
+    if op in ("rotate", "unrotate"):
+        back = op == "unrotate"
+        w = _rows_times_U(inp["W"].double(), inp["V"], back)
+        return _rows_times_U(w.t().contiguous(), inp["U"], back).t().contiguous()
+    if op != "grad":
+        return _rows_times_U(inp["X"].double(), inp["processor"], op == "apply_transpose")
+    K, rad, st, sg = _on_device(inp["processor"])
+    xs = [inp["X"].double() * sg]
+    for t in range(len(rad)):
+        xs.append(_stage(xs[t], K[t], rad[t], st[t], False))
+    g, dK = inp["G"].double(), [None] * len(rad)
+    n, d = g.shape
+    for t in range(len(rad) - 1, -1, -1):
+        b, s = rad[t], st[t]
+        x4, g4 = xs[t].view(n, d // (b * s), b, s), g.view(n, d // (b * s), b, s)
+        dK[t] = torch.stack([torch.stack([(x4[:, :, r, :] * g4[:, :, q, :]).sum(0).reshape(-1)
+                                          for q in range(b)], -1) for r in range(b)], -2)
+        g = _stage(g, K[t], b, s, True)
+    return dK + [g * sg]
