@@ -695,14 +695,16 @@ int grad_chunks(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, 256));
 }
 
-// Segments of the backward pass: runs of up to three radix-2 stages, single stages otherwise.
+// Segments of the backward pass: the first `lead` stages as one segment of 64 coordinates
+// (harp_grad_seg.hip), then runs of up to three radix-2 stages, single stages otherwise.
 struct GradSegment {
   int t0, k;
 };
-static std::vector<GradSegment> grad_segments(const harp_plan *plan) {
+static std::vector<GradSegment> grad_segments(const harp_plan *plan, int lead) {
   std::vector<GradSegment> seg;
   const int m = plan->m;
-  int t = 0;
+  if (lead > 0) seg.push_back(GradSegment{0, lead});
+  int t = lead;
   while (t < m) {
     int k = 1;
     if (plan->radices[t] == 2)
@@ -729,18 +731,28 @@ size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
   int bbig = 0;
   for (int32_t b : plan->radices) (b > 8 ? bbig : bsmall) = std::max(b > 8 ? bbig : bsmall, (int)b);
   const size_t mat = (size_t)n * (size_t)plan->d * 4;
-  const size_t nseg = grad_segments(plan).size();
   const size_t partial = std::max((size_t)grad_chunks(n) * bsmall, (size_t)grad_big_chunks(n) * bbig) *
                          (size_t)plan->d * 4;
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
-  return (nseg + 1 + (bbig > 0 ? 1 : 0)) * mat + partial;
+  const size_t extra = 1 + (bbig > 0 ? 1 : 0);
+  size_t need = (grad_segments(plan, 0).size() + extra) * mat + partial;
+  // (the call's alignment decides whether the leading segment is taken: room for either way)
+  const int lead = grad_seg_stages(plan, n);
+  if (lead > 0)
+    need = std::max(need, (grad_segments(plan, lead).size() + extra) * mat +
+                              std::max(partial, grad_seg_partial_bytes(plan, n)));
+  return need;
 }
 
 harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, const void *G,
                           int64_t ldg, int64_t n, harp_dtype_t dt, float *const *dK, void *dX,
                           int64_t lddx, void *ws, hipStream_t st) {
   const std::vector<ColStage> &stages = plan->col[DIR_FWD];
-  const std::vector<GradSegment> seg = grad_segments(plan);
+  // the leading segment reads and writes the caller's rows in 16-byte pieces of 8 elements
+  int lead = grad_seg_stages(plan, n);
+  if (ldx % 8 || (uintptr_t)X % 16 || (uintptr_t)ws % 16) lead = 0;
+  if (dX && (lddx % 8 || (uintptr_t)dX % 16)) lead = 0;
+  const std::vector<GradSegment> seg = grad_segments(plan, lead);
   const int nseg = (int)seg.size();
   const int64_t d = plan->d;
   const int nchunks = grad_chunks(n);
@@ -780,7 +792,10 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
       const ColStage &cs = stages[seg[i].t0];
       const float *in = act + (size_t)i * mat;
       float *out = act + (size_t)(i + 1) * mat;
-      if (seg[i].k > 1) {
+      if (i == 0 && lead > 0) {
+        const harp_status_t rc = launch_grad_seg_fwd(plan, lead, X, ldx, bf, out, n, st);
+        if (rc != HARP_OK) return rc;
+      } else if (seg[i].k > 1) {
         const int nitems = (int)(d >> seg[i].k);
         const dim3 grid((nitems + kGradThreads - 1) / kGradThreads, nchunks);
 #define HARP_GRAD_FWD_RUN(KK)                                                                       \
@@ -824,6 +839,11 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   for (int i = nseg - 1; i >= 0; --i) {
     const ColStage &cs = stages[seg[i].t0];
     const float *in = act + (size_t)i * mat;
+    if (i == 0 && lead > 0) {
+      const harp_status_t rc = launch_grad_seg_bwd(plan, lead, X, ldx, bf, g, dX, lddx, n, partial, dK, st);
+      if (rc != HARP_OK) return rc;
+      break;
+    }
     if (n > 0) {
       if (seg[i].k > 1) {
         const int nitems = (int)(d >> seg[i].k);

@@ -342,6 +342,14 @@ size_t grad_workspace_bytes(const harp_plan *plan, int64_t n);
 harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, const void *G,
                           int64_t ldg, int64_t n, harp_dtype_t dt, float *const *dK, void *dX,
                           int64_t lddx, void *ws, hipStream_t st);
+// leading segment of 64 coordinates of the gradient path (harp_grad_seg.hip)
+int grad_seg_stages(const harp_plan *plan, int64_t n);
+size_t grad_seg_partial_bytes(const harp_plan *plan, int64_t n);
+harp_status_t launch_grad_seg_fwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, float *Y,
+                                  int64_t n, hipStream_t st);
+harp_status_t launch_grad_seg_bwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf,
+                                  const float *G, void *dX, int64_t lddx, int64_t n, float *partial,
+                                  float *const *dK, hipStream_t st);
 int choose_pipe_rows(const harp_plan *plan, int64_t n, int64_t nchunk, int chunk);
 const HostProgram *select_program(const harp_plan *plan, Direction dir, int64_t n,
                                   const char **name);

@@ -135,3 +135,39 @@ def test_grad_blocks_llama7b_shape_sampled(harp):
     rows = np.arange(0, n, 97)
     assert_parity(to_host64(dX)[rows], rX[rows], "bf16", "dX rows")
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,radices,n", [
+    # one stage behind the leading segment of 64 coordinates, at the fewest rows it takes
+    (128, [2] * 7, 64), (512, [8, 8, 8], 64),
+    # ragged runs of rows: a wave with one row, a wave with none, more than one workgroup per group
+    (320, [2] * 6 + [5], 65), (704, [8, 8, 11], 71), (2048, [8, 8, 8, 4], 297), (4096, [2] * 12, 1033)])
+def test_leading_segment_and_stage_by_stage_agree_with_the_oracle(harp, d, radices, n, dtype):
+    """Rows on 16-byte boundaries take the first 64 coordinates' stages as one segment, rows that are
+    not (here: shifted by one element) stage by stage; both against the oracle.  The tolerance is
+    the one derived above (the segment sums runs of at most 64 rows before they meet)."""
+    import torch
+    rng = np.random.default_rng(7 * d + n)
+    blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    X[:, :: 97] *= 20.0
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    if dtype == "bf16":
+        X, G = gi.round_to_bf16(X), gi.round_to_bf16(G)
+    plan = harp.Plan(d, radices, blocks, signs)
+    say("grad leading segment", d, radices, n, dtype)
+    rK, rX = ho.grad_blocks(X, G, d, radices, blocks, signs)
+    Xd, Gd = to_device(X, dtype), to_device(G, dtype)
+    wide = torch.zeros(n, d + 8, device="cuda", dtype=Xd.dtype)
+    wide[:, 1:1 + d] = Xd
+    for Xin in (Xd, wide[:, 1:1 + d]):
+        dK, dX = harp.harp_grad_blocks(plan, Xin, Gd)
+        dK2, none = harp.harp_grad_blocks(plan, Xin, Gd, want_dX=False)
+        torch.cuda.synchronize()
+        assert none is None
+        assert_dk_parity(dK, rK, X, G, "dK")
+        assert_parity(to_host64(dX), rX, dtype, "dX")
+        for a, b in zip(dK, dK2):
+            assert torch.equal(a, b)
+    plan.destroy()
