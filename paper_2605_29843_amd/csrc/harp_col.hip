@@ -716,6 +716,122 @@ __global__ __launch_bounds__(kColThreads, 2) void harp_colrow_kernel(
   work(t0 + tpw - 1);
 }
 
+// ------------------------------------------------------------------------------------------
+// A column pass of ONE stage (what a schedule leaves over beside the passes of two radix-8 stages:
+// 28672 = 8 8 | 8 | 8 7), alone (BV == 1) or together with plan_V's streamed radix-2 stage on the
+// top digit (BV == 2, columns lo and lo + Sv, 2 x 2 block lo).  Bound by bytes: each element is used
+// once, so nothing goes through LDS.  A thread owns the B rows of block c at four consecutive
+// columns (16-byte float32 accesses; twice four with BV == 2), all its loads are independent and
+// no barrier separates workgroups' loads from their stores; block c is uniform over the workgroup
+// and arrives by scalar loads.  The LDS-tile kernel spends as long on the block table, the
+// barriers and the trips through LDS of a tile of 8 rows x 128 columns as of one of 64 rows.
+// 28672 x 8192 bf16, radix-8 schedules: that pass took 700 us and the radix-2 stage on its own
+// trips 324 us; with both in this kernel the whole rotation went from 2316 to 1594 us.
+// The sums run over r in ascending order, as in the kernels whose place it takes.
+// Every thread has read its elements before it writes them and owns them alone: in place is fine.
+template <typename T> struct Col4;
+template <> struct Col4<float> {
+  float4 v;
+  __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
+  __device__ __forceinline__ void widen(float (&x)[4]) const { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
+};
+template <> struct Col4<uint16_t> {
+  uint2 v;
+  __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
+  __device__ __forceinline__ void widen(float (&x)[4]) const {
+    x[0] = bf16_to_f32(v.x & 0xffffu); x[1] = __uint_as_float(v.x & 0xffff0000u);
+    x[2] = bf16_to_f32(v.y & 0xffffu); x[3] = __uint_as_float(v.y & 0xffff0000u);
+  }
+};
+__device__ __forceinline__ void col4_store(float *p, const float (&x)[4]) {
+  *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
+}
+__device__ __forceinline__ void col4_store(uint16_t *p, const float (&x)[4]) {
+  *reinterpret_cast<uint2 *>(p) = make_uint2(f32_to_bf16(x[0]) | (f32_to_bf16(x[1]) << 16),
+                                             f32_to_bf16(x[2]) | (f32_to_bf16(x[3]) << 16));
+}
+
+// Workgroup = 256 threads = 1024 columns (of the first segment) of one block; ncol1 = columns per
+// segment (ncols, or Sv with BV == 2), a multiple of 4; threads past the end have no work.
+template <typename TI, typename TO, int B, int BV>
+__global__ __launch_bounds__(kColThreads) void harp_col_one_kernel(
+    const TI *src, int64_t lds_, TO *dst, int64_t ldd, const float *__restrict__ blocks, int S, int ncol1,
+    unsigned nct, const float *__restrict__ vparams) {
+  const unsigned c = blockIdx.x / nct;
+  const int col = (int)((blockIdx.x % nct) * kColThreads + threadIdx.x) * 4;
+  if (col >= ncol1) return;
+  const int64_t row0 = (int64_t)(c / (unsigned)S) * B * S + c % (unsigned)S;
+  Col4<TI> raw[BV][B];
+#pragma unroll
+  for (int h = 0; h < BV; ++h)
+#pragma unroll
+    for (int r = 0; r < B; ++r) raw[h][r].load(src + (row0 + (int64_t)r * S) * lds_ + h * ncol1 + col);
+  float4 kv[4];
+  if (BV == 2) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) kv[v] = *reinterpret_cast<const float4 *>(vparams + (size_t)v * ncol1 + col);
+  }
+  const float *K = blocks + (size_t)c * (B * B);
+  float x[BV][B][4];
+#pragma unroll
+  for (int r = 0; r < B; ++r) {
+#pragma unroll
+    for (int h = 0; h < BV; ++h) raw[h][r].widen(x[h][r]);
+    if constexpr (BV == 2) {
+      const float k[4][4] = {{kv[0].x, kv[0].y, kv[0].z, kv[0].w}, {kv[1].x, kv[1].y, kv[1].z, kv[1].w},
+                             {kv[2].x, kv[2].y, kv[2].z, kv[2].w}, {kv[3].x, kv[3].y, kv[3].z, kv[3].w}};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float a = x[0][r][j], b = x[BV - 1][r][j];
+        x[0][r][j] = fmaf(b, k[2][j], a * k[0][j]);
+        x[BV - 1][r][j] = fmaf(b, k[3][j], a * k[1][j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r2 = 0; r2 < B; ++r2)
+#pragma unroll
+    for (int h = 0; h < BV; ++h) {
+      float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < B; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = fmaf(x[h][r][j], K[r * B + r2], y[j]);
+      col4_store(dst + (row0 + (int64_t)r2 * S) * ldd + h * ncol1 + col, y);
+    }
+}
+
+// One stage, four columns per access on both sides, fewer than 2^31 workgroups.
+static bool col_one_pass(const ColPass &hp, const void *src, int64_t lds_, size_t ei, const void *dst,
+                         int64_t ldd, size_t eo, int64_t nrows, int64_t ncol1) {
+  if (hp.nops != 1 || hp.op[0].k != 1 || hp.op[0].b != hp.P || hp.P > 8 || hp.P < 2) return false;
+  if (ncol1 % 4 || lds_ % 4 || ldd % 4 || (uintptr_t)src % (4 * ei) || (uintptr_t)dst % (4 * eo)) return false;
+  const int64_t nct = (ncol1 + 4 * kColThreads - 1) / (4 * kColThreads);
+  return ncol1 < ((int64_t)1 << 29) && (nrows / hp.P) * nct <= 0x7fffffff;
+}
+
+template <typename TI, typename TO, int BV>
+harp_status_t launch_col_one(const ColPass &hp, const TI *src, int64_t lds_, TO *dst, int64_t ldd, int64_t nrows,
+                             int64_t ncol1, const float *vparams, hipStream_t stream) {
+  const unsigned nct = (unsigned)((ncol1 + 4 * kColThreads - 1) / (4 * kColThreads));
+  const dim3 grid((unsigned)(nrows / hp.P) * nct);
+  if (grid.x == 0) return HARP_OK;
+#define HARP_COL_ONE(B)                                                                                    \
+  hipLaunchKernelGGL((harp_col_one_kernel<TI, TO, B, BV>), grid, dim3(kColThreads), 0, stream, src, lds_, \
+                     dst, ldd, hp.blocks, (int)hp.S, (int)ncol1, nct, vparams)
+  switch (hp.P) {
+    case 2: HARP_COL_ONE(2); break;
+    case 3: HARP_COL_ONE(3); break;
+    case 4: HARP_COL_ONE(4); break;
+    case 5: HARP_COL_ONE(5); break;
+    case 6: HARP_COL_ONE(6); break;
+    case 7: HARP_COL_ONE(7); break;
+    default: HARP_COL_ONE(8); break;
+  }
+#undef HARP_COL_ONE
+  return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
+}
+
 // Does the pass consist of radix-2 stages on the tile-row bits 0 .. k-1 in ascending or descending
 // order, 32 <= P = 2^k <= 128?  Then it runs with the tile in registers (harp_col2_kernel).
 static bool col2_pass(const ColPass &hp, Col2Stages &cs, int &logp, bool &desc) {
@@ -845,6 +961,11 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
                                const void *src, int64_t lds_, void *dst, int64_t ldd,
                                int64_t nrows, int64_t ncols, hipStream_t stream) {
   const size_t ei = sizeof(TI), eo = sizeof(TO);
+  // a single stage never gains from a tile in LDS: whenever the accesses can be four columns wide
+  if constexpr (!IsZ16<TI>::value && !IsZ16<TO>::value) {
+    if (col_one_pass(hp, src, lds_, ei, dst, ldd, eo, nrows, ncols))
+      return launch_col_one<TI, TO, 1>(hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, nullptr, stream);
+  }
   const bool vec = (ncols % 2 == 0) && (lds_ % 2 == 0) && (ldd % 2 == 0) &&
                    ((uintptr_t)src % (2 * ei) == 0) && ((uintptr_t)dst % (2 * eo) == 0);
   const bool shape_ok = vec && hp.P >= kColWaves && hp.P <= kColMaxP;
@@ -902,6 +1023,11 @@ harp_status_t launch_colrow_typed(const harp_plan *plan, const ColPass *dpass, c
                                   const PassDesc &vp, const void *src, int64_t lds_, void *dst,
                                   int64_t ldd, int64_t nrows, int64_t ncols, hipStream_t stream) {
   switch (vp.b) {
+    case 2:
+      if constexpr (!IsZ16<TI>::value && !IsZ16<TO>::value)
+        return launch_col_one<TI, TO, 2>(hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, vp.S, vp.params, stream);
+      else
+        return HARP_ERR_UNSUPPORTED;
     case 3: return launch_colrow_bv<TI, TO, 3>(plan, dpass, hp, vp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, stream);
     case 4: return launch_colrow_bv<TI, TO, 4>(plan, dpass, hp, vp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, stream);
     case 5: return launch_colrow_bv<TI, TO, 5>(plan, dpass, hp, vp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, stream);
@@ -972,6 +1098,7 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
     cp.P = P;
     cp.S = S;
     cp.image = image;
+    cp.blocks = st[i].blocks;
     std::vector<uint32_t> fix, fa, fb;
     int t = i;
     while (t < e) {
@@ -1065,10 +1192,19 @@ bool col_pass_in_registers(const ColPass &hp, int64_t ncols) {
 
 // The fused launch applies when: the column pass has exactly 32 or 64 rows per tile; the row
 // stage is a dense small-radix stage (3..8) on the top digit of a processor on ncols coordinates
-// whose stride is a multiple of 32; pairs of columns are aligned in both matrices.
+// whose stride is a multiple of 32; pairs of columns are aligned in both matrices.  A row stage of
+// radix 2 goes with a column pass of one stage (harp_col_one_kernel; no halves): beside a pass of
+// several stages its tile would be half as wide in memory as the plain one.
 bool colrow_supported(const harp_plan *plan, const ColPass &hp, const PassDesc &vp, const void *src,
                       int64_t lds_, harp_dtype_t dt_src, const void *dst, int64_t ldd,
                       harp_dtype_t dt_dst, int64_t nrows, int64_t ncols) {
+  if (vp.kind == PASS_POW2_DENSE && vp.k == 1 && vp.P == 2 && vp.V == 4 && !vp.tied) {
+    if (dt_src != HARP_F32 && dt_src != HARP_BF16) return false;
+    if (dt_dst != HARP_F32 && dt_dst != HARP_BF16) return false;
+    return 2 * (int64_t)vp.S == ncols && vp.nq == vp.S && vp.nqp == vp.nq && nrows % hp.P == 0 &&
+           (uintptr_t)vp.params % 16 == 0 &&
+           col_one_pass(hp, src, lds_, dt_src == HARP_F32 ? 4 : 2, dst, ldd, dt_dst == HARP_F32 ? 4 : 2, nrows, vp.S);
+  }
   if (hp.P != 64 && hp.P != 32) return false;
   if (hp.P == 64 && vp.b == 8) return false;   // would not fit 256 vector registers
   if (nrows % hp.P != 0) return false;

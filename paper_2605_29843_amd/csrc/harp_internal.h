@@ -135,6 +135,7 @@ struct ColPass {
   int32_t S;      // row stride between consecutive tile rows
   int32_t npar;   // block values per tile (padded blocks)
   const float *image;     // device: every stage's dense blocks
+  const float *blocks;    // device: the blocks of the pass's first stage inside the image
   // device, [3][npar]: value e of tile (hi, lo) is image[fix[e] + hi * fa[e] + lo * fb[e]];
   // fa[e] == 0xffffffff marks padding
   const uint32_t *ptab;
