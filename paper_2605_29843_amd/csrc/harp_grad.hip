@@ -234,7 +234,7 @@ constexpr int kDkJS = 16 * kDkLS + 4;       // LDS stride between consecutive r
 
 template <int KT>
 __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
-    const float *__restrict__ X, const float *__restrict__ Gm, int64_t ld, int64_t n, int rows,
+    const float *__restrict__ X, int64_t ldx, const float *__restrict__ Gm, int64_t ldg, int64_t n, int rows,
     int D, int s, int b, int gx, int paired, float *__restrict__ partial) {
   typedef float f4v __attribute__((ext_vector_type(4)));
   constexpr int MAXG = (kDkRows * 16 * KT * 4 + 1023) / 1024;
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
   const int64_t r_end = (r_begin + rows < n) ? r_begin + rows : n;
 
   const int ngroups = kDkRows * b * 4;   // (row, r, quarter of the 16 blocks) per step
-  unsigned off[MAXG];
+  unsigned off[MAXG], offg[MAXG];
   int grow[MAXG], slot[MAXG];
 #pragma unroll
   for (int u = 0; u < MAXG; ++u) {
@@ -264,17 +264,18 @@ __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
     const int lo4 = gi & 3, rem = gi >> 2;
     const int row = rem & (kDkRows - 1), j = rem / kDkRows;
     grow[u] = row;
-    off[u] = (unsigned)(row * (int)ld + j * s + lo4 * 4);
+    off[u] = (unsigned)(row * (int)ldx + j * s + lo4 * 4);
+    offg[u] = (unsigned)(row * (int)ldg + j * s + lo4 * 4);
     slot[u] = j * kDkJS + (lo4 * 4) * kDkLS + row;
   }
   float4 px[MAXG], pg[MAXG];
   auto fetch = [&](int64_t r0, int left) {
-    const float *xc = X + r0 * ld + base, *gc = Gm + r0 * ld + base;
+    const float *xc = X + r0 * ldx + base, *gc = Gm + r0 * ldg + base;
     if (left >= kDkRows) {
 #pragma unroll
       for (int u = 0; u < MAXG; ++u) {
         px[u] = *reinterpret_cast<const float4 *>(xc + off[u]);
-        pg[u] = *reinterpret_cast<const float4 *>(gc + off[u]);
+        pg[u] = *reinterpret_cast<const float4 *>(gc + offg[u]);
       }
     } else {
 #pragma unroll
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
         px[u] = pg[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (grow[u] < left) {
           px[u] = *reinterpret_cast<const float4 *>(xc + off[u]);
-          pg[u] = *reinterpret_cast<const float4 *>(gc + off[u]);
+          pg[u] = *reinterpret_cast<const float4 *>(gc + offg[u]);
         }
       }
     }
@@ -348,19 +349,19 @@ __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
 }
 
 template <int KT>
-static void launch_dk_mfma(const float *X, const float *Gm, int64_t ld, int64_t n, int rows, int nchunks,
+static void launch_dk_mfma(const float *X, int64_t ldx, const float *Gm, int64_t ldg, int64_t n, int rows, int nchunks,
                            int D, int s, int b, float *partial, hipStream_t st) {
   const int gx = D / 16;
   const int64_t total = (int64_t)gx * nchunks;
   const int paired = (gx % 2 == 0) && (total % 16 == 0);
-  hipLaunchKernelGGL((harp_grad_dk_mfma_kernel<KT>), dim3((unsigned)total), dim3(1024), 0, st, X, Gm, ld, n,
+  hipLaunchKernelGGL((harp_grad_dk_mfma_kernel<KT>), dim3((unsigned)total), dim3(1024), 0, st, X, ldx, Gm, ldg, n,
                      rows, D, s, b, gx, paired, partial);
 }
 
-static bool dk_mfma_supported(int b, int s, int D, const void *X, const void *Gm, int64_t ld,
+static bool dk_mfma_supported(int b, int s, int D, const void *X, int64_t ldx, const void *Gm, int64_t ldg,
                               const void *partial, int64_t nchunks) {
   if (b < 9 || b > 64 || s % 16 != 0 || D % 16 != 0) return false;
-  if (ld % 4 != 0 || ld >= ((int64_t)1 << 26)) return false;
+  if (ldx % 4 || ldg % 4 || ldx >= ((int64_t)1 << 26) || ldg >= ((int64_t)1 << 26)) return false;
   if ((uintptr_t)X % 16 || (uintptr_t)Gm % 16 || (uintptr_t)partial % 16) return false;
   return (int64_t)(D / 16) * nchunks <= 0x7fffffff;
 }
@@ -779,12 +780,22 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   const bool bf = (dt == HARP_BF16);
   const bool first_run = seg[0].k > 1, last_run = seg[nseg - 1].k > 1;
   const bool dx_direct = first_run && dX != nullptr;
+  // A stage of radix above 8 at the end passes the gradient back out of place, so with float32 rows
+  // its two matrix-core kernels read the caller's G where it lies (1537 x 11008 float32, last radix
+  // 43: 348 -> 311 us for the whole call).  Their plain fallbacks take one leading dimension and keep
+  // the copy.
+  const ColStage &last = stages[seg[nseg - 1].t0];
+  const bool g_direct =
+      !bf && last.b > 8 && (uintptr_t)G % 16 == 0 && ldg % 4 == 0 &&
+      mfma_pass_supported(plan->grad_mfma[1][seg[nseg - 1].t0], G, ldg, g2, d) &&
+      dk_mfma_supported(last.b, last.s, (int)(d / last.b), act + (size_t)(nseg - 1) * mat, d, G, ldg, partial,
+                        nchunks_big);
   if (n > 0) {
     if (!first_run) {
       if (bf) launch_convert((const uint16_t *)X, ldx, act, d, n, d, st);
       else launch_convert((const float *)X, ldx, act, d, n, d, st);
     }
-    if (!last_run) {
+    if (!last_run && !g_direct) {
       if (bf) launch_convert((const uint16_t *)G, ldg, g, d, n, d, st);
       else launch_convert((const float *)G, ldg, g, d, n, d, st);
     }
@@ -874,14 +885,17 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         const int D = (int)(d / cs.b);
         const dim3 grid((D + 63) / 64, nchunks_big, (cs.b + 3) / 4);
         // gradient passed back: the transposed blocks on the matrix cores where the stage allows
-        const bool mf = mfma_pass_supported(plan->grad_mfma[1][seg[i].t0], g, d, g2, d);
-        const bool dkm = dk_mfma_supported(cs.b, cs.s, D, in, g, d, partial, nchunks_big);
+        const bool own = g_direct && i == nseg - 1;   // reads the caller's G
+        const float *gsrc = own ? (const float *)G : g;
+        const int64_t gld = own ? ldg : d;
+        const bool mf = mfma_pass_supported(plan->grad_mfma[1][seg[i].t0], gsrc, gld, g2, d);
+        const bool dkm = dk_mfma_supported(cs.b, cs.s, D, in, d, gsrc, gld, partial, nchunks_big);
         if (dkm) {
           switch ((cs.b + 15) / 16) {
-            case 1: launch_dk_mfma<1>(in, g, d, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            case 2: launch_dk_mfma<2>(in, g, d, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            case 3: launch_dk_mfma<3>(in, g, d, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            default: launch_dk_mfma<4>(in, g, d, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
+            case 1: launch_dk_mfma<1>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
+            case 2: launch_dk_mfma<2>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
+            case 3: launch_dk_mfma<3>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
+            default: launch_dk_mfma<4>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
           }
         }
 #define HARP_GRAD_BIG_BWD(BM)                                                                      \
@@ -893,7 +907,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
                        g2, d, n, rows_big, cs.blocks, D, cs.s, cs.b)
         HARP_GRAD_BIG(cs.b, HARP_GRAD_BIG_BWD);
 #undef HARP_GRAD_BIG_BWD
-        if (mf && launch_mfma_pass(plan, plan->grad_mfma[1][seg[i].t0], g, d, HARP_F32, g2, d, HARP_F32, n,
+        if (mf && launch_mfma_pass(plan, plan->grad_mfma[1][seg[i].t0], gsrc, gld, HARP_F32, g2, d, HARP_F32, n,
                                    false, st) != HARP_OK)
           return HARP_ERR_DEVICE;
         std::swap(g, g2);
