@@ -920,26 +920,29 @@ harp_status_t launch_col_tiles(const harp_plan *plan, const ColPass *dpass, cons
   }
   typedef void (*kern_t)(const ColPass *, const TI *, int64_t, TO *, int64_t, int64_t, unsigned,
                          unsigned, unsigned, unsigned);
-  // unguarded: the variant with the fewest row steps per wave that covers P
+  // unguarded: the variant with the fewest row steps per wave that covers P, and one of exactly 56
+  // rows (a radix-8 and a radix-7 stage: 14336, 28672), which repeats no row and needs no clamped
+  // pointers (28672 x 8192 bf16, radix-8 schedules: 1594 -> 1568 us)
   const int which = !fast ? (vec ? 1 : 0)
+                          : hp.P == 56 ? 7
                           : (hp.P > 64 ? 2 : (hp.P > 32 ? 3 : (hp.P > 16 ? 4 : (hp.P > 8 ? 5 : 6))));
   kern_t kern = nullptr;
   if constexpr (IsZ16<TI>::value || IsZ16<TO>::value) {
     // block-scaled halves exist in the unguarded variants only
-    static const kern_t table[7] = {nullptr, nullptr,
+    static const kern_t table[8] = {nullptr, nullptr,
                                     harp_col_kernel<TI, TO, true, 32>, harp_col_kernel<TI, TO, true, 16>,
                                     harp_col_kernel<TI, TO, true, 8>,  harp_col_kernel<TI, TO, true, 4>,
-                                    harp_col_kernel<TI, TO, true, 2>};
+                                    harp_col_kernel<TI, TO, true, 2>,  harp_col_kernel<TI, TO, true, 14>};
     kern = table[which];
   } else {
-    static const kern_t table[7] = {harp_col_kernel<TI, TO, false, 0>, harp_col_kernel<TI, TO, true, 0>,
+    static const kern_t table[8] = {harp_col_kernel<TI, TO, false, 0>, harp_col_kernel<TI, TO, true, 0>,
                                     harp_col_kernel<TI, TO, true, 32>, harp_col_kernel<TI, TO, true, 16>,
                                     harp_col_kernel<TI, TO, true, 8>,  harp_col_kernel<TI, TO, true, 4>,
-                                    harp_col_kernel<TI, TO, true, 2>};
+                                    harp_col_kernel<TI, TO, true, 2>,  harp_col_kernel<TI, TO, true, 14>};
     kern = table[which];
   }
   if (!kern) return HARP_ERR_UNSUPPORTED;
-  static thread_local int attr_done_dev[7] = {-1, -1, -1, -1, -1, -1, -1};   // per instantiation
+  static thread_local int attr_done_dev[8] = {-1, -1, -1, -1, -1, -1, -1, -1};   // per instantiation
   if (attr_done_dev[which] != plan->device) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
