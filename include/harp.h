@@ -251,6 +251,7 @@ harp_status_t harp_plan_create_from_theta(harp_plan_t **out, int64_t d, int32_t 
  *   dX     device, [n, d] of type dt with leading dimension lddx, or NULL to skip it.
  *   workspace  device memory of at least harp_grad_blocks_workspace_size bytes (up to m + 2
  *          float32 copies of the batch plus partial sums); may be NULL when that size is 0.
+ *          The size does not fall as n grows: a workspace for n rows serves smaller batches.
  * Float32 arithmetic; the sum over rows is taken in a fixed order (bit-reproducible for the same
  * n).  Asynchronous on `stream`.  Every radix up to HARP_MAX_RADIX; stages of radix above 8 run
  * on a plain one-value-per-thread kernel.

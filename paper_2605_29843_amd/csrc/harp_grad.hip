@@ -726,13 +726,20 @@ static int grad_big_chunks(int64_t n) {
   const int rb = grad_big_rows(n);
   return (int)std::max<int64_t>(1, (n + rb - 1) / rb);
 }
+// At least grad_big_chunks(n), and never less for more rows (longer chunks can mean fewer of them).
+static int64_t grad_big_chunks_bound(int64_t n) {
+  return std::max<int64_t>(1, std::min<int64_t>((n + 63) / 64, 256));
+}
 
+// Does not fall as n grows: a workspace for n rows serves every smaller batch (every count of chunks
+// in it is one that never falls, and the plan without the leading segment keeps one matrix more, so
+// neither end of that segment's range of n is a step down).
 size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
   int bsmall = 6;   // a run of three radix-2 stages leaves 3 * (d / 2) * 4 partial values per chunk
   int bbig = 0;
   for (int32_t b : plan->radices) (b > 8 ? bbig : bsmall) = std::max(b > 8 ? bbig : bsmall, (int)b);
   const size_t mat = (size_t)n * (size_t)plan->d * 4;
-  const size_t partial = std::max((size_t)grad_chunks(n) * bsmall, (size_t)grad_big_chunks(n) * bbig) *
+  const size_t partial = std::max((size_t)grad_chunks(n) * bsmall, (size_t)grad_big_chunks_bound(n) * bbig) *
                          (size_t)plan->d * 4;
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
   const size_t extra = 1 + (bbig > 0 ? 1 : 0);

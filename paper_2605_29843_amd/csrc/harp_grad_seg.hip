@@ -460,9 +460,12 @@ int grad_seg_stages(const harp_plan *plan, int64_t n) {
 // 32 rows before it meets the others (256 left dK of 1537 x 11008 float32 at 2.2e-7 of its norm
 // from the float64 result where the sums by 8 rows are at 1.9e-7), at least 32.  Forward: no sums, so
 // a wave reads its blocks once for as many rows as three workgroups per compute unit leave it.
-int grad_seg_rows(const harp_plan *plan, int64_t n) {
+static int64_t grad_seg_target(const harp_plan *plan) {   // chunks that give four workgroups per compute unit
   const int64_t groups = plan->d / kSegP;
-  const int64_t chunks = std::max<int64_t>(1, (4 * (int64_t)(plan->num_cu > 0 ? plan->num_cu : 256) + groups - 1) / groups);
+  return std::max<int64_t>(1, (4 * (int64_t)(plan->num_cu > 0 ? plan->num_cu : 256) + groups - 1) / groups);
+}
+static int grad_seg_rows(const harp_plan *plan, int64_t n) {
+  const int64_t chunks = grad_seg_target(plan);
   const int64_t rows = std::min<int64_t>((n + chunks - 1) / chunks, 128);
   return (int)std::max<int64_t>((rows + 31) / 32 * 32, 32);
 }
@@ -476,8 +479,11 @@ static int64_t grad_seg_chunks(const harp_plan *plan, int64_t n) {
   const int rows = grad_seg_rows(plan, n);
   return (n + rows - 1) / rows;
 }
+// Room for at least grad_seg_chunks(n) chunks that never falls as n grows: rows per chunk are rounded up
+// to multiples of 32, so the chunks themselves get fewer wherever that rounding takes a step.
 size_t grad_seg_partial_bytes(const harp_plan *plan, int64_t n) {
-  return (size_t)grad_seg_chunks(plan, n) * (size_t)plan->d * kSegP * 4;
+  const int64_t chunks = std::max<int64_t>((n + 127) / 128, std::min<int64_t>((n + 31) / 32, grad_seg_target(plan)));
+  return (size_t)chunks * (size_t)plan->d * kSegP * 4;
 }
 
 harp_status_t launch_grad_seg_fwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, float *Y,

@@ -197,3 +197,31 @@ def test_last_stage_of_large_radix_reads_gradient_rows_at_any_pitch(harp, n):
         dK, dX = harp.harp_grad_blocks(plan, X, view)
         assert torch.equal(dX, dX0) and all(torch.equal(a, b) for a, b in zip(dK, dK0)), (pad, off)
     plan.destroy()
+
+
+# plans whose chunks get fewer as n grows: the leading segment's (64 coordinates) where its rows per
+# chunk step up by 32, and those of a radix above 8 beyond 16384 rows
+@pytest.mark.parametrize("d,radices", [(2048, [2] * 11), (4096, [2] * 12), (5120, [2] * 10 + [5]), (512, [8, 8, 8]),
+                                       (704, [8, 8, 11]), (44, [4, 11]), (11008, [8, 8, 4, 43])])
+def test_workspace_size_does_not_fall_as_the_batch_grows(harp, d, radices):
+    rng = np.random.default_rng(d)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), None)
+    sizes = [harp.harp_grad_blocks_workspace_size(plan, n) for n in range(18000)]
+    sizes += [harp.harp_grad_blocks_workspace_size(plan, n) for n in range(65535 * 128 - 2, 65535 * 128 + 3)]
+    assert all(b >= a for a, b in zip(sizes, sizes[1:]))
+    plan.destroy()
+
+
+def test_workspace_of_a_larger_batch_serves_a_smaller_one(harp):
+    import torch
+    d, radices = 4096, [2] * 12
+    rng = np.random.default_rng(5)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    ws = torch.empty(harp.harp_grad_blocks_workspace_size(plan, 513), dtype=torch.uint8, device="cuda")
+    for n in (513, 512, 63):
+        X = torch.from_numpy(rng.standard_normal((n, d)).astype(np.float32)).cuda()
+        G = torch.from_numpy(rng.standard_normal((n, d)).astype(np.float32)).cuda()
+        dK, dX = harp.harp_grad_blocks(plan, X, G, workspace=ws)
+        ref, ref_dx = harp.harp_grad_blocks(plan, X, G)
+        assert torch.equal(dX, ref_dx) and all(torch.equal(a, b) for a, b in zip(dK, ref))
+    plan.destroy()
