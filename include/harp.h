@@ -252,9 +252,11 @@ harp_status_t harp_plan_create_from_theta(harp_plan_t **out, int64_t d, int32_t 
  *   workspace  device memory of at least harp_grad_blocks_workspace_size bytes (up to m + 2
  *          float32 copies of the batch plus partial sums); may be NULL when that size is 0.
  *          The size does not fall as n grows: a workspace for n rows serves smaller batches.
- * Float32 arithmetic; the sum over rows is taken in a fixed order (bit-reproducible for the same
- * n).  Asynchronous on `stream`.  Every radix up to HARP_MAX_RADIX; stages of radix above 8 run
- * on a plain one-value-per-thread kernel.
+ * Float32 arithmetic; the sum over rows is taken in an order that depends on the plan, n, dt and the
+ * device alone: the same values give the same bits, whatever the alignment and leading dimensions
+ * of X, G, dX and the workspace and with or without dX.  Asynchronous on `stream`.  Every radix up
+ * to HARP_MAX_RADIX; stages of radix above 8 whose stride is not a multiple of 16 run on a plain
+ * one-value-per-thread kernel, others on the matrix cores.
  */
 harp_status_t harp_grad_blocks_workspace_size(const harp_plan_t *plan, int64_t n, size_t *bytes);
 harp_status_t harp_grad_blocks(const harp_plan_t *plan, const void *X, int64_t ldx, const void *G,

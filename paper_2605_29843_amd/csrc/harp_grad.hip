@@ -744,22 +744,21 @@ size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
   const size_t extra = 1 + (bbig > 0 ? 1 : 0);
   size_t need = (grad_segments(plan, 0).size() + extra) * mat + partial;
-  // (the call's alignment decides whether the leading segment is taken: room for either way)
   const int lead = grad_seg_stages(plan, n);
   if (lead > 0)
     need = std::max(need, (grad_segments(plan, lead).size() + extra) * mat +
                               std::max(partial, grad_seg_partial_bytes(plan, n)));
-  return need;
+  return need + 16;   // launch_grad starts at the next multiple of 16 bytes
 }
 
 harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, const void *G,
                           int64_t ldg, int64_t n, harp_dtype_t dt, float *const *dK, void *dX,
                           int64_t lddx, void *ws, hipStream_t st) {
   const std::vector<ColStage> &stages = plan->col[DIR_FWD];
-  // the leading segment reads and writes the caller's rows in 16-byte pieces of 8 elements
-  int lead = grad_seg_stages(plan, n);
-  if (ldx % 8 || (uintptr_t)X % 16 || (uintptr_t)ws % 16) lead = 0;
-  if (dX && (lddx % 8 || (uintptr_t)dX % 16)) lead = 0;
+  // The path follows from the plan and n alone, never from where the matrices lie: kernels sum in
+  // different orders, and the same numbers are to give the same bits.
+  ws = (void *)(((uintptr_t)ws + 15) & ~(uintptr_t)15);
+  const int lead = grad_seg_stages(plan, n);
   const std::vector<GradSegment> seg = grad_segments(plan, lead);
   const int nseg = (int)seg.size();
   const int64_t d = plan->d;
@@ -776,7 +775,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   float *partial = g + (bmax > 8 ? 2 : 1) * mat;
   const size_t pstride = (size_t)nchunks * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
   // 16-byte accesses of the stride-1 runs need the float32 copies on 16-byte boundaries
-  const int aligned = ((uintptr_t)ws % 16 == 0) && (mat % 4 == 0);
+  const int aligned = (mat % 4 == 0);
   auto run_of = [&](const GradSegment &sg) {
     GradRun run;
     for (int i = 0; i < 3; ++i) run.blocks[i] = stages[sg.t0 + std::min(i, sg.k - 1)].blocks;

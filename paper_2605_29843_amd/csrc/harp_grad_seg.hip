@@ -42,14 +42,16 @@ __device__ __forceinline__ uint32_t seg_bf16(float f) {   // round to nearest ev
   return ((u & 0x7fffffffu) > 0x7f800000u) ? ((u >> 16) | 0x40u) : rounded;
 }
 
-// Four consecutive coordinates as loaded, widened when they are used.
-template <typename T> struct SegRaw4;
-template <> struct SegRaw4<float> {
+// Four consecutive coordinates as loaded, widened when they are used.  VEC: one access of 16 (float32)
+// or 8 (bf16) bytes; otherwise one per element, for a caller's rows that are not on such boundaries.
+// The same values go through the same arithmetic either way.
+template <typename T, bool VEC> struct SegRaw4;
+template <> struct SegRaw4<float, true> {
   float4 v;
   __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
   __device__ __forceinline__ void widen(float (&x)[4]) const { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
 };
-template <> struct SegRaw4<uint16_t> {
+template <> struct SegRaw4<uint16_t, true> {
   uint2 v;
   __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
   __device__ __forceinline__ void widen(float (&x)[4]) const {
@@ -57,13 +59,48 @@ template <> struct SegRaw4<uint16_t> {
     x[2] = __uint_as_float(v.y << 16); x[3] = __uint_as_float(v.y & 0xffff0000u);
   }
 };
+template <> struct SegRaw4<float, false> {
+  float v[4];
+  __device__ __forceinline__ void load(const float *p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[i];
+  }
+  __device__ __forceinline__ void widen(float (&x)[4]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = v[i];
+  }
+};
+template <> struct SegRaw4<uint16_t, false> {
+  uint32_t v[4];
+  __device__ __forceinline__ void load(const uint16_t *p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[i];
+  }
+  __device__ __forceinline__ void widen(float (&x)[4]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(v[i] << 16);
+  }
+};
 __device__ __forceinline__ void seg_store8(float *p, const float (&v)[8]) {
   *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
   *reinterpret_cast<float4 *>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
-__device__ __forceinline__ void seg_store4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
+template <bool VEC>
+__device__ __forceinline__ void seg_store4(float *p, float4 v) {
+  if constexpr (VEC) {
+    *reinterpret_cast<float4 *>(p) = v;
+  } else {
+    p[0] = v.x; p[1] = v.y; p[2] = v.z; p[3] = v.w;
+  }
+}
+template <bool VEC>
 __device__ __forceinline__ void seg_store4(uint16_t *p, float4 v) {
-  *reinterpret_cast<uint2 *>(p) = make_uint2(seg_bf16(v.x) | (seg_bf16(v.y) << 16), seg_bf16(v.z) | (seg_bf16(v.w) << 16));
+  if constexpr (VEC) {
+    *reinterpret_cast<uint2 *>(p) = make_uint2(seg_bf16(v.x) | (seg_bf16(v.y) << 16), seg_bf16(v.z) | (seg_bf16(v.w) << 16));
+  } else {
+    p[0] = (uint16_t)seg_bf16(v.x); p[1] = (uint16_t)seg_bf16(v.y);
+    p[2] = (uint16_t)seg_bf16(v.z); p[3] = (uint16_t)seg_bf16(v.w);
+  }
 }
 
 // Eight coordinates base + e s of a row held by one thread: three radix-2 stages at strides s, 2s,
@@ -169,7 +206,7 @@ __device__ __forceinline__ void seg_rows(int64_t n, int rows, int wave, int64_t 
 // contiguous bytes per row (lane (g4 = l >> 4, c = l & 15): rows g4 and 4 + g4, coordinates 4c..);
 // the wave's LDS region hands them to the two stage passes and back.  Two steps of rows are
 // requested ahead.
-template <bool R8, typename TX>
+template <bool R8, bool VEC, typename TX>
 __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_fwd_kernel(
     const TX *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t n, int rows,
     SegBlocks sb) {
@@ -181,8 +218,8 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_fwd_kernel(
   seg_rows(n, rows, wave, r0, r1);
   if (r0 >= r1) return;
   float *w = lds[wave], *t = w + row * kSegRowP;
-  SegRaw4<TX> nx[2][2];
-  auto fetch = [&](SegRaw4<TX> (&q)[2], int64_t r) {   // rows past the end repeat the last one and are not stored
+  SegRaw4<TX, VEC> nx[2][2];
+  auto fetch = [&](SegRaw4<TX, VEC> (&q)[2], int64_t r) {   // rows past the end repeat the last one and are not stored
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int64_t rr = r + 4 * h + g4 < r1 ? r + 4 * h + g4 : r1 - 1;
@@ -194,7 +231,7 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_fwd_kernel(
   Pass8<R8> pa, pb;
   pa.template load_as<true>(sb.blocks, base + 8 * item, 1, l);
   pb.template load_as<true>(sb.blocks + (R8 ? 1 : 3), base + item, 8, l);
-  auto step = [&](SegRaw4<TX> (&q)[2], int64_t r) {
+  auto step = [&](SegRaw4<TX, VEC> (&q)[2], int64_t r) {
     float v[8], x[4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -232,7 +269,7 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_fwd_kernel(
 // product whose row (column) index c stands for coordinate 4c + t, so x and g go from memory
 // into the matrix cores with no exchange.  g then passes through the wave's LDS region
 // into the layout of the two stage passes, and dX back into the layout of the loads.
-template <bool R8, typename TX>
+template <bool R8, bool VEC, typename TX>
 __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
     const TX *__restrict__ X, int64_t ldx, const float *__restrict__ G, int64_t ldg, TX *dX, int64_t lddx,
     int64_t n, int rows, SegBlocks sb, float *__restrict__ partial) {
@@ -251,9 +288,9 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
   if (r0 < r1) {
     float *w = lds + wave * kTile;
     float *t = w + row * kSegRowP;
-    SegRaw4<TX> nx[2][2];
-    SegRaw4<float> ng[2][2];
-    auto fetch = [&](SegRaw4<TX> (&qx)[2], SegRaw4<float> (&qg)[2], int64_t r) {
+    SegRaw4<TX, VEC> nx[2][2];
+    SegRaw4<float, true> ng[2][2];
+    auto fetch = [&](SegRaw4<TX, VEC> (&qx)[2], SegRaw4<float, true> (&qg)[2], int64_t r) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int64_t rr = r + 4 * h + g4 < r1 ? r + 4 * h + g4 : r1 - 1;
@@ -266,7 +303,7 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
     Pass8<R8> pa, pb;
     pa.template load_as<false>(sb.blocks, base + 8 * item, 1, l);
     pb.template load_as<false>(sb.blocks + (R8 ? 1 : 3), base + item, 8, l);
-    auto step = [&](SegRaw4<TX> (&qx)[2], SegRaw4<float> (&qg)[2], int64_t r) {
+    auto step = [&](SegRaw4<TX, VEC> (&qx)[2], SegRaw4<float, true> (&qg)[2], int64_t r) {
       float x[2][4], g[2][4];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -306,7 +343,7 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const float4 o = *reinterpret_cast<const float4 *>(w + (4 * h + g4) * kSegRowP + 4 * c);
-          if (r + 4 * h + g4 < r1) seg_store4(dX + (r + 4 * h + g4) * lddx + base + 4 * c, o);
+          if (r + 4 * h + g4 < r1) seg_store4<VEC>(dX + (r + 4 * h + g4) * lddx + base + 4 * c, o);
         }
         wave_lds_fence();
       }
@@ -486,21 +523,31 @@ size_t grad_seg_partial_bytes(const harp_plan *plan, int64_t n) {
   return (size_t)chunks * (size_t)plan->d * kSegP * 4;
 }
 
+// X and dX are the caller's: one access per element where rows do not lie on boundaries of four.
+// Whole call with X shifted by one element, 2048 x 4096 float32 radix 2: 117 us (113 us where it is
+// not shifted; 174 us stage by stage).
+static bool seg_vec(const void *p, int64_t ld, bool bf) { return ld % 4 == 0 && (uintptr_t)p % (bf ? 8 : 16) == 0; }
+
 harp_status_t launch_grad_seg_fwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, float *Y,
                                   int64_t n, hipStream_t st) {
   const int rows = grad_seg_fwd_rows(plan, n);
   const dim3 grid((unsigned)(plan->d / kSegP), (unsigned)((n + rows - 1) / rows)), blk(64 * kSegWaves);
   const SegBlocks sb = seg_blocks(plan, nst);
   const int64_t d = plan->d;
-#define HARP_SEG_FWD(R8, T) \
-  hipLaunchKernelGGL((harp_grad_seg_fwd_kernel<R8, T>), grid, blk, 0, st, (const T *)X, ldx, Y, d, n, rows, sb)
-  if (nst == 2) {
-    if (bf) HARP_SEG_FWD(true, uint16_t);
-    else HARP_SEG_FWD(true, float);
-  } else {
-    if (bf) HARP_SEG_FWD(false, uint16_t);
-    else HARP_SEG_FWD(false, float);
-  }
+  const bool vec = seg_vec(X, ldx, bf);
+#define HARP_SEG_FWD(R8, VEC, T)                                                                       \
+  hipLaunchKernelGGL((harp_grad_seg_fwd_kernel<R8, VEC, T>), grid, blk, 0, st, (const T *)X, ldx, Y, d, n, \
+                     rows, sb)
+#define HARP_SEG_FWD_TYPES(R8)                 \
+  do {                                         \
+    if (bf && vec) HARP_SEG_FWD(R8, true, uint16_t);   \
+    else if (bf) HARP_SEG_FWD(R8, false, uint16_t);    \
+    else if (vec) HARP_SEG_FWD(R8, true, float);       \
+    else HARP_SEG_FWD(R8, false, float);               \
+  } while (0)
+  if (nst == 2) HARP_SEG_FWD_TYPES(true);
+  else HARP_SEG_FWD_TYPES(false);
+#undef HARP_SEG_FWD_TYPES
 #undef HARP_SEG_FWD
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
@@ -513,22 +560,24 @@ harp_status_t launch_grad_seg_bwd(const harp_plan *plan, int nst, const void *X,
   const SegBlocks sb = seg_blocks(plan, nst);
   const int rows = grad_seg_rows(plan, n);
   const int64_t d = plan->d;
+  const bool vec = seg_vec(X, ldx, bf) && (!dX || seg_vec(dX, lddx, bf));
   SegOut out{};
   for (int t = 0; t < nst; ++t) out.dK[t] = dK[t];
-#define HARP_SEG_BWD(R8, T)                                                                            \
-  hipLaunchKernelGGL((harp_grad_seg_bwd_kernel<R8, T>), grid, blk, 0, st, (const T *)X, ldx, G, d, (T *)dX, \
-                     lddx, n, rows, sb, partial)
-  if (nst == 2) {
-    if (bf) HARP_SEG_BWD(true, uint16_t);
-    else HARP_SEG_BWD(true, float);
-    hipLaunchKernelGGL((harp_grad_seg_expand_kernel<true>), dim3(grid.x), dim3(kExpThreads), 0, st, partial,
-                       (int)chunks, sb, plan->dev_signs, out);
-  } else {
-    if (bf) HARP_SEG_BWD(false, uint16_t);
-    else HARP_SEG_BWD(false, float);
-    hipLaunchKernelGGL((harp_grad_seg_expand_kernel<false>), dim3(grid.x), dim3(kExpThreads), 0, st, partial,
-                       (int)chunks, sb, plan->dev_signs, out);
-  }
+#define HARP_SEG_BWD(R8, VEC, T)                                                                         \
+  hipLaunchKernelGGL((harp_grad_seg_bwd_kernel<R8, VEC, T>), grid, blk, 0, st, (const T *)X, ldx, G, d, \
+                     (T *)dX, lddx, n, rows, sb, partial)
+#define HARP_SEG_BWD_TYPES(R8)                                                                           \
+  do {                                                                                                   \
+    if (bf && vec) HARP_SEG_BWD(R8, true, uint16_t);                                                     \
+    else if (bf) HARP_SEG_BWD(R8, false, uint16_t);                                                      \
+    else if (vec) HARP_SEG_BWD(R8, true, float);                                                         \
+    else HARP_SEG_BWD(R8, false, float);                                                                 \
+    hipLaunchKernelGGL((harp_grad_seg_expand_kernel<R8>), dim3(grid.x), dim3(kExpThreads), 0, st, partial, \
+                       (int)chunks, sb, plan->dev_signs, out);                                           \
+  } while (0)
+  if (nst == 2) HARP_SEG_BWD_TYPES(true);
+  else HARP_SEG_BWD_TYPES(false);
+#undef HARP_SEG_BWD_TYPES
 #undef HARP_SEG_BWD
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }

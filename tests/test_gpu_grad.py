@@ -144,9 +144,9 @@ def test_grad_blocks_llama7b_shape_sampled(harp):
     # ragged runs of rows: a wave with one row, a wave with none, more than one workgroup per group
     (320, [2] * 6 + [5], 65), (704, [8, 8, 11], 71), (2048, [8, 8, 8, 4], 297), (4096, [2] * 12, 1033)])
 def test_leading_segment_and_stage_by_stage_agree_with_the_oracle(harp, d, radices, n, dtype):
-    """Rows on 16-byte boundaries take the first 64 coordinates' stages as one segment, rows that are
-    not (here: shifted by one element) stage by stage; both against the oracle.  The tolerance is
-    the one derived above (the segment sums runs of at most 64 rows before they meet)."""
+    """The first 64 coordinates' stages as one segment (n >= 64), rows on boundaries of four elements and
+    rows that are not (here: shifted by one element), both against the oracle.  The tolerance is the
+    one derived above (the segment sums runs of at most 32 rows before they meet)."""
     import torch
     rng = np.random.default_rng(7 * d + n)
     blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
@@ -224,4 +224,53 @@ def test_workspace_of_a_larger_batch_serves_a_smaller_one(harp):
         dK, dX = harp.harp_grad_blocks(plan, X, G, workspace=ws)
         ref, ref_dx = harp.harp_grad_blocks(plan, X, G)
         assert torch.equal(dX, ref_dx) and all(torch.equal(a, b) for a, b in zip(dK, ref))
+    plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,radices,n", [(128, [2] * 7, 64), (512, [8, 8, 8], 71), (2048, [8, 8, 8, 4], 297),
+                                         (704, [8, 8, 11], 130), (1376, [2] * 5 + [43], 65), (4096, [2] * 12, 200),
+                                         (512, [8, 8, 8], 63)])
+def test_bits_do_not_depend_on_where_the_matrices_lie(harp, d, radices, n, dtype):
+    """The same values in views that break the boundaries of four elements or of 16 bytes, for each of
+    the matrices and the workspace, with and without dX."""
+    import ctypes
+    import torch
+    rng = np.random.default_rng(3 * d + n)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    if dtype == "bf16":
+        X, G = gi.round_to_bf16(X), gi.round_to_bf16(G)
+    X, G = to_device(X, dtype), to_device(G, dtype)
+    dK0, dX0 = harp.harp_grad_blocks(plan, X, G)
+    need = harp.harp_grad_blocks_workspace_size(plan, n)
+    ws = torch.empty(need + 64, dtype=torch.uint8, device="cuda")
+    code = 0 if dtype == "f32" else 1
+
+    def placed(x, pad, off):
+        big = torch.zeros(n, d + pad + off, device="cuda", dtype=x.dtype)
+        big[:, off:off + d] = x
+        return big[:, off:off + d]
+
+    # (pad, off) of X, G, dX (None: no dX), bytes by which the workspace starts late
+    for px, pg, pdx, late in (((8, 1), (0, 0), (0, 0), 0), ((4, 0), (0, 0), (0, 0), 0), ((3, 0), (5, 2), (1, 0), 0),
+                              ((0, 0), (8, 1), (8, 1), 0), ((0, 0), (0, 0), (7, 0), 0), ((0, 0), (0, 0), None, 0),
+                              ((4, 4), (4, 4), (4, 4), 0), ((0, 0), (0, 0), (0, 0), 4), ((8, 1), (0, 0), None, 12)):
+        xv, gv = placed(X, *px), placed(G, *pg)
+        dxv = None if pdx is None else placed(torch.full_like(X, 7.0), *pdx)
+        dK = [torch.full_like(a, 7.0) for a in dK0]
+        ptrs = (ctypes.c_void_p * len(dK))(*[a.data_ptr() for a in dK])
+        st = harp.lib.harp_grad_blocks(plan.handle, xv.data_ptr(), xv.stride(0), gv.data_ptr(), gv.stride(0), n, code,
+                                       ptrs, None if dxv is None else dxv.data_ptr(),
+                                       0 if dxv is None else dxv.stride(0), ws.data_ptr() + late, need,
+                                       torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        where = (px, pg, pdx, late)
+        assert st == 0, where
+        assert all(torch.equal(a, b) for a, b in zip(dK, dK0)), where
+        assert dxv is None or torch.equal(dxv, dX0), where
+        # nothing beside the rows of dX was written
+        if dxv is not None:
+            full = torch.as_strided(dxv, (n, dxv.stride(0)), (dxv.stride(0), 1), dxv.storage_offset() - pdx[1])
+            assert bool((full[:, :pdx[1]] == 0).all()) and bool((full[:, pdx[1] + d:] == 0).all()), where
     plan.destroy()
