@@ -248,7 +248,9 @@ harp_status_t harp_plan_create_from_theta(harp_plan_t **out, int64_t d, int32_t 
  *   X, G   device, [n, d] row-major, element type dt, leading dimensions ldx, ldg >= d.
  *   dK     host array of m DEVICE pointers; dK[t] receives D_t * b_t * b_t float32 values in
  *          the layout of harp_plan_create's blocks[t] (overwritten; zeros when n == 0).
- *   dX     device, [n, d] of type dt with leading dimension lddx, or NULL to skip it.
+ *   dX     device, [n, d] of type dt with leading dimension lddx, or NULL to skip it.  It may be X
+ *          or G itself (same pointer and leading dimension); no other overlap of X, G, dX, the
+ *          dK[t] and the workspace is allowed, except that X and G may overlap.
  *   workspace  device memory of at least harp_grad_blocks_workspace_size bytes (up to m + 2
  *          float32 copies of the batch plus partial sums); may be NULL when that size is 0.
  *          The size does not fall as n grows: a workspace for n rows serves smaller batches.

@@ -511,10 +511,11 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_run_kernel(
 // TX: element type of the run's input rows X; the gradient is read from Gin (TGI) and the
 // gradient passed back is written to Gout (TGO): the same float32 matrix in place, or the
 // caller's G on the way in (last run) and the caller's dX on the way out (first run).  A thread
-// reads its item of a row before it writes it, and no other thread touches that item.
+// reads its item of a row (X and gradient) before it writes it, and no other thread touches that item:
+// dX may be X or G.
 template <int K, typename TX = float, typename TGI = float, typename TGO = float>
 __global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_run_kernel(
-    const TX *__restrict__ X, int64_t ldx, const TGI *Gin, int64_t ldgi, TGO *Gout, int64_t ldgo,
+    const TX *X, int64_t ldx, const TGI *Gin, int64_t ldgi, TGO *Gout, int64_t ldgo,
     int64_t ld, int64_t n, int rows, GradRun run, int nitems, int s, int D,
     float *__restrict__ partial, size_t pstride, int aligned) {
   constexpr int E = 1 << K, H = E / 2;

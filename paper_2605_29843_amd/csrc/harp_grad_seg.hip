@@ -268,10 +268,12 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_fwd_kernel(
 // 4c .. 4c+3 of rows g4 and 4 + g4: element t of those four is exactly its operand of a 16x16x4
 // product whose row (column) index c stands for coordinate 4c + t, so x and g go from memory
 // into the matrix cores with no exchange.  g then passes through the wave's LDS region
-// into the layout of the two stage passes, and dX back into the layout of the loads.
+// into the layout of the two stage passes, and dX back into the layout of the loads.  dX may be X:
+// a lane reads its pieces of a row before it writes them and no other lane touches them (X is not
+// __restrict__; the last row read again past the end is replaced by zeros).
 template <bool R8, bool VEC, typename TX>
 __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
-    const TX *__restrict__ X, int64_t ldx, const float *__restrict__ G, int64_t ldg, TX *dX, int64_t lddx,
+    const TX *X, int64_t ldx, const float *__restrict__ G, int64_t ldg, TX *dX, int64_t lddx,
     int64_t n, int rows, SegBlocks sb, float *__restrict__ partial) {
   constexpr int kTile = kSegP * kSegP;
   __shared__ __attribute__((aligned(16))) float lds[kSegWaves * kTile];

@@ -274,3 +274,34 @@ def test_bits_do_not_depend_on_where_the_matrices_lie(harp, d, radices, n, dtype
             full = torch.as_strided(dxv, (n, dxv.stride(0)), (dxv.stride(0), 1), dxv.storage_offset() - pdx[1])
             assert bool((full[:, :pdx[1]] == 0).all()) and bool((full[:, pdx[1] + d:] == 0).all()), where
     plan.destroy()
+
+
+# dX written over X or G: a leading segment (radix 2, radix 8), a run of radix-2 stages, a single
+# stage at either end, one run and nothing else
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,radices,n", [(512, [2] * 9, 133), (512, [8, 8, 8], 133), (512, [2] * 9, 20), (176, [2] * 4 + [11], 70),
+                                         (8, [2] * 3, 300), (240, [5, 6, 8], 37), (11, [11], 5)])
+def test_dX_may_be_X_or_G(harp, d, radices, n, dtype):
+    import ctypes
+    import torch
+    rng = np.random.default_rng(d + n)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    if dtype == "bf16":
+        X, G = gi.round_to_bf16(X), gi.round_to_bf16(G)
+    X, G = to_device(X, dtype), to_device(G, dtype)
+    dK0, dX0 = harp.harp_grad_blocks(plan, X, G)
+    need = harp.harp_grad_blocks_workspace_size(plan, n)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for over in ("X", "G"):
+        x, g = X.clone(), G.clone()
+        out = x if over == "X" else g
+        dK = [torch.empty_like(a) for a in dK0]
+        ptrs = (ctypes.c_void_p * len(dK))(*[a.data_ptr() for a in dK])
+        st = harp.lib.harp_grad_blocks(plan.handle, x.data_ptr(), d, g.data_ptr(), d, n, 0 if dtype == "f32" else 1,
+                                       ptrs, out.data_ptr(), d, ws.data_ptr(), need,
+                                       torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert st == 0
+        assert torch.equal(out, dX0) and all(torch.equal(a, b) for a, b in zip(dK, dK0)), over
+    plan.destroy()
