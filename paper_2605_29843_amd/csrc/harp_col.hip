@@ -870,6 +870,19 @@ struct Col2Types {   // element types the register-tile kernel is built for
       IsZ16<TI>::value || IsZ16<TO>::value;                                         // the halves
 };
 
+// Row steps per wave of the unguarded variants: 2, 4, .. 16, then 20, .. 32.  A pass of P rows takes the
+// smallest that covers P / 4 rows per wave.  Every step too many moves a row again, and a height
+// that fills its steps exactly also needs no clamped pointers.  Against the powers of two alone (us;
+// rotations by plan_U only, two or three passes of one height, 8192 or 4096 columns, float32 / bf16):
+//   24 rows 340 / 320 -> 318 / 296,  40 rows 72 / 71 -> 65 / 57,  48 rows 89 / 87 -> 82 / 72,
+//   72 rows 221 / 200 -> 194 / 173,  80 rows 252 / 236 -> 220 / 197,  96 rows 321 / 290 -> 293 / 255,
+//   112 rows 230 / 206 -> 222 / 192;  28672 x 8192 bf16 (a pass of 56 rows) 1594 -> 1568.
+constexpr int kColStepVariants = 12;
+inline int col_step_variant(int P) {
+  const int steps = (P + kColWaves - 1) / kColWaves;
+  return steps <= 16 ? (steps < 2 ? 2 : (steps + 1) / 2 * 2) / 2 - 1 : 8 + ((steps + 3) / 4 * 4 - 20) / 4;
+}
+
 template <typename TI, typename TO>
 harp_status_t launch_col_tiles(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                                const TI *src, int64_t lds_, TO *dst, int64_t ldd, int64_t nrows,
@@ -920,37 +933,38 @@ harp_status_t launch_col_tiles(const harp_plan *plan, const ColPass *dpass, cons
   }
   typedef void (*kern_t)(const ColPass *, const TI *, int64_t, TO *, int64_t, int64_t, unsigned,
                          unsigned, unsigned, unsigned);
-  // unguarded: the variant with the fewest row steps per wave that covers P, and one of exactly 56
-  // rows (a radix-8 and a radix-7 stage: 14336, 28672), which repeats no row and needs no clamped
-  // pointers (28672 x 8192 bf16, radix-8 schedules: 1594 -> 1568 us)
-  const int which = !fast ? (vec ? 1 : 0)
-                          : hp.P == 56 ? 7
-                          : (hp.P > 64 ? 2 : (hp.P > 32 ? 3 : (hp.P > 16 ? 4 : (hp.P > 8 ? 5 : 6))));
+  // 0, 1: guarded; 2 ..: unguarded, by the row steps per wave
+  constexpr int kVariants = 2 + kColStepVariants;
+  const int which = fast ? 2 + col_step_variant(hp.P) : (vec ? 1 : 0);
+#define HARP_COL_STEPS                                                                                  \
+  harp_col_kernel<TI, TO, true, 2>, harp_col_kernel<TI, TO, true, 4>, harp_col_kernel<TI, TO, true, 6>, \
+      harp_col_kernel<TI, TO, true, 8>, harp_col_kernel<TI, TO, true, 10>,                              \
+      harp_col_kernel<TI, TO, true, 12>, harp_col_kernel<TI, TO, true, 14>,                             \
+      harp_col_kernel<TI, TO, true, 16>, harp_col_kernel<TI, TO, true, 20>,                             \
+      harp_col_kernel<TI, TO, true, 24>, harp_col_kernel<TI, TO, true, 28>,                             \
+      harp_col_kernel<TI, TO, true, 32>
   kern_t kern = nullptr;
   if constexpr (IsZ16<TI>::value || IsZ16<TO>::value) {
     // block-scaled halves exist in the unguarded variants only
-    static const kern_t table[8] = {nullptr, nullptr,
-                                    harp_col_kernel<TI, TO, true, 32>, harp_col_kernel<TI, TO, true, 16>,
-                                    harp_col_kernel<TI, TO, true, 8>,  harp_col_kernel<TI, TO, true, 4>,
-                                    harp_col_kernel<TI, TO, true, 2>,  harp_col_kernel<TI, TO, true, 14>};
+    static const kern_t table[kVariants] = {nullptr, nullptr, HARP_COL_STEPS};
     kern = table[which];
   } else {
-    static const kern_t table[8] = {harp_col_kernel<TI, TO, false, 0>, harp_col_kernel<TI, TO, true, 0>,
-                                    harp_col_kernel<TI, TO, true, 32>, harp_col_kernel<TI, TO, true, 16>,
-                                    harp_col_kernel<TI, TO, true, 8>,  harp_col_kernel<TI, TO, true, 4>,
-                                    harp_col_kernel<TI, TO, true, 2>,  harp_col_kernel<TI, TO, true, 14>};
+    static const kern_t table[kVariants] = {harp_col_kernel<TI, TO, false, 0>,
+                                            harp_col_kernel<TI, TO, true, 0>, HARP_COL_STEPS};
     kern = table[which];
   }
+#undef HARP_COL_STEPS
   if (!kern) return HARP_ERR_UNSUPPORTED;
-  static thread_local int attr_done_dev[8] = {-1, -1, -1, -1, -1, -1, -1, -1};   // per instantiation
-  if (attr_done_dev[which] != plan->device) {
+  // device whose attribute this thread has set, plus one (0: none), per instantiation
+  static thread_local int attr_done_dev[kVariants] = {};
+  if (attr_done_dev[which] != plan->device + 1) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             plan->lds_bytes) != hipSuccess) {
       (void)hipGetLastError();
       return HARP_ERR_DEVICE;
     }
-    attr_done_dev[which] = plan->device;
+    attr_done_dev[which] = plan->device + 1;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kColThreads), shmem, stream, dpass, src, lds_,
                      dst, ldd, ncols, (unsigned)ctiles, (unsigned)tiles, (unsigned)tpw, xg);
