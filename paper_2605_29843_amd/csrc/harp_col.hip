@@ -726,7 +726,8 @@ __global__ __launch_bounds__(kColThreads, 2) void harp_colrow_kernel(
 // and arrives by scalar loads.  The LDS-tile kernel spends as long on the block table, the
 // barriers and the trips through LDS of a tile of 8 rows x 128 columns as of one of 64 rows.
 // 28672 x 8192 bf16, radix-8 schedules: that pass took 700 us and the radix-2 stage on its own
-// trips 324 us; with both in this kernel the whole rotation went from 2316 to 1594 us.
+// trips 324 us.  The whole rotation: 2316 us before, 1945 us with the pass alone in this kernel, 1572 us
+// with the radix-2 stage beside it (this kernel then takes 347 us, 5.4 TB/s).
 // The sums run over r in ascending order, as in the kernels whose place it takes.
 // Every thread has read its elements before it writes them and owns them alone: in place is fine.
 template <typename T> struct Col4;
@@ -801,7 +802,10 @@ __global__ __launch_bounds__(kColThreads) void harp_col_one_kernel(
     }
 }
 
-// One stage, four columns per access on both sides, fewer than 2^31 workgroups.
+// One stage, four columns per access on both sides, fewer than 2^31 workgroups.  No lower bound on the
+// columns: a workgroup with few of them leaves lanes idle, yet the tile kernel is slower at every width
+// (plan_U only, float32, 28672 rows, radix 8: 4 columns 63 -> 28 us, 128 45 -> 33, 512 116 -> 87, 1024
+// 214 -> 162, 8192 1501 -> 1149) and never faster (8 rows, any width, and 512 x 128: equal, launches).
 static bool col_one_pass(const ColPass &hp, const void *src, int64_t lds_, size_t ei, const void *dst,
                          int64_t ldd, size_t eo, int64_t nrows, int64_t ncol1) {
   if (hp.nops != 1 || hp.op[0].k != 1 || hp.op[0].b != hp.P || hp.P > 8 || hp.P < 2) return false;
@@ -978,7 +982,9 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
                                const void *src, int64_t lds_, void *dst, int64_t ldd,
                                int64_t nrows, int64_t ncols, hipStream_t stream) {
   const size_t ei = sizeof(TI), eo = sizeof(TO);
-  // a single stage never gains from a tile in LDS: whenever the accesses can be four columns wide
+  // A single stage gains nothing from a tile in LDS: in registers whenever the accesses can be four
+  // columns wide.  Passes with block-scaled halves on a side keep the tile (harp_col_one_kernel is
+  // not built for the format): the 8-row pass of a one-sided 28672 x 8192 bf16 rotation takes 696 us.
   if constexpr (!IsZ16<TI>::value && !IsZ16<TO>::value) {
     if (col_one_pass(hp, src, lds_, ei, dst, ldd, eo, nrows, ncols))
       return launch_col_one<TI, TO, 1>(hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, nullptr, stream);

@@ -5,16 +5,21 @@
 // idx = the b_t coordinates alpha b s + r s + beta of block c = alpha s + beta, and dX = g_0
 // diag(sigma).  Nothing is assumed about the blocks (they need not be orthogonal).
 //
-// First version, stage by stage through device memory: the forward pass keeps the input of
-// every stage (m float32 copies of the batch in the workspace), the backward pass runs one kernel
-// per stage that updates g in place and leaves per-row-chunk partial sums of dK, and a
-// reduction kernel adds the chunks in a fixed order (no atomics: results are reproducible).
-// One thread owns one block c for a chunk of rows: its b*b kernel values and b*b accumulators
-// stay in registers.  Up to three consecutive radix-2 stages share one kernel: a thread owns
-// the 2^k coordinates base + e s and the k 2^(k-1) blocks that act on them, the forward kernel
-// stores only the run's output, and the backward kernel recomputes the run's inner activations
-// in registers.  Radices up to 8 (the plan's dense per-stage image with the signs folded into
-// stage 0 is the one the column-mode passes use).
+// Segment by segment through device memory: the forward pass keeps the input of every segment
+// (float32 copies of the batch in the workspace; the first segment, and the last one on the way
+// back, use the caller's rows where their kernel can), the backward pass runs one kernel per segment
+// that passes g back and leaves per-row-chunk partial sums of dK, and a reduction kernel adds the
+// chunks in a fixed order (no atomics: results are reproducible).  The segments:
+//   - the stages of the first 64 coordinates together (harp_grad_seg.hip: radix 2 or 8, orthogonal);
+//   - up to three consecutive radix-2 stages: a thread owns the 2^k coordinates base + e s and the
+//     k 2^(k-1) blocks that act on them, the forward kernel stores only the run's output, and the
+//     backward kernel recomputes the run's inner activations in registers;
+//   - one stage of radix up to 8: a thread owns one block for a chunk of rows, its b*b values and b*b
+//     accumulators in registers, g in place;
+//   - one stage of radix 9 .. 64, g out of place: on the matrix cores where the stride is a multiple
+//     of 16, else one value per thread.
+// All read the plan's dense per-stage image with the signs folded into stage 0 (the one the
+// column-mode passes use).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -14,7 +14,8 @@
 // end: no barrier in the row loop, x and g read once, dX written once.  The matrix product is
 // 64 multiply-adds per coordinate at twice the vector rate (7 us for 2048 x 4096), below the time
 // the rows take to stream.  Measured (whole call): 2048 x 4096 bf16 radix 2 158 -> 115 us,
-// 1537 x 11008 float32 (8, 8, 4, 43) 653 -> 349 us (the three kernels: 31 + 53 + 11 us for 471 MB).
+// 1537 x 11008 float32 (8, 8, 4, 43) 653 -> 349 us (the three kernels: 29 + 52 + 10 us for the 412 MB of
+// five passes over the batch and the partial sums of 13 chunks, written and read).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -376,8 +377,8 @@ __global__ __launch_bounds__(64 * kSegWaves, 2) void harp_grad_seg_bwd_kernel(
   }
 }
 
-// dK of the segment's stages out of dM (the chunks added in ascending order).  One workgroup per
-// group; everything in LDS.  A_t[i][j] is zero unless i and j share the digits from t up, so a
+// dK of the segment's stages out of dM (chunks of rows added in ascending order within each eight, then
+// the sums of eight in ascending order).  One workgroup per group; everything in LDS.  A_t[i][j] is zero unless i and j share the digits from t up, so a
 // row of A_t is kept as its S_t entries j = (digits of i from t up, lo), lo < S_t.
 struct SegOut {
   float *dK[6];
@@ -483,8 +484,11 @@ SegBlocks seg_blocks(const harp_plan *plan, int nst) {
 
 // Stages 0 .. k-1 of the plan that form the segment (6 of radix 2, 2 of radix 8), or 0.  Orthogonal
 // blocks only: the contractions of dM then leave its rounding errors at the size that sums
-// taken block by block have.  n >= 64: below, the launches are latency and the per-group work
-// would outweigh the rows.
+// taken block by block have.  n >= 64 is the range over which that has been measured and is tested,
+// not where the segment stops paying: whole calls with 1 / 8 / 32 / 63 rows in float32 take 61 / 66 /
+// 68 / 69 us stage by stage and 54 / 54 / 54 / 54 us with it at 4096 radix 2, 69 / 112 / 122 / 139 and
+// 52 / 59 / 68 / 86 us at 11008 (8, 8, 4, 43).  At 64 rows and up it is 1.15 - 3.3 times as fast from d = 128
+// (262144 rows: 2811 -> 1220 us radix 2, 3644 -> 1213 us radix 8) to 28672 (64 rows: 126 -> 105, 166 -> 107 us).
 int grad_seg_stages(const harp_plan *plan, int64_t n) {
   if (!plan->orthogonal || n < 64 || plan->d <= kSegP || plan->d % kSegP) return 0;
   if (n > (int64_t)65535 * 128) return 0;   // one workgroup per 128 rows at most: blockIdx.y
