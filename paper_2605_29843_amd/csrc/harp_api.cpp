@@ -389,6 +389,9 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
     build_effective(plan, blocks, signs, algo, dir, false, eff, dense_t, dense_both);
   }
   auto local = [&](int i) { return eff[i].t < tb; };
+  // chunk of radices 8, 8, 8, 3..8: its kernel has its own image (build_chain_image)
+  const bool chain = fused && tb == 4 && plan->radices[0] == 8 && plan->radices[1] == 8 && plan->radices[2] == 8 &&
+                     plan->radices[3] >= 3 && plan->radices[3] <= 8;
   hp.chunk = (int32_t)chunk;
   hp.n_chunk = 0;
   hp.chunk_first = (dir == DIR_FWD);
@@ -558,7 +561,7 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
       for (int r = 0; r < b; ++r)
         for (int r2 = 0; r2 < b; ++r2)
           img[(size_t)(r * b + r2) * nqp + q] = se.dense[((size_t)q * b + r) * b + r2];
-    if (small && (b == 4 || b == 8)) {
+    if (small && (b == 4 || b == 8) && !(chain && local(i))) {
       // second copy for the equal-radix tile kernel, four values per 16-byte load:
       // value v = 4 * v4 + i of sub-tensor q at float index ((v4 * nq) + q) * 4 + i
       std::vector<uint16_t> &a = aux[pg.npass - 1];
@@ -629,6 +632,8 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
       hp.dpp.offT = (int64_t)off - hp.dpp.host_off;
     }
   }
+  if (chain)
+    build_chain_image(hp, dir == DIR_FWD ? 0 : pg.npass - hp.n_chunk, hp.n_chunk, d, offsets, image);
   hp.ok = true;
   return true;
 }
@@ -720,7 +725,7 @@ harp_status_t run_chunk_passes(const harp_plan_t *plan, const HostProgram &hp, i
                               stream);
   // tied parameters and in-kernel signs exist in the wave kernel only (16-byte aligned rows)
   if (plan->tied_K > 0) return HARP_ERR_UNSUPPORTED;
-  if (radix_supported(plan, hp.prog, p0, p1 - p0, hp.chunk, X, ldx, Y, ldy))
+  if (radix_supported(plan, hp, p0, p1 - p0, hp.chunk, X, ldx, Y, ldy))
     return launch_radix_kernel(plan, hp, p0, p1 - p0, hp.chunk, X, ldx, dt_in, Y, ldy, dt_out, n,
                                stream);
   return launch_tile_kernel(plan, hp.dev, p0, p1, hp.chunk, X, ldx, dt_in, Y, ldy, dt_out, n,
@@ -1299,6 +1304,7 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
           break;
         }
         if (hp.dpp.host_off >= 0) hp.dpp.img = dimg + hp.dpp.host_off;
+        if (hp.chain.host_off >= 0) hp.chain.img = dimg + hp.chain.host_off;
         for (int p = 0; p < hp.prog.npass; ++p) {
           hp.prog.pass[p].params = dimg + offsets[p];
           hp.prog.pass[p].aux = nullptr;
@@ -1705,7 +1711,7 @@ const char *harp_plan_kernel_name(const harp_plan_t *plan, int64_t n, harp_dtype
       wave_supported(plan, hp->prog, 0, hp->prog.npass, hp->chunk, nullptr, 8, nullptr, 8))
     return "wave_radix2";
   if (hp && hp->n_chunk == hp->prog.npass &&
-      radix_supported(plan, hp->prog, 0, hp->prog.npass, hp->chunk, nullptr, 8, nullptr, 8))
+      radix_supported(plan, *hp, 0, hp->prog.npass, hp->chunk, nullptr, 8, nullptr, 8))
     return radix_rebuilds_in_kernel(plan, hp->prog, 0, hp->prog.npass, hp->chunk) ? "radix_tile_int8"
                                                                                   : "radix_tile";
   if (hp && hp->n_chunk != hp->prog.npass) {
@@ -1720,7 +1726,7 @@ const char *harp_plan_kernel_name(const harp_plan_t *plan, int64_t n, harp_dtype
       return "split_pipe_stream";
     if (wave_supported(plan, hp->prog, p0, hp->n_chunk, hp->chunk, nullptr, 8, nullptr, 8))
       return "split_wave_stream";
-    if (radix_supported(plan, hp->prog, p0, hp->n_chunk, hp->chunk, nullptr, 8, nullptr, 8))
+    if (radix_supported(plan, *hp, p0, hp->n_chunk, hp->chunk, nullptr, 8, nullptr, 8))
       return radix_rebuilds_in_kernel(plan, hp->prog, p0, hp->n_chunk, hp->chunk)
                  ? "split_radix_stream_int8"
                  : "split_radix_stream";

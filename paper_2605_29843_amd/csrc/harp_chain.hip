@@ -1,0 +1,583 @@
+// Chains of three or four small dense stages (8, 8, R3[, R4]) on chunks of 64 * R3 * R4 coordinates: the
+// radix-8 schedules, on the float32 matrix instruction v_mfma_f32_4x4x1_16b_f32.
+//
+// That instruction is sixteen independent 4 x 4 outer-product updates.  Sixteen blocks of a stage
+// times four rows are one operand: lane 4 b + row holds the coordinates of block slot b and that row
+// in registers, lane 4 b + i the block's values K[k][4 h + i]; after one instruction per input k and
+// half h of the outputs the lane (b, row) holds the outputs -- the layout the inputs had.  A block
+// of 64 values costs 16 registers per lane and is used for four rows at once, and a product runs at
+// twice the rate of the vector units, with the same float32 chain of fused multiply-adds.
+//
+// A workgroup takes eight rows of one chunk.  A wave owns sixteen groups of 64 coordinates (R3 * R4 in
+// the high stages) of the eight rows, and a lane holds all coordinates of its group and of two rows
+// (row, row + 4): two stages whose digits both lie inside the group follow each other by renaming
+// registers.  A tile so makes one exchange through LDS, between the two low stages (groups of 64
+// consecutive coordinates) and the high ones (groups of R3 * R4 coordinates 64 apart); one block per
+// thread needed three.  The exchange takes four rows at a time, so that a workgroup needs half the
+// LDS of its rows and two of them (four small ones) share a compute unit: one's loads, exchanges
+// and stores run under the other's products.  Rows enter and leave in 16-byte pieces through the
+// same LDS rows; bf16 rows r and r + 4 travel as the two halves of one word.
+//
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "harp_internal.h"
+
+namespace harp {
+
+namespace {
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+constexpr int kChainRows = 8;   // rows per tile
+
+// registers (16-byte pieces) of one lane for one stage batch: B inputs times one or two halves of the outputs
+constexpr int chain_pieces(int B) { return (B * (B > 4 ? 2 : 1) + 3) / 4; }
+
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  bf2 v;
+  v.x = (__bf16)lo;
+  v.y = (__bf16)hi;
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+// Sizes of one instance; also the layout of the block values: per chunk the stages at strides 1, 8,
+// 64, 64 R3 one after the other, a stage as [unit or block of 16 lo][batch][piece][lane][4].
+template <int R3, int R4>
+struct ChainShape {
+  static constexpr int H = R3 * R4;                   // groups of 64 in a chunk, coordinates of a high group
+  static constexpr int CHUNK = 64 * H;
+  static constexpr int UNITS = (H + 15) / 16;         // sixteen groups each; the last one may be half full
+  static constexpr int NW = H > 32 ? 4 : 2;           // waves
+  static constexpr int LB = 4 / NW;                   // blocks of 16 lo per wave in the high stages
+  static constexpr int PITCH = CHUNK + 8;             // LDS row (floats): four rows x 8 lo hit 32 banks
+  // 16-byte pieces of block values a lane holds: those in use and the next two batches.  Outputs come in
+  // aligned quads while the inputs they replace are spread over other quads, so a stage needs up to 64
+  // registers more than its coordinates: with a ring of 16 every shape spilled, with 8 none of these
+  // is faster (radix 4 has smaller batches: eight pieces are as many ahead and leave it its registers)
+  static constexpr int RING = R4 == 4 ? 8 : 12;
+  static constexpr int NA = 32;                       // pieces per unit, stages at strides 1 and 8
+  static constexpr int NC = R4 * chain_pieces(R3);    // pieces per block of 16 lo
+  static constexpr int ND = R3 * chain_pieces(R4);
+  static constexpr int64_t OFF_B = (int64_t)UNITS * NA * 256;   // floats
+  static constexpr int64_t OFF_C = 2 * OFF_B;
+  static constexpr int64_t OFF_D = OFF_C + (int64_t)4 * NC * 256;
+  static constexpr int64_t TOTAL = OFF_D + (int64_t)4 * ND * 256;
+};
+
+// The block values of a chunk: a buffer descriptor, so that a piece is addressed by one register (16
+// times the lane), a scalar offset and an immediate.  With 64-bit addresses the compiler kept one per
+// piece, spilled them, and every reload waited for all loads in flight (a stage took twice as long).
+struct ChainValues {
+  __amdgpu_buffer_rsrc_t rsrc;
+  int voff;
+  __device__ __forceinline__ f4v piece(int stage_piece, int s) const {   // piece s of the stage that starts at piece stage_piece
+    return __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, (stage_piece + s) * 1024, 0));
+  }
+};
+
+// One stage on the registers of a lane: NB blocks of radix B, input r of block v at x[v * SV + r * SR].
+// Piece s of the stage lies in ring slot s % RING.  A slot that has been used takes the stage's piece
+// RING further on, or, when there is none, the next stage's piece of that slot.
+template <int B, int NB, int SV, int SR, int NNEXT, int NX, int RING>
+__device__ __forceinline__ void chain_stage(float (&x)[2][NX], f4v (&ring)[RING], const ChainValues &val, int own,
+                                            int next) {
+  constexpr int NH = B > 4 ? 2 : 1, NP = chain_pieces(B), CNT = NB * NP;
+#pragma unroll
+  for (int s = CNT; s < RING; ++s)   // slots the stage does not use
+    if (s < NNEXT) ring[s] = val.piece(next, s);
+#pragma unroll
+  for (int v = 0; v < NB; ++v) {
+    f4v acc[2][NH];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int h = 0; h < NH; ++h) acc[g][h] = (f4v){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < B; ++r)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+          acc[g][h] = __builtin_amdgcn_mfma_f32_4x4x1f32(ring[(v * NP + (r * NH + h) / 4) % RING][(r * NH + h) % 4],
+                                                         x[g][v * SV + r * SR], acc[g][h], 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int c = 0; c < B; ++c) x[g][v * SV + c * SR] = acc[g][c / 4][c % 4];
+#pragma unroll
+    for (int s = v * NP; s < (v + 1) * NP; ++s) {
+      if (s + RING < CNT)
+        ring[s % RING] = val.piece(own, s + RING);
+      else if (s % RING < NNEXT)
+        ring[s % RING] = val.piece(next, s % RING);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+__device__ __forceinline__ void lds_barrier() {   // LDS only: loads in flight stay in flight
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ __forceinline__ void wave_fence() {   // other lanes of this wave read what it wrote to LDS
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename TI, typename TO, int R3, int R4, bool TRN>
+__global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_kernel(
+    const TI *X, int64_t ldx, TO *Y, int64_t ldy, int64_t n, int R, unsigned ntile, unsigned total,
+    const float *__restrict__ image) {
+  using S = ChainShape<R3, R4>;
+  constexpr int H = S::H, NW = S::NW, LB = S::LB;
+  constexpr bool BI = sizeof(TI) == 2, BO = sizeof(TO) == 2;
+  constexpr int NR8 = S::CHUNK / 512, NR4 = S::CHUNK / 256;   // 16-byte pieces of a row per lane: bf16, float32
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slot = lane >> 2, row = lane & 3;   // block slot and row of the operand layout
+  // Workgroups go to the eight XCDs in turn; an XCD takes a run of tiles of the same chunk, so that its
+  // L2 holds the block values of few chunks.
+  const unsigned id = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (id >= total) return;   // the whole workgroup
+  const int kch = (int)(id / ntile);
+  const int64_t r0 = (int64_t)(id % ntile) * R;
+  const int nr = (int)((n - r0 < R) ? (n - r0) : R);
+  const ChainValues val = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(image + (int64_t)kch * S::TOTAL), 0,
+                                                              (int)(S::TOTAL * 4), 0x00020000),
+                           lane * 16};
+  const TI *Xt = X + r0 * ldx + (int64_t)kch * S::CHUNK;
+  TO *Yt = Y + r0 * ldy + (int64_t)kch * S::CHUNK;
+
+  // low side: unit u, its groups and coordinates (40 and 48 groups: the fourth wave repeats the last
+  // unit's work and keeps nothing of it)
+  const int u = S::UNITS < NW && w >= S::UNITS ? S::UNITS - 1 : w;
+  const bool low = S::UNITS == NW || w < S::UNITS;
+  const int ngr = (H % 16 != 0 && u == S::UNITS - 1) ? H % 16 : 16;   // groups in the unit (8 or 16)
+  const int gl = slot < ngr ? slot : ngr - 1;
+  // first pieces of the wave's block values in each stage
+  const int iA = u * S::NA, iB = (int)(S::OFF_B / 256) + u * S::NA;
+  const int iC = (int)(S::OFF_C / 256) + w * LB * S::NC, iD = (int)(S::OFF_D / 256) + w * LB * S::ND;
+
+  // LDS position of coordinate (group j, lo) of row r & 3: bit 2 of lo flipped in odd groups (16-byte
+  // accesses of four rows x two groups then fall into different banks)
+  auto pos = [](int r, int j, int lo) { return r * S::PITCH + j * 64 + (lo ^ ((j & 1) << 2)); };
+  // a row's consecutive coordinates 4 c .. 4 c + 3
+  auto pos4 = [](int r, int c) { return r * S::PITCH + ((c ^ ((c >> 4) & 1)) << 2); };
+  // rows past the end repeat the last one and are not stored
+  auto row_ptr = [&](int r) { return Xt + (int64_t)(r < nr ? r : nr - 1) * ldx; };
+
+  f4v ring[S::RING];
+  auto first_pieces = [&](int p, int cnt) {
+#pragma unroll
+    for (int s = 0; s < S::RING; ++s)
+      if (s < cnt) ring[s] = val.piece(p, s);
+  };
+  // a lane's 16-byte pieces 2 l and 2 l + 1 of eight words: which one goes first alternates every four
+  // lanes, so that eight lanes hit all banks
+  const int sw = (lane >> 2) & 1;
+
+  if constexpr (!TRN) {
+    float x[2][64];
+    // rows of the unit through the wave's own part of the LDS rows (bf16: rows r and r + 4 one after
+    // the other), coordinates of a group side by side
+    if constexpr (BI) {
+      u4v raw[8][2];
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (i * 512 < ngr * 64)
+            raw[r][i] = *reinterpret_cast<const u4v *>(row_ptr(r) + u * 1024 + (i * 64 + lane) * 8);
+      first_pieces(iA, S::NA);
+      __builtin_amdgcn_sched_barrier(0);
+      char *base = reinterpret_cast<char *>(lds) + u * 4096;
+      auto at = [&](int r, int g, int s) {
+        return reinterpret_cast<u4v *>(base + (r & 3) * S::PITCH * 4 + (r >> 2) * (ngr * 128) + g * 128 +
+                                       ((s ^ (((g & 1) << 2) + (r & 3))) << 4));
+      };
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (low && i * 512 < ngr * 64) *at(r, i * 8 + (lane >> 3), lane & 7) = raw[r][i];
+      wave_fence();
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const u4v q = *at(row + 4 * h, gl, s);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            x[h][8 * s + 2 * e] = __uint_as_float(q[e] << 16);
+            x[h][8 * s + 2 * e + 1] = __uint_as_float(q[e] & 0xffff0000u);
+          }
+        }
+    } else {
+      u4v raw[8][4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i * 256 < ngr * 64)
+            raw[r][i] = *reinterpret_cast<const u4v *>(row_ptr(r) + u * 1024 + (i * 64 + lane) * 4);
+      first_pieces(iA, S::NA);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (low && i * 256 < ngr * 64)
+              *reinterpret_cast<u4v *>(lds + pos4(r, u * 256 + i * 64 + lane)) = raw[4 * h + r][i];
+        wave_fence();
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+          const f4v q = *reinterpret_cast<const f4v *>(lds + pos(row, u * 16 + gl, 4 * s));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[h][4 * s + e] = q[e];
+        }
+        wave_fence();
+      }
+    }
+    wave_fence();
+    chain_stage<8, 8, 8, 1, S::NA>(x, ring, val, iA, iB);
+    chain_stage<8, 8, 1, 8, S::NC>(x, ring, val, iB, iC);
+    float y[LB][2][H];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (low && slot < ngr) {
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+          *reinterpret_cast<f4v *>(lds + pos(row, u * 16 + slot, 4 * s)) =
+              (f4v){x[h][4 * s], x[h][4 * s + 1], x[h][4 * s + 2], x[h][4 * s + 3]};
+      }
+      lds_barrier();
+#pragma unroll
+      for (int b = 0; b < LB; ++b)
+#pragma unroll
+        for (int j = 0; j < H; ++j) y[b][h][j] = lds[pos(row, j, (w * LB + b) * 16 + slot)];
+      lds_barrier();
+    }
+#pragma unroll
+    for (int b = 0; b < LB; ++b) {
+      chain_stage<R3, R4, R3, 1, S::ND>(y[b], ring, val, iC + b * S::NC, iD + b * S::ND);
+      chain_stage<R4, R3, 1, R3, (S::LB > 1 ? S::NC : 0)>(y[b], ring, val, iD + b * S::ND,
+                                                          iC + (b + 1 < LB ? b + 1 : b) * S::NC);
+    }
+    if constexpr (BO) {
+#pragma unroll
+      for (int b = 0; b < LB; ++b)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+          lds[pos(row, j, (w * LB + b) * 16 + slot)] = __uint_as_float(pack2(y[b][0][j], y[b][1][j]));
+      lds_barrier();
+#pragma unroll
+      for (int r = w; r < 4; r += NW) {
+#pragma unroll
+        for (int i = 0; i < NR8; ++i) {
+          const int c = 2 * (i * 64 + lane);
+          const u4v a = *reinterpret_cast<const u4v *>(lds + pos4(r, c + sw));
+          const u4v b = *reinterpret_cast<const u4v *>(lds + pos4(r, c + 1 - sw));
+          const u4v lo = sw ? b : a, hi = sw ? a : b;
+          const u4v p0 = {__builtin_amdgcn_perm(lo[1], lo[0], 0x05040100u), __builtin_amdgcn_perm(lo[3], lo[2], 0x05040100u),
+                          __builtin_amdgcn_perm(hi[1], hi[0], 0x05040100u), __builtin_amdgcn_perm(hi[3], hi[2], 0x05040100u)};
+          const u4v p1 = {__builtin_amdgcn_perm(lo[1], lo[0], 0x07060302u), __builtin_amdgcn_perm(lo[3], lo[2], 0x07060302u),
+                          __builtin_amdgcn_perm(hi[1], hi[0], 0x07060302u), __builtin_amdgcn_perm(hi[3], hi[2], 0x07060302u)};
+          if (r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + (i * 64 + lane) * 8) = p0;
+          if (r + 4 < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)(r + 4) * ldy + (i * 64 + lane) * 8) = p1;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h) lds_barrier();
+#pragma unroll
+        for (int b = 0; b < LB; ++b)
+#pragma unroll
+          for (int j = 0; j < H; ++j) lds[pos(row, j, (w * LB + b) * 16 + slot)] = y[b][h][j];
+        lds_barrier();
+#pragma unroll
+        for (int r = w; r < 4; r += NW)
+          if (4 * h + r < nr) {
+#pragma unroll
+            for (int i = 0; i < NR4; ++i)
+              *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + (i * 64 + lane) * 4) =
+                  *reinterpret_cast<const u4v *>(lds + pos4(r, i * 64 + lane));
+          }
+      }
+    }
+  } else {
+    float y[LB][2][H];
+    if constexpr (BI) {
+      u4v raw[LB][2][NR8];   // wave w: rows w (w, w + 2) and the one four further on
+#pragma unroll
+      for (int k = 0; k < LB; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < NR8; ++i)
+            raw[k][h][i] = *reinterpret_cast<const u4v *>(row_ptr(w + k * NW + 4 * h) + (i * 64 + lane) * 8);
+      first_pieces(iD, S::ND);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < LB; ++k)
+#pragma unroll
+        for (int i = 0; i < NR8; ++i) {
+          const u4v p = raw[k][0][i], q = raw[k][1][i];
+          u4v a, b;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            a[2 * e] = __builtin_amdgcn_perm(q[e], p[e], 0x05040100u);
+            a[2 * e + 1] = __builtin_amdgcn_perm(q[e], p[e], 0x07060302u);
+            b[2 * e] = __builtin_amdgcn_perm(q[2 + e], p[2 + e], 0x05040100u);
+            b[2 * e + 1] = __builtin_amdgcn_perm(q[2 + e], p[2 + e], 0x07060302u);
+          }
+          const int c = 2 * (i * 64 + lane);
+          *reinterpret_cast<u4v *>(lds + pos4(w + k * NW, c + sw)) = sw ? b : a;
+          *reinterpret_cast<u4v *>(lds + pos4(w + k * NW, c + 1 - sw)) = sw ? a : b;
+        }
+      lds_barrier();
+#pragma unroll
+      for (int b = 0; b < LB; ++b)
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          const uint32_t q = __float_as_uint(lds[pos(row, j, (w * LB + b) * 16 + slot)]);
+          y[b][0][j] = __uint_as_float(q << 16);
+          y[b][1][j] = __uint_as_float(q & 0xffff0000u);
+        }
+    } else {
+      u4v raw[2][LB][NR4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < LB; ++k)
+#pragma unroll
+          for (int i = 0; i < NR4; ++i)
+            raw[h][k][i] = *reinterpret_cast<const u4v *>(row_ptr(4 * h + w + k * NW) + (i * 64 + lane) * 4);
+      first_pieces(iD, S::ND);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h) lds_barrier();
+#pragma unroll
+        for (int k = 0; k < LB; ++k)
+#pragma unroll
+          for (int i = 0; i < NR4; ++i)
+            *reinterpret_cast<u4v *>(lds + pos4(w + k * NW, i * 64 + lane)) = raw[h][k][i];
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < LB; ++b)
+#pragma unroll
+          for (int j = 0; j < H; ++j) y[b][h][j] = lds[pos(row, j, (w * LB + b) * 16 + slot)];
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < LB; ++b) {
+      chain_stage<R4, R3, 1, R3, S::NC>(y[b], ring, val, iD + b * S::ND, iC + b * S::NC);
+      if (b + 1 < LB)
+        chain_stage<R3, R4, R3, 1, S::ND>(y[b], ring, val, iC + b * S::NC, iD + (b + 1 < LB ? b + 1 : b) * S::ND);
+      else
+        chain_stage<R3, R4, R3, 1, S::NA>(y[b], ring, val, iC + b * S::NC, iB);
+    }
+    float x[2][64];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      lds_barrier();   // everyone has read the rows that are overwritten here
+#pragma unroll
+      for (int b = 0; b < LB; ++b)
+#pragma unroll
+        for (int j = 0; j < H; ++j) lds[pos(row, j, (w * LB + b) * 16 + slot)] = y[b][h][j];
+      lds_barrier();
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const f4v q = *reinterpret_cast<const f4v *>(lds + pos(row, u * 16 + gl, 4 * s));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[h][4 * s + e] = q[e];
+      }
+    }
+    wave_fence();
+    chain_stage<8, 8, 1, 8, S::NA>(x, ring, val, iB, iA);
+    chain_stage<8, 8, 8, 1, 0>(x, ring, val, iA, iA);
+    // back through the wave's own part of the LDS rows: 16-byte stores of whole lines
+    if constexpr (BO) {
+      char *base = reinterpret_cast<char *>(lds) + u * 4096;
+      auto at = [&](int r, int g, int s) {
+        return reinterpret_cast<u4v *>(base + (r & 3) * S::PITCH * 4 + (r >> 2) * (ngr * 128) + g * 128 +
+                                       ((s ^ (((g & 1) << 2) + (r & 3))) << 4));
+      };
+      if (low && slot < ngr) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int s = 0; s < 8; ++s) {
+            u4v q;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[e] = pack2(x[h][8 * s + 2 * e], x[h][8 * s + 2 * e + 1]);
+            *at(row + 4 * h, slot, s) = q;
+          }
+      }
+      wave_fence();
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (low && i * 512 < ngr * 64) {
+            const u4v q = *at(r, i * 8 + (lane >> 3), lane & 7);
+            if (r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + u * 1024 + (i * 64 + lane) * 8) = q;
+          }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (low && slot < ngr) {
+#pragma unroll
+          for (int s = 0; s < 16; ++s)
+            *reinterpret_cast<f4v *>(lds + pos(row, u * 16 + slot, 4 * s)) =
+                (f4v){x[h][4 * s], x[h][4 * s + 1], x[h][4 * s + 2], x[h][4 * s + 3]};
+        }
+        wave_fence();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (low && i * 256 < ngr * 64) {
+              const u4v q = *reinterpret_cast<const u4v *>(lds + pos4(r, u * 256 + i * 64 + lane));
+              if (4 * h + r < nr)
+                *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + u * 1024 + (i * 64 + lane) * 4) = q;
+            }
+        wave_fence();
+      }
+    }
+  }
+}
+
+template <typename TI, typename TO, int R3, int R4, bool TRN>
+harp_status_t launch_chain_inst(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx, void *Y,
+                                int64_t ldy, int64_t n, hipStream_t stream) {
+  using S = ChainShape<R3, R4>;
+  constexpr size_t lds = (size_t)(kChainRows / 2) * S::PITCH * 4;
+  if (lds > (size_t)plan->lds_bytes) return HARP_ERR_UNSUPPORTED;
+  int R = kChainRows;
+  if (plan->rows_override > 0 && plan->rows_override < R) R = plan->rows_override;
+  const int nchunk = (int)(plan->d / S::CHUNK);
+  const int64_t ntile = (n + R - 1) / R;
+  const int64_t total = ntile * nchunk;
+  if (total > 0x7ffffff0) return HARP_ERR_UNSUPPORTED;
+  auto kern = harp_chain_kernel<TI, TO, R3, R4, TRN>;
+  static thread_local int attr_done_dev = -1;   // per instantiation
+  if (attr_done_dev != plan->device) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            plan->lds_bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return HARP_ERR_DEVICE;
+    }
+    attr_done_dev = plan->device;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * S::NW), lds, stream, (const TI *)X, ldx,
+                     (TO *)Y, ldy, n, R, (unsigned)ntile, (unsigned)total, ci.img);
+  return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
+}
+
+template <int R3, int R4>
+harp_status_t launch_chain_shape(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx,
+                                 harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
+                                 hipStream_t stream) {
+#define HARP_CHAIN_IO(TI, TO)                                                                  \
+  (ci.trn ? launch_chain_inst<TI, TO, R3, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream)      \
+          : launch_chain_inst<TI, TO, R3, R4, false>(plan, ci, X, ldx, Y, ldy, n, stream))
+  if (dt_in == HARP_BF16)
+    return dt_out == HARP_BF16 ? HARP_CHAIN_IO(uint16_t, uint16_t) : HARP_CHAIN_IO(uint16_t, float);
+  if (dt_out == HARP_F32) return HARP_CHAIN_IO(float, float);
+  // float32 in, bf16 out: only behind the streamed stages of a transposed split program
+  if (!ci.trn) return HARP_ERR_UNSUPPORTED;
+  return launch_chain_inst<float, uint16_t, R3, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream);
+#undef HARP_CHAIN_IO
+}
+
+template <int R3, int R4>
+void pack_chain(const Program &pg, int p0, bool trn, const std::vector<size_t> &offsets, int64_t nchunk,
+                std::vector<float> &image, size_t off) {
+  using S = ChainShape<R3, R4>;
+  for (int e = 0; e < 4; ++e) {   // the stages by stride
+    const int p = trn ? p0 + 3 - e : p0 + e, b = pg.pass[p].b, nh = b > 4 ? 2 : 1, np = chain_pieces(b);
+    const int64_t nq = pg.pass[p].nq, s = pg.pass[p].S, nqc = S::CHUNK / b;
+    const int units = e < 2 ? S::UNITS : 4, batches = e < 2 ? 8 : (e == 2 ? R4 : R3);
+    const int64_t base = e == 0 ? 0 : (e == 1 ? S::OFF_B : (e == 2 ? S::OFF_C : S::OFF_D));
+    for (int64_t k = 0; k < nchunk; ++k)
+      for (int u = 0; u < units; ++u) {
+        // (past the chunk's groups: zeros)
+        const int slots = e < 2 && S::H - 16 * u < 16 ? S::H - 16 * u : 16;
+        for (int v = 0; v < batches; ++v)
+          for (int r = 0; r < b; ++r)
+            for (int c = 0; c < b; ++c) {
+              const int w = r * nh + c / 4;
+              const float *from = image.data() + offsets[p] + (size_t)(r * b + c) * nq + k * nqc;
+              float *to = image.data() + off + (size_t)(k * S::TOTAL + base) +
+                          ((((size_t)u * batches + v) * np + w / 4) * 64 + c % 4) * 4 + w % 4;
+              for (int slot = 0; slot < slots; ++slot) {
+                // coordinate of the block's input 0 inside the chunk, then the block
+                const int64_t c0 = e == 0   ? (u * 16 + slot) * 64 + 8 * v
+                                   : e == 1 ? (u * 16 + slot) * 64 + v
+                                   : e == 2 ? (int64_t)v * 64 * R3 + u * 16 + slot
+                                            : (int64_t)v * 64 + u * 16 + slot;
+                to[slot * 16] = from[(c0 / (b * s)) * s + c0 % s];
+              }
+            }
+      }
+  }
+}
+
+#define HARP_CHAIN_R4(r4, STMT)                              \
+  switch (r4) {                                               \
+    case 3: { constexpr int R4 = 3; STMT; } break;            \
+    case 4: { constexpr int R4 = 4; STMT; } break;            \
+    case 5: { constexpr int R4 = 5; STMT; } break;            \
+    case 6: { constexpr int R4 = 6; STMT; } break;            \
+    case 7: { constexpr int R4 = 7; STMT; } break;            \
+    default: { constexpr int R4 = 8; STMT; } break;           \
+  }
+
+}  // namespace
+
+// The chunk passes [p0, p0 + np) as a chain of radices 8, 8, 8, R4: appends the block values in the
+// kernel's order to the program's host image.
+void build_chain_image(HostProgram &hp, int p0, int np, int64_t d, const std::vector<size_t> &offsets,
+                       std::vector<float> &image) {
+  hp.chain = ChainImage();
+  if (np != 4) return;
+  const Program &pg = hp.prog;
+  const bool trn = pg.pass[p0].S != 1;
+  int64_t s = 1;
+  for (int e = 0; e < 4; ++e) {
+    const PassDesc &pd = pg.pass[trn ? p0 + 3 - e : p0 + e];
+    if (pd.kind != PASS_SMALL || pd.tied || pd.S != s || (e < 3 ? pd.b != 8 : pd.b < 3)) return;
+    s *= pd.b;
+  }
+  if (s != hp.chunk || d % s) return;
+  const int r4 = pg.pass[trn ? p0 : p0 + 3].b;
+  const size_t off = (image.size() + 63) / 64 * 64;
+  const int64_t nchunk = d / s;
+  HARP_CHAIN_R4(r4, (image.resize(off + (size_t)(nchunk * ChainShape<8, R4>::TOTAL), 0.0f),
+                     pack_chain<8, R4>(pg, p0, trn, offsets, nchunk, image, off)));
+  hp.chain.host_off = (int64_t)off;
+  hp.chain.r4 = r4;
+  hp.chain.trn = trn;
+}
+
+harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx,
+                                  harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
+                                  hipStream_t stream) {
+  harp_status_t st = HARP_ERR_UNSUPPORTED;
+  HARP_CHAIN_R4(ci.r4, (st = launch_chain_shape<8, R4>(plan, ci, X, ldx, dt_in, Y, ldy, dt_out, n, stream)));
+  return st;
+}
+
+}  // namespace harp

@@ -98,8 +98,17 @@ struct DppImage {
   int64_t offT = 0;
 };
 
+// Block values of a chunk's stages of radices 8, 8, 8, r4 in the order of harp_chain_kernel.
+struct ChainImage {
+  const float *img = nullptr;   // device; null: the chunk is not such a chain
+  int64_t host_off = -1;        // offset (floats) inside the program's host image, -1: none
+  int32_t r4 = 0;
+  bool trn = false;
+};
+
 struct HostProgram {
   DppImage dpp;
+  ChainImage chain;
   Program prog{};
   const Program *dev = nullptr;  // device copy of prog (what the kernels read)
   int64_t param_bytes = 0;
@@ -310,12 +319,18 @@ harp_status_t plan_attach_theta_int8(harp_plan *plan, const int8_t *const *codes
                                      const float *const *scales, const int32_t *mixer_kinds,
                                      const int8_t *signs);
 // tile kernel for chains of equal radix 4 or 8 on chunks of 4^m / 8^m coordinates (harp_radix.hip)
-bool radix_supported(const harp_plan *plan, const Program &prog, int p0, int np, int chunk,
+bool radix_supported(const harp_plan *plan, const HostProgram &hp, int p0, int np, int chunk,
                      const void *X, int64_t ldx, const void *Y, int64_t ldy);
 bool radix_rebuilds_in_kernel(const harp_plan *plan, const Program &prog, int p0, int np, int chunk);
 harp_status_t launch_radix_kernel(const harp_plan *plan, const HostProgram &hp, int p0, int np,
                                   int chunk, const void *X, int64_t ldx, harp_dtype_t dt_in,
                                   void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
+                                  hipStream_t stream);
+// chain of radices 8, 8, 8, 3..8 on the float32 matrix instruction (harp_chain.hip)
+void build_chain_image(HostProgram &hp, int p0, int np, int64_t d, const std::vector<size_t> &offsets,
+                       std::vector<float> &image);
+harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx,
+                                  harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
                                   hipStream_t stream);
 // column-mode passes (harp_col.hip): group plan->col[dir] into passes; launch one pass on a
 // row-major [nrows, ncols] matrix (nrows == plan->d; may run in place)

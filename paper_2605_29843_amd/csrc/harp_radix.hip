@@ -580,7 +580,7 @@ RadixShape radix_decode(const Program &pg, int p0, int np, int chunk) {
   if (B != 4 && B != 8) return rs;
   int64_t prod = 1;
   for (int p = 0; p < np; ++p) {
-    if (ps[p].kind != PASS_SMALL || ps[p].b != B || ps[p].aux == nullptr) return rs;
+    if (ps[p].kind != PASS_SMALL || ps[p].b != B || (!ps[p].aux && !ps[p].q8)) return rs;
     prod *= B;
   }
   if (prod != chunk) return rs;
@@ -663,10 +663,13 @@ harp_status_t launch_radix_io(const harp_plan *plan, const HostProgram &hp, int 
 
 }  // namespace
 
-bool radix_supported(const harp_plan *plan, const Program &pg, int p0, int np, int chunk,
+bool radix_supported(const harp_plan *plan, const HostProgram &hp, int p0, int np, int chunk,
                      const void *X, int64_t ldx, const void *Y, int64_t ldy) {
+  const Program &pg = hp.prog;
   if (plan->algo == HARP_ALGO_GENERIC) return false;
-  if (!radix_decode(pg, p0, np, chunk).ok && mixed_decode(pg, p0, np, chunk) == 0) return false;
+  if (!(hp.chain.img && np == hp.n_chunk) && !radix_decode(pg, p0, np, chunk).ok &&
+      mixed_decode(pg, p0, np, chunk) == 0)
+    return false;
   // 16-byte accesses of the contiguous stage for either element type
   if ((ldx % 8) || (ldy % 8) || ((uintptr_t)X % 16) || ((uintptr_t)Y % 16)) return false;
   return (size_t)(chunk + (chunk >> 6) * 8) * 4 <= (size_t)plan->lds_bytes;
@@ -682,6 +685,8 @@ harp_status_t launch_radix_kernel(const harp_plan *plan, const HostProgram &hp, 
                                   void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
                                   hipStream_t stream) {
   const RadixShape rs = radix_decode(hp.prog, p0, np, chunk);
+  if (hp.chain.img && np == hp.n_chunk && !(rs.q8 && plan->theta_in_kernel))
+    return launch_chain_kernel(plan, hp.chain, X, ldx, dt_in, Y, ldy, dt_out, n, stream);
   if (!rs.ok) {
     const int nt = mixed_decode(hp.prog, p0, np, chunk);
     if (nt == 0) return HARP_ERR_UNSUPPORTED;
