@@ -1,5 +1,6 @@
-// Tile kernel for chains of equal small radices (all stages radix 4 or all radix 8, e.g. the
-// 4 x radix-8 schedule of d = 4096): rows, or contiguous row chunks, of B^m coordinates.
+// Tile kernel for chains of equal small radices (all stages radix 4 or all radix 8): rows, or contiguous
+// row chunks, of B^m coordinates.  (Chains of radices 8, 8, 8, 3..8 run on harp_chain_kernel, except
+// those whose blocks are rebuilt from int8 codes.)
 //
 // A dense B x B block costs B^2 parameters per B coordinates, so the parameters of a whole row
 // (0.5 MB for 4096 = 8^4) do not fit the register file of a compute unit: they are re-read for
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(512) void harp_radix_kernel(const TI *__restrict__ 
 
 // ------------------------------------------------------------------------------------------
 // The same organisation for chunks whose stages have different radices in 3..8 (the greedy
-// schedules of the paper: (8,8,8,7) inside d = 14336, (8,8,8,5) inside 5120): the radix of a
+// schedules of the paper: (8,8,4) inside d = 11008): the radix of a
 // stage is a run-time value dispatched to the compile-time bodies above, one block per thread
 // (blockDim.x = the largest number of blocks of any stage; threads beyond a stage's count idle).
 typedef float vec4f_t __attribute__((ext_vector_type(4)));
