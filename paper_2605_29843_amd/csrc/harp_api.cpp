@@ -557,10 +557,12 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
     image.resize(image.size() + (size_t)pd.V * nqp);
     float *img = image.data() + offsets.back();
     // sub-tensor q = hi*S + lo is exactly block c = alpha*s + beta with alpha = hi, beta = lo
-    for (int64_t q = 0; q < nqp; ++q)
-      for (int r = 0; r < b; ++r)
-        for (int r2 = 0; r2 < b; ++r2)
-          img[(size_t)(r * b + r2) * nqp + q] = se.dense[((size_t)q * b + r) * b + r2];
+    // (sixteen blocks at a time: whole lines are written, and the lines read stay in the cache)
+    for (int64_t q0 = 0; q0 < nqp; q0 += 16) {
+      const int64_t q1 = std::min<int64_t>(q0 + 16, nqp);
+      for (int v = 0; v < b * b; ++v)
+        for (int64_t q = q0; q < q1; ++q) img[(size_t)v * nqp + q] = se.dense[(size_t)q * b * b + v];
+    }
     if (small && (b == 4 || b == 8) && !(chain && local(i))) {
       // second copy for the equal-radix tile kernel, four values per 16-byte load:
       // value v = 4 * v4 + i of sub-tensor q at float index ((v4 * nq) + q) * 4 + i
@@ -878,8 +880,8 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
   // place of a transposed copy (the same direction flag as the row side: U^T M uses the
   // forward stage order, U M the transposed one).  Intermediates stay in float32 so that a
   // bf16 matrix is rounded once, at the final store.
-  const std::vector<ColPassHost> &cps = pu->colpass[dir];
-  if (!cps.empty()) {
+  if (!pu->colpass[dir].empty()) {
+    const std::vector<ColPassHost> *cps = &pu->colpass[dir];
     float *A = (float *)ws;   // [d_out, d_in] float32, or block-scaled halves (see below)
     // plan_V as a split program with one streamed small-radix stage: that stage acts on the
     // columns and commutes with plan_U's stages, so it rides along with one column pass instead
@@ -897,10 +899,10 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
     const int64_t zl = z16_ld(d_in);
     bool zws = dt == HARP_BF16 && pu->orthogonal && (!pv || pv->orthogonal) && !pu->f32_only &&
                !(pv && pv->f32_only) &&
-               (cps.size() > 1 || pv) && (uintptr_t)ws % 16 == 0;
-    for (size_t p = 0; p < cps.size() && zws; ++p)
-      zws = col_z16_supported(cps[p].pass, W, ldw, Wout, ldo, d_out, d_in) &&
-            col_z16_supported(cps[p].pass, A, zl, A, zl, d_out, d_in);
+               (cps->size() > 1 || pv) && (uintptr_t)ws % 16 == 0;
+    for (size_t p = 0; p < cps->size() && zws; ++p)
+      zws = col_z16_supported((*cps)[p].pass, W, ldw, Wout, ldo, d_out, d_in) &&
+            col_z16_supported((*cps)[p].pass, A, zl, A, zl, d_out, d_in);
     // plan_V's on-chip passes with the halves on the workspace side
     auto chunk_z16_ok = [&]() {
       return dir == DIR_FWD ? dpp_supported(pv, vhp->dpp, vhp->chunk, W, ldw, HARP_BF16, A, zl, ZT)
@@ -913,14 +915,14 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
     auto find_fuse = [&](bool z) {
       const harp_dtype_t wt = z ? ZT : HARP_F32;
       const int64_t wld = z ? zl : d_in;
-      for (int p = (int)cps.size() - 1; p >= 0; --p) {
-        const bool first = (p == 0), last = (p + 1 == (int)cps.size());
+      for (int p = (int)cps->size() - 1; p >= 0; --p) {
+        const bool first = (p == 0), last = (p + 1 == (int)cps->size());
         // what this pass reads and writes in the fused order
         const bool reads_w = (dir == DIR_TRN) && first;
         const bool writes_out = (dir == DIR_FWD) && last;
         const void *src = reads_w ? W : (const void *)A;
         const void *dst = writes_out ? (const void *)Wout : (const void *)A;
-        if (colrow_supported(pu, cps[p].pass, *vp, src, reads_w ? ldw : wld, reads_w ? dt : wt, dst,
+        if (colrow_supported(pu, (*cps)[p].pass, *vp, src, reads_w ? ldw : wld, reads_w ? dt : wt, dst,
                              writes_out ? ldo : wld, writes_out ? dt : wt, d_out, d_in))
           return p;
       }
@@ -942,6 +944,23 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
       zws = false;   // several streamed trips: plan_V runs on its own, through float32
     }
     if (zws && pv && fuse < 0 && !own_trip && vhp->n_chunk != vhp->prog.npass) zws = false;
+    // Float32 workspace: the passes of 512 rows, if they are fewer and take every matrix as it lies -- unless
+    // plan_V's streamed stage then loses the pass it rides along with (a trip saved, a trip added).
+    if (!zws && !pu->colwide[dir].empty()) {
+      const std::vector<ColPassHost> *narrow = cps;
+      const int narrow_fuse = fuse;
+      cps = &pu->colwide[dir];
+      fuse = one_streamed ? find_fuse(false) : -1;
+      bool ok = fuse >= 0 || narrow_fuse < 0;
+      for (size_t p = 0; p < cps->size(); ++p)
+        if ((*cps)[p].pass.wide)
+          ok = ok && col_wide_supported(pu, (*cps)[p].pass, nullptr, W, ldw, dt, Wout, ldo, dt, d_out, d_in) &&
+               col_wide_supported(pu, (*cps)[p].pass, nullptr, A, d_in, HARP_F32, A, d_in, HARP_F32, d_out, d_in);
+      if (!ok) {
+        cps = narrow;
+        fuse = narrow_fuse;
+      }
+    }
     const harp_dtype_t wt = zws ? ZT : HARP_F32;
     const int64_t wld = zws ? zl : d_in;
     const void *src = W;
@@ -955,7 +974,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
     // (also when no column pass can take the stage along: a radix-2 stage on the top digit)
     if (zws && own_trip) {
       bool regs = true;
-      for (size_t p = 0; p < cps.size(); ++p) regs = regs && col_pass_in_registers(cps[p].pass, d_in);
+      for (size_t p = 0; p < cps->size(); ++p) regs = regs && col_pass_in_registers((*cps)[p].pass, d_in);
       const int ps = vhp->chunk_first ? vhp->n_chunk : 0, c0 = vhp->chunk_first ? 0 : 1;
       const bool fwd = (dir == DIR_FWD);
       if (regs || fuse < 0) {
@@ -963,8 +982,8 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
           st = run_chunk_passes(pv, *vhp, c0, c0 + vhp->n_chunk, W, ldw, dt, A, zl, ZT, d_out, s);
         else
           st = launch_stream_pass(pv, *vhp, ps, W, ldw, dt, A, zl, ZT, d_out, true, s);
-        for (size_t p = 0; p < cps.size() && st == HARP_OK; ++p)
-          st = launch_col_pass(pu, cps[p].dev, cps[p].pass, A, zl, ZT, A, zl, ZT, d_out, d_in, s);
+        for (size_t p = 0; p < cps->size() && st == HARP_OK; ++p)
+          st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, A, zl, ZT, A, zl, ZT, d_out, d_in, s);
         if (st != HARP_OK) return st;
         if (fwd) return launch_stream_pass(pv, *vhp, ps, A, zl, ZT, Wout, ldo, dt, d_out, true, s);
         return run_chunk_passes(pv, *vhp, c0, c0 + vhp->n_chunk, A, zl, ZT, Wout, ldo, dt, d_out, s);
@@ -979,16 +998,16 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
         src_ld = wld;
         src_dt = wt;
       }
-      for (size_t p = 0; p < cps.size(); ++p) {
-        const bool to_out = (dir == DIR_FWD) && (p + 1 == cps.size());
+      for (size_t p = 0; p < cps->size(); ++p) {
+        const bool to_out = (dir == DIR_FWD) && (p + 1 == cps->size());
         void *dst = to_out ? Wout : (void *)A;
         const int64_t dst_ld = to_out ? ldo : wld;
         const harp_dtype_t dst_dt = to_out ? dt : wt;
         if ((int)p == fuse)
-          st = launch_colrow_pass(pu, cps[p].dev, cps[p].pass, *vp, src, src_ld, src_dt, dst, dst_ld,
+          st = launch_colrow_pass(pu, (*cps)[p].dev, (*cps)[p].pass, *vp, src, src_ld, src_dt, dst, dst_ld,
                                   dst_dt, d_out, d_in, s);
         else
-          st = launch_col_pass(pu, cps[p].dev, cps[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
+          st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
                                d_out, d_in, s);
         if (st != HARP_OK) return st;
         src = dst;
@@ -1012,12 +1031,12 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
       src_ld = wld;
       src_dt = wt;
     }
-    for (size_t p = 0; p < cps.size(); ++p) {
-      const bool last = (p + 1 == cps.size()) && !v_last;
+    for (size_t p = 0; p < cps->size(); ++p) {
+      const bool last = (p + 1 == cps->size()) && !v_last;
       void *dst = last ? Wout : (void *)A;
       const int64_t dst_ld = last ? ldo : wld;
       const harp_dtype_t dst_dt = last ? dt : wt;
-      st = launch_col_pass(pu, cps[p].dev, cps[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
+      st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
                            d_out, d_in, s);
       if (st != HARP_OK) return st;
       src = dst;
@@ -1444,32 +1463,29 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
         plan->colpass[dir].clear();
         continue;
       }
-      ColPass *dp = nullptr;
-      const size_t np = plan->colpass[dir].size();
-      if (hipMalloc((void **)&dp, np * sizeof(ColPass)) != hipSuccess) {
-        st = HARP_ERR_OOM;
-        break;
-      }
-      plan->dev_allocs.push_back(dp);
-      for (size_t i = 0; i < np && st == HARP_OK; ++i) {
-        ColPassHost &ph = plan->colpass[dir][i];
-        uint32_t *dtab = nullptr;
-        if (hipMalloc((void **)&dtab, ph.ptab.size() * 4) != hipSuccess) {
-          st = HARP_ERR_OOM;
-          break;
+      if (!build_col_passes(plan, (Direction)dir, plan->colwide[dir], image.data()) ||
+          plan->colwide[dir].size() >= plan->colpass[dir].size())
+        plan->colwide[dir].clear();
+      auto upload = [&](const void *host, size_t bytes, void **dev) {
+        if (hipMalloc(dev, bytes) != hipSuccess) return HARP_ERR_OOM;
+        plan->dev_allocs.push_back(*dev);
+        return hipMemcpy(*dev, host, bytes, hipMemcpyHostToDevice) == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
+      };
+      for (std::vector<ColPassHost> *passes : {&plan->colpass[dir], &plan->colwide[dir]})
+        for (ColPassHost &ph : *passes) {
+          void *dev = nullptr;
+          if (st == HARP_OK && !ph.ptab.empty()) {
+            st = upload(ph.ptab.data(), ph.ptab.size() * 4, &dev);
+            ph.pass.ptab = (const uint32_t *)dev;
+          }
+          if (st == HARP_OK && !ph.wide.empty()) {
+            st = upload(ph.wide.data(), ph.wide.size() * 4, &dev);
+            ph.pass.wide = (const float *)dev;
+            std::vector<float>().swap(ph.wide);
+          }
+          if (st == HARP_OK) st = upload(&ph.pass, sizeof(ColPass), &dev);
+          ph.dev = (const ColPass *)dev;
         }
-        plan->dev_allocs.push_back(dtab);
-        if (hipMemcpy(dtab, ph.ptab.data(), ph.ptab.size() * 4, hipMemcpyHostToDevice) !=
-            hipSuccess) {
-          st = HARP_ERR_DEVICE;
-          break;
-        }
-        ph.pass.ptab = dtab;
-        if (hipMemcpy(dp + i, &plan->colpass[dir][i].pass, sizeof(ColPass),
-                      hipMemcpyHostToDevice) != hipSuccess)
-          st = HARP_ERR_DEVICE;
-        plan->colpass[dir][i].dev = dp + i;
-      }
     }
   } catch (const std::bad_alloc &) {
     st = HARP_ERR_OOM;

@@ -1066,7 +1066,7 @@ harp_status_t launch_colrow_typed(const harp_plan *plan, const ColPass *dpass, c
 // Host side: group the stages of plan->col[dir] (execution order) into passes and steps, and
 // list for every pass the block values a tile needs.  Returns false when the plan has no
 // column-mode image (a radix above 8).
-bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out) {
+bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out, const float *host_image) {
   const std::vector<ColStage> &st = plan->col[dir];
   out.clear();
   if (st.empty()) return false;
@@ -1080,6 +1080,10 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
   // per tile: 28672 = 7 * 2^12 ended in a pass of P = 2 that took three times as long as the
   // other two together).  Ties go to the taller first pass.
   auto fits = [&](int i0, int e0, int &Pout) {
+    if (host_image && e0 == i0 + 3 && col_wide_stages(st, i0)) {
+      Pout = 512;
+      return true;
+    }
     int P = 1;
     for (int t = i0; t < e0; ++t) {
       if (P * st[t].b > kColMaxP) return false;
@@ -1118,6 +1122,11 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
     ph.dev = nullptr;
     ColPass &cp = ph.pass;
     memset(&cp, 0, sizeof(cp));
+    if (P == 512) {
+      col_wide_image(st, i, plan->d, host_image, cp, ph.wide);
+      i = e;
+      continue;
+    }
     cp.P = P;
     cp.S = S;
     cp.image = image;
@@ -1178,6 +1187,7 @@ harp_status_t launch_col_pass(const harp_plan *plan, const ColPass *dpass, const
                               harp_dtype_t dt_dst, int64_t nrows, int64_t ncols,
                               hipStream_t stream) {
   if (nrows % hp.P != 0) return HARP_ERR_INVALID_ARG;
+  if (hp.wide) return launch_col_wide(plan, hp, nullptr, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
   const bool zs = (int)dt_src == kDtZ16, zd = (int)dt_dst == kDtZ16;
   if (zs && zd)
     return launch_col_typed<zh16, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
@@ -1221,6 +1231,7 @@ bool col_pass_in_registers(const ColPass &hp, int64_t ncols) {
 bool colrow_supported(const harp_plan *plan, const ColPass &hp, const PassDesc &vp, const void *src,
                       int64_t lds_, harp_dtype_t dt_src, const void *dst, int64_t ldd,
                       harp_dtype_t dt_dst, int64_t nrows, int64_t ncols) {
+  if (hp.wide) return col_wide_supported(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols);
   if (vp.kind == PASS_POW2_DENSE && vp.k == 1 && vp.P == 2 && vp.V == 4 && !vp.tied) {
     if (dt_src != HARP_F32 && dt_src != HARP_BF16) return false;
     if (dt_dst != HARP_F32 && dt_dst != HARP_BF16) return false;
@@ -1246,6 +1257,7 @@ harp_status_t launch_colrow_pass(const harp_plan *plan, const ColPass *dpass, co
                                  const PassDesc &vp, const void *src, int64_t lds_,
                                  harp_dtype_t dt_src, void *dst, int64_t ldd, harp_dtype_t dt_dst,
                                  int64_t nrows, int64_t ncols, hipStream_t stream) {
+  if (hp.wide) return launch_col_wide(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
   if ((int)dt_src == kDtZ16 && dt_dst == HARP_BF16)
     return launch_colrow_typed<zh16, uint16_t>(plan, dpass, hp, vp, src, lds_, dst, ldd, nrows, ncols, stream);
   if (dt_src == HARP_BF16 && (int)dt_dst == kDtZ16)

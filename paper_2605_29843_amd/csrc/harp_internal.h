@@ -148,12 +148,17 @@ struct ColPass {
   // device, [3][npar]: value e of tile (hi, lo) is image[fix[e] + hi * fa[e] + lo * fb[e]];
   // fa[e] == 0xffffffff marks padding
   const uint32_t *ptab;
+  // pass of 512 rows (harp_colwide.hip; nops == 0, none of the fields above but P and S): its block values
+  const float *wide;
+  int32_t wide_desc;
+  int32_t pad;
   ColOp op[kColMaxOps];
 };
 struct ColPassHost {
   ColPass pass;
   const ColPass *dev;   // device copy
   std::vector<uint32_t> ptab;
+  std::vector<float> wide;
 };
 // stage of the column-mode image, execution order: dense blocks [d / b][b][b] with the signs
 // folded in (device memory)
@@ -246,6 +251,9 @@ struct harp_plan {
   // (aux == nullptr: none)
   std::vector<harp::PassDesc> grad_mfma[2];
   std::vector<harp::ColPassHost> colpass[2];
+  // the same stages in fewer passes, some of 512 rows (empty when that saves none); needs aligned rows
+  // and a workspace that is not in block-scaled halves
+  std::vector<harp::ColPassHost> colwide[2];
   const int8_t *dev_signs = nullptr;   // device copy of the signs (null: all +1)
   bool orthogonal = true;              // every block satisfies |K^T K - I| <= 1e-5
   bool f32_only = false;               // HARP_F32_INTERMEDIATES: no block-scaled half intermediates
@@ -334,7 +342,19 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
                                   hipStream_t stream);
 // column-mode passes (harp_col.hip): group plan->col[dir] into passes; launch one pass on a
 // row-major [nrows, ncols] matrix (nrows == plan->d; may run in place)
-bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out);
+// host_image: passes of 512 rows are allowed as well, their block values taken from that copy of the dense blocks
+bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out,
+                      const float *host_image = nullptr);
+// passes of 512 rows (harp_colwide.hip)
+bool col_wide_stages(const std::vector<ColStage> &st, int i0);
+void col_wide_image(const std::vector<ColStage> &st, int i0, int64_t d, const float *host_image, ColPass &cp,
+                    std::vector<float> &out);
+bool col_wide_supported(const harp_plan *plan, const ColPass &hp, const PassDesc *vp, const void *src, int64_t lds_,
+                        harp_dtype_t dt_src, const void *dst, int64_t ldd, harp_dtype_t dt_dst, int64_t nrows,
+                        int64_t ncols);
+harp_status_t launch_col_wide(const harp_plan *plan, const ColPass &hp, const PassDesc *vp, const void *src,
+                              int64_t lds_, harp_dtype_t dt_src, void *dst, int64_t ldd, harp_dtype_t dt_dst,
+                              int64_t nrows, int64_t ncols, hipStream_t stream);
 harp_status_t launch_col_pass(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                               const void *src,
                               int64_t lds_, harp_dtype_t dt_src, void *dst, int64_t ldd,
