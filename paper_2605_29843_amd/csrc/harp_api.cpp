@@ -953,7 +953,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
       fuse = one_streamed ? find_fuse(false) : -1;
       bool ok = fuse >= 0 || narrow_fuse < 0;
       for (size_t p = 0; p < cps->size(); ++p)
-        if ((*cps)[p].pass.wide)
+        if ((*cps)[p].pass.P == 512)
           ok = ok && col_wide_supported(pu, (*cps)[p].pass, nullptr, W, ldw, dt, Wout, ldo, dt, d_out, d_in) &&
                col_wide_supported(pu, (*cps)[p].pass, nullptr, A, d_in, HARP_F32, A, d_in, HARP_F32, d_out, d_in);
       if (!ok) {
@@ -1459,11 +1459,11 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
         }
         if (st != HARP_OK) break;
       }
-      if (!col_ok || !build_col_passes(plan, (Direction)dir, plan->colpass[dir])) {
+      if (!col_ok || !build_col_passes(plan, (Direction)dir, image.data(), false, plan->colpass[dir])) {
         plan->colpass[dir].clear();
         continue;
       }
-      if (!build_col_passes(plan, (Direction)dir, plan->colwide[dir], image.data()) ||
+      if (!build_col_passes(plan, (Direction)dir, image.data(), true, plan->colwide[dir]) ||
           plan->colwide[dir].size() >= plan->colpass[dir].size())
         plan->colwide[dir].clear();
       auto upload = [&](const void *host, size_t bytes, void **dev) {
@@ -1478,10 +1478,10 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
             st = upload(ph.ptab.data(), ph.ptab.size() * 4, &dev);
             ph.pass.ptab = (const uint32_t *)dev;
           }
-          if (st == HARP_OK && !ph.wide.empty()) {
-            st = upload(ph.wide.data(), ph.wide.size() * 4, &dev);
-            ph.pass.wide = (const float *)dev;
-            std::vector<float>().swap(ph.wide);
+          if (st == HARP_OK && !ph.packed.empty()) {
+            st = upload(ph.packed.data(), ph.packed.size() * 4, &dev);
+            ph.pass.packed = (const float *)dev;
+            std::vector<float>().swap(ph.packed);
           }
           if (st == HARP_OK) st = upload(&ph.pass, sizeof(ColPass), &dev);
           ph.dev = (const ColPass *)dev;

@@ -995,7 +995,11 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
   const int64_t full = shape_ok ? (ncols / kColCols) * kColCols : 0;
   if ((IsZ16<TI>::value || IsZ16<TO>::value) && full != ncols) return HARP_ERR_UNSUPPORTED;
   harp_status_t st = HARP_OK;
-  if (full > 0)
+  constexpr bool plain = !IsZ16<TI>::value && !IsZ16<TO>::value;
+  if (full > 0 && plain && hp.packed)
+    st = launch_col_pair(hp, src, lds_, sizeof(TI) == 4 ? HARP_F32 : HARP_BF16, dst, ldd,
+                         sizeof(TO) == 4 ? HARP_F32 : HARP_BF16, nrows, full, stream);
+  else if (full > 0)
     st = launch_col_tiles<TI, TO>(plan, dpass, hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows,
                                   full, true, true, stream);
   if (st == HARP_OK && full < ncols)
@@ -1066,7 +1070,8 @@ harp_status_t launch_colrow_typed(const harp_plan *plan, const ColPass *dpass, c
 // Host side: group the stages of plan->col[dir] (execution order) into passes and steps, and
 // list for every pass the block values a tile needs.  Returns false when the plan has no
 // column-mode image (a radix above 8).
-bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out, const float *host_image) {
+bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_image, bool wide,
+                      std::vector<ColPassHost> &out) {
   const std::vector<ColStage> &st = plan->col[dir];
   out.clear();
   if (st.empty()) return false;
@@ -1080,7 +1085,7 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
   // per tile: 28672 = 7 * 2^12 ended in a pass of P = 2 that took three times as long as the
   // other two together).  Ties go to the taller first pass.
   auto fits = [&](int i0, int e0, int &Pout) {
-    if (host_image && e0 == i0 + 3 && col_wide_stages(st, i0)) {
+    if (wide && e0 == i0 + 3 && col_wide_stages(st, i0)) {
       Pout = 512;
       return true;
     }
@@ -1123,7 +1128,7 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
     ColPass &cp = ph.pass;
     memset(&cp, 0, sizeof(cp));
     if (P == 512) {
-      col_wide_image(st, i, plan->d, host_image, cp, ph.wide);
+      col_wide_image(st, i, plan->d, host_image, cp, ph.packed);
       i = e;
       continue;
     }
@@ -1173,6 +1178,7 @@ bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassH
     }
     cp.npar = (int32_t)fix.size();
     if (cp.npar > kColMaxPar) return false;
+    if (e == i + 2 && col_pair_stages(st, i)) col_pair_image(st, i, plan->d, host_image, cp, ph.packed);
     ph.ptab = fix;
     ph.ptab.insert(ph.ptab.end(), fa.begin(), fa.end());
     ph.ptab.insert(ph.ptab.end(), fb.begin(), fb.end());
@@ -1187,7 +1193,7 @@ harp_status_t launch_col_pass(const harp_plan *plan, const ColPass *dpass, const
                               harp_dtype_t dt_dst, int64_t nrows, int64_t ncols,
                               hipStream_t stream) {
   if (nrows % hp.P != 0) return HARP_ERR_INVALID_ARG;
-  if (hp.wide) return launch_col_wide(plan, hp, nullptr, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
+  if (hp.P == 512) return launch_col_wide(plan, hp, nullptr, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
   const bool zs = (int)dt_src == kDtZ16, zd = (int)dt_dst == kDtZ16;
   if (zs && zd)
     return launch_col_typed<zh16, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
@@ -1231,7 +1237,7 @@ bool col_pass_in_registers(const ColPass &hp, int64_t ncols) {
 bool colrow_supported(const harp_plan *plan, const ColPass &hp, const PassDesc &vp, const void *src,
                       int64_t lds_, harp_dtype_t dt_src, const void *dst, int64_t ldd,
                       harp_dtype_t dt_dst, int64_t nrows, int64_t ncols) {
-  if (hp.wide) return col_wide_supported(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols);
+  if (hp.P == 512) return col_wide_supported(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols);
   if (vp.kind == PASS_POW2_DENSE && vp.k == 1 && vp.P == 2 && vp.V == 4 && !vp.tied) {
     if (dt_src != HARP_F32 && dt_src != HARP_BF16) return false;
     if (dt_dst != HARP_F32 && dt_dst != HARP_BF16) return false;
@@ -1257,7 +1263,7 @@ harp_status_t launch_colrow_pass(const harp_plan *plan, const ColPass *dpass, co
                                  const PassDesc &vp, const void *src, int64_t lds_,
                                  harp_dtype_t dt_src, void *dst, int64_t ldd, harp_dtype_t dt_dst,
                                  int64_t nrows, int64_t ncols, hipStream_t stream) {
-  if (hp.wide) return launch_col_wide(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
+  if (hp.P == 512) return launch_col_wide(plan, hp, &vp, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
   if ((int)dt_src == kDtZ16 && dt_dst == HARP_BF16)
     return launch_colrow_typed<zh16, uint16_t>(plan, dpass, hp, vp, src, lds_, dst, ldd, nrows, ncols, stream);
   if (dt_src == HARP_BF16 && (int)dt_dst == kDtZ16)

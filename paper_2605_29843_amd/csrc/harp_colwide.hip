@@ -239,7 +239,7 @@ harp_status_t launch_wide_inst(const harp_plan *plan, const ColPass &hp, const v
     attr_done_dev = plan->device;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(kWideThreads), kWideLds, stream, (const TI *)src,
-                     lds_, (TO *)dst, ldd, (int)hp.S, (unsigned)nct, (unsigned)total, hp.wide, vparams, Sv);
+                     lds_, (TO *)dst, ldd, (int)hp.S, (unsigned)nct, (unsigned)total, hp.packed, vparams, Sv);
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
@@ -250,8 +250,8 @@ harp_status_t launch_wide_typed(const harp_plan *plan, const ColPass &hp, const 
   const int Sv = vp ? (int)vp->S : 0;
 #define HARP_WIDE(BV, DESC) \
   launch_wide_inst<TI, TO, BV, DESC>(plan, hp, src, lds_, dst, ldd, nrows, ncols, vpar, Sv, stream)
-  if (vp) return hp.wide_desc ? HARP_WIDE(2, true) : HARP_WIDE(2, false);
-  return hp.wide_desc ? HARP_WIDE(1, true) : HARP_WIDE(1, false);
+  if (vp) return hp.desc ? HARP_WIDE(2, true) : HARP_WIDE(2, false);
+  return hp.desc ? HARP_WIDE(1, true) : HARP_WIDE(1, false);
 #undef HARP_WIDE
 }
 
@@ -273,7 +273,7 @@ void col_wide_image(const std::vector<ColStage> &st, int i0, int64_t d, const fl
   const bool desc = st[i0].s > st[i0 + 1].s;
   cp.P = kWideP;
   cp.S = (int)st[desc ? i0 + 2 : i0].s;
-  cp.wide_desc = desc ? 1 : 0;
+  cp.desc = desc ? 1 : 0;
   const int64_t S = cp.S, tiles = d / kWideP;
   out.assign((size_t)tiles * kWideTile, 0.0f);
   for (int e = 0; e < 3; ++e) {   // by stride
@@ -303,7 +303,7 @@ void col_wide_image(const std::vector<ColStage> &st, int i0, int64_t d, const fl
 bool col_wide_supported(const harp_plan *plan, const ColPass &hp, const PassDesc *vp, const void *src, int64_t lds_,
                         harp_dtype_t dt_src, const void *dst, int64_t ldd, harp_dtype_t dt_dst, int64_t nrows,
                         int64_t ncols) {
-  if (!hp.wide || nrows % kWideP != 0 || kWideLds > (size_t)plan->lds_bytes) return false;
+  if (!hp.packed || hp.P != kWideP || nrows % kWideP != 0 || kWideLds > (size_t)plan->lds_bytes) return false;
   if ((dt_src != HARP_F32 && dt_src != HARP_BF16) || (dt_dst != HARP_F32 && dt_dst != HARP_BF16)) return false;
   if (lds_ % (dt_src == HARP_F32 ? 4 : 8) || ldd % (dt_dst == HARP_F32 ? 4 : 8)) return false;
   if ((uintptr_t)src % 16 || (uintptr_t)dst % 16) return false;

@@ -148,17 +148,19 @@ struct ColPass {
   // device, [3][npar]: value e of tile (hi, lo) is image[fix[e] + hi * fa[e] + lo * fb[e]];
   // fa[e] == 0xffffffff marks padding
   const uint32_t *ptab;
-  // pass of 512 rows (harp_colwide.hip; nops == 0, none of the fields above but P and S): its block values
-  const float *wide;
-  int32_t wide_desc;
-  int32_t pad;
+  // Passes on the float32 matrix instruction: their block values in the kernel's order (device), or null.
+  // P == 512: harp_colwide.hip (nops == 0, none of the fields above but P and S); else two stages with
+  // the tile in registers, harp_colpair.hip (r1 = the radix at the lower stride).
+  const float *packed;
+  int32_t desc;   // stages from the highest stride down
+  int32_t r1;
   ColOp op[kColMaxOps];
 };
 struct ColPassHost {
   ColPass pass;
   const ColPass *dev;   // device copy
   std::vector<uint32_t> ptab;
-  std::vector<float> wide;
+  std::vector<float> packed;
 };
 // stage of the column-mode image, execution order: dense blocks [d / b][b][b] with the signs
 // folded in (device memory)
@@ -342,9 +344,15 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
                                   hipStream_t stream);
 // column-mode passes (harp_col.hip): group plan->col[dir] into passes; launch one pass on a
 // row-major [nrows, ncols] matrix (nrows == plan->d; may run in place)
-// host_image: passes of 512 rows are allowed as well, their block values taken from that copy of the dense blocks
-bool build_col_passes(const harp_plan *plan, Direction dir, std::vector<ColPassHost> &out,
-                      const float *host_image = nullptr);
+// host_image: the dense blocks on the host; wide: passes of 512 rows are allowed as well
+bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_image, bool wide,
+                      std::vector<ColPassHost> &out);
+// passes of two stages with the tile in registers (harp_colpair.hip)
+bool col_pair_stages(const std::vector<ColStage> &st, int i0);
+void col_pair_image(const std::vector<ColStage> &st, int i0, int64_t d, const float *host_image, ColPass &cp,
+                    std::vector<float> &out);
+harp_status_t launch_col_pair(const ColPass &hp, const void *src, int64_t lds_, harp_dtype_t dt_src, void *dst,
+                              int64_t ldd, harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, hipStream_t stream);
 // passes of 512 rows (harp_colwide.hip)
 bool col_wide_stages(const std::vector<ColStage> &st, int i0);
 void col_wide_image(const std::vector<ColStage> &st, int i0, int64_t d, const float *host_image, ColPass &cp,

@@ -1,0 +1,43 @@
+"""Column passes of two stages with the tile in registers: every pair of radices the kernel is built for, row
+strides of one and more, ascending and descending stages, every pair of element types (a float32
+workspace between two passes of a bf16 matrix comes with a plan_V that has no half-precision form) and
+widths with a ragged last tile."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import harp_oracle as ho
+from paper_2605_29843_amd import inputs as gi
+from parity_util import assert_parity, to_device, to_host64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rv", [None, [8, 8, 4], [4, 5, 7]])     # 256 and 140 columns with plan_V, 260 without
+@pytest.mark.parametrize("ru", [[7, 4], [8, 3], [8, 4], [8, 5], [8, 6], [8, 7], [8, 8],
+                                [8, 8, 8, 4], [8, 7, 7, 4], [3, 7, 4, 8, 5]])
+def test_column_pass_of_two_stages(ru, rv, dtype):
+    from paper_2605_29843_amd import harp
+    do, cols = int(np.prod(ru)), int(np.prod(rv)) if rv else 260
+    rng = np.random.default_rng(do + cols)
+    bu, su = gi.make_blocks(do, ru, "qr", rng), gi.make_signs(do, rng)
+    pu, pv = harp.Plan(do, ru, bu, su), None
+    if rv:
+        bv, sv = gi.make_blocks(cols, rv, "qr", rng), gi.make_signs(cols, rng)
+        pv = harp.Plan(cols, rv, bv, sv)
+    print("two-stage pass", ru, rv, dtype, file=sys.stderr, flush=True)
+    W = rng.standard_normal((do, cols)).astype(np.float32)
+    if dtype == "bf16":
+        W = gi.round_to_bf16(W)
+    Wd = to_device(W, dtype)
+    W64 = W.astype(np.float64)
+    for fn, rows_fn in ((harp.harp_rotate_weight, ho.apply_staged), (harp.harp_rotate_weight_inverse, ho.apply_transpose_staged)):
+        M = rows_fn(W64, cols, rv, bv, sv) if rv else W64
+        ref = rows_fn(np.ascontiguousarray(M.T), do, ru, bu, su).T
+        rho = np.linalg.norm(M, axis=0, keepdims=True) / np.sqrt(do)
+        assert_parity(to_host64(fn(pu, pv, Wd)), ref, dtype, fn.__name__, rho=rho)
+    pu.destroy()
+    if pv:
+        pv.destroy()
