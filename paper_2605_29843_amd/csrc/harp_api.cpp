@@ -983,7 +983,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
         else
           st = launch_stream_pass(pv, *vhp, ps, W, ldw, dt, A, zl, ZT, d_out, true, s);
         for (size_t p = 0; p < cps->size() && st == HARP_OK; ++p)
-          st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, A, zl, ZT, A, zl, ZT, d_out, d_in, s);
+          st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, A, zl, ZT, A, zl, ZT, d_out, d_in, true, s);
         if (st != HARP_OK) return st;
         if (fwd) return launch_stream_pass(pv, *vhp, ps, A, zl, ZT, Wout, ldo, dt, d_out, true, s);
         return run_chunk_passes(pv, *vhp, c0, c0 + vhp->n_chunk, A, zl, ZT, Wout, ldo, dt, d_out, s);
@@ -1008,7 +1008,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
                                   dst_dt, d_out, d_in, s);
         else
           st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
-                               d_out, d_in, s);
+                               d_out, d_in, dt == HARP_BF16, s);
         if (st != HARP_OK) return st;
         src = dst;
         src_ld = dst_ld;
@@ -1037,7 +1037,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
       const int64_t dst_ld = last ? ldo : wld;
       const harp_dtype_t dst_dt = last ? dt : wt;
       st = launch_col_pass(pu, (*cps)[p].dev, (*cps)[p].pass, src, src_ld, src_dt, dst, dst_ld, dst_dt,
-                           d_out, d_in, s);
+                           d_out, d_in, dt == HARP_BF16, s);
       if (st != HARP_OK) return st;
       src = dst;
       src_ld = dst_ld;

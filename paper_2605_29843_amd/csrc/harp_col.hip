@@ -980,7 +980,7 @@ harp_status_t launch_col_tiles(const harp_plan *plan, const ColPass *dpass, cons
 template <typename TI, typename TO>
 harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                                const void *src, int64_t lds_, void *dst, int64_t ldd,
-                               int64_t nrows, int64_t ncols, hipStream_t stream) {
+                               int64_t nrows, int64_t ncols, bool caller_bf16, hipStream_t stream) {
   const size_t ei = sizeof(TI), eo = sizeof(TO);
   // A single stage gains nothing from a tile in LDS: in registers whenever the accesses can be four
   // columns wide.  Passes with block-scaled halves on a side keep the tile (harp_col_one_kernel is
@@ -996,7 +996,7 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
   if ((IsZ16<TI>::value || IsZ16<TO>::value) && full != ncols) return HARP_ERR_UNSUPPORTED;
   harp_status_t st = HARP_OK;
   constexpr bool plain = !IsZ16<TI>::value && !IsZ16<TO>::value;
-  if (full > 0 && plain && hp.packed)
+  if (full > 0 && plain && hp.packed && (caller_bf16 || !hp.composite))
     st = launch_col_pair(hp, src, lds_, sizeof(TI) == 4 ? HARP_F32 : HARP_BF16, dst, ldd,
                          sizeof(TO) == 4 ? HARP_F32 : HARP_BF16, nrows, full, stream);
   else if (full > 0)
@@ -1178,7 +1178,9 @@ bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_im
     }
     cp.npar = (int32_t)fix.size();
     if (cp.npar > kColMaxPar) return false;
-    if (e == i + 2 && col_pair_stages(st, i)) col_pair_image(st, i, plan->d, host_image, cp, ph.packed);
+    // (products of blocks only where they cannot outgrow float32)
+    const int split = e == i + 2 || plan->orthogonal ? col_pair_split(st, i, e) : 0;
+    if (split) col_pair_image(st, i, e, split, plan->d, host_image, cp, ph.packed);
     ph.ptab = fix;
     ph.ptab.insert(ph.ptab.end(), fa.begin(), fa.end());
     ph.ptab.insert(ph.ptab.end(), fb.begin(), fb.end());
@@ -1190,25 +1192,25 @@ bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_im
 harp_status_t launch_col_pass(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                               const void *src,
                               int64_t lds_, harp_dtype_t dt_src, void *dst, int64_t ldd,
-                              harp_dtype_t dt_dst, int64_t nrows, int64_t ncols,
+                              harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, bool caller_bf16,
                               hipStream_t stream) {
   if (nrows % hp.P != 0) return HARP_ERR_INVALID_ARG;
   if (hp.P == 512) return launch_col_wide(plan, hp, nullptr, src, lds_, dt_src, dst, ldd, dt_dst, nrows, ncols, stream);
   const bool zs = (int)dt_src == kDtZ16, zd = (int)dt_dst == kDtZ16;
   if (zs && zd)
-    return launch_col_typed<zh16, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<zh16, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
   if (zs && dt_dst == HARP_BF16)
-    return launch_col_typed<zh16, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<zh16, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
   if (zd && dt_src == HARP_BF16)
-    return launch_col_typed<uint16_t, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<uint16_t, zh16>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
   if (zs || zd) return HARP_ERR_UNSUPPORTED;
   if (dt_src == HARP_F32 && dt_dst == HARP_F32)
-    return launch_col_typed<float, float>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<float, float>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
   if (dt_src == HARP_BF16 && dt_dst == HARP_F32)
-    return launch_col_typed<uint16_t, float>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<uint16_t, float>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
   if (dt_src == HARP_F32 && dt_dst == HARP_BF16)
-    return launch_col_typed<float, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
-  return launch_col_typed<uint16_t, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, stream);
+    return launch_col_typed<float, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
+  return launch_col_typed<uint16_t, uint16_t>(plan, dpass, hp, src, lds_, dst, ldd, nrows, ncols, caller_bf16, stream);
 }
 
 // A column pass with block-scaled halves on either side runs in the unguarded variants only:

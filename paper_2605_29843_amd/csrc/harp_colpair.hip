@@ -119,37 +119,91 @@ harp_status_t launch_pair_inst(const ColPass &hp, const void *src, int64_t lds_,
 
 }  // namespace
 
-// Stages i0, i0 + 1 of the column image as one such pass.
-bool col_pair_stages(const std::vector<ColStage> &st, int i0) {
-  const ColStage &a = st[i0], &b = st[i0 + 1];
-  const ColStage &lo = a.s < b.s ? a : b, &hi = a.s < b.s ? b : a;
-  if (hi.s != (int64_t)lo.s * lo.b) return false;
-  return (lo.b == 7 && hi.b == 4) || (lo.b == 8 && hi.b >= 3 && hi.b <= 8);
+// Stages [i0, e0) of the column image, consecutive digits in ascending or descending order, as one such pass: the
+// number of stages of the group at the lower strides, or 0.  A group of several stages acts as one
+// dense block of the product of their radices (three radix-2 stages as a block of 8 rows).  Such a
+// pass is taken for bf16 matrices only: sums of eight products round more often than three of two, and
+// a float32 result of radix-2 schedules would be 1.58e-7 of its norm from the float64 one instead
+// of 1.51e-7 (4096 x 2048), which a bf16 result does not show.  bf16 matrix, float32 workspace: 4096 x 11008
+// radix 2 inverse 346 -> 308 us (64 rows: 90 -> 73 us in float32, 82 -> 57 us to bf16), 3072 x 11008 261 -> 225.
+int col_pair_split(const std::vector<ColStage> &st, int i0, int e0) {
+  const int n = e0 - i0;
+  if (n < 2) return 0;
+  const bool desc = st[i0].s > st[i0 + 1].s;
+  auto at = [&](int k) -> const ColStage & { return st[desc ? e0 - 1 - k : i0 + k]; };   // by stride
+  for (int k = 0; k + 1 < n; ++k)
+    if (at(k + 1).s != at(k).s * at(k).b) return 0;
+  int r1 = 1;
+  for (int k = 1; k < n; ++k) {
+    r1 *= at(k - 1).b;
+    if (r1 > 8) return 0;
+    int r2 = 1;
+    for (int q = k; q < n && r2 <= 8; ++q) r2 *= at(q).b;
+    if ((r1 == 7 && r2 == 4) || (r1 == 8 && r2 >= 3 && r2 <= 8)) return k;
+  }
+  return 0;
 }
 
-void col_pair_image(const std::vector<ColStage> &st, int i0, int64_t d, const float *host_image, ColPass &cp,
-                    std::vector<float> &out) {
+void col_pair_image(const std::vector<ColStage> &st, int i0, int e0, int split, int64_t d, const float *host_image,
+                    ColPass &cp, std::vector<float> &out) {
   const bool desc = st[i0].s > st[i0 + 1].s;
-  const ColStage &c1 = st[desc ? i0 + 1 : i0], &c2 = st[desc ? i0 : i0 + 1];
+  // the two groups, stages in the order they run
+  std::vector<ColStage> grp[2];
+  for (int t = i0; t < e0; ++t) grp[(desc ? e0 - 1 - t : t - i0) < split ? 0 : 1].push_back(st[t]);
+  int R[2] = {1, 1};
+  int64_t s0[2];
+  for (int g = 0; g < 2; ++g) {
+    s0[g] = grp[g][0].s;
+    for (const ColStage &c : grp[g]) {
+      R[g] *= c.b;
+      s0[g] = std::min<int64_t>(s0[g], c.s);
+    }
+  }
   cp.desc = desc ? 1 : 0;
-  cp.r1 = c1.b;
-  const int R1 = c1.b, R2 = c2.b, P = R1 * R2;
-  const int64_t S = c1.s, tiles = d / P;
-  const int n1 = R2 * chain_pieces(R1), n2 = R1 * chain_pieces(R2);
+  cp.composite = grp[0].size() > 1 || grp[1].size() > 1 ? 1 : 0;
+  cp.r1 = R[0];
+  const int P = R[0] * R[1];
+  const int64_t S = s0[0], tiles = d / P;
+  const int n1 = R[1] * chain_pieces(R[0]), n2 = R[0] * chain_pieces(R[1]);
   out.assign((size_t)tiles * (n1 + n2) * 16, 0.0f);
+  float K[64];
   for (int64_t T = 0; T < tiles; ++T)
-    for (int e = 0; e < 2; ++e) {
-      const ColStage &cs = e ? c2 : c1;
-      const int b = cs.b, nh = b > 4 ? 2 : 1, np = chain_pieces(b);
-      const float *blocks = host_image + (cs.blocks - st[0].blocks);
-      float *o = out.data() + (size_t)T * (n1 + n2) * 16 + (e ? n1 * 16 : 0);
+    for (int g = 0; g < 2; ++g) {
+      const int b = R[g], nh = b > 4 ? 2 : 1, np = chain_pieces(b);
+      float *o = out.data() + (size_t)T * (n1 + n2) * 16 + (g ? n1 * 16 : 0);
       for (int v = 0; v < P / b; ++v) {
-        const int64_t row = (T / S) * P * S + T % S + (int64_t)(e ? v : v * R1) * S;
-        const float *K = blocks + ((row / ((int64_t)b * cs.s)) * cs.s + row % cs.s) * b * b;
+        const int64_t row = (T / S) * P * S + T % S + (int64_t)(g ? v : v * R[0]) * S;
+        const float *Kp = K;
+        if (grp[g].size() == 1) {
+          const ColStage &c = grp[g][0];
+          Kp = host_image + (c.blocks - st[0].blocks) + ((row / (b * s0[g])) * s0[g] + row % s0[g]) * b * b;
+        } else {
+          // row i of the group's block: unit vector i through the group's stages (float64, rounded once)
+          for (int i = 0; i < b; ++i) {
+            double x[8] = {0.0}, y[8];
+            x[i] = 1.0;
+            for (const ColStage &c : grp[g]) {
+              const int sp = (int)(c.s / s0[g]);
+              const float *blocks = host_image + (c.blocks - st[0].blocks);
+              for (int p = 0; p < b; ++p) {
+                if ((p / sp) % c.b) continue;   // p: digit zero of this stage
+                const int64_t r0 = row + (int64_t)p * s0[g];
+                const float *k = blocks + ((r0 / ((int64_t)c.b * c.s)) * c.s + r0 % c.s) * c.b * c.b;
+                for (int q = 0; q < c.b; ++q) {
+                  double a = 0.0;
+                  for (int r = 0; r < c.b; ++r) a += x[p + r * sp] * (double)k[r * c.b + q];
+                  y[p + q * sp] = a;
+                }
+              }
+              std::copy(y, y + b, x);
+            }
+            for (int q = 0; q < b; ++q) K[i * b + q] = (float)x[q];
+          }
+        }
         for (int r = 0; r < b; ++r)
           for (int c = 0; c < b; ++c) {
             const int w = r * nh + c / 4;
-            o[((v * np + w / 4) * 4 + c % 4) * 4 + w % 4] = K[r * b + c];
+            o[((v * np + w / 4) * 4 + c % 4) * 4 + w % 4] = Kp[r * b + c];
           }
       }
     }

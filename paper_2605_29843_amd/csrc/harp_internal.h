@@ -154,6 +154,9 @@ struct ColPass {
   const float *packed;
   int32_t desc;   // stages from the highest stride down
   int32_t r1;
+  // some block of `packed` is the product of several stages' blocks (bf16 matrices only, see col_pair_split)
+  int32_t composite;
+  int32_t pad;
   ColOp op[kColMaxOps];
 };
 struct ColPassHost {
@@ -348,9 +351,9 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
 bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_image, bool wide,
                       std::vector<ColPassHost> &out);
 // passes of two stages with the tile in registers (harp_colpair.hip)
-bool col_pair_stages(const std::vector<ColStage> &st, int i0);
-void col_pair_image(const std::vector<ColStage> &st, int i0, int64_t d, const float *host_image, ColPass &cp,
-                    std::vector<float> &out);
+int col_pair_split(const std::vector<ColStage> &st, int i0, int e0);
+void col_pair_image(const std::vector<ColStage> &st, int i0, int e0, int split, int64_t d, const float *host_image,
+                    ColPass &cp, std::vector<float> &out);
 harp_status_t launch_col_pair(const ColPass &hp, const void *src, int64_t lds_, harp_dtype_t dt_src, void *dst,
                               int64_t ldd, harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, hipStream_t stream);
 // passes of 512 rows (harp_colwide.hip)
@@ -366,7 +369,7 @@ harp_status_t launch_col_wide(const harp_plan *plan, const ColPass &hp, const Pa
 harp_status_t launch_col_pass(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                               const void *src,
                               int64_t lds_, harp_dtype_t dt_src, void *dst, int64_t ldd,
-                              harp_dtype_t dt_dst, int64_t nrows, int64_t ncols,
+                              harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, bool caller_bf16,
                               hipStream_t stream);
 // block-scaled halves (kDtZ16) on either side of a column pass: unguarded tiles only
 bool col_z16_supported(const ColPass &hp, const void *src, int64_t lds_, const void *dst,

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("rv", [None, [8, 8, 4], [4, 5, 7]])     # 256 and 140 columns with plan_V, 260 without
 @pytest.mark.parametrize("ru", [[7, 4], [8, 3], [8, 4], [8, 5], [8, 6], [8, 7], [8, 8],
-                                [8, 8, 8, 4], [8, 7, 7, 4], [3, 7, 4, 8, 5]])
+                                [8, 8, 8, 4], [8, 7, 7, 4], [3, 7, 4, 8, 5],
+                                [2] * 6, [2] * 12, [2, 4, 2, 3], [4, 2, 5, 2, 2, 2, 7]])
 def test_column_pass_of_two_stages(ru, rv, dtype):
     from paper_2605_29843_amd import harp
     do, cols = int(np.prod(ru)), int(np.prod(rv)) if rv else 260
