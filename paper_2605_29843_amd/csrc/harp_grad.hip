@@ -116,12 +116,54 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_kernel(
 
 // For the rows of chunk blockIdx.y: acc[r][r2] += x[idx_r] g[idx_r2];  g[idx_r] <- sum_r2
 // g[idx_r2] K[r][r2] (in place).  Partial sums go to partial[(chunk * B*B + v) * D + c].
+// Backward kernels: a workgroup is 128 items x four groups of rows.  The partial sums of a stage's block
+// gradients are a fifth of the bytes such a kernel moves when every 8 rows write theirs; the four groups
+// add theirs in LDS first (2048 x 4096 radix 2: see launch_grad), in a fixed order.
+constexpr int kSumItems = 128, kSumGroups = 4, kSumThreads = kSumItems * kSumGroups;
+struct SumRows {
+  int item, group;
+  int64_t r0, r1;   // rows of this group
+};
+__device__ __forceinline__ SumRows sum_rows(int64_t n, int rows) {
+  SumRows sr;
+  sr.item = (int)threadIdx.x % kSumItems;
+  sr.group = (int)threadIdx.x / kSumItems;
+  const int per = (rows + kSumGroups - 1) / kSumGroups;
+  const int64_t w0 = (int64_t)blockIdx.y * rows, w1 = (w0 + rows < n) ? w0 + rows : n;
+  sr.r0 = w0 + (int64_t)sr.group * per;
+  sr.r1 = (sr.r0 + per < w1) ? sr.r0 + per : w1;
+  return sr;
+}
+// acc of group 0 <- (group 0 + group 2) + (group 1 + group 3); every thread of the workgroup takes part
+template <int NV>
+__device__ __forceinline__ void sum_groups(float (&acc)[NV], const SumRows &sr) {
+  __shared__ float red[2][NV][kSumItems];
+  if (sr.group >= 2) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) red[sr.group - 2][v][sr.item] = acc[v];
+  }
+  __syncthreads();
+  if (sr.group < 2) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] += red[sr.group][v][sr.item];
+  }
+  if (sr.group == 1) {   // into the slots that this thread alone has read
+#pragma unroll
+    for (int v = 0; v < NV; ++v) red[1][v][sr.item] = acc[v];
+  }
+  __syncthreads();
+  if (sr.group == 0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] += red[1][v][sr.item];
+  }
+}
+
 template <int B>
-__global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_kernel(
+__global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
     const float *__restrict__ X, float *__restrict__ Gm, int64_t ld, int64_t n, int rows,
     const float *__restrict__ blocks, int D, int s, float *__restrict__ partial) {
-  const int c = blockIdx.x * kGradThreads + threadIdx.x;
-  if (c >= D) return;
+  const SumRows sr = sum_rows(n, rows);
+  const int c0 = blockIdx.x * kSumItems + sr.item, c = c0 < D ? c0 : D - 1;
   float K[B * B], acc[B * B];
 #pragma unroll
   for (int v = 0; v < B * B; ++v) {
@@ -129,17 +171,25 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_kernel(
     acc[v] = 0.f;
   }
   const int base = (c / s) * B * s + c % s;
-  const int64_t r0 = (int64_t)blockIdx.y * rows;
-  const int64_t r1 = (r0 + rows < n) ? r0 + rows : n;
-  for (int64_t row = r0; row < r1; ++row) {
-    const float *x = X + row * ld + base;
+  const int64_t r1 = c0 < D ? sr.r1 : sr.r0;   // threads past the last block have no rows
+  float nx[B], ng[B];
+  auto request = [&](int64_t row) {
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+      nx[r] = X[row * ld + base + (size_t)r * s];
+      ng[r] = Gm[row * ld + base + (size_t)r * s];
+    }
+  };
+  if (sr.r0 < r1) request(sr.r0);
+  for (int64_t row = sr.r0; row < r1; ++row) {
     float *g = Gm + row * ld + base;
     float xv[B], gv[B];
 #pragma unroll
     for (int r = 0; r < B; ++r) {
-      xv[r] = x[(size_t)r * s];
-      gv[r] = g[(size_t)r * s];
+      xv[r] = nx[r];
+      gv[r] = ng[r];
     }
+    if (row + 1 < r1) request(row + 1);   // (nobody but this thread writes its g)
 #pragma unroll
     for (int r = 0; r < B; ++r) {
       float back = 0.f;
@@ -151,9 +201,12 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_kernel(
       g[(size_t)r * s] = back;
     }
   }
+  sum_groups<B * B>(acc, sr);
+  if (sr.group == 0 && c0 < D) {
 #pragma unroll
-  for (int v = 0; v < B * B; ++v)
-    partial[((size_t)blockIdx.y * (B * B) + v) * D + c] = acc[v];
+    for (int v = 0; v < B * B; ++v)
+      partial[((size_t)blockIdx.y * (B * B) + v) * D + c] = acc[v];
+  }
 }
 
 // Radix 9..64 (the leftover prime of a schedule): a block no longer fits one thread's registers,
@@ -519,25 +572,20 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_run_kernel(
 // reads its item of a row (X and gradient) before it writes it, and no other thread touches that item:
 // dX may be X or G.
 template <int K, typename TX = float, typename TGI = float, typename TGO = float>
-__global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_run_kernel(
+__global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
     const TX *X, int64_t ldx, const TGI *Gin, int64_t ldgi, TGO *Gout, int64_t ldgo,
     int64_t ld, int64_t n, int rows, GradRun run, int nitems, int s, int D,
     float *__restrict__ partial, size_t pstride, int aligned) {
   constexpr int E = 1 << K, H = E / 2;
-  const int q = blockIdx.x * kGradThreads + threadIdx.x;
-  if (q >= nitems) return;
+  const SumRows sr = sum_rows(n, rows);
+  const int q0 = blockIdx.x * kSumItems + sr.item, q = q0 < nitems ? q0 : nitems - 1;
   const int base = (q / s) * E * s + q % s;
-  float kv[K][H][4], acc[K][H][4];
+  float kv[K][H][4], acc[K * H * 4];
   int cidx[K][H];
   grad_run_blocks<K>(run, base, s, D, kv, cidx);
 #pragma unroll
-  for (int i = 0; i < K; ++i)
-#pragma unroll
-    for (int p = 0; p < H; ++p)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) acc[i][p][w] = 0.f;
-  const int64_t r0 = (int64_t)blockIdx.y * rows;
-  const int64_t r1 = (r0 + rows < n) ? r0 + rows : n;
+  for (int v = 0; v < K * H * 4; ++v) acc[v] = 0.f;
+  const int64_t r0 = sr.r0, r1 = q0 < nitems ? sr.r1 : sr.r0;   // threads past the last item have no rows
   const bool vec = aligned && (s == 1) && (E % 4 == 0) && (ld % 4 == 0);
   const bool vecx = vec && ldx % (16 / (int)sizeof(TX)) == 0 && (uintptr_t)X % 16 == 0;
   const bool vecgi = vec && ldgi % (16 / (int)sizeof(TGI)) == 0 && (uintptr_t)Gin % 16 == 0;
@@ -580,23 +628,25 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_bwd_run_kernel(
         const int eh = p >> i, el = p & ((1 << i) - 1);
         const int e0 = (eh << (i + 1)) | el, e1 = e0 | (1 << i);
         const float x0 = xs[i][e0], x1 = xs[i][e1], g0 = gv[e0], g1 = gv[e1];
-        acc[i][p][0] = fmaf(x0, g0, acc[i][p][0]);
-        acc[i][p][1] = fmaf(x0, g1, acc[i][p][1]);
-        acc[i][p][2] = fmaf(x1, g0, acc[i][p][2]);
-        acc[i][p][3] = fmaf(x1, g1, acc[i][p][3]);
+        acc[(i * H + p) * 4 + 0] = fmaf(x0, g0, acc[(i * H + p) * 4 + 0]);
+        acc[(i * H + p) * 4 + 1] = fmaf(x0, g1, acc[(i * H + p) * 4 + 1]);
+        acc[(i * H + p) * 4 + 2] = fmaf(x1, g0, acc[(i * H + p) * 4 + 2]);
+        acc[(i * H + p) * 4 + 3] = fmaf(x1, g1, acc[(i * H + p) * 4 + 3]);
         gv[e0] = fmaf(g1, kv[i][p][1], g0 * kv[i][p][0]);   // g K^T, row 0: k00 g0 + k01 g1
         gv[e1] = fmaf(g1, kv[i][p][3], g0 * kv[i][p][2]);
       }
     }
     grad_store_item<E, TGO>(g, s, vecgo, gv);
   }
+  sum_groups<K * H * 4>(acc, sr);
+  if (sr.group != 0 || q0 >= nitems) return;
 #pragma unroll
   for (int i = 0; i < K; ++i)
 #pragma unroll
     for (int p = 0; p < H; ++p)
 #pragma unroll
       for (int w = 0; w < 4; ++w)
-        partial[(size_t)i * pstride + ((size_t)blockIdx.y * 4 + w) * D + cidx[i][p]] = acc[i][p][w];
+        partial[(size_t)i * pstride + ((size_t)blockIdx.y * 4 + w) * D + cidx[i][p]] = acc[(i * H + p) * 4 + w];
 }
 
 // dK[c][v] = sum over the chunks of partial[(chunk * BB + v) * D + c], in a fixed order: eight
@@ -659,8 +709,8 @@ void launch_fwd(const float *X, float *Y, int64_t ld, int64_t n, int rows, int n
 template <int B>
 void launch_bwd(const float *X, float *G, int64_t ld, int64_t n, int rows, int nchunks,
                 const float *blocks, int D, int s, float *partial, hipStream_t st) {
-  hipLaunchKernelGGL((harp_grad_bwd_kernel<B>), dim3((D + kGradThreads - 1) / kGradThreads, nchunks),
-                     dim3(kGradThreads), 0, st, X, G, ld, n, rows, blocks, D, s, partial);
+  hipLaunchKernelGGL((harp_grad_bwd_kernel<B>), dim3((D + kSumItems - 1) / kSumItems, nchunks),
+                     dim3(kSumThreads), 0, st, X, G, ld, n, rows, blocks, D, s, partial);
 }
 
 #define HARP_GRAD_SWITCH(b, CALL)  \
@@ -699,6 +749,13 @@ void launch_convert(const TS *src, int64_t lds_, TD *dst, int64_t ldd, int64_t n
 // rows have to supply the parallelism (d = 4096: 2 workgroups x 256 chunks).
 int grad_chunks(int64_t n) {
   const int64_t c = (n + 7) / 8;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(c, 256));
+}
+
+// Row chunks of the backward kernels of stages up to radix 8: four groups of eight rows each, longer ones
+// beyond 8192 rows.
+int grad_sum_chunks(int64_t n) {
+  const int64_t c = (n + 8 * kSumGroups - 1) / (8 * kSumGroups);
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, 256));
 }
 
@@ -745,7 +802,7 @@ size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
   int bbig = 0;
   for (int32_t b : plan->radices) (b > 8 ? bbig : bsmall) = std::max(b > 8 ? bbig : bsmall, (int)b);
   const size_t mat = (size_t)n * (size_t)plan->d * 4;
-  const size_t partial = std::max((size_t)grad_chunks(n) * bsmall, (size_t)grad_big_chunks_bound(n) * bbig) *
+  const size_t partial = std::max((size_t)grad_sum_chunks(n) * bsmall, (size_t)grad_big_chunks_bound(n) * bbig) *
                          (size_t)plan->d * 4;
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
   const size_t extra = 1 + (bbig > 0 ? 1 : 0);
@@ -770,6 +827,8 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   const int64_t d = plan->d;
   const int nchunks = grad_chunks(n);
   const int rows = (int)((n + nchunks - 1) / nchunks);
+  const int nsum = grad_sum_chunks(n);
+  const int rows_sum = (int)((n + nsum - 1) / nsum);
   const int rows_big = grad_big_rows(n);
   const int nchunks_big = grad_big_chunks(n);
   const size_t mat = (size_t)n * (size_t)d;
@@ -779,7 +838,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   float *g = act + (size_t)nseg * mat;      // gradient, updated in place (radix <= 8) ...
   float *g2 = g + mat;                      // ... or into the other of two matrices (radix >= 9)
   float *partial = g + (bmax > 8 ? 2 : 1) * mat;
-  const size_t pstride = (size_t)nchunks * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
+  const size_t pstride = (size_t)nsum * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
   // 16-byte accesses of the stride-1 runs need the float32 copies on 16-byte boundaries
   const int aligned = (mat % 4 == 0);
   auto run_of = [&](const GradSegment &sg) {
@@ -870,14 +929,14 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
     if (n > 0) {
       if (seg[i].k > 1) {
         const int nitems = (int)(d >> seg[i].k);
-        const dim3 grid((nitems + kGradThreads - 1) / kGradThreads, nchunks);
+        const dim3 grid((nitems + kSumItems - 1) / kSumItems, nsum);
         // what this run reads and writes: the caller's rows at either end, float32 copies between
         const bool xc = (i == 0), gic = (i == nseg - 1), goc = (i == 0) && dx_direct;
 #define HARP_GRAD_BWD_RUN(KK, TX_, TGI_, TGO_)                                                       \
-  hipLaunchKernelGGL((harp_grad_bwd_run_kernel<KK, TX_, TGI_, TGO_>), grid, dim3(kGradThreads), 0,   \
+  hipLaunchKernelGGL((harp_grad_bwd_run_kernel<KK, TX_, TGI_, TGO_>), grid, dim3(kSumThreads), 0,    \
                      st, xc ? (const TX_ *)X : (const TX_ *)in, xc ? ldx : d,                        \
                      gic ? (const TGI_ *)G : (const TGI_ *)g, gic ? ldg : d,                         \
-                     goc ? (TGO_ *)dX : (TGO_ *)g, goc ? lddx : d, d, n, rows, run_of(seg[i]),      \
+                     goc ? (TGO_ *)dX : (TGO_ *)g, goc ? lddx : d, d, n, rows_sum, run_of(seg[i]),      \
                      nitems, cs.s, (int)(d / 2), partial, pstride, aligned)
 #define HARP_GRAD_BWD_TYPES(KK)                                                          \
   do {                                                                                   \
@@ -925,7 +984,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         std::swap(g, g2);
       } else {
         const int D = (int)(d / cs.b);
-#define HARP_GRAD_BWD(BB) launch_bwd<BB>(in, g, d, n, rows, nchunks, cs.blocks, D, cs.s, partial, st)
+#define HARP_GRAD_BWD(BB) launch_bwd<BB>(in, g, d, n, rows_sum, nsum, cs.blocks, D, cs.s, partial, st)
         HARP_GRAD_SWITCH(cs.b, HARP_GRAD_BWD)
 #undef HARP_GRAD_BWD
       }
@@ -942,7 +1001,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         ro.signs[j] = (seg[i].t0 + j == 0) ? plan->dev_signs : nullptr;
       }
       hipLaunchKernelGGL(harp_grad_reduce_kernel, dim3(gx, (unsigned)seg[i].k), dim3(kGradThreads), 0, st,
-                         partial, pstride, n > 0 ? (b > 8 ? nchunks_big : nchunks) : 0, D, b, ro);
+                         partial, pstride, n > 0 ? (b > 8 ? nchunks_big : nsum) : 0, D, b, ro);
     }
   }
   if (dX && n > 0 && !dx_direct) {
