@@ -275,7 +275,10 @@ void build_dpp_image(const harp_plan *plan, const std::vector<StageEff> &eff, in
   float *base = image.data() + off;
   // factor of global coordinate i in execution stage e: the member with digit value 0 holds
   // m10 / m00 (it receives the other member), the member with digit value 1 holds m01 / m11
-  auto block_of = [&](const StageEff &se, int64_t i) { return (i / (2 * se.s)) * se.s + i % se.s; };
+  auto block_of = [&](const StageEff &se, int64_t i) {
+    const uint32_t at = (uint32_t)i, st = (uint32_t)se.s;   // d <= 2^24: 32-bit divisions
+    return (int64_t)(at / (2 * st) * st + at % st);
+  };
   for (int64_t kch = 0; kch < nchunk; ++kch)
     for (int grp = 0; grp < 2; ++grp) {
       // group A works in the low layout going up and in the high layout going down; B the other
@@ -290,7 +293,7 @@ void build_dpp_image(const harp_plan *plan, const std::vector<StageEff> &eff, in
             for (int q = 0; q < 4; ++q) {
               const int64_t i = kch * D + 16 * (int64_t)dpp_segment_of(high, (unsigned)t, L) + 4 * k + q;
               const int64_t c = block_of(se, i);
-              const int r = (int)((i / se.s) & 1);
+              const int r = (int)(((uint32_t)i / (uint32_t)se.s) & 1);
               const size_t slot = ((size_t)(ee * 4 + k) * TG + t) * 4 + q;
               if (!dense) {
                 g[slot] = r == 0 ? se.la[c] : se.lb[c];
@@ -457,14 +460,13 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
           const int bp = ilog2(se.s / S);
           // the kernels assume digit position e (ascending) or k-1-e (descending)
           if (bp != (pd.desc ? k - 1 - e : e)) return false;
+          const uint32_t s32 = (uint32_t)se.s, S32 = (uint32_t)S;   // d <= 2^24: 32-bit divisions
           for (int64_t q = 0; q < nqp; ++q) {
-            const int64_t hi = q / S, lo = q % S;
-            const int64_t base = hi * P * S + lo;
+            const uint32_t base = (uint32_t)q / S32 * (uint32_t)P * S32 + (uint32_t)q % S32;
             for (int p = 0; p < P / 2; ++p) {
               const int j0 = ((p >> bp) << (bp + 1)) | (p & ((1 << bp) - 1));
-              const int64_t idx0 = base + (int64_t)j0 * S;
-              const int64_t beta = idx0 % se.s, alpha = idx0 / (2 * se.s);
-              const int64_t c = alpha * se.s + beta;
+              const uint32_t idx0 = base + (uint32_t)j0 * S32;
+              const uint32_t c = idx0 / (2 * s32) * s32 + idx0 % s32;
               if (se.form != FORM_DENSE) {
                 const size_t v0 = (size_t)(e * (P / 2) + p) * 2;
                 img[(v0 + 0) * nqp + q] = se.la[c];
@@ -1466,26 +1468,40 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
       if (!build_col_passes(plan, (Direction)dir, image.data(), true, plan->colwide[dir]) ||
           plan->colwide[dir].size() >= plan->colpass[dir].size())
         plan->colwide[dir].clear();
-      auto upload = [&](const void *host, size_t bytes, void **dev) {
-        if (hipMalloc(dev, bytes) != hipSuccess) return HARP_ERR_OOM;
-        plan->dev_allocs.push_back(*dev);
-        return hipMemcpy(*dev, host, bytes, hipMemcpyHostToDevice) == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
+      // tables, block values and pass descriptors of a direction in one allocation and one copy
+      std::vector<ColPassHost> *lists[2] = {&plan->colpass[dir], &plan->colwide[dir]};
+      size_t bytes = 0;
+      auto place = [&](size_t size) {
+        const size_t at = bytes;
+        bytes += (size + 255) / 256 * 256;
+        return at;
       };
-      for (std::vector<ColPassHost> *passes : {&plan->colpass[dir], &plan->colwide[dir]})
+      for (auto *passes : lists)
         for (ColPassHost &ph : *passes) {
-          void *dev = nullptr;
-          if (st == HARP_OK && !ph.ptab.empty()) {
-            st = upload(ph.ptab.data(), ph.ptab.size() * 4, &dev);
-            ph.pass.ptab = (const uint32_t *)dev;
-          }
-          if (st == HARP_OK && !ph.packed.empty()) {
-            st = upload(ph.packed.data(), ph.packed.size() * 4, &dev);
-            ph.pass.packed = (const float *)dev;
-            std::vector<float>().swap(ph.packed);
-          }
-          if (st == HARP_OK) st = upload(&ph.pass, sizeof(ColPass), &dev);
-          ph.dev = (const ColPass *)dev;
+          place(ph.ptab.size() * 4);
+          place(ph.packed.size() * 4);
+          place(sizeof(ColPass));
         }
+      char *dev = nullptr;
+      if (hipMalloc((void **)&dev, bytes) != hipSuccess) {
+        st = HARP_ERR_OOM;
+        break;
+      }
+      plan->dev_allocs.push_back(dev);
+      std::vector<char> stage(bytes);
+      bytes = 0;
+      for (auto *passes : lists)
+        for (ColPassHost &ph : *passes) {
+          const size_t tab = place(ph.ptab.size() * 4), pack = place(ph.packed.size() * 4), desc = place(sizeof(ColPass));
+          ph.pass.ptab = ph.ptab.empty() ? nullptr : (const uint32_t *)(dev + tab);
+          ph.pass.packed = ph.packed.empty() ? nullptr : (const float *)(dev + pack);
+          memcpy(stage.data() + tab, ph.ptab.data(), ph.ptab.size() * 4);
+          memcpy(stage.data() + pack, ph.packed.data(), ph.packed.size() * 4);
+          memcpy(stage.data() + desc, &ph.pass, sizeof(ColPass));
+          ph.dev = (const ColPass *)(dev + desc);
+          std::vector<float>().swap(ph.packed);
+        }
+      if (hipMemcpy(dev, stage.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) st = HARP_ERR_DEVICE;
     }
   } catch (const std::bad_alloc &) {
     st = HARP_ERR_OOM;

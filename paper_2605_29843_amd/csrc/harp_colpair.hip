@@ -117,6 +117,21 @@ harp_status_t launch_pair_inst(const ColPass &hp, const void *src, int64_t lds_,
     }                                                       \
   } while (0)
 
+// K[i][q] of three radix-2 stages on eight coordinates (see col_pair_image), digits from the lowest up or down
+template <bool DESC>
+void product_of_three(const float *const (&blk)[6][8], float (&K)[64]) {
+  for (int i = 0; i < 8; ++i) {
+    double v[8];
+    for (int q = 0; q < 8; ++q) {
+      constexpr int b0 = DESC ? 2 : 0, b2 = DESC ? 0 : 2;
+      const int e1 = (i & ~(1 << b0)) | (q & (1 << b0)), e2 = (q & ~(1 << b2)) | (i & (1 << b2));
+      v[q] = (double)blk[0][i][(i >> b0 & 1) * 2 + (q >> b0 & 1)] * (double)blk[1][e1][(i >> 1 & 1) * 2 + (q >> 1 & 1)] *
+             (double)blk[2][e2][(i >> b2 & 1) * 2 + (q >> b2 & 1)];
+    }
+    for (int q = 0; q < 8; ++q) K[i * 8 + q] = (float)v[q];
+  }
+}
+
 }  // namespace
 
 // Stages [i0, e0) of the column image, consecutive digits in ascending or descending order, as one such pass: the
@@ -167,46 +182,74 @@ void col_pair_image(const std::vector<ColStage> &st, int i0, int e0, int split, 
   const int n1 = R[1] * chain_pieces(R[0]), n2 = R[0] * chain_pieces(R[1]);
   out.assign((size_t)tiles * (n1 + n2) * 16, 0.0f);
   float K[64];
-  for (int64_t T = 0; T < tiles; ++T)
+  int place[2][64];   // [group][entry]: where it lies among a block's pieces
+  bool three2[2];
+  for (int g = 0; g < 2; ++g) {
+    const int b = R[g], nh = b > 4 ? 2 : 1;
+    for (int r = 0; r < b; ++r)
+      for (int c = 0; c < b; ++c) {
+        const int w = r * nh + c / 4;
+        place[g][r * b + c] = (w / 4 * 4 + c % 4) * 4 + w % 4;
+      }
+    three2[g] = grp[g].size() == 3 && b == 8;
+  }
+  int digit[2][6][8], step[2][6];   // [group][stage]: its digit of a coordinate of the group, and that digit's stride
+  for (int g = 0; g < 2; ++g)
+    for (size_t t = 0; t < grp[g].size(); ++t) {
+      step[g][t] = (int)(grp[g][t].s / s0[g]);
+      for (int e = 0; e < R[g]; ++e) digit[g][t][e] = e / step[g][t] % grp[g][t].b;
+    }
+  for (int64_t T = 0; T < tiles; ++T) {
+    const int64_t row0 = (T / S) * P * S + T % S;
     for (int g = 0; g < 2; ++g) {
-      const int b = R[g], nh = b > 4 ? 2 : 1, np = chain_pieces(b);
+      const int b = R[g];
       float *o = out.data() + (size_t)T * (n1 + n2) * 16 + (g ? n1 * 16 : 0);
       for (int v = 0; v < P / b; ++v) {
-        const int64_t row = (T / S) * P * S + T % S + (int64_t)(g ? v : v * R[0]) * S;
+        const int64_t row = row0 + (int64_t)(g ? v : v * R[0]) * S;
         const float *Kp = K;
         if (grp[g].size() == 1) {
           const ColStage &c = grp[g][0];
           Kp = host_image + (c.blocks - st[0].blocks) + ((row / (b * s0[g])) * s0[g] + row % s0[g]) * b * b;
         } else {
-          // row i of the group's block: unit vector i through the group's stages (float64, rounded once)
-          for (int i = 0; i < b; ++i) {
-            double x[8] = {0.0}, y[8];
-            x[i] = 1.0;
-            for (const ColStage &c : grp[g]) {
-              const int sp = (int)(c.s / s0[g]);
-              const float *blocks = host_image + (c.blocks - st[0].blocks);
-              for (int p = 0; p < b; ++p) {
-                if ((p / sp) % c.b) continue;   // p: digit zero of this stage
-                const int64_t r0 = row + (int64_t)p * s0[g];
-                const float *k = blocks + ((r0 / ((int64_t)c.b * c.s)) * c.s + r0 % c.s) * c.b * c.b;
-                for (int q = 0; q < c.b; ++q) {
-                  double a = 0.0;
-                  for (int r = 0; r < c.b; ++r) a += x[p + r * sp] * (double)k[r * c.b + q];
-                  y[p + q * sp] = a;
-                }
+          // Each stage replaces one digit of the coordinate, so entry (i, q) is one product: for every stage
+          // the entry (its digit of i, its digit of q) of the block at the digits already replaced by q's
+          // and not yet replaced from i's (float64, rounded once).
+          const float *blk[6][8];   // [stage][coordinate]: the block of the coordinate in that stage
+          for (size_t t = 0; t < grp[g].size(); ++t) {
+            const ColStage &c = grp[g][t];
+            const unsigned cs = (unsigned)c.s, bs = (unsigned)c.b * cs;
+            for (int e = 0; e < b; ++e) {
+              if (digit[g][t][e]) {
+                blk[t][e] = blk[t][e - digit[g][t][e] * step[g][t]];
+                continue;
               }
-              std::copy(y, y + b, x);
+              const unsigned at = (unsigned)row + (unsigned)e * (unsigned)s0[g];
+              blk[t][e] = host_image + (c.blocks - st[0].blocks) + (size_t)(at / bs * cs + at % cs) * (unsigned)(c.b * c.b);
             }
-            for (int q = 0; q < b; ++q) K[i * b + q] = (float)x[q];
           }
+          if (three2[g])
+            desc ? product_of_three<true>(blk, K) : product_of_three<false>(blk, K);
+          else
+            for (int i = 0; i < b; ++i) {
+              double val[8] = {1.0};
+              int pos[8] = {i}, cnt = 1;
+              for (size_t t = 0; t < grp[g].size(); ++t) {
+                const int cb = grp[g][t].b, r = digit[g][t][i], sp = step[g][t];
+                for (int q = cb - 1; q >= 0; --q)   // (the last copy overwrites the values it is made from)
+                  for (int n = 0; n < cnt; ++n) {
+                    val[q * cnt + n] = val[n] * (double)blk[t][pos[n]][r * cb + q];
+                    pos[q * cnt + n] = pos[n] + (q - r) * sp;
+                  }
+                cnt *= cb;
+              }
+              for (int n = 0; n < b; ++n) K[i * b + pos[n]] = (float)val[n];
+            }
         }
-        for (int r = 0; r < b; ++r)
-          for (int c = 0; c < b; ++c) {
-            const int w = r * nh + c / 4;
-            o[((v * np + w / 4) * 4 + c % 4) * 4 + w % 4] = Kp[r * b + c];
-          }
+        float *ov = o + (size_t)v * chain_pieces(b) * 16;
+        for (int n = 0; n < b * b; ++n) ov[place[g][n]] = Kp[n];
       }
     }
+  }
 }
 
 // whole tiles of 128 columns, pairs of columns aligned (the caller's check for every unguarded column pass)
