@@ -984,7 +984,7 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
   const size_t ei = sizeof(TI), eo = sizeof(TO);
   // A single stage gains nothing from a tile in LDS: in registers whenever the accesses can be four
   // columns wide.  Passes with block-scaled halves on a side keep the tile (harp_col_one_kernel is
-  // not built for the format): the 8-row pass of a one-sided 28672 x 8192 bf16 rotation takes 696 us.
+  // not built for the format): the 8-row pass of 28672 x 8192 takes 696 us there.
   if constexpr (!IsZ16<TI>::value && !IsZ16<TO>::value) {
     if (col_one_pass(hp, src, lds_, ei, dst, ldd, eo, nrows, ncols))
       return launch_col_one<TI, TO, 1>(hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows, ncols, nullptr, stream);

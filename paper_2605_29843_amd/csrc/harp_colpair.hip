@@ -120,15 +120,20 @@ harp_status_t launch_pair_inst(const ColPass &hp, const void *src, int64_t lds_,
 // K[i][q] of three radix-2 stages on eight coordinates (see col_pair_image), digits from the lowest up or down
 template <bool DESC>
 void product_of_three(const float *const (&blk)[6][8], float (&K)[64]) {
+  constexpr int b0 = DESC ? 2 : 0, b2 = DESC ? 0 : 2;   // the bits in the order the stages run (1 is in the middle)
   for (int i = 0; i < 8; ++i) {
-    double v[8];
-    for (int q = 0; q < 8; ++q) {
-      constexpr int b0 = DESC ? 2 : 0, b2 = DESC ? 0 : 2;
-      const int e1 = (i & ~(1 << b0)) | (q & (1 << b0)), e2 = (q & ~(1 << b2)) | (i & (1 << b2));
-      v[q] = (double)blk[0][i][(i >> b0 & 1) * 2 + (q >> b0 & 1)] * (double)blk[1][e1][(i >> 1 & 1) * 2 + (q >> 1 & 1)] *
-             (double)blk[2][e2][(i >> b2 & 1) * 2 + (q >> b2 & 1)];
+    const float *p0 = blk[0][i] + (i >> b0 & 1) * 2;
+    for (int q0 = 0; q0 < 2; ++q0) {
+      const int e1 = (i & ~(1 << b0)) | q0 << b0;
+      const float *p1 = blk[1][e1] + (i >> 1 & 1) * 2;
+      for (int q1 = 0; q1 < 2; ++q1) {
+        const int e2 = (e1 & ~2) | q1 << 1;
+        const float *p2 = blk[2][e2] + (i >> b2 & 1) * 2;
+        const double f = (double)p0[q0] * (double)p1[q1];
+        K[i * 8 + (e2 & ~(1 << b2))] = (float)(f * p2[0]);
+        K[i * 8 + (e2 | 1 << b2)] = (float)(f * p2[1]);
+      }
     }
-    for (int q = 0; q < 8; ++q) K[i * 8 + q] = (float)v[q];
   }
 }
 
