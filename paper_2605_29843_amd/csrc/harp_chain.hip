@@ -23,7 +23,7 @@
 // 2048 x 4096 bf16 (8,8,8,8), one tile per compute unit: 18.3 us on one block per thread -> 14.5 us, of
 // which 1.6 us are the launch, 3 us the rows' arrival, 6 us stages, 2 us the exchange, 2 us the
 // stores; 777 x 14336 transposed (8,8,8,7 | 4), both launches: 60 -> 36 us; six rows of 14336:
-// 18.3 -> 12.5 us; 28672 x 8192 bf16 -> float32: 472 -> 310 us (1.41 GB).  Touching every line of the
+// 18.3 -> 12.5 us; 28672 x 8192 bf16 -> float32: 472 -> 325 us (1.41 GB).  Touching every line of the
 // values at the start of a launch, so that the first reads find them in the L2, was slower (six
 // rows: 13.6 -> 15.5 us).
 #include <hip/hip_runtime.h>
@@ -37,7 +37,6 @@
 namespace harp {
 
 namespace {
-
 
 constexpr int kChainRows = 8;   // rows per tile
 
@@ -53,8 +52,9 @@ struct ChainShape {
   static constexpr int PITCH = CHUNK + 8;             // LDS row (floats): four rows x 8 lo hit 32 banks
   // 16-byte pieces of block values a lane holds: those in use and the next two batches.  Outputs come in
   // aligned quads while the inputs they replace are spread over other quads, so a stage needs up to 64
-  // registers more than its coordinates: with a ring of 16 every shape spilled, with 8 none of these
-  // is faster (radix 4 has smaller batches: eight pieces are as many ahead and leave it its registers)
+  // registers more than its coordinates: with a ring of 16 most shapes spilled (2048 x 4096 bf16 15.3 us
+  // against 14.6, six rows of 14336 13.6 against 12.5).  Radix 4 has smaller batches: eight pieces are as
+  // many ahead, and its waves hold two blocks of 16 lo.
   static constexpr int RING = R4 == 4 ? 8 : 12;
   static constexpr int NA = 32;                       // pieces per unit, stages at strides 1 and 8
   static constexpr int NC = R4 * chain_pieces(R3);    // pieces per block of 16 lo

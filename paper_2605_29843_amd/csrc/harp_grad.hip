@@ -118,7 +118,8 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_kernel(
 // g[idx_r2] K[r][r2] (in place).  Partial sums go to partial[(chunk * B*B + v) * D + c].
 // Backward kernels: a workgroup is 128 items x four groups of rows.  The partial sums of a stage's block
 // gradients are a fifth of the bytes such a kernel moves when every 8 rows write theirs; the four groups
-// add theirs in LDS first (2048 x 4096 radix 2: see launch_grad), in a fixed order.
+// add theirs in LDS first, in a fixed order (2048 x 4096 bf16 radix 2: a run of three stages 20 -> 18 - 19 us, its
+// reduction 5.7 -> 4.5; 1537 x 11008 float32: radix-4 stage 45 -> 38 us, reduction 8.0 -> 5.2).
 constexpr int kSumItems = 128, kSumGroups = 4, kSumThreads = kSumItems * kSumGroups;
 struct SumRows {
   int item, group;
