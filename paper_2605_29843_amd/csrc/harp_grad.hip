@@ -24,6 +24,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "harp_internal.h"
@@ -32,6 +33,13 @@ namespace harp {
 namespace {
 
 constexpr int kGradThreads = 256;
+
+// Element i of a row of fewer than 2^24: a scalar row address and a 32-bit byte offset per lane.
+template <typename T>
+__device__ __forceinline__ T *grad_at(T *row, int i) {
+  typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte_t;
+  return reinterpret_cast<T *>(reinterpret_cast<byte_t *>(row) + (uint32_t)i * (uint32_t)sizeof(T));
+}
 
 __device__ __forceinline__ float grad_widen(float v) { return v; }
 __device__ __forceinline__ float grad_widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
@@ -128,7 +136,7 @@ struct SumRows {
 __device__ __forceinline__ SumRows sum_rows(int64_t n, int rows) {
   SumRows sr;
   sr.item = (int)threadIdx.x % kSumItems;
-  sr.group = (int)threadIdx.x / kSumItems;
+  sr.group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSumItems);   // whole waves: row addresses are scalar
   const int per = (rows + kSumGroups - 1) / kSumGroups;
   const int64_t w0 = (int64_t)blockIdx.y * rows, w1 = (w0 + rows < n) ? w0 + rows : n;
   sr.r0 = w0 + (int64_t)sr.group * per;
@@ -177,13 +185,13 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
   auto request = [&](int64_t row) {
 #pragma unroll
     for (int r = 0; r < B; ++r) {
-      nx[r] = X[row * ld + base + (size_t)r * s];
-      ng[r] = Gm[row * ld + base + (size_t)r * s];
+      nx[r] = *grad_at(X + row * ld, base + r * s);
+      ng[r] = *grad_at(Gm + row * ld, base + r * s);
     }
   };
   if (sr.r0 < r1) request(sr.r0);
   for (int64_t row = sr.r0; row < r1; ++row) {
-    float *g = Gm + row * ld + base;
+    float *g = Gm + row * ld;
     float xv[B], gv[B];
 #pragma unroll
     for (int r = 0; r < B; ++r) {
@@ -199,7 +207,7 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
         acc[r * B + r2] = fmaf(xv[r], gv[r2], acc[r * B + r2]);
         back = fmaf(gv[r2], K[r * B + r2], back);
       }
-      g[(size_t)r * s] = back;
+      *grad_at(g, base + r * s) = back;
     }
   }
   sum_groups<B * B>(acc, sr);
@@ -435,40 +443,31 @@ static bool dk_mfma_supported(int b, int s, int D, const void *X, int64_t ldx, c
   } while (0)
 
 // Run of K radix-2 stages with strides s, 2s, .., 2^(K-1) s.  Item q = hi s + lo owns the
-// coordinates base + e s, e < 2^K, base = hi 2^K s + lo.  Stage i pairs e0 (bit i clear) with
-// e0 + 2^i; that pair is block c = (i0 / (2 s_i)) s_i + i0 % s_i of the stage, i0 = base + e0 s,
-// s_i = 2^i s.
+// coordinates base + e s, e < 2^K, base = hi 2^K s + lo.  Stage i pairs e0 (bit i clear) with e0 + 2^i.
+// Pair p (e0 with bit i taken out) is block hi 2^(K-1) s + lo + p s of its stage, whatever the stage.
 struct GradRun {
   const float *blocks[3];
 };
 
+// c0: the item's block of pair 0
 template <int K>
-__device__ __forceinline__ void grad_run_blocks(const GradRun &run, int base, int s, int D,
-                                                float (&kv)[K][1 << (K - 1)][4],
-                                                int (&cidx)[K][1 << (K - 1)]) {
+__device__ __forceinline__ void grad_run_blocks(const GradRun &run, int c0, int s, float (&kv)[K][1 << (K - 1)][4]) {
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const int si = s << i;
+  for (int i = 0; i < K; ++i)
 #pragma unroll
     for (int p = 0; p < (1 << (K - 1)); ++p) {
-      const int eh = p >> i, el = p & ((1 << i) - 1);
-      const int e0 = (eh << (i + 1)) | el;
-      const int i0 = base + e0 * s;
-      const int c = (i0 / (2 * si)) * si + i0 % si;
-      cidx[i][p] = c;
-      const float4 f = *reinterpret_cast<const float4 *>(run.blocks[i] + (size_t)c * 4);
+      const float4 f = *reinterpret_cast<const float4 *>(run.blocks[i] + (size_t)(c0 + p * s) * 4);
       kv[i][p][0] = f.x; kv[i][p][1] = f.y; kv[i][p][2] = f.z; kv[i][p][3] = f.w;
     }
-  }
-  (void)D;
 }
 
 // The E coordinates x[e s] of an item, float32 or bf16 (the caller's own rows in the first and
 // last run, so that no separate conversion pass is needed); vec: stride 1 and aligned rows, the
 // item is contiguous and moves with 16-byte accesses.
 template <int E, typename T>
-__device__ __forceinline__ void grad_load_item(const T *x, int s, bool vec, float (&v)[E]) {
+__device__ __forceinline__ void grad_load_item(const T *row, int base, int s, bool vec, float (&v)[E]) {
   if (vec) {
+    const T *x = grad_at(row, base);
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
       for (int q = 0; q < E / 4; ++q) {
@@ -490,12 +489,13 @@ __device__ __forceinline__ void grad_load_item(const T *x, int s, bool vec, floa
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = grad_widen(x[(size_t)e * s]);
+    for (int e = 0; e < E; ++e) v[e] = grad_widen(*grad_at(row, base + e * s));
   }
 }
 template <int E, typename T>
-__device__ __forceinline__ void grad_store_item(T *y, int s, bool vec, const float (&v)[E]) {
+__device__ __forceinline__ void grad_store_item(T *row, int base, int s, bool vec, const float (&v)[E]) {
   if (vec) {
+    T *y = grad_at(row, base);
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
       for (int q = 0; q < E / 4; ++q)
@@ -512,7 +512,7 @@ __device__ __forceinline__ void grad_store_item(T *y, int s, bool vec, const flo
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) grad_narrow(v[e], y + (size_t)e * s);
+    for (int e = 0; e < E; ++e) grad_narrow(v[e], grad_at(row, base + e * s));
   }
 }
 
@@ -526,25 +526,24 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_run_kernel(
   if (q >= nitems) return;
   const int base = (q / s) * E * s + q % s;
   float kv[K][H][4];
-  int cidx[K][H];
-  grad_run_blocks<K>(run, base, s, 0, kv, cidx);
+  grad_run_blocks<K>(run, (q / s) * H * s + q % s, s, kv);
   const int64_t r0 = (int64_t)blockIdx.y * rows;
   const int64_t r1 = (r0 + rows < n) ? r0 + rows : n;
   // the next row is requested before the work on the current one
   // stride 1: the item's coordinates are contiguous (16-byte accesses when the row allows it)
   const bool vec = aligned && (s == 1) && (E % 4 == 0) && (ld % 4 == 0);
   const bool vecx = vec && ldx % (16 / (int)sizeof(TX)) == 0 && (uintptr_t)X % 16 == 0;
-  auto load_item = [&](const TX *x, float (&v)[E]) { grad_load_item<E, TX>(x, s, vecx, v); };
+  auto load_item = [&](const TX *row_, float (&v)[E]) { grad_load_item<E, TX>(row_, base, s, vecx, v); };
   float nx[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) nx[e] = 0.f;
-  if (r0 < r1) load_item(X + r0 * ldx + base, nx);
+  if (r0 < r1) load_item(X + r0 * ldx, nx);
   for (int64_t row = r0; row < r1; ++row) {
     float *y = Y + row * ld + base;
     float v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = nx[e];
-    if (row + 1 < r1) load_item(X + (row + 1) * ldx + base, nx);
+    if (row + 1 < r1) load_item(X + (row + 1) * ldx, nx);
 #pragma unroll
     for (int i = 0; i < K; ++i)
 #pragma unroll
@@ -582,8 +581,8 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
   const int q0 = blockIdx.x * kSumItems + sr.item, q = q0 < nitems ? q0 : nitems - 1;
   const int base = (q / s) * E * s + q % s;
   float kv[K][H][4], acc[K * H * 4];
-  int cidx[K][H];
-  grad_run_blocks<K>(run, base, s, D, kv, cidx);
+  const int c0 = (q / s) * H * s + q % s;
+  grad_run_blocks<K>(run, c0, s, kv);
 #pragma unroll
   for (int v = 0; v < K * H * 4; ++v) acc[v] = 0.f;
   const int64_t r0 = sr.r0, r1 = q0 < nitems ? sr.r1 : sr.r0;   // threads past the last item have no rows
@@ -595,11 +594,10 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
 #pragma unroll
   for (int e = 0; e < E; ++e) nx[e] = ng[e] = 0.f;
   if (r0 < r1) {
-    grad_load_item<E, TX>(X + r0 * ldx + base, s, vecx, nx);
-    grad_load_item<E, TGI>(Gin + r0 * ldgi + base, s, vecgi, ng);
+    grad_load_item<E, TX>(X + r0 * ldx, base, s, vecx, nx);
+    grad_load_item<E, TGI>(Gin + r0 * ldgi, base, s, vecgi, ng);
   }
   for (int64_t row = r0; row < r1; ++row) {
-    TGO *g = Gout + row * ldgo + base;
     float xs[K][E], gv[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -607,8 +605,8 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
       gv[e] = ng[e];
     }
     if (row + 1 < r1) {   // the next row (its g is not written by anyone before this thread does)
-      grad_load_item<E, TX>(X + (row + 1) * ldx + base, s, vecx, nx);
-      grad_load_item<E, TGI>(Gin + (row + 1) * ldgi + base, s, vecgi, ng);
+      grad_load_item<E, TX>(X + (row + 1) * ldx, base, s, vecx, nx);
+      grad_load_item<E, TGI>(Gin + (row + 1) * ldgi, base, s, vecgi, ng);
     }
     // inputs of the inner stages, recomputed
 #pragma unroll
@@ -637,7 +635,7 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
         gv[e1] = fmaf(g1, kv[i][p][3], g0 * kv[i][p][2]);
       }
     }
-    grad_store_item<E, TGO>(g, s, vecgo, gv);
+    grad_store_item<E, TGO>(Gout + row * ldgo, base, s, vecgo, gv);
   }
   sum_groups<K * H * 4>(acc, sr);
   if (sr.group != 0 || q0 >= nitems) return;
@@ -647,7 +645,7 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
     for (int p = 0; p < H; ++p)
 #pragma unroll
       for (int w = 0; w < 4; ++w)
-        partial[(size_t)i * pstride + ((size_t)blockIdx.y * 4 + w) * D + cidx[i][p]] = acc[(i * H + p) * 4 + w];
+        partial[(size_t)i * pstride + ((size_t)blockIdx.y * 4 + w) * D + c0 + p * s] = acc[(i * H + p) * 4 + w];
 }
 
 // dK[c][v] = sum over the chunks of partial[(chunk * BB + v) * D + c], in a fixed order: eight
