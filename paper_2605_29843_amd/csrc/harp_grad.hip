@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "harp_internal.h"
+#include "harp_mfma4.h"
 
 namespace harp {
 namespace {
@@ -122,8 +123,6 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_fwd_kernel(
   }
 }
 
-// For the rows of chunk blockIdx.y: acc[r][r2] += x[idx_r] g[idx_r2];  g[idx_r] <- sum_r2
-// g[idx_r2] K[r][r2] (in place).  Partial sums go to partial[(chunk * B*B + v) * D + c].
 // Backward kernels: a workgroup is 128 items x four groups of rows.  The partial sums of a stage's block
 // gradients are a fifth of the bytes such a kernel moves when every 8 rows write theirs; the four groups
 // add theirs in LDS first, in a fixed order (2048 x 4096 bf16 radix 2: a run of three stages 20 -> 18 - 19 us, its
@@ -144,44 +143,61 @@ __device__ __forceinline__ SumRows sum_rows(int64_t n, int rows) {
   return sr;
 }
 // acc of group 0 <- (group 0 + group 2) + (group 1 + group 3); every thread of the workgroup takes part
+// (red: 2 NV kSumItems floats of LDS that nobody uses any more)
 template <int NV>
-__device__ __forceinline__ void sum_groups(float (&acc)[NV], const SumRows &sr) {
-  __shared__ float red[2][NV][kSumItems];
+__device__ __forceinline__ void sum_groups(float (&acc)[NV], const SumRows &sr, float *red) {
+  auto at = [&](int half, int v) -> float & { return red[(half * NV + v) * kSumItems + sr.item]; };
   if (sr.group >= 2) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) red[sr.group - 2][v][sr.item] = acc[v];
+    for (int v = 0; v < NV; ++v) at(sr.group - 2, v) = acc[v];
   }
   __syncthreads();
   if (sr.group < 2) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] += red[sr.group][v][sr.item];
+    for (int v = 0; v < NV; ++v) acc[v] += at(sr.group, v);
   }
   if (sr.group == 1) {   // into the slots that this thread alone has read
 #pragma unroll
-    for (int v = 0; v < NV; ++v) red[1][v][sr.item] = acc[v];
+    for (int v = 0; v < NV; ++v) at(1, v) = acc[v];
   }
   __syncthreads();
   if (sr.group == 0) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] += red[1][v][sr.item];
+    for (int v = 0; v < NV; ++v) acc[v] += at(1, v);
   }
 }
 
+// For the rows of chunk blockIdx.y: acc[r][r2] += x[idx_r] g[idx_r2];  g[idx_r] <- sum_r2
+// g[idx_r2] K[r][r2] (in place).  Partial sums go to partial[(chunk * B*B + v) * D + c].
+// The blocks of a workgroup lie one after the other in memory.  From radix 5 on they enter by whole lines
+// through LDS (odd pitch: 64 blocks spread over the banks) under the first rows' way: with each lane
+// fetching its own block, 64 lines a load, the kernel of 4096 radix 8 took 14.6 instead of 9.1 us at 256
+// rows and 21.5 instead of 19.5 us at 2048.  Smaller blocks are fetched by their lanes (radix 4: 1.5 % faster).
 template <int B>
 __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
     const float *__restrict__ X, float *__restrict__ Gm, int64_t ld, int64_t n, int rows,
     const float *__restrict__ blocks, int D, int s, float *__restrict__ partial) {
   const SumRows sr = sum_rows(n, rows);
   const int c0 = blockIdx.x * kSumItems + sr.item, c = c0 < D ? c0 : D - 1;
-  float K[B * B], acc[B * B];
+  constexpr int BB = B * B, PITCH = BB | 1, NK = (kSumItems * BB + kSumThreads - 1) / kSumThreads;
+  constexpr bool STAGED = B > 4;
+  static_assert(PITCH <= 2 * BB, "the blocks fit in the space of the sums");
+  __shared__ float red[2 * BB * kSumItems];
+  const int first = (int)blockIdx.x * kSumItems;
+  const int left = (D - first < kSumItems ? D - first : kSumItems) * BB;   // block values of the workgroup
+  float K[BB], acc[BB], kk[NK], nx[B], ng[B];
+  if constexpr (STAGED) {
 #pragma unroll
-  for (int v = 0; v < B * B; ++v) {
-    K[v] = blocks[(size_t)c * (B * B) + v];
-    acc[v] = 0.f;
+    for (int i = 0; i < NK; ++i) {
+      const int at = (int)threadIdx.x + i * kSumThreads;
+      kk[i] = blocks[(size_t)first * BB + (at < left ? at : 0)];
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < BB; ++v) K[v] = blocks[(size_t)c * BB + v];
   }
   const int base = (c / s) * B * s + c % s;
   const int64_t r1 = c0 < D ? sr.r1 : sr.r0;   // threads past the last block have no rows
-  float nx[B], ng[B];
   auto request = [&](int64_t row) {
 #pragma unroll
     for (int r = 0; r < B; ++r) {
@@ -190,6 +206,18 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
     }
   };
   if (sr.r0 < r1) request(sr.r0);
+  if constexpr (STAGED) {
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      const int at = (int)threadIdx.x + i * kSumThreads;
+      if (at < left) red[at / BB * PITCH + at % BB] = kk[i];
+    }
+    lds_barrier();   // the first rows stay on their way
+#pragma unroll
+    for (int v = 0; v < BB; ++v) K[v] = red[(c - first) * PITCH + v];
+  }
+#pragma unroll
+  for (int v = 0; v < BB; ++v) acc[v] = 0.f;
   for (int64_t row = sr.r0; row < r1; ++row) {
     float *g = Gm + row * ld;
     float xv[B], gv[B];
@@ -210,7 +238,8 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_kernel(
       *grad_at(g, base + r * s) = back;
     }
   }
-  sum_groups<B * B>(acc, sr);
+  if constexpr (STAGED) __syncthreads();   // everyone has its block
+  sum_groups<BB>(acc, sr, red);
   if (sr.group == 0 && c0 < D) {
 #pragma unroll
     for (int v = 0; v < B * B; ++v)
@@ -637,7 +666,8 @@ __global__ __launch_bounds__(kSumThreads) void harp_grad_bwd_run_kernel(
     }
     grad_store_item<E, TGO>(Gout + row * ldgo, base, s, vecgo, gv);
   }
-  sum_groups<K * H * 4>(acc, sr);
+  __shared__ float red[2 * K * H * 4 * kSumItems];
+  sum_groups<K * H * 4>(acc, sr, red);
   if (sr.group != 0 || q0 >= nitems) return;
 #pragma unroll
   for (int i = 0; i < K; ++i)
@@ -751,11 +781,25 @@ int grad_chunks(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, 256));
 }
 
-// Row chunks of the backward kernels of stages up to radix 8: four groups of eight rows each, longer ones
-// beyond 8192 rows.
-int grad_sum_chunks(int64_t n) {
-  const int64_t c = (n + 8 * kSumGroups - 1) / (8 * kSumGroups);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(c, 256));
+// Row chunks of the backward kernel of a stage (or run) with `items` blocks (or items) per row.  A workgroup
+// of four groups takes 4, 8 or 16 rows as long as the launch then has no more than 64, 128 or 256 workgroups,
+// else 32 (more beyond 8192 rows).  The rows of a group follow one another, so few rows want many
+// workgroups, while each workgroup costs its block values and a set of partial sums, which the reduction
+// reads again.  4096 radix 8 (four workgroups wide), kernel + reduction, us, at 4 / 8 / 16 / 32 rows each:
+// 128 rows 12.2 / 11.4 / 11.6 / 14.8, 256 rows 15.2 / 13.6 / 13.3 / 16.3, 1024 rows 34 / 22.5 / 17.6 / 17.6,
+// 2048 rows 38 / 38 / 27.7 / 24.1.  Whole calls against 32 rows each throughout, us: 60 rows 132 -> 79,
+// 256 rows 149 -> 104 (radix 8, generic blocks), 512 rows 94 -> 77 (radix 2).
+int grad_sum_chunks(int64_t n, int64_t items) {
+  const int64_t wide = (items + kSumItems - 1) / kSumItems;
+  for (int64_t rows = kSumGroups; rows <= 4 * kSumGroups; rows *= 2)
+    if ((n + rows - 1) / rows * wide <= 16 * rows) return (int)std::max<int64_t>(1, (n + rows - 1) / rows);
+  return (int)std::min<int64_t>((n + 8 * kSumGroups - 1) / (8 * kSumGroups), 256);
+}
+// At least grad_sum_chunks(n, items), and never less for more rows.
+static int64_t grad_sum_chunks_bound(int64_t n, int64_t items) {
+  const int64_t wide = (items + kSumItems - 1) / kSumItems;
+  const int64_t few = std::min<int64_t>((n + kSumGroups - 1) / kSumGroups, std::max<int64_t>(16 * 4 * kSumGroups / wide, 1));
+  return std::max<int64_t>(1, std::max(few, std::min<int64_t>((n + 8 * kSumGroups - 1) / (8 * kSumGroups), 256)));
 }
 
 // Segments of the backward pass: the first `lead` stages as one segment of 64 coordinates
@@ -797,16 +841,25 @@ static int64_t grad_big_chunks_bound(int64_t n) {
 // in it is one that never falls, and the plan without the leading segment keeps one matrix more, so
 // neither end of that segment's range of n is a step down).
 size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
-  int bsmall = 6;   // a run of three radix-2 stages leaves 3 * (d / 2) * 4 partial values per chunk
   int bbig = 0;
-  for (int32_t b : plan->radices) (b > 8 ? bbig : bsmall) = std::max(b > 8 ? bbig : bsmall, (int)b);
+  size_t per_row = 0;   // the most partial sums of one launch, times 1 / d: chunks * b of a stage, chunks * 2 k of a run
+  for (int32_t b : plan->radices) {
+    if (b > 8) {
+      bbig = std::max(bbig, (int)b);
+      per_row = std::max(per_row, (size_t)grad_big_chunks_bound(n) * b);
+    } else {
+      per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d / b) * b);
+    }
+  }
+  const int lead = grad_seg_stages(plan, n);
+  // (the segments behind the leading one are among these, or shorter runs with fewer chunks)
+  for (const GradSegment &sg : grad_segments(plan, 0))
+    if (sg.k > 1) per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d >> sg.k) * 2 * sg.k);
   const size_t mat = (size_t)n * (size_t)plan->d * 4;
-  const size_t partial = std::max((size_t)grad_sum_chunks(n) * bsmall, (size_t)grad_big_chunks_bound(n) * bbig) *
-                         (size_t)plan->d * 4;
+  const size_t partial = per_row * (size_t)plan->d * 4;
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
   const size_t extra = 1 + (bbig > 0 ? 1 : 0);
   size_t need = (grad_segments(plan, 0).size() + extra) * mat + partial;
-  const int lead = grad_seg_stages(plan, n);
   if (lead > 0)
     need = std::max(need, (grad_segments(plan, lead).size() + extra) * mat +
                               std::max(partial, grad_seg_partial_bytes(plan, n)));
@@ -826,8 +879,6 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   const int64_t d = plan->d;
   const int nchunks = grad_chunks(n);
   const int rows = (int)((n + nchunks - 1) / nchunks);
-  const int nsum = grad_sum_chunks(n);
-  const int rows_sum = (int)((n + nsum - 1) / nsum);
   const int rows_big = grad_big_rows(n);
   const int nchunks_big = grad_big_chunks(n);
   const size_t mat = (size_t)n * (size_t)d;
@@ -837,7 +888,6 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   float *g = act + (size_t)nseg * mat;      // gradient, updated in place (radix <= 8) ...
   float *g2 = g + mat;                      // ... or into the other of two matrices (radix >= 9)
   float *partial = g + (bmax > 8 ? 2 : 1) * mat;
-  const size_t pstride = (size_t)nsum * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
   // 16-byte accesses of the stride-1 runs need the float32 copies on 16-byte boundaries
   const int aligned = (mat % 4 == 0);
   auto run_of = [&](const GradSegment &sg) {
@@ -920,6 +970,9 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   for (int i = nseg - 1; i >= 0; --i) {
     const ColStage &cs = stages[seg[i].t0];
     const float *in = act + (size_t)i * mat;
+    const int nsum = grad_sum_chunks(n, seg[i].k > 1 ? d >> seg[i].k : d / cs.b);
+    const int rows_sum = (int)((n + nsum - 1) / nsum);
+    const size_t pstride = (size_t)nsum * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
     if (i == 0 && lead > 0) {
       const harp_status_t rc = launch_grad_seg_bwd(plan, lead, X, ldx, bf, g, dX, lddx, n, partial, dK, st);
       if (rc != HARP_OK) return rc;

@@ -1,5 +1,6 @@
 // Building blocks of the kernels that multiply small dense blocks on v_mfma_f32_4x4x1_16b_f32 (sixteen
-// independent 4 x 4 outer-product updates): harp_chain.hip (rows) and harp_colwide.hip (columns).
+// independent 4 x 4 outer-product updates): harp_chain.hip (rows), harp_colwide.hip and harp_colpair.hip
+// (columns).  The barrier is harp_grad.hip's as well.
 #ifndef HARP_MFMA4_H_
 #define HARP_MFMA4_H_
 

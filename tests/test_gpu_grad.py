@@ -85,6 +85,30 @@ def test_grad_blocks_matches_the_oracle(harp, d, radices, n, kind, dtype):
     plan.destroy()
 
 
+# Row chunks of the backward kernels: 4, 8, 16 and 32 rows per workgroup of four groups, at the counts
+# where the next one is taken (n x workgroups per row = 256, 1024, 4096), with groups and chunks that are
+# not full; rows of 128 blocks, of fewer, and of several workgroups with a last one that is not full.
+# (assert_dk_parity's bound: at most 16 rows a group here, then up to 129 chunks, so its 2e-5 holds.)
+@pytest.mark.parametrize("d,radices,counts", [
+    (512, [8, 8, 8], (2, 5, 256, 257, 1024, 1025)), (280, [5, 8, 7], (3, 255, 259, 4097)),
+    (2688, [6, 7, 8, 8], (64, 65, 86, 257)), (1536, [3, 4, 2, 8, 8], (51, 129, 1366)),
+    (2048, [2] * 11, (33, 63, 129, 513)), (3125, [5] * 5, (52, 205))])
+def test_grad_row_chunks(harp, d, radices, counts):
+    rng = np.random.default_rng(d)
+    kind = "generic" if d % 2 else "orth"
+    blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
+    plan = harp.Plan(d, radices, blocks, signs)
+    for n in counts:
+        say("grad row chunks", radices, n)
+        X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+        dK, dX = harp.harp_grad_blocks(plan, to_device(X, "f32"), to_device(G, "f32"))
+        rK, rX = ho.grad_blocks(X, G, d, radices, blocks, signs)
+        assert_dk_parity(dK, rK, X, G, f"dK, {n} rows")
+        mag = summand_magnitude(G, d, radices, blocks, transpose=True) if kind == "generic" else None
+        assert_parity(to_host64(dX), rX, "f32", f"dX, {n} rows", mag=mag)
+    plan.destroy()
+
+
 def test_grad_blocks_without_signs_and_with_padded_rows(harp):
     import torch
     d, radices, n = 512, [2, 4, 8, 8], 70
