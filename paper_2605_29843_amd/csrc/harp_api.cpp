@@ -1396,7 +1396,7 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
     // Column-mode image (the plan as the U side of a weight rotation, and the blocks the
     // gradient kernels read): per direction the dense effective blocks [d / b][b][b] of every
     // stage in execution order, and -- when every radix is at most 8 -- the passes over them.
-    bool col_ok = true;
+    bool col_ok = true, launched = false;
     for (int t = 0; t < m; ++t) col_ok = col_ok && radices[t] <= 8;
     // (a plan with tied parameters keeps no expanded per-stage images: it cannot be the U side of
     // a column-mode rotation and has no block gradients)
@@ -1476,44 +1476,56 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
         plan->colpass[dir].clear();
         continue;
       }
-      if (!build_col_passes(plan, (Direction)dir, image.data(), true, plan->colwide[dir]) ||
-          plan->colwide[dir].size() >= plan->colpass[dir].size())
+      bool any_wide = false;
+      for (int t = 0; t < m; ++t) any_wide = any_wide || col_wide_stages(plan->col[dir], t);
+      if (any_wide && (!build_col_passes(plan, (Direction)dir, image.data(), true, plan->colwide[dir]) ||
+                       plan->colwide[dir].size() >= plan->colpass[dir].size()))
         plan->colwide[dir].clear();
-      // tables, block values and pass descriptors of a direction in one allocation and one copy
-      std::vector<ColPassHost> *lists[2] = {&plan->colpass[dir], &plan->colwide[dir]};
+      // tables, block values and pass descriptors of a direction in one allocation and one copy; the block
+      // values that the device makes itself lie behind them
+      std::vector<ColPassHost *> passes;
+      for (auto *list : {&plan->colpass[dir], &plan->colwide[dir]})
+        for (ColPassHost &ph : *list) passes.push_back(&ph);
       size_t bytes = 0;
       auto place = [&](size_t size) {
         const size_t at = bytes;
         bytes += (size + 255) / 256 * 256;
         return at;
       };
-      for (auto *passes : lists)
-        for (ColPassHost &ph : *passes) {
-          place(ph.ptab.size() * 4);
-          place(ph.packed.size() * 4);
-          place(sizeof(ColPass));
-        }
+      struct Place {
+        size_t tab, pack, desc;
+      };
+      std::vector<Place> at;
+      for (ColPassHost *ph : passes)
+        at.push_back(Place{place(ph->ptab.size() * 4), place(ph->packed.size() * 4), place(sizeof(ColPass))});
+      const size_t from_host = bytes;
+      for (size_t i = 0; i < passes.size(); ++i)
+        if (passes[i]->pair.grp[0].n > 0) at[i].pack = place(col_pair_floats(passes[i]->pair, d) * 4);
       char *dev = nullptr;
       if (hipMalloc((void **)&dev, bytes) != hipSuccess) {
         st = HARP_ERR_OOM;
         break;
       }
       plan->dev_allocs.push_back(dev);
-      std::vector<char> stage(bytes);
-      bytes = 0;
-      for (auto *passes : lists)
-        for (ColPassHost &ph : *passes) {
-          const size_t tab = place(ph.ptab.size() * 4), pack = place(ph.packed.size() * 4), desc = place(sizeof(ColPass));
-          ph.pass.ptab = ph.ptab.empty() ? nullptr : (const uint32_t *)(dev + tab);
-          ph.pass.packed = ph.packed.empty() ? nullptr : (const float *)(dev + pack);
-          memcpy(stage.data() + tab, ph.ptab.data(), ph.ptab.size() * 4);
-          memcpy(stage.data() + pack, ph.packed.data(), ph.packed.size() * 4);
-          memcpy(stage.data() + desc, &ph.pass, sizeof(ColPass));
-          ph.dev = (const ColPass *)(dev + desc);
-          std::vector<float>().swap(ph.packed);
-        }
-      if (hipMemcpy(dev, stage.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) st = HARP_ERR_DEVICE;
+      std::vector<char> stage(from_host);
+      for (size_t i = 0; i < passes.size() && st == HARP_OK; ++i) {
+        ColPassHost &ph = *passes[i];
+        const bool pair = ph.pair.grp[0].n > 0;
+        ph.pass.ptab = ph.ptab.empty() ? nullptr : (const uint32_t *)(dev + at[i].tab);
+        ph.pass.packed = ph.packed.empty() && !pair ? nullptr : (const float *)(dev + at[i].pack);
+        ph.dev = (const ColPass *)(dev + at[i].desc);
+        if (!ph.ptab.empty()) memcpy(stage.data() + at[i].tab, ph.ptab.data(), ph.ptab.size() * 4);
+        if (!ph.packed.empty()) memcpy(stage.data() + at[i].pack, ph.packed.data(), ph.packed.size() * 4);
+        memcpy(stage.data() + at[i].desc, &ph.pass, sizeof(ColPass));
+        std::vector<float>().swap(ph.packed);
+        if (pair) st = launch_pair_pack(ph.pair, d, (float *)(dev + at[i].pack), nullptr);
+        launched = launched || pair;
+      }
+      if (st == HARP_OK && hipMemcpy(dev, stage.data(), from_host, hipMemcpyHostToDevice) != hipSuccess)
+        st = HARP_ERR_DEVICE;
     }
+    // (the plan may be used on any stream as soon as this call returns)
+    if (st == HARP_OK && launched && hipStreamSynchronize(nullptr) != hipSuccess) st = HARP_ERR_DEVICE;
   } catch (const std::bad_alloc &) {
     st = HARP_ERR_OOM;
   }

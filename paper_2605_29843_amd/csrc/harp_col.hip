@@ -1180,7 +1180,7 @@ bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_im
     if (cp.npar > kColMaxPar) return false;
     // (products of blocks only where they cannot outgrow float32)
     const int split = e == i + 2 || plan->orthogonal ? col_pair_split(st, i, e) : 0;
-    if (split) col_pair_image(st, i, e, split, plan->d, host_image, cp, ph.packed);
+    if (split) col_pair_blocks(st, i, e, split, cp, ph.pair);
     ph.ptab = fix;
     ph.ptab.insert(ph.ptab.end(), fa.begin(), fa.end());
     ph.ptab.insert(ph.ptab.end(), fb.begin(), fb.end());

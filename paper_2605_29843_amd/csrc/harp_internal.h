@@ -159,11 +159,22 @@ struct ColPass {
   int32_t pad;
   ColOp op[kColMaxOps];
 };
+// Where the block values of a pass of two groups of stages come from (harp_colpair.hip): group 0 is the one
+// at the lower strides; words[g] floats of a tile are group g's.
+struct PairBlocks {
+  struct Group {
+    const float *blocks[3];   // device: the stage's dense blocks, stages in the order they run
+    int32_t b[3], s[3], step[3];   // radix, stride, stride in units of s0
+    int32_t n, R, s0;              // stages, product of their radices, lowest stride
+  } grp[2];
+  int32_t S, words[2];
+};
 struct ColPassHost {
   ColPass pass;
   const ColPass *dev;   // device copy
   std::vector<uint32_t> ptab;
-  std::vector<float> packed;
+  std::vector<float> packed;   // block values of a pass of 512 rows
+  PairBlocks pair{};           // pair.grp[0].n > 0: a pass of two groups, its block values made on the device
 };
 // stage of the column-mode image, execution order: dense blocks [d / b][b][b] with the signs
 // folded in (device memory)
@@ -352,8 +363,9 @@ bool build_col_passes(const harp_plan *plan, Direction dir, const float *host_im
                       std::vector<ColPassHost> &out);
 // passes of two stages with the tile in registers (harp_colpair.hip)
 int col_pair_split(const std::vector<ColStage> &st, int i0, int e0);
-void col_pair_image(const std::vector<ColStage> &st, int i0, int e0, int split, int64_t d, const float *host_image,
-                    ColPass &cp, std::vector<float> &out);
+void col_pair_blocks(const std::vector<ColStage> &st, int i0, int e0, int split, ColPass &cp, PairBlocks &pb);
+size_t col_pair_floats(const PairBlocks &pb, int64_t d);
+harp_status_t launch_pair_pack(const PairBlocks &pb, int64_t d, float *out, hipStream_t stream);
 harp_status_t launch_col_pair(const ColPass &hp, const void *src, int64_t lds_, harp_dtype_t dt_src, void *dst,
                               int64_t ldd, harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, hipStream_t stream);
 // passes of 512 rows (harp_colwide.hip)

@@ -42,3 +42,25 @@ def test_column_pass_of_two_stages(ru, rv, dtype):
     pu.destroy()
     if pv:
         pv.destroy()
+
+
+@pytest.mark.parametrize("ru", [[2] * 12, [8, 8, 8, 7]])
+def test_a_new_plan_is_ready_on_every_stream(ru):
+    """The block values of these passes are made by a kernel while the plan is created: they are there when
+    the call returns, for a stream that does not wait for any other."""
+    import torch
+    from paper_2605_29843_amd import harp
+    do, cols = int(np.prod(ru)), 128
+    rng = np.random.default_rng(do)
+    bu, su = gi.make_blocks(do, ru, "qr", rng), gi.make_signs(do, rng)
+    W = to_device(gi.round_to_bf16(rng.standard_normal((do, cols)).astype(np.float32)), "bf16")
+    side = torch.cuda.Stream()
+    for _ in range(5):
+        torch.cuda.synchronize()
+        plan = harp.Plan(do, ru, bu, su)
+        with torch.cuda.stream(side):
+            first = harp.harp_rotate_weight(plan, None, W)
+        torch.cuda.synchronize()
+        again = harp.harp_rotate_weight(plan, None, W)
+        assert torch.equal(first, again)
+        plan.destroy()
