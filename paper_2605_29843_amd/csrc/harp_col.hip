@@ -975,8 +975,9 @@ harp_status_t launch_col_tiles(const harp_plan *plan, const ColPass *dpass, cons
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
-// The full column tiles go to the fast variant when the shape allows it, the ragged last
-// column tile (and every other shape) to the guarded one.
+// A single stage goes to the register kernel, two groups of stages to the pair kernel; else the full column
+// tiles go to the fast variant of the LDS-tile kernel when the shape allows it, the ragged last column tile
+// (and every other shape) to the guarded one.
 template <typename TI, typename TO>
 harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, const ColPass &hp,
                                const void *src, int64_t lds_, void *dst, int64_t ldd,
@@ -991,15 +992,18 @@ harp_status_t launch_col_typed(const harp_plan *plan, const ColPass *dpass, cons
   }
   const bool vec = (ncols % 2 == 0) && (lds_ % 2 == 0) && (ldd % 2 == 0) &&
                    ((uintptr_t)src % (2 * ei) == 0) && ((uintptr_t)dst % (2 * eo) == 0);
+  // Every column of the matrix, whole tile or not: a pass over products of blocks rounds otherwise than one stage
+  // after the other, and equal columns are to give equal results.
+  if constexpr (!IsZ16<TI>::value && !IsZ16<TO>::value) {
+    if (vec && hp.packed && (caller_bf16 || !hp.composite))
+      return launch_col_pair(hp, src, lds_, ei == 4 ? HARP_F32 : HARP_BF16, dst, ldd, eo == 4 ? HARP_F32 : HARP_BF16,
+                             nrows, ncols, stream);
+  }
   const bool shape_ok = vec && hp.P >= kColWaves && hp.P <= kColMaxP;
   const int64_t full = shape_ok ? (ncols / kColCols) * kColCols : 0;
   if ((IsZ16<TI>::value || IsZ16<TO>::value) && full != ncols) return HARP_ERR_UNSUPPORTED;
   harp_status_t st = HARP_OK;
-  constexpr bool plain = !IsZ16<TI>::value && !IsZ16<TO>::value;
-  if (full > 0 && plain && hp.packed && (caller_bf16 || !hp.composite))
-    st = launch_col_pair(hp, src, lds_, sizeof(TI) == 4 ? HARP_F32 : HARP_BF16, dst, ldd,
-                         sizeof(TO) == 4 ? HARP_F32 : HARP_BF16, nrows, full, stream);
-  else if (full > 0)
+  if (full > 0)
     st = launch_col_tiles<TI, TO>(plan, dpass, hp, (const TI *)src, lds_, (TO *)dst, ldd, nrows,
                                   full, true, true, stream);
   if (st == HARP_OK && full < ncols)

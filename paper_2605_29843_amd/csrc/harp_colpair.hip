@@ -12,6 +12,8 @@
 // 300 us (4.7 TB/s); the rotation 1148 -> 1062 us.  Whole calls, radix-8 schedules, us: 64 x 4096 float32 (plan_U
 // only) 10.6 -> 7.0, 4096 x 128 15.0 -> 12.2, 2048 x 2048 bf16 55 -> 31, 4096 x 4096 bf16 118 -> 70,
 // 28672 x 3072 bf16 494 -> 446 (chunks of plan_V included).
+// Narrow matrices and the last columns beside whole tiles run here too, lanes past the end idle, on guarded LDS
+// tiles before (float32, us): 4096 x 32 18.2 -> 11.7, 4096 x 130 30.4 -> 12.4, 4096 x 4100 64 -> 48, 28672 x 1000 159 -> 137.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,9 +49,10 @@ __device__ __forceinline__ void pair_load(const uint16_t *p, float &a, float &b)
 __device__ __forceinline__ void pair_store(float *p, float a, float b) { *reinterpret_cast<float2 *>(p) = make_float2(a, b); }
 __device__ __forceinline__ void pair_store(uint16_t *p, float a, float b) { *reinterpret_cast<uint32_t *>(p) = pack2(a, b); }
 
+// (four waves per SIMD where the tile leaves room for them; the descending forms would spill)
 template <typename TI, typename TO, int R1, int R2, bool DESC>
-__global__ __launch_bounds__(64, 2) void harp_colpair_kernel(const TI *src, int64_t lds_, TO *dst, int64_t ldd, int S,
-                                                             unsigned nct, unsigned total,
+__global__ __launch_bounds__(64, !DESC && R1 * R2 <= 28 ? 4 : 2) void harp_colpair_kernel(const TI *src, int64_t lds_, TO *dst, int64_t ldd, int S,
+                                                             int ncols, unsigned nct, unsigned total,
                                                              const float *__restrict__ image) {
   using Sh = PairShape<R1, R2>;
   constexpr int P = Sh::P, RING = 8;
@@ -59,16 +62,18 @@ __global__ __launch_bounds__(64, 2) void harp_colpair_kernel(const TI *src, int6
   if (id >= total) return;
   const unsigned T = id / nct;
   const int64_t row0 = (int64_t)(T / (unsigned)S) * P * S + T % (unsigned)S;
-  const int64_t c0 = (int64_t)(id % nct) * kPairCols;
+  const int c0 = (int)(id % nct) * kPairCols;
   src += row0 * lds_ + c0;
   dst += row0 * ldd + c0;
+  // the lane's columns behind c0 (ncols is even; lanes past the last columns repeat them and store nothing)
+  const unsigned left = (unsigned)(ncols - c0), col = 2 * (unsigned)lane < left ? 2 * (unsigned)lane : left - 2;
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(image + (size_t)T * Sh::TILE), 0, Sh::TILE * 4,
                                                       0x00020000);
   const BlockValues<64> val = {rsrc, (lane & 3) * 16};
   float x[2][P];
   f4v ring[RING];
 #pragma unroll
-  for (int j = 0; j < P; ++j) pair_load(src + (int64_t)j * S * lds_ + 2 * lane, x[0][j], x[1][j]);
+  for (int j = 0; j < P; ++j) pair_load(src + (int64_t)j * S * lds_ + col, x[0][j], x[1][j]);
   constexpr int FIRST = DESC ? Sh::N1 : 0, NF = DESC ? Sh::N2 : Sh::N1;
 #pragma unroll
   for (int s = 0; s < RING; ++s)
@@ -80,27 +85,30 @@ __global__ __launch_bounds__(64, 2) void harp_colpair_kernel(const TI *src, int6
     chain_stage<R2, R1, 1, R1, Sh::N1>(x, ring, val, Sh::N1, 0);
     chain_stage<R1, R2, R1, 1, 0>(x, ring, val, 0, 0);
   }
+  if (2 * (unsigned)lane >= left) return;
 #pragma unroll
-  for (int j = 0; j < P; ++j) pair_store(dst + (int64_t)j * S * ldd + 2 * lane, x[0][j], x[1][j]);
+  for (int j = 0; j < P; ++j) pair_store(dst + (int64_t)j * S * ldd + col, x[0][j], x[1][j]);
 }
 
 template <typename TI, typename TO, int R1, int R2>
 harp_status_t launch_pair_inst(const ColPass &hp, const void *src, int64_t lds_, void *dst, int64_t ldd, int64_t nrows,
                                int64_t ncols, hipStream_t stream) {
-  const int64_t nct = ncols / kPairCols, total = (nrows / hp.P) * nct;
+  const int64_t nct = (ncols + kPairCols - 1) / kPairCols, total = (nrows / hp.P) * nct;
   if (total <= 0) return HARP_OK;
-  if (total > 0x7ffffff0) return HARP_ERR_UNSUPPORTED;
+  if (total > 0x7ffffff0 || ncols > 0x7fffff00) return HARP_ERR_UNSUPPORTED;
   const dim3 grid((unsigned)((total + 7) / 8 * 8));
   if (hp.desc)
     hipLaunchKernelGGL((harp_colpair_kernel<TI, TO, R1, R2, true>), grid, dim3(64), 0, stream, (const TI *)src, lds_,
-                       (TO *)dst, ldd, (int)hp.S, (unsigned)nct, (unsigned)total, hp.packed);
+                       (TO *)dst, ldd, (int)hp.S, (int)ncols, (unsigned)nct, (unsigned)total, hp.packed);
   else
     hipLaunchKernelGGL((harp_colpair_kernel<TI, TO, R1, R2, false>), grid, dim3(64), 0, stream, (const TI *)src, lds_,
-                       (TO *)dst, ldd, (int)hp.S, (unsigned)nct, (unsigned)total, hp.packed);
+                       (TO *)dst, ldd, (int)hp.S, (int)ncols, (unsigned)nct, (unsigned)total, hp.packed);
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
-// the pairs (radix at the lower stride, radix at the higher one) the kernel is built for
+// The pairs (radix at the lower stride, radix at the higher one) the kernel is built for: what greedy schedules of
+// base 8 leave to a pass -- 8 below any last radix 3 .. 8, and 7 below 4 (14336 = 8 8 8 7 4).  Others (7 8, 6 8, 5 4)
+// do not come out of those schedules and keep the LDS-tile kernel.
 #define HARP_PAIR_SWITCH(r1, r2, CALL)                      \
   do {                                                      \
     if ((r1) == 7 && (r2) == 4) { CALL(7, 4); }             \
@@ -211,10 +219,10 @@ harp_status_t launch_pair_pack(const PairBlocks &pb, int64_t d, float *out, hipS
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
-// whole tiles of 128 columns, pairs of columns aligned (the caller's check for every unguarded column pass)
+// an even number of columns, pairs of columns aligned (the caller's check)
 harp_status_t launch_col_pair(const ColPass &hp, const void *src, int64_t lds_, harp_dtype_t dt_src, void *dst,
                               int64_t ldd, harp_dtype_t dt_dst, int64_t nrows, int64_t ncols, hipStream_t stream) {
-  if (!hp.packed || hp.P == 512 || ncols % kPairCols) return HARP_ERR_UNSUPPORTED;
+  if (!hp.packed || hp.P == 512 || ncols % 2) return HARP_ERR_UNSUPPORTED;
   harp_status_t st = HARP_ERR_UNSUPPORTED;
   const int r2 = hp.P / hp.r1;
 #define HARP_PAIR(TI, TO, A, B) st = launch_pair_inst<TI, TO, A, B>(hp, src, lds_, dst, ldd, nrows, ncols, stream)

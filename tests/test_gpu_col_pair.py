@@ -64,3 +64,20 @@ def test_a_new_plan_is_ready_on_every_stream(ru):
         again = harp.harp_rotate_weight(plan, None, W)
         assert torch.equal(first, again)
         plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cols", [130, 260, 380, 2, 66])
+@pytest.mark.parametrize("ru", [[2] * 6, [2] * 9, [2, 4, 2, 3], [8, 7]])
+def test_equal_columns_give_equal_results(ru, cols, dtype):
+    """Whatever the column's place: a ragged last tile takes the arithmetic of the whole ones."""
+    from paper_2605_29843_amd import harp
+    do = int(np.prod(ru))
+    rng = np.random.default_rng(do + cols)
+    plan = harp.Plan(do, ru, gi.make_blocks(do, ru, "qr", rng), gi.make_signs(do, rng))
+    two = rng.standard_normal((do, 2)).astype(np.float32)
+    W = to_device(gi.round_to_bf16(np.tile(two, (1, cols // 2))), dtype)
+    for fn in (harp.harp_rotate_weight, harp.harp_rotate_weight_inverse):
+        got = fn(plan, None, W)
+        assert bool((got.view(do, cols // 2, 2) == got[:, :2].reshape(do, 1, 2)).all()), fn.__name__
+    plan.destroy()
