@@ -902,14 +902,22 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
     bool zws = dt == HARP_BF16 && pu->orthogonal && (!pv || pv->orthogonal) && !pu->f32_only &&
                !(pv && pv->f32_only) &&
                (cps->size() > 1 || pv) && (uintptr_t)ws % 16 == 0;
+    // The passes of 512 rows take every matrix as it lies?
+    auto wide_fits = [&]() {
+      bool ok = !pu->colwide[dir].empty();
+      for (const ColPassHost &ph : pu->colwide[dir])
+        if (ph.pass.P == 512)
+          ok = ok && col_wide_supported(pu, ph.pass, nullptr, W, ldw, dt, Wout, ldo, dt, d_out, d_in) &&
+               col_wide_supported(pu, ph.pass, nullptr, A, d_in, HARP_F32, A, d_in, HARP_F32, d_out, d_in);
+      return ok;
+    };
     if (!pv && zws) {
       // One-sided, every pass of the float32 route on the matrix instruction or a single stage: twice the bytes
       // between the passes, yet faster than halves on the LDS-tile kernel (bf16, radix-8 schedules, forward,
       // us: 4096 x 128 15.6 -> 12.2, 4096 x 4096 71 -> 40, 3072 x 14336 160 -> 113, 14336 x 4096 380 -> 175,
       // 28672 x 8192 1399 -> 667).
-      const std::vector<ColPassHost> &wide = pu->colwide[dir];
       bool fast = true;
-      for (const ColPassHost &ph : wide.empty() ? *cps : wide)
+      for (const ColPassHost &ph : wide_fits() ? pu->colwide[dir] : *cps)
         fast = fast && ((ph.pass.packed && !ph.pass.composite) || (ph.pass.nops == 1 && ph.pass.op[0].k == 1));
       if (fast) zws = false;
     }
@@ -964,12 +972,7 @@ harp_status_t rotate_impl(const harp_plan_t *pu, const harp_plan_t *pv, Directio
       const int narrow_fuse = fuse;
       cps = &pu->colwide[dir];
       fuse = one_streamed ? find_fuse(false) : -1;
-      bool ok = fuse >= 0 || narrow_fuse < 0;
-      for (size_t p = 0; p < cps->size(); ++p)
-        if ((*cps)[p].pass.P == 512)
-          ok = ok && col_wide_supported(pu, (*cps)[p].pass, nullptr, W, ldw, dt, Wout, ldo, dt, d_out, d_in) &&
-               col_wide_supported(pu, (*cps)[p].pass, nullptr, A, d_in, HARP_F32, A, d_in, HARP_F32, d_out, d_in);
-      if (!ok) {
+      if (!wide_fits() || (fuse < 0 && narrow_fuse >= 0)) {
         cps = narrow;
         fuse = narrow_fuse;
       }

@@ -730,26 +730,30 @@ __global__ __launch_bounds__(kColThreads, 2) void harp_colrow_kernel(
 // with the radix-2 stage beside it (this kernel then takes 347 us, 5.4 TB/s).
 // The sums run over r in ascending order, as in the kernels whose place it takes.
 // Every thread has read its elements before it writes them and owns them alone: in place is fine.
+// Rows need not start on 16-byte boundaries: any float32 pitch and every even bf16 pitch is taken in the same
+// accesses (a row in a view: 28672 x 4096 bf16 under a pitch of 4098 675 -> 487 us, the way back).
+typedef float col4f __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t col4h __attribute__((ext_vector_type(2), aligned(4)));
 template <typename T> struct Col4;
 template <> struct Col4<float> {
-  float4 v;
-  __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
+  col4f v;
+  __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const col4f *>(p); }
   __device__ __forceinline__ void widen(float (&x)[4]) const { x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
 };
 template <> struct Col4<uint16_t> {
-  uint2 v;
-  __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
+  col4h v;
+  __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const col4h *>(p); }
   __device__ __forceinline__ void widen(float (&x)[4]) const {
     x[0] = bf16_to_f32(v.x & 0xffffu); x[1] = __uint_as_float(v.x & 0xffff0000u);
     x[2] = bf16_to_f32(v.y & 0xffffu); x[3] = __uint_as_float(v.y & 0xffff0000u);
   }
 };
 __device__ __forceinline__ void col4_store(float *p, const float (&x)[4]) {
-  *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
+  *reinterpret_cast<col4f *>(p) = (col4f){x[0], x[1], x[2], x[3]};
 }
 __device__ __forceinline__ void col4_store(uint16_t *p, const float (&x)[4]) {
-  *reinterpret_cast<uint2 *>(p) = make_uint2(f32_to_bf16(x[0]) | (f32_to_bf16(x[1]) << 16),
-                                             f32_to_bf16(x[2]) | (f32_to_bf16(x[3]) << 16));
+  *reinterpret_cast<col4h *>(p) = (col4h){f32_to_bf16(x[0]) | (f32_to_bf16(x[1]) << 16),
+                                          f32_to_bf16(x[2]) | (f32_to_bf16(x[3]) << 16)};
 }
 
 // Workgroup = 256 threads = 1024 columns (of the first segment) of one block; ncol1 = columns per
@@ -802,14 +806,14 @@ __global__ __launch_bounds__(kColThreads) void harp_col_one_kernel(
     }
 }
 
-// One stage, four columns per access on both sides, fewer than 2^31 workgroups.  No lower bound on the
+// One stage, four columns per access and rows on 4-byte boundaries on both sides, fewer than 2^31 workgroups.  No lower bound on the
 // columns: a workgroup with few of them leaves lanes idle, yet the tile kernel is slower at every width
 // (plan_U only, float32, 28672 rows, radix 8: 4 columns 63 -> 28 us, 128 45 -> 33, 512 116 -> 87, 1024
 // 214 -> 162, 8192 1501 -> 1149) and never faster (8 rows, any width, and 512 x 128: equal, launches).
 static bool col_one_pass(const ColPass &hp, const void *src, int64_t lds_, size_t ei, const void *dst,
                          int64_t ldd, size_t eo, int64_t nrows, int64_t ncol1) {
   if (hp.nops != 1 || hp.op[0].k != 1 || hp.op[0].b != hp.P || hp.P > 8 || hp.P < 2) return false;
-  if (ncol1 % 4 || lds_ % 4 || ldd % 4 || (uintptr_t)src % (4 * ei) || (uintptr_t)dst % (4 * eo)) return false;
+  if (ncol1 % 4 || lds_ * ei % 4 || ldd * eo % 4 || (uintptr_t)src % 4 || (uintptr_t)dst % 4) return false;
   const int64_t nct = (ncol1 + 4 * kColThreads - 1) / (4 * kColThreads);
   return ncol1 < ((int64_t)1 << 29) && (nrows / hp.P) * nct <= 0x7fffffff;
 }

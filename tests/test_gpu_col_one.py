@@ -93,3 +93,42 @@ def test_single_stage_column_pass_with_radix2_row_stage(harp, ru, rv, dtype):
     assert torch.equal(W2, out)
     pu.destroy()
     pv.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ru,rv,cols", [([8], None, 128), ([7], None, 132), ([8, 8, 8, 7], None, 256), ([8, 8, 7, 4], None, 128),
+                                        ([8], [8, 8, 8, 5, 2], 5120)])
+def test_rows_on_four_byte_boundaries(ru, rv, cols, dtype):
+    """Rows of a view: every float32 pitch, every even bf16 one.  The same bits as rows side by side, and
+    nothing beside them is written."""
+    import torch
+    from paper_2605_29843_amd import harp
+    do = int(np.prod(ru))
+    rng = np.random.default_rng(do + cols)
+    pu = harp.Plan(do, ru, gi.make_blocks(do, ru, "qr", rng), gi.make_signs(do, rng))
+    pv = harp.Plan(cols, rv, gi.make_blocks(cols, rv, "qr", rng), gi.make_signs(cols, rng)) if rv else None
+    W = to_device(gi.round_to_bf16(rng.standard_normal((do, cols)).astype(np.float32)), dtype)
+    unit = 1 if dtype == "f32" else 2
+
+    def view(pad, off):
+        big = torch.full((do * (cols + pad) + off,), 7.0, device="cuda", dtype=W.dtype)
+        return big[off:].view(do, cols + pad), big[:off]
+
+    for fn in (harp.harp_rotate_weight, harp.harp_rotate_weight_inverse):
+        # (the first: rows on 16-byte boundaries in float32)
+        ref = None
+        for pi, oi, po, oo in ((4, 0, 4, 0), (unit, 0, unit, unit), (3 * unit, unit, 8, 0), (8, 0, unit, 3 * unit)):
+            print("rows on four-byte boundaries", ru, rv, dtype, fn.__name__, pi, oi, po, oo, file=sys.stderr, flush=True)
+            src, dst = view(pi, oi)[0], view(po, oo)
+            src[:, :cols] = W
+            fn(pu, pv, src[:, :cols], dst[0][:, :cols])
+            got = dst[0][:, :cols].clone()
+            assert bool((dst[0][:, cols:] == 7).all()) and bool((dst[1] == 7).all())
+            ref = got if ref is None else ref
+            if rv is None:
+                assert torch.equal(got, ref), (pi, oi, po, oo)
+            else:   # plan_V's kernels follow the alignment: two results, each rounded to bf16 (2^-9) or by float32 sums
+                assert float((got.double() - ref.double()).norm() / ref.double().norm()) < (1e-6 if dtype == "f32" else 4e-3)
+    pu.destroy()
+    if pv:
+        pv.destroy()
