@@ -32,6 +32,7 @@ KERNEL_SYMBOL = {"dpp_radix2": "harp_dpp_kernel",
                  "split_wave_stream": "harp_wave_kernel", "radix_tile": "harp_radix_kernel",
                  "split_radix_stream": "harp_radix_kernel", "radix_tile_int8": "harp_radix_kernel",
                  "split_radix_stream_int8": "harp_radix_kernel",
+                 "chain_radix8": "harp_chain_kernel", "split_chain_stream": "harp_chain_kernel",
                  "split_dpp_stream_h16": "harp_dpp_kernel", "split_wave_stream_h16": "harp_wave_kernel"}
 
 

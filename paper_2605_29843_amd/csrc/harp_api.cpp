@@ -1771,6 +1771,7 @@ const char *harp_plan_kernel_name(const harp_plan_t *plan, int64_t n, harp_dtype
   if (hp && hp->n_chunk == hp->prog.npass &&
       radix_supported(plan, *hp, 0, hp->prog.npass, hp->chunk, nullptr, 8, nullptr, 8))
     return radix_rebuilds_in_kernel(plan, hp->prog, 0, hp->prog.npass, hp->chunk) ? "radix_tile_int8"
+           : hp->chain.img                                                        ? "chain_radix8"
                                                                                   : "radix_tile";
   if (hp && hp->n_chunk != hp->prog.npass) {
     const int p0 = hp->chunk_first ? 0 : hp->prog.npass - hp->n_chunk;
@@ -1787,7 +1788,8 @@ const char *harp_plan_kernel_name(const harp_plan_t *plan, int64_t n, harp_dtype
     if (radix_supported(plan, *hp, p0, hp->n_chunk, hp->chunk, nullptr, 8, nullptr, 8))
       return radix_rebuilds_in_kernel(plan, hp->prog, p0, hp->n_chunk, hp->chunk)
                  ? "split_radix_stream_int8"
-                 : "split_radix_stream";
+             : hp->chain.img ? "split_chain_stream"
+                             : "split_radix_stream";
   }
   return nm;
 }

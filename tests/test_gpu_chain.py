@@ -28,6 +28,9 @@ def test_chain(r4, top, dtype):
     kind = "qr" if r4 % 2 else "generic"
     blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
     plan = harp.Plan(d, radices, blocks, signs)
+    assert plan.kernel_name(8, harp.HARP_BF16 if dtype == "bf16" else harp.HARP_F32) == \
+        ("chain_radix8" if not top else "split_chain_stream" if d // np.prod(top[1:], dtype=int) > 4096
+         else "split_chunk_stream")   # (a fifth stage that still fits the chunk is no chain: 1536 or 2048 times 2)
     for n in (1, 4, 5, 8, 19):
         print("chain", radices, dtype, n, file=sys.stderr, flush=True)
         X = rng.standard_normal((n, d)).astype(np.float32)
@@ -53,3 +56,29 @@ def test_chain(r4, top, dtype):
         keep = [r for r in range(Xd.shape[0]) if r != 3]
         assert torch.equal(got[keep], good[keep])
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ru", [[8, 3], [7, 4], [5, 11]])     # 24 and 28 rows along the columns, 55 by way of the transpose
+@pytest.mark.parametrize("r4", [3, 4, 5, 6, 7, 8])
+def test_rotation_with_a_chain_on_whole_rows(r4, ru, dtype):
+    """plan_V is one chain: bf16 rows in, float32 rows out, in both directions."""
+    from paper_2605_29843_amd import harp
+    rv = [8, 8, 8, r4]
+    do, cols = int(np.prod(ru)), int(np.prod(rv))
+    rng = np.random.default_rng(do + cols)
+    bu, su = gi.make_blocks(do, ru, "qr", rng), gi.make_signs(do, rng)
+    bv, sv = gi.make_blocks(cols, rv, "qr", rng), gi.make_signs(cols, rng)
+    pu, pv = harp.Plan(do, ru, bu, su), harp.Plan(cols, rv, bv, sv)
+    print("rotation with a chain", ru, rv, dtype, file=sys.stderr, flush=True)
+    W = rng.standard_normal((do, cols)).astype(np.float32)
+    if dtype == "bf16":
+        W = gi.round_to_bf16(W)
+    Wd, W64 = to_device(W, dtype), W.astype(np.float64)
+    for fn, rows_fn in ((harp.harp_rotate_weight, ho.apply_staged), (harp.harp_rotate_weight_inverse, ho.apply_transpose_staged)):
+        M = rows_fn(W64, cols, rv, bv, sv)
+        ref = rows_fn(np.ascontiguousarray(M.T), do, ru, bu, su).T
+        rho = np.linalg.norm(M, axis=0, keepdims=True) / np.sqrt(do)
+        assert_parity(to_host64(fn(pu, pv, Wd)), ref, dtype, fn.__name__, rho=rho)
+    pu.destroy()
+    pv.destroy()

@@ -1070,10 +1070,11 @@ RADIX_TILE_CASES = [
 @pytest.mark.parametrize("d,radices,n", RADIX_TILE_CASES)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_equal_small_radix_tile_kernel(harp, d, radices, n, dtype):
-    """All stages radix 4 or all radix 8: the tile kernel with prefetched block parameters."""
+    """All stages radix 4 or all radix 8: the tile kernel with prefetched block parameters, or, from four stages
+    of radix 8, the chain kernel."""
     blocks = gi.make_blocks(d, radices, "qr", np.random.default_rng(1))
     plan = harp.Plan(d, radices, blocks, None)
-    assert plan.kernel_name(n) == "radix_tile", plan.kernel_name(n)
+    assert plan.kernel_name(n) == ("chain_radix8" if radices == [8] * 4 else "radix_tile"), plan.kernel_name(n)
     plan.destroy()
     run_case(harp, d, radices, n, dtype, kind="qr", seed=d + n)
     run_case(harp, d, radices, n, dtype, kind="orth", seed=d + n + 1, ld_pad=8, with_signs=False)
