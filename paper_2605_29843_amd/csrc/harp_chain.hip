@@ -1,5 +1,5 @@
-// Chains of three or four small dense stages (8, 8, R3[, R4]) on chunks of 64 * R3 * R4 coordinates: the
-// radix-8 schedules, on the float32 matrix instruction v_mfma_f32_4x4x1_16b_f32.
+// Chains of four small dense stages 8, 8, 8, R4 (R4 = 3 .. 8) on chunks of 512 R4 coordinates: the radix-8
+// schedules, on the float32 matrix instruction v_mfma_f32_4x4x1_16b_f32.
 //
 // That instruction is sixteen independent 4 x 4 outer-product updates.  Sixteen blocks of a stage
 // times four rows are one operand: lane 4 b + row holds the coordinates of block slot b and that row
@@ -8,11 +8,11 @@
 // of 64 values costs 16 registers per lane and is used for four rows at once, and a product runs at
 // twice the rate of the vector units, with the same float32 chain of fused multiply-adds.
 //
-// A workgroup takes eight rows of one chunk.  A wave owns sixteen groups of 64 coordinates (R3 * R4 in
-// the high stages) of the eight rows, and a lane holds all coordinates of its group and of two rows
+// A workgroup takes eight rows of one chunk (HV == 2), or four where there are few (HV == 1, see the launch).  A wave owns sixteen groups of 64 coordinates (8 R4 in
+// the high stages) of the rows, and a lane holds all coordinates of its group and of HV rows
 // (row, row + 4): two stages whose digits both lie inside the group follow each other by renaming
 // registers.  A tile so makes one exchange through LDS, between the two low stages (groups of 64
-// consecutive coordinates) and the high ones (groups of R3 * R4 coordinates 64 apart); one block per
+// consecutive coordinates) and the high ones (groups of 8 R4 coordinates 64 apart); one block per
 // thread needed three.  The exchange takes four rows at a time, so that a workgroup needs half the
 // LDS of its rows and two of them (four small ones) share a compute unit: one's loads, exchanges
 // and stores run under the other's products.  Rows enter and leave in 16-byte pieces through the
@@ -23,7 +23,9 @@
 // 2048 x 4096 bf16 (8,8,8,8), one tile per compute unit: 18.3 us on one block per thread -> 14.5 us, of
 // which 1.6 us are the launch, 3 us the rows' arrival, 6 us stages, 2 us the exchange, 2 us the
 // stores; 777 x 14336 transposed (8,8,8,7 | 4), both launches: 60 -> 36 us; six rows of 14336:
-// 18.3 -> 12.5 us; 28672 x 8192 bf16 -> float32: 472 -> 325 us (1.41 GB).  Touching every line of the
+// 18.3 -> 12.5 us (9.9 in tiles of four rows); 28672 x 8192 bf16 -> float32: 472 -> 325 us (1.41 GB).  One row of 4096
+// (float32 / bf16, replayed): 7.0 / 6.9 us on one block per thread, 9.9 / 9.8 in a tile of eight, 7.0 / 6.9 in one of four
+// (rows that are not there are neither loaded nor stored, and all waves share a row's stores).  Touching every line of the
 // values at the start of a launch, so that the first reads find them in the L2, was slower (six
 // rows: 13.6 -> 15.5 us).
 #include <hip/hip_runtime.h>
@@ -38,11 +40,11 @@ namespace harp {
 
 namespace {
 
-constexpr int kChainRows = 8;   // rows per tile
+constexpr int R3 = 8;   // radix of the third stage
 
 // Sizes of one instance; also the layout of the block values: per chunk the stages at strides 1, 8,
 // 64, 64 R3 one after the other, a stage as [unit or block of 16 lo][batch][piece][lane][4].
-template <int R3, int R4>
+template <int R4, int HV = 2>
 struct ChainShape {
   static constexpr int H = R3 * R4;                   // groups of 64 in a chunk, coordinates of a high group
   static constexpr int CHUNK = 64 * H;
@@ -51,11 +53,12 @@ struct ChainShape {
   static constexpr int LB = 4 / NW;                   // blocks of 16 lo per wave in the high stages
   static constexpr int PITCH = CHUNK + 8;             // LDS row (floats): four rows x 8 lo hit 32 banks
   // 16-byte pieces of block values a lane holds: those in use and the next two batches.  Outputs come in
-  // aligned quads while the inputs they replace are spread over other quads, so a stage needs up to 64
-  // registers more than its coordinates: with a ring of 16 most shapes spilled (2048 x 4096 bf16 15.3 us
-  // against 14.6, six rows of 14336 13.6 against 12.5).  Radix 4 has smaller batches: eight pieces are as
-  // many ahead, and its waves hold two blocks of 16 lo.
-  static constexpr int RING = R4 == 4 ? 8 : 12;
+  // aligned quads while the inputs they replace are spread over other quads, so a stage of two rows per lane
+  // needs up to 64 registers more than its coordinates: with a ring of 16 most shapes spilled (2048 x 4096 bf16
+  // 15.3 us against 14.6, six rows of 14336 13.6 against 12.5).  Radix 4 has smaller batches: eight pieces are as
+  // many ahead; its waves hold two blocks of 16 lo, and five of its seven instances still spill 8 to 35 registers.
+  // One row per lane has room: one row of 4096 bf16 7.1 us with a ring of 12, 6.9 with 16, 7.0 with 24, 7.3 with 48.
+  static constexpr int RING = HV == 1 ? 16 : R4 == 4 ? 8 : 12;
   static constexpr int NA = 32;                       // pieces per unit, stages at strides 1 and 8
   static constexpr int NC = R4 * chain_pieces(R3);    // pieces per block of 16 lo
   static constexpr int ND = R3 * chain_pieces(R4);
@@ -65,11 +68,11 @@ struct ChainShape {
   static constexpr int64_t TOTAL = OFF_D + (int64_t)4 * ND * 256;
 };
 
-template <typename TI, typename TO, int R3, int R4, bool TRN>
-__global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_kernel(
+template <typename TI, typename TO, int R4, bool TRN, int HV>
+__global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kernel(
     const TI *X, int64_t ldx, TO *Y, int64_t ldy, int64_t n, int R, unsigned ntile, unsigned total,
     const float *__restrict__ image) {
-  using S = ChainShape<R3, R4>;
+  using S = ChainShape<R4, HV>;
   constexpr int H = S::H, NW = S::NW, LB = S::LB;
   constexpr bool BI = sizeof(TI) == 2, BO = sizeof(TO) == 2;
   constexpr int NR8 = S::CHUNK / 512, NR4 = S::CHUNK / 256;   // 16-byte pieces of a row per lane: bf16, float32
@@ -105,8 +108,11 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
   auto pos = [](int r, int j, int lo) { return r * S::PITCH + j * 64 + (lo ^ ((j & 1) << 2)); };
   // a row's consecutive coordinates 4 c .. 4 c + 3
   auto pos4 = [](int r, int c) { return r * S::PITCH + ((c ^ ((c >> 4) & 1)) << 2); };
-  // rows past the end repeat the last one and are not stored
-  auto row_ptr = [&](int r) { return Xt + (int64_t)(r < nr ? r : nr - 1) * ldx; };
+  // 16 bytes of a row; rows past the end are zero (a tile of four rows) or repeat the last one, and are not stored
+  auto row_piece = [&](int r, int at) {
+    if (HV == 1 && r >= nr) return (u4v){0u, 0u, 0u, 0u};
+    return *reinterpret_cast<const u4v *>(Xt + (int64_t)(r < nr ? r : nr - 1) * ldx + at);
+  };
 
   f4v ring[S::RING];
   auto first_pieces = [&](int p, int cnt) {
@@ -119,17 +125,17 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
   const int sw = (lane >> 2) & 1;
 
   if constexpr (!TRN) {
-    float x[2][64];
+    float x[HV][64];
     // rows of the unit through the wave's own part of the LDS rows (bf16: rows r and r + 4 one after
     // the other), coordinates of a group side by side
     if constexpr (BI) {
-      u4v raw[8][2];
+      u4v raw[4 * HV][2];
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < 4 * HV; ++r)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
           if (i * 512 < ngr * 64)
-            raw[r][i] = *reinterpret_cast<const u4v *>(row_ptr(r) + u * 1024 + (i * 64 + lane) * 8);
+            raw[r][i] = row_piece(r, u * 1024 + (i * 64 + lane) * 8);
       first_pieces(iA, S::NA);
       __builtin_amdgcn_sched_barrier(0);
       char *base = reinterpret_cast<char *>(lds) + u * 4096;
@@ -138,13 +144,13 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
                                        ((s ^ (((g & 1) << 2) + (r & 3))) << 4));
       };
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < 4 * HV; ++r)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
           if (low && i * 512 < ngr * 64) *at(r, i * 8 + (lane >> 3), lane & 7) = raw[r][i];
       wave_fence();
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < HV; ++h)
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
           const u4v q = *at(row + 4 * h, gl, s);
@@ -155,17 +161,17 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
           }
         }
     } else {
-      u4v raw[8][4];
+      u4v raw[4 * HV][4];
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < 4 * HV; ++r)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (i * 256 < ngr * 64)
-            raw[r][i] = *reinterpret_cast<const u4v *>(row_ptr(r) + u * 1024 + (i * 64 + lane) * 4);
+            raw[r][i] = row_piece(r, u * 1024 + (i * 64 + lane) * 4);
       first_pieces(iA, S::NA);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HV; ++h) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -185,9 +191,9 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
     wave_fence();
     chain_stage<8, 8, 8, 1, S::NA>(x, ring, val, iA, iB);
     chain_stage<8, 8, 1, 8, S::NC>(x, ring, val, iB, iC);
-    float y[LB][2][H];
+    float y[LB][HV][H];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < HV; ++h) {
       if (low && slot < ngr) {
 #pragma unroll
         for (int s = 0; s < 16; ++s)
@@ -212,12 +218,16 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
       for (int b = 0; b < LB; ++b)
 #pragma unroll
         for (int j = 0; j < H; ++j)
-          lds[pos(row, j, (w * LB + b) * 16 + slot)] = __uint_as_float(pack2(y[b][0][j], y[b][1][j]));
+          lds[pos(row, j, (w * LB + b) * 16 + slot)] = __uint_as_float(pack2(y[b][0][j], y[b][HV - 1][j]));
       lds_barrier();
+      // (a row's pieces over the waves: a lone row is not one wave's work)
 #pragma unroll
-      for (int r = w; r < 4; r += NW) {
+      for (int r = 0; r < 4; ++r) {
+        if (r >= nr) break;
 #pragma unroll
-        for (int i = 0; i < NR8; ++i) {
+        for (int i0 = 0; i0 < NR8; i0 += NW) {
+          const int i = i0 + w;
+          if (i >= NR8) break;
           const int c = 2 * (i * 64 + lane);
           const u4v a = *reinterpret_cast<const u4v *>(lds + pos4(r, c + sw));
           const u4v b = *reinterpret_cast<const u4v *>(lds + pos4(r, c + 1 - sw));
@@ -226,13 +236,13 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
                           __builtin_amdgcn_perm(hi[1], hi[0], 0x05040100u), __builtin_amdgcn_perm(hi[3], hi[2], 0x05040100u)};
           const u4v p1 = {__builtin_amdgcn_perm(lo[1], lo[0], 0x07060302u), __builtin_amdgcn_perm(lo[3], lo[2], 0x07060302u),
                           __builtin_amdgcn_perm(hi[1], hi[0], 0x07060302u), __builtin_amdgcn_perm(hi[3], hi[2], 0x07060302u)};
-          if (r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + (i * 64 + lane) * 8) = p0;
-          if (r + 4 < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)(r + 4) * ldy + (i * 64 + lane) * 8) = p1;
+          *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + (i * 64 + lane) * 8) = p0;
+          if (HV == 2 && r + 4 < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)(r + 4) * ldy + (i * 64 + lane) * 8) = p1;
         }
       }
     } else {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HV; ++h) {
         if (h) lds_barrier();
 #pragma unroll
         for (int b = 0; b < LB; ++b)
@@ -240,33 +250,33 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
           for (int j = 0; j < H; ++j) lds[pos(row, j, (w * LB + b) * 16 + slot)] = y[b][h][j];
         lds_barrier();
 #pragma unroll
-        for (int r = w; r < 4; r += NW)
+        for (int r = 0; r < 4; ++r)
           if (4 * h + r < nr) {
 #pragma unroll
-            for (int i = 0; i < NR4; ++i)
+            for (int i = w; i < NR4; i += NW)
               *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + (i * 64 + lane) * 4) =
                   *reinterpret_cast<const u4v *>(lds + pos4(r, i * 64 + lane));
           }
       }
     }
   } else {
-    float y[LB][2][H];
+    float y[LB][HV][H];
     if constexpr (BI) {
-      u4v raw[LB][2][NR8];   // wave w: rows w (w, w + 2) and the one four further on
+      u4v raw[LB][HV][NR8];   // wave w: rows w (w, w + 2) and the one four further on
 #pragma unroll
       for (int k = 0; k < LB; ++k)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < HV; ++h)
 #pragma unroll
           for (int i = 0; i < NR8; ++i)
-            raw[k][h][i] = *reinterpret_cast<const u4v *>(row_ptr(w + k * NW + 4 * h) + (i * 64 + lane) * 8);
+            raw[k][h][i] = row_piece(w + k * NW + 4 * h, (i * 64 + lane) * 8);
       first_pieces(iD, S::ND);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int k = 0; k < LB; ++k)
 #pragma unroll
         for (int i = 0; i < NR8; ++i) {
-          const u4v p = raw[k][0][i], q = raw[k][1][i];
+          const u4v p = raw[k][0][i], q = raw[k][HV - 1][i];
           u4v a, b;
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
@@ -286,21 +296,21 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
         for (int j = 0; j < H; ++j) {
           const uint32_t q = __float_as_uint(lds[pos(row, j, (w * LB + b) * 16 + slot)]);
           y[b][0][j] = __uint_as_float(q << 16);
-          y[b][1][j] = __uint_as_float(q & 0xffff0000u);
+          if constexpr (HV == 2) y[b][1][j] = __uint_as_float(q & 0xffff0000u);
         }
     } else {
-      u4v raw[2][LB][NR4];
+      u4v raw[HV][LB][NR4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < HV; ++h)
 #pragma unroll
         for (int k = 0; k < LB; ++k)
 #pragma unroll
           for (int i = 0; i < NR4; ++i)
-            raw[h][k][i] = *reinterpret_cast<const u4v *>(row_ptr(4 * h + w + k * NW) + (i * 64 + lane) * 4);
+            raw[h][k][i] = row_piece(4 * h + w + k * NW, (i * 64 + lane) * 4);
       first_pieces(iD, S::ND);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HV; ++h) {
         if (h) lds_barrier();
 #pragma unroll
         for (int k = 0; k < LB; ++k)
@@ -322,9 +332,9 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
       else
         chain_stage<R3, R4, R3, 1, S::NA>(y[b], ring, val, iC + b * S::NC, iB);
     }
-    float x[2][64];
+    float x[HV][64];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < HV; ++h) {
       lds_barrier();   // everyone has read the rows that are overwritten here
 #pragma unroll
       for (int b = 0; b < LB; ++b)
@@ -350,7 +360,7 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
       };
       if (low && slot < ngr) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < HV; ++h)
 #pragma unroll
           for (int s = 0; s < 8; ++s) {
             u4v q;
@@ -361,16 +371,16 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
       }
       wave_fence();
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < 4 * HV; ++r)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-          if (low && i * 512 < ngr * 64) {
+          if (low && i * 512 < ngr * 64 && r < nr) {
             const u4v q = *at(r, i * 8 + (lane >> 3), lane & 7);
-            if (r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + u * 1024 + (i * 64 + lane) * 8) = q;
+            *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + u * 1024 + (i * 64 + lane) * 8) = q;
           }
     } else {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HV; ++h) {
         if (low && slot < ngr) {
 #pragma unroll
           for (int s = 0; s < 16; ++s)
@@ -382,10 +392,9 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (low && i * 256 < ngr * 64) {
+            if (low && i * 256 < ngr * 64 && 4 * h + r < nr) {
               const u4v q = *reinterpret_cast<const u4v *>(lds + pos4(r, u * 256 + i * 64 + lane));
-              if (4 * h + r < nr)
-                *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + u * 1024 + (i * 64 + lane) * 4) = q;
+              *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + u * 1024 + (i * 64 + lane) * 4) = q;
             }
         wave_fence();
       }
@@ -393,19 +402,19 @@ __global__ __launch_bounds__((64 * ChainShape<R3, R4>::NW), 2) void harp_chain_k
   }
 }
 
-template <typename TI, typename TO, int R3, int R4, bool TRN>
-harp_status_t launch_chain_inst(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx, void *Y,
+template <typename TI, typename TO, int R4, bool TRN, int HV>
+harp_status_t launch_chain_rows(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx, void *Y,
                                 int64_t ldy, int64_t n, hipStream_t stream) {
-  using S = ChainShape<R3, R4>;
-  constexpr size_t lds = (size_t)(kChainRows / 2) * S::PITCH * 4;
+  using S = ChainShape<R4, HV>;
+  constexpr size_t lds = (size_t)4 * S::PITCH * 4;
   if (lds > (size_t)plan->lds_bytes) return HARP_ERR_UNSUPPORTED;
-  int R = kChainRows;
+  int R = 4 * HV;
   if (plan->rows_override > 0 && plan->rows_override < R) R = plan->rows_override;
   const int nchunk = (int)(plan->d / S::CHUNK);
   const int64_t ntile = (n + R - 1) / R;
   const int64_t total = ntile * nchunk;
   if (total > 0x7ffffff0) return HARP_ERR_UNSUPPORTED;
-  auto kern = harp_chain_kernel<TI, TO, R3, R4, TRN>;
+  auto kern = harp_chain_kernel<TI, TO, R4, TRN, HV>;
   static thread_local int attr_done_dev = -1;   // per instantiation
   if (attr_done_dev != plan->device) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -420,26 +429,41 @@ harp_status_t launch_chain_inst(const harp_plan *plan, const ChainImage &ci, con
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
-template <int R3, int R4>
+template <typename TI, typename TO, int R4, bool TRN>
+harp_status_t launch_chain_inst(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx, void *Y,
+                                int64_t ldy, int64_t n, hipStream_t stream) {
+  // Tiles of four rows while they are no more than compute units: each is done sooner (a stage's products are
+  // half), and the units with a tile of eight would otherwise stand beside idle ones.  Beyond that a tile of eight
+  // uses the block values twice as often.  Eight / four rows, bf16, us: 4096 at 1 row 9.8 / 6.9, 512 rows 10.6 / 8.2,
+  // 1024 rows (256 tiles) 12.0 / 9.6, 1030 rows 12.1 / 13.8; 14336 (two launches) at 6 rows 12.5 / 9.9, 256 rows (256 tiles)
+  // 17.9 / 15.7, 512 rows 23.0 / 24.0; 2048 at 1024 rows 8.9 / 5.8.
+  const int64_t cus = plan->num_cu > 0 ? plan->num_cu : 256;
+  const bool four = plan->rows_override > 0 ? plan->rows_override <= 4
+                                            : (n + 3) / 4 * (plan->d / ChainShape<R4>::CHUNK) <= cus;
+  return four ? launch_chain_rows<TI, TO, R4, TRN, 1>(plan, ci, X, ldx, Y, ldy, n, stream)
+              : launch_chain_rows<TI, TO, R4, TRN, 2>(plan, ci, X, ldx, Y, ldy, n, stream);
+}
+
+template <int R4>
 harp_status_t launch_chain_shape(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx,
                                  harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
                                  hipStream_t stream) {
 #define HARP_CHAIN_IO(TI, TO)                                                                  \
-  (ci.trn ? launch_chain_inst<TI, TO, R3, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream)      \
-          : launch_chain_inst<TI, TO, R3, R4, false>(plan, ci, X, ldx, Y, ldy, n, stream))
+  (ci.trn ? launch_chain_inst<TI, TO, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream)      \
+          : launch_chain_inst<TI, TO, R4, false>(plan, ci, X, ldx, Y, ldy, n, stream))
   if (dt_in == HARP_BF16)
     return dt_out == HARP_BF16 ? HARP_CHAIN_IO(uint16_t, uint16_t) : HARP_CHAIN_IO(uint16_t, float);
   if (dt_out == HARP_F32) return HARP_CHAIN_IO(float, float);
   // float32 in, bf16 out: only behind the streamed stages of a transposed split program
   if (!ci.trn) return HARP_ERR_UNSUPPORTED;
-  return launch_chain_inst<float, uint16_t, R3, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream);
+  return launch_chain_inst<float, uint16_t, R4, true>(plan, ci, X, ldx, Y, ldy, n, stream);
 #undef HARP_CHAIN_IO
 }
 
-template <int R3, int R4>
+template <int R4>
 void pack_chain(const Program &pg, int p0, bool trn, const std::vector<size_t> &offsets, int64_t nchunk,
                 std::vector<float> &image, size_t off) {
-  using S = ChainShape<R3, R4>;
+  using S = ChainShape<R4>;
   for (int e = 0; e < 4; ++e) {   // the stages by stride
     const int p = trn ? p0 + 3 - e : p0 + e, b = pg.pass[p].b, nh = b > 4 ? 2 : 1, np = chain_pieces(b);
     const int64_t nq = pg.pass[p].nq, s = pg.pass[p].S, nqc = S::CHUNK / b;
@@ -499,8 +523,8 @@ void build_chain_image(HostProgram &hp, int p0, int np, int64_t d, const std::ve
   const int r4 = pg.pass[trn ? p0 : p0 + 3].b;
   const size_t off = (image.size() + 63) / 64 * 64;
   const int64_t nchunk = d / s;
-  HARP_CHAIN_R4(r4, (image.resize(off + (size_t)(nchunk * ChainShape<8, R4>::TOTAL), 0.0f),
-                     pack_chain<8, R4>(pg, p0, trn, offsets, nchunk, image, off)));
+  HARP_CHAIN_R4(r4, (image.resize(off + (size_t)(nchunk * ChainShape<R4>::TOTAL), 0.0f),
+                     pack_chain<R4>(pg, p0, trn, offsets, nchunk, image, off)));
   hp.chain.host_off = (int64_t)off;
   hp.chain.r4 = r4;
   hp.chain.trn = trn;
@@ -510,7 +534,7 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
                                   harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
                                   hipStream_t stream) {
   harp_status_t st = HARP_ERR_UNSUPPORTED;
-  HARP_CHAIN_R4(ci.r4, (st = launch_chain_shape<8, R4>(plan, ci, X, ldx, dt_in, Y, ldy, dt_out, n, stream)));
+  HARP_CHAIN_R4(ci.r4, (st = launch_chain_shape<R4>(plan, ci, X, ldx, dt_in, Y, ldy, dt_out, n, stream)));
   return st;
 }
 

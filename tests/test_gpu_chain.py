@@ -82,3 +82,34 @@ def test_rotation_with_a_chain_on_whole_rows(r4, ru, dtype):
         assert_parity(to_host64(fn(pu, pv, Wd)), ref, dtype, fn.__name__, rho=rho)
     pu.destroy()
     pv.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("radices,counts", [([8, 8, 8, r], (1, 2, 4, 5, 7, 8, 13)) for r in range(3, 9)] +
+                         [([8, 8, 8, 7, 4], (1, 3, 6, 9)), ([8, 8, 8, 8, 7], (1, 6)),
+                          # the last batch in tiles of four rows on 256 compute units, and the first in tiles of eight
+                          ([8, 8, 8, 3], (1024, 1025)), ([8, 8, 8, 5, 2], (512, 513))])
+def test_tiles_of_four_and_eight_rows(radices, counts, dtype):
+    """The same sums in the same order whatever the tile: rows per tile given (three, eight) and chosen."""
+    import torch
+    from paper_2605_29843_amd import harp
+    d = int(np.prod(radices))
+    rng = np.random.default_rng(d)
+    blocks, signs = gi.make_blocks(d, radices, "qr", rng), gi.make_signs(d, rng)
+    plan = harp.Plan(d, radices, blocks, signs)
+    for n in counts:
+        print("tiles of four and eight rows", radices, dtype, n, file=sys.stderr, flush=True)
+        X = rng.standard_normal((n, d)).astype(np.float32)
+        X = gi.round_to_bf16(X) if dtype == "bf16" else X
+        Xd = to_device(X, dtype)
+        for fn, oracle in ((harp.harp_apply, ho.apply_staged), (harp.harp_apply_transpose, ho.apply_transpose_staged)):
+            outs = []
+            for rows in (0, 3, 8):
+                plan.set_rows_per_tile(rows)
+                Y = torch.full((n + 1, d), 7.0, dtype=Xd.dtype, device="cuda")
+                outs.append(fn(plan, Xd, Y[:n]))
+                assert bool((Y[n] == 7).all())
+            assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (n, fn.__name__)
+            some = np.unique(np.linspace(0, n - 1, 9).astype(int))
+            assert_parity(to_host64(outs[2])[some], oracle(X[some], d, radices, blocks, signs), dtype, f"{fn.__name__} n={n}")
+    plan.destroy()
