@@ -8,26 +8,27 @@
 // of 64 values costs 16 registers per lane and is used for four rows at once, and a product runs at
 // twice the rate of the vector units, with the same float32 chain of fused multiply-adds.
 //
-// A workgroup takes eight rows of one chunk (HV == 2), or four where there are few (HV == 1, see the launch).  A wave owns sixteen groups of 64 coordinates (8 R4 in
-// the high stages) of the rows, and a lane holds all coordinates of its group and of HV rows
-// (row, row + 4): two stages whose digits both lie inside the group follow each other by renaming
-// registers.  A tile so makes one exchange through LDS, between the two low stages (groups of 64
-// consecutive coordinates) and the high ones (groups of 8 R4 coordinates 64 apart); one block per
-// thread needed three.  The exchange takes four rows at a time, so that a workgroup needs half the
-// LDS of its rows and two of them (four small ones) share a compute unit: one's loads, exchanges
-// and stores run under the other's products.  Rows enter and leave in 16-byte pieces through the
-// same LDS rows; bf16 rows r and r + 4 travel as the two halves of one word.
+// A workgroup takes eight rows of one chunk (HV == 2), or four where there are few (HV == 1, see the
+// launch).  A wave owns sixteen groups of 64 coordinates (8 R4 in the high stages) of the rows, and a
+// lane holds all coordinates of its group and of HV rows (row, row + 4): two stages whose digits both
+// lie inside the group follow each other by renaming registers.  A tile so makes one exchange through
+// LDS, between the two low stages (groups of 64 consecutive coordinates) and the high ones (groups of
+// 8 R4 coordinates 64 apart); one block per thread needed three.  The exchange takes four rows at a
+// time, so that a workgroup needs half the LDS of its rows and two of them (four small ones) share a
+// compute unit: one's loads, exchanges and stores run under the other's products.  Rows enter and
+// leave in 16-byte pieces through the same LDS rows; bf16 rows r and r + 4 travel as the two halves
+// of one word.
 //
 // What bounds it: the block values (0.5 MB for a chunk of 4096) come through the compute unit's load path
 // of 64 bytes per clock once per tile, as long as its matrix instructions take (2300 clocks a stage).
 // 2048 x 4096 bf16 (8,8,8,8), one tile per compute unit: 18.3 us on one block per thread -> 14.5 us, of
 // which 1.6 us are the launch, 3 us the rows' arrival, 6 us stages, 2 us the exchange, 2 us the
 // stores; 777 x 14336 transposed (8,8,8,7 | 4), both launches: 60 -> 36 us; six rows of 14336:
-// 18.3 -> 12.5 us (9.9 in tiles of four rows); 28672 x 8192 bf16 -> float32: 472 -> 325 us (1.41 GB).  One row of 4096
-// (float32 / bf16, replayed): 7.0 / 6.9 us on one block per thread, 9.9 / 9.8 in a tile of eight, 7.0 / 6.9 in one of four
-// (rows that are not there are neither loaded nor stored, and all waves share a row's stores).  Touching every line of the
-// values at the start of a launch, so that the first reads find them in the L2, was slower (six
-// rows: 13.6 -> 15.5 us).
+// 18.3 -> 12.5 us (9.9 in tiles of four rows); 28672 x 8192 bf16 -> float32: 472 -> 325 us (1.41 GB).
+// One row of 4096 (float32 / bf16, replayed): 7.0 / 6.9 us on one block per thread, 9.9 / 9.8 in a tile
+// of eight, 7.0 / 6.9 in one of four (rows that are not there are neither loaded nor stored, and all
+// waves share a row's stores).  Touching every line of the values at the start of a launch, so that
+// the first reads find them in the L2, was slower (six rows: 13.6 -> 15.5 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -123,6 +124,11 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
   // a lane's 16-byte pieces 2 l and 2 l + 1 of eight words: which one goes first alternates every four
   // lanes, so that eight lanes hit all banks
   const int sw = (lane >> 2) & 1;
+
+  // Stores.  A tile of eight: a wave writes whole rows (forward) and reads LDS for all its rows at once, stored or
+  // not; a tile of four: a row's pieces go over the waves, as a lone row is not one wave's work, and rows that are
+  // not there cost nothing.  Tiles of eight stored the second way: rotation of 28672 x 8192 1077 -> 1085 us.
+  constexpr bool SHARE = HV == 1;
 
   if constexpr (!TRN) {
     float x[HV][64];
@@ -220,13 +226,12 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
         for (int j = 0; j < H; ++j)
           lds[pos(row, j, (w * LB + b) * 16 + slot)] = __uint_as_float(pack2(y[b][0][j], y[b][HV - 1][j]));
       lds_barrier();
-      // (a row's pieces over the waves: a lone row is not one wave's work)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (r >= nr) break;
+      for (int r = SHARE ? 0 : w; r < 4; r += SHARE ? 1 : NW) {
+        if (SHARE && r >= nr) break;
 #pragma unroll
-        for (int i0 = 0; i0 < NR8; i0 += NW) {
-          const int i = i0 + w;
+        for (int i0 = 0; i0 < NR8; i0 += SHARE ? NW : 1) {
+          const int i = i0 + (SHARE ? w : 0);
           if (i >= NR8) break;
           const int c = 2 * (i * 64 + lane);
           const u4v a = *reinterpret_cast<const u4v *>(lds + pos4(r, c + sw));
@@ -236,7 +241,7 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
                           __builtin_amdgcn_perm(hi[1], hi[0], 0x05040100u), __builtin_amdgcn_perm(hi[3], hi[2], 0x05040100u)};
           const u4v p1 = {__builtin_amdgcn_perm(lo[1], lo[0], 0x07060302u), __builtin_amdgcn_perm(lo[3], lo[2], 0x07060302u),
                           __builtin_amdgcn_perm(hi[1], hi[0], 0x07060302u), __builtin_amdgcn_perm(hi[3], hi[2], 0x07060302u)};
-          *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + (i * 64 + lane) * 8) = p0;
+          if (SHARE || r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + (i * 64 + lane) * 8) = p0;
           if (HV == 2 && r + 4 < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)(r + 4) * ldy + (i * 64 + lane) * 8) = p1;
         }
       }
@@ -250,10 +255,10 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
           for (int j = 0; j < H; ++j) lds[pos(row, j, (w * LB + b) * 16 + slot)] = y[b][h][j];
         lds_barrier();
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = SHARE ? 0 : w; r < 4; r += SHARE ? 1 : NW)
           if (4 * h + r < nr) {
 #pragma unroll
-            for (int i = w; i < NR4; i += NW)
+            for (int i = SHARE ? w : 0; i < NR4; i += SHARE ? NW : 1)
               *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + (i * 64 + lane) * 4) =
                   *reinterpret_cast<const u4v *>(lds + pos4(r, i * 64 + lane));
           }
@@ -374,9 +379,9 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
       for (int r = 0; r < 4 * HV; ++r)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-          if (low && i * 512 < ngr * 64 && r < nr) {
+          if (low && i * 512 < ngr * 64 && (!SHARE || r < nr)) {
             const u4v q = *at(r, i * 8 + (lane >> 3), lane & 7);
-            *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + u * 1024 + (i * 64 + lane) * 8) = q;
+            if (r < nr) *reinterpret_cast<u4v *>(Yt + (int64_t)r * ldy + u * 1024 + (i * 64 + lane) * 8) = q;
           }
     } else {
 #pragma unroll
@@ -392,9 +397,10 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (low && i * 256 < ngr * 64 && 4 * h + r < nr) {
+            if (low && i * 256 < ngr * 64 && (!SHARE || r < nr)) {
               const u4v q = *reinterpret_cast<const u4v *>(lds + pos4(r, u * 256 + i * 64 + lane));
-              *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + u * 1024 + (i * 64 + lane) * 4) = q;
+              if (4 * h + r < nr)
+                *reinterpret_cast<u4v *>(Yt + (int64_t)(4 * h + r) * ldy + u * 1024 + (i * 64 + lane) * 4) = q;
             }
         wave_fence();
       }
