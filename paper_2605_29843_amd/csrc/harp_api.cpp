@@ -588,6 +588,9 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
     }
     ++i;
   }
+  // what one launch reads: the images appended below hold the same values in another kernel's order (a plan
+  // of radix-8 chains keeps its block values several times: two kernels' images per direction, dense
+  // blocks per direction, and those of the column passes), and a launch reads one of them
   hp.param_bytes = (int64_t)image.size() * 4;
   // second image of the same chunk-local stages for the two-group DPP kernel (chunks of 4096)
   hp.dpp = DppImage();
