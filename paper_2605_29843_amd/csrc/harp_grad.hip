@@ -10,7 +10,8 @@
 // back, use the caller's rows where their kernel can), the backward pass runs one kernel per segment
 // that passes g back and leaves per-row-chunk partial sums of dK, and a reduction kernel adds the
 // chunks in a fixed order (no atomics: results are reproducible).  The segments:
-//   - the stages of the first 64 coordinates together (harp_grad_seg.hip: radix 2 or 8, orthogonal);
+//   - the stages of the first 64 coordinates together (radix 2 or 8, orthogonal), and behind them eight
+//     coordinates and up to eight more in one launch (harp_grad_pair.hip; harp_grad_seg.hip, forward);
 //   - up to three consecutive radix-2 stages: a thread owns the 2^k coordinates base + e s and the
 //     k 2^(k-1) blocks that act on them, the forward kernel stores only the run's output, and the
 //     backward kernel recomputes the run's inner activations in registers;
@@ -802,21 +803,26 @@ static int64_t grad_sum_chunks_bound(int64_t n, int64_t items) {
   return std::max<int64_t>(1, std::max(few, std::min<int64_t>((n + 8 * kSumGroups - 1) / (8 * kSumGroups), 256)));
 }
 
-// Segments of the backward pass: the first `lead` stages as one segment of 64 coordinates
-// (harp_grad_seg.hip), then runs of up to three radix-2 stages, single stages otherwise.
+// Segments of the backward pass: the first `lead` stages as one segment of 64 coordinates and pairs of
+// passes behind it (harp_grad_pair.hip), then runs of up to three radix-2 stages, single stages otherwise.
 struct GradSegment {
   int t0, k;
+  bool pair;
 };
 static std::vector<GradSegment> grad_segments(const harp_plan *plan, int lead) {
   std::vector<GradSegment> seg;
   const int m = plan->m;
-  if (lead > 0) seg.push_back(GradSegment{0, lead});
+  if (lead > 0) seg.push_back(GradSegment{0, lead, false});
   int t = lead;
   while (t < m) {
-    int k = 1;
-    if (plan->radices[t] == 2)
-      while (k < 3 && t + k < m && plan->radices[t + k] == 2) ++k;
-    seg.push_back(GradSegment{t, k});
+    int k = lead > 0 ? grad_pair_stages(plan, t) : 0;
+    const bool pair = k > 0;
+    if (!pair) {
+      k = 1;
+      if (plan->radices[t] == 2)
+        while (k < 3 && t + k < m && plan->radices[t + k] == 2) ++k;
+    }
+    seg.push_back(GradSegment{t, k, pair});
     t += k;
   }
   return seg;
@@ -840,29 +846,34 @@ static int64_t grad_big_chunks_bound(int64_t n) {
 // Does not fall as n grows: a workspace for n rows serves every smaller batch (every count of chunks
 // in it is one that never falls, and the plan without the leading segment keeps one matrix more, so
 // neither end of that segment's range of n is a step down).
-size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
-  int bbig = 0;
-  size_t per_row = 0;   // the most partial sums of one launch, times 1 / d: chunks * b of a stage, chunks * 2 k of a run
+static size_t grad_partial_floats(const harp_plan *plan, int64_t n) {   // the most partial sums of one launch of this file
+  size_t per_row = 0;   // times 1 / d: chunks * b of a stage, chunks * 2 k of a run
   for (int32_t b : plan->radices) {
-    if (b > 8) {
-      bbig = std::max(bbig, (int)b);
-      per_row = std::max(per_row, (size_t)grad_big_chunks_bound(n) * b);
-    } else {
-      per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d / b) * b);
-    }
+    if (b > 8) per_row = std::max(per_row, (size_t)grad_big_chunks_bound(n) * b);
+    else per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d / b) * b);
   }
-  const int lead = grad_seg_stages(plan, n);
   // (the segments behind the leading one are among these, or shorter runs with fewer chunks)
   for (const GradSegment &sg : grad_segments(plan, 0))
     if (sg.k > 1) per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d >> sg.k) * 2 * sg.k);
+  return (per_row * (size_t)plan->d + 3) / 4 * 4;
+}
+size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
+  int bbig = 0;
+  for (int32_t b : plan->radices) bbig = std::max(bbig, (int)b);
+  if (bbig <= 8) bbig = 0;
+  const int lead = grad_seg_stages(plan, n);
   const size_t mat = (size_t)n * (size_t)plan->d * 4;
-  const size_t partial = per_row * (size_t)plan->d * 4;
+  const size_t partial = grad_partial_floats(plan, n) * 4;
   // a stage of radix above 8 passes the gradient back out of place: one more matrix
   const size_t extra = 1 + (bbig > 0 ? 1 : 0);
   size_t need = (grad_segments(plan, 0).size() + extra) * mat + partial;
-  if (lead > 0)
-    need = std::max(need, (grad_segments(plan, lead).size() + extra) * mat +
-                              std::max(partial, grad_seg_partial_bytes(plan, n)));
+  if (lead > 0) {
+    size_t sums = partial + grad_lead_partial_bytes(plan, n);
+    const std::vector<GradSegment> seg = grad_segments(plan, lead);
+    for (const GradSegment &sg : seg)
+      if (sg.pair) sums += grad_pair_partial_bytes(plan, sg.t0, n);
+    need = std::max(need, (seg.size() + extra) * mat + sums);
+  }
   return need + 16;   // launch_grad starts at the next multiple of 16 bytes
 }
 
@@ -888,6 +899,8 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   float *g = act + (size_t)nseg * mat;      // gradient, updated in place (radix <= 8) ...
   float *g2 = g + mat;                      // ... or into the other of two matrices (radix >= 9)
   float *partial = g + (bmax > 8 ? 2 : 1) * mat;
+  float *sums_at = partial + grad_partial_floats(plan, n);   // of harp_grad_pair.hip, all until the end of the call
+  GradSums sums{};
   // 16-byte accesses of the stride-1 runs need the float32 copies on 16-byte boundaries
   const int aligned = (mat % 4 == 0);
   auto run_of = [&](const GradSegment &sg) {
@@ -898,7 +911,9 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   // A run of radix-2 stages at the start reads the caller's X itself (forward and backward), one
   // at the end reads the caller's G, and the first run writes dX: no separate conversion pass.
   const bool bf = (dt == HARP_BF16);
-  const bool first_run = seg[0].k > 1, last_run = seg[nseg - 1].k > 1;
+  const bool first_run = seg[0].k > 1;
+  // (rows of a pair are addressed by 32-bit offsets from the first of a few)
+  const bool last_run = seg[nseg - 1].k > 1 && !(seg[nseg - 1].pair && ldg >= ((int64_t)1 << 25));
   const bool dx_direct = first_run && dX != nullptr;
   // A stage of radix above 8 at the end passes the gradient back out of place, so with float32 rows
   // its two matrix-core kernels read the caller's G where it lies (1537 x 11008 float32, last radix
@@ -925,6 +940,9 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
       float *out = act + (size_t)(i + 1) * mat;
       if (i == 0 && lead > 0) {
         const harp_status_t rc = launch_grad_seg_fwd(plan, lead, X, ldx, bf, out, n, st);
+        if (rc != HARP_OK) return rc;
+      } else if (seg[i].pair) {
+        const harp_status_t rc = launch_grad_pair_fwd(plan, seg[i].t0, in, out, n, st);
         if (rc != HARP_OK) return rc;
       } else if (seg[i].k > 1) {
         const int nitems = (int)(d >> seg[i].k);
@@ -974,9 +992,17 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
     const int rows_sum = (int)((n + nsum - 1) / nsum);
     const size_t pstride = (size_t)nsum * 4 * (size_t)(d / 2);   // one radix-2 stage's partials
     if (i == 0 && lead > 0) {
-      const harp_status_t rc = launch_grad_seg_bwd(plan, lead, X, ldx, bf, g, dX, lddx, n, partial, dK, st);
+      const harp_status_t rc = launch_grad_lead_bwd(plan, lead, X, ldx, bf, g, dX, lddx, n, sums_at, dK, sums, st);
       if (rc != HARP_OK) return rc;
       break;
+    }
+    if (seg[i].pair) {
+      const bool own = last_run && i == nseg - 1;   // reads the caller's G
+      const harp_status_t rc = launch_grad_pair_bwd(plan, seg[i].t0, in, own ? G : (const void *)g, own ? ldg : d,
+                                                    own && bf, g, n, sums_at, dK, sums, st);
+      if (rc != HARP_OK) return rc;
+      sums_at += grad_pair_partial_bytes(plan, seg[i].t0, n) / 4;
+      continue;
     }
     if (n > 0) {
       if (seg[i].k > 1) {
@@ -1055,6 +1081,10 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
       hipLaunchKernelGGL(harp_grad_reduce_kernel, dim3(gx, (unsigned)seg[i].k), dim3(kGradThreads), 0, st,
                          partial, pstride, n > 0 ? (b > 8 ? nchunks_big : nsum) : 0, D, b, ro);
     }
+  }
+  if (sums.nsides > 0) {
+    const harp_status_t rc = launch_grad_sums(sums, st);
+    if (rc != HARP_OK) return rc;
   }
   if (dX && n > 0 && !dx_direct) {
     if (bf) launch_convert(g, d, (uint16_t *)dX, lddx, n, d, st);

@@ -401,14 +401,37 @@ size_t grad_workspace_bytes(const harp_plan *plan, int64_t n);
 harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, const void *G,
                           int64_t ldg, int64_t n, harp_dtype_t dt, float *const *dK, void *dX,
                           int64_t lddx, void *ws, hipStream_t st);
-// leading segment of 64 coordinates of the gradient path (harp_grad_seg.hip)
+// leading segment of 64 coordinates of the gradient path: rule and forward kernel (harp_grad_seg.hip)
 int grad_seg_stages(const harp_plan *plan, int64_t n);
-size_t grad_seg_partial_bytes(const harp_plan *plan, int64_t n);
 harp_status_t launch_grad_seg_fwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, float *Y,
                                   int64_t n, hipStream_t st);
-harp_status_t launch_grad_seg_bwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf,
-                                  const float *G, void *dX, int64_t lddx, int64_t n, float *partial,
-                                  float *const *dK, hipStream_t st);
+// its backward kernel, and pairs of passes at larger strides (harp_grad_pair.hip).  partial: the sums of a
+// launch, read by launch_grad_sums; G of a pair may be Gout
+struct PassBlocks {   // dense image of a pass's stages ([c][b][b] each)
+  const float *blocks[3];
+  int nst;   // radix-2 stages taken together; 0: one stage as it is
+};
+struct GradSums {
+  struct Side {
+    const float *partial;
+    PassBlocks pb;
+    float *dK[3];
+    const int8_t *signs;            // the pass's first stage is stage 0
+    int B, s, blocks, nchunks;      // size, stride and blocks of the pass, chunks of rows
+  } side[8];                        // two for 64 coordinates, or for 16 or more behind them (d <= 2^24)
+  int nsides;
+};
+size_t grad_lead_partial_bytes(const harp_plan *plan, int64_t n);
+harp_status_t launch_grad_lead_bwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, const float *G,
+                                   void *dX, int64_t lddx, int64_t n, float *partial, float *const *dK, GradSums &sums,
+                                   hipStream_t st);
+int grad_pair_stages(const harp_plan *plan, int t);
+size_t grad_pair_partial_bytes(const harp_plan *plan, int t, int64_t n);
+harp_status_t launch_grad_pair_fwd(const harp_plan *plan, int t, const float *X, float *Y, int64_t n, hipStream_t st);
+harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf,
+                                   float *Gout, int64_t n, float *partial, float *const *dK, GradSums &sums,
+                                   hipStream_t st);
+harp_status_t launch_grad_sums(const GradSums &sums, hipStream_t st);
 int choose_pipe_rows(const harp_plan *plan, int64_t n, int64_t nchunk, int chunk);
 const HostProgram *select_program(const harp_plan *plan, Direction dir, int64_t n,
                                   const char **name);

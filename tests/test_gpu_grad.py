@@ -221,6 +221,34 @@ def test_leading_segment_and_stage_by_stage_agree_with_the_oracle(harp, d, radic
     plan.destroy()
 
 
+# Two passes of one launch behind the leading segment: eight coordinates (one stage, or three of radix 2), then
+# 2 .. 8 (one stage, or one, two, three of radix 2), at the end of the plan and with a stage behind them; rows that
+# fill a workgroup's chunk, leave a set of four with one row, and leave whole sets empty; tiles of 16 groups that share
+# lines with neighbours and that do not.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("radices,n", [
+    ([8, 8, 8, 2], 64), ([8, 8, 8, 3], 81), ([8, 8, 8, 4], 65), ([8, 8, 8, 5], 97), ([8, 8, 8, 6], 70),
+    ([8, 8, 8, 7], 67), ([8, 8, 8, 8], 145), ([2] * 6 + [8, 3], 131), ([2] * 6 + [8, 2, 2], 66), ([2] * 6 + [8, 2], 79),
+    ([2] * 10, 96), ([2] * 11, 161), ([2] * 12, 73), ([2] * 9 + [5], 64), ([8, 8] + [2] * 6, 99), ([8, 8, 2, 2, 2, 7], 77),
+    ([8, 8, 8, 2, 3], 66), ([2] * 12 + [3], 65), ([8, 8, 8, 5, 2], 83), ([8, 8, 8, 3, 3], 70), ([2] * 6 + [8, 4, 2], 69),
+    ([8, 8, 8, 6, 2], 64), ([8, 8, 8, 7, 2], 64)])
+def test_pairs_of_passes_behind_the_leading_segment(harp, radices, n, dtype):
+    d = int(np.prod(radices))
+    rng = np.random.default_rng(d + n)
+    blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
+    X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    if dtype == "bf16":
+        X, G = gi.round_to_bf16(X), gi.round_to_bf16(G)
+    plan = harp.Plan(d, radices, blocks, signs)
+    say("grad pairs of passes", radices, n, dtype)
+    dK, dX = harp.harp_grad_blocks(plan, to_device(X, dtype), to_device(G, dtype))
+    rK, rX = ho.grad_blocks(X, G, d, radices, blocks, signs)
+    assert_dk_parity(dK, rK, X, G, "dK")
+    assert_dk_accuracy(dK, rK, X, G, d, radices, blocks, signs, "dK")
+    assert_parity(to_host64(dX), rX, dtype, "dX")
+    plan.destroy()
+
+
 @pytest.mark.parametrize("n", [1, 65, 130])
 def test_last_stage_of_large_radix_reads_gradient_rows_at_any_pitch(harp, n):
     """float32 rows, a last stage of radix above 8 at a stride that is a multiple of 16: G is read
