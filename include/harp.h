@@ -118,10 +118,13 @@ harp_status_t harp_plan_destroy(harp_plan_t *plan);
  * follows stages of radix <= 8 with a product that is a multiple of 16 and at least 64 (a
  * leftover prime at the end of the schedule), and -- for forward calls with n >= 512 -- plans of
  * radix-2 stages followed by one radix-3 stage, run in two or more launches through a
- * float32 intermediate of at most 128 MB that the plan allocates (hipMalloc) the first time
- * it is used on a stream and keeps, one per stream, until harp_plan_destroy.  That first
- * call may therefore block; inside a stream capture it returns HARP_ERR_UNSUPPORTED instead
- * (run the plan once on the stream before capturing).  HARP_ERR_OOM if it cannot be had.
+ * float32 intermediate of at most 128 MB.  It is allocated (hipMalloc) the first time a stream sees
+ * a call that needs it, so that call may block: up to 8 MB by the plan, which keeps it until
+ * harp_plan_destroy; larger ones are shared by all plans of the device on that stream (eight
+ * streams; beyond them each plan has its own) until the last plan is destroyed.  A captured call
+ * uses a buffer of the plan's; if the plan has not run on the stream before with as many rows, it
+ * returns HARP_ERR_UNSUPPORTED (run the plan once on the stream before capturing).  HARP_ERR_OOM
+ * if the memory cannot be had.
  * Arithmetic is float32 with one rounding at a bf16 store, with one exception: when dt is
  * HARP_BF16, a stage of radix 9..64 of such a plan runs on the matrix cores with every float32
  * operand split into two bf16 terms (x_hi K_hi + x_lo K_hi + x_hi K_lo accumulated in float32,

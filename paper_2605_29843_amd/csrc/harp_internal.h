@@ -241,15 +241,16 @@ struct harp_plan {
   int device = 0;
   int lds_bytes = 0;   // usable LDS per workgroup
   int num_cu = 0;
-  // float32 intermediates of split programs, one per stream the plan has been used on (work
-  // on one stream is ordered, so consecutive calls can share the buffer).  Nothing is freed
+  // Per stream the plan has run on in two launches or more: a buffer for small intermediates and captured calls, and
+  // the size up to which a captured call may ask for one.  Nothing is freed
   // before the plan is destroyed: a buffer that a later, larger call outgrows moves to
   // `retired`, because launches already queued and HIP graphs captured earlier still hold
   // its address.
+  bool counted = false;   // among its device's plans, which keep the shared buffers
   struct Scratch {
     hipStream_t stream;
-    float *ptr;
-    size_t bytes;
+    float *ptr;      // null: none yet
+    size_t bytes, seen;
   };
   mutable std::mutex scratch_mu;
   mutable std::vector<Scratch> scratch;

@@ -771,6 +771,76 @@ def test_graph_capture_and_replay(harp, d, radices, n):
     plan.destroy()
 
 
+def test_plans_share_the_intermediate_of_a_stream(harp):
+    """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
+    stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
+    bits of the plan alone; more streams than there are shared buffers; the memory of many plans is
+    that of one buffer and goes with the last plan."""
+    import threading
+    import torch
+    d, radices, n = 14336, [2] * 11 + [7], 600
+    rng = np.random.default_rng(31)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    plans = [harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)) for _ in range(6)]
+    plan_bytes = free0 - torch.cuda.mem_get_info()[0]
+    X = to_device(gi.round_to_bf16(rng.standard_normal((n, d)).astype(np.float32)), "bf16")
+    out = [torch.zeros_like(X) for _ in plans]
+    ref = [torch.zeros_like(X) for _ in plans]
+    torch.cuda.synchronize()
+    free1 = torch.cuda.mem_get_info()[0]
+    for p, r in zip(plans, ref):
+        harp.harp_apply(p, X, r)
+        torch.cuda.synchronize()
+    assert free1 - torch.cuda.mem_get_info()[0] < 100 << 20   # 34 MB each, six plans: one buffer
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        harp.harp_apply(plans[2], X, out[2], side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            harp.harp_apply(plans[2], X, out[2], side)
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(i):
+        try:
+            for _ in range(40):
+                harp.harp_apply(plans[i], X, out[i], side)
+        except Exception as e:   # noqa: BLE001
+            errors.append(e)
+    for rep in range(3):
+        for o in out:
+            o.zero_()
+        torch.cuda.synchronize()
+        ts = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+        for t in ts:
+            t.start()
+        with torch.cuda.stream(other):
+            for _ in range(20):
+                g.replay()
+        for t in ts:
+            t.join()
+        torch.cuda.synchronize()
+        assert not errors, errors
+        for i in range(3):
+            assert torch.equal(out[i], ref[i]), (rep, i)
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    ys = [torch.zeros_like(X) for _ in streams]
+    torch.cuda.synchronize()
+    for s, y in zip(streams, ys):
+        harp.harp_apply(plans[3], X, y, s)
+    torch.cuda.synchronize()
+    assert all(torch.equal(y, ref[3]) for y in ys)
+    del g
+    held = torch.cuda.mem_get_info()[0]
+    for p in plans:
+        p.destroy()
+    torch.cuda.synchronize()
+    # every plan's own memory and at least one buffer came back (plans of other tests may be alive and keep theirs)
+    assert torch.cuda.mem_get_info()[0] - held >= plan_bytes // 2
+
+
 def test_one_plan_on_two_streams_and_two_host_threads(harp):
     """A plan is immutable after create: two host threads drive it on two streams at the same
     time (a split program, whose float32 intermediate is kept per stream) and both reproduce the
