@@ -918,7 +918,9 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
   const int64_t d = plan->d;
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);
-  const int64_t slab = slab_cap > n ? n : slab_cap;
+  // slabs of one size: the last one would otherwise be a launch with little to do
+  const int64_t nslab = (n + slab_cap - 1) / slab_cap;
+  const int64_t slab = nslab == 1 ? n : std::min(slab_cap, ((n + nslab - 1) / nslab + 127) / 128 * 128);
   const size_t row_bytes = z16 ? (size_t)z16_ld(d) * 2 : (size_t)d * 4;
   // one buffer per stream serves both forms: its full size is the larger of the two slabs
   const size_t cap = std::max((size_t)slab_rows_cap(d) * d * 4,
