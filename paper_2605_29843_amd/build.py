@@ -13,7 +13,7 @@ LIB = os.path.join(PKG, "libharp.so")
 
 SOURCES = ["harp_api.cpp", "harp_theta.cpp", "harp_kernels.hip", "harp_pipe.hip", "harp_dpp.hip", "harp_mfma.hip",
            "harp_radix.hip", "harp_chain.hip", "harp_col.hip", "harp_colwide.hip",
-           "harp_colpair.hip", "harp_grad.hip", "harp_grad_seg.hip", "harp_grad_pair.hip"]
+           "harp_colpair.hip", "harp_grad.hip", "harp_grad_seg.hip", "harp_grad_pair.hip", "harp_grad_big.hip"]
 HEADERS = [os.path.join(ROOT, "include", "harp.h"), os.path.join(CSRC, "harp_internal.h"),
            os.path.join(CSRC, "harp_mfma4.h")]
 

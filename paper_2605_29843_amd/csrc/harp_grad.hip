@@ -18,7 +18,7 @@
 //   - one stage of radix up to 8: a thread owns one block for a chunk of rows, its b*b values and b*b
 //     accumulators in registers, g in place;
 //   - one stage of radix 9 .. 64, g out of place: on the matrix cores where the stride is a multiple
-//     of 16, else one value per thread.
+//     of 16 (up to 48 in one launch, harp_grad_big.hip), else one value per thread.
 // All read the plan's dense per-stage image with the signs folded into stage 0 (the one the
 // column-mode passes use).
 #include <hip/hip_runtime.h>
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kGradThreads) void harp_grad_dk_big_kernel(
     if (r < b) partial[((size_t)blockIdx.y * (b * b) + r * b + r2) * D + c] = acc[r];
 }
 
-// The same sums on the matrix cores: dK[c] = sum over rows of x[idx]^T g[idx] is a b x rows x b
+// Radix 49 .. 64: the same sums on the matrix cores: dK[c] = sum over rows of x[idx]^T g[idx] is a b x rows x b
 // product per block (v_mfma_f32_16x16x4_f32, unsplit float32 operands: the k index is the row).
 // Needs 16 consecutive blocks to be 16 consecutive coordinates (s a multiple of 16).  A workgroup
 // of 16 waves owns 16 consecutive blocks and one row chunk and walks down its rows 8 at a time:
@@ -457,7 +457,7 @@ static void launch_dk_mfma(const float *X, int64_t ldx, const float *Gm, int64_t
 
 static bool dk_mfma_supported(int b, int s, int D, const void *X, int64_t ldx, const void *Gm, int64_t ldg,
                               const void *partial, int64_t nchunks) {
-  if (b < 9 || b > 64 || s % 16 != 0 || D % 16 != 0) return false;
+  if (b < 49 || b > 64 || s % 16 != 0 || D % 16 != 0) return false;
   if (ldx % 4 || ldg % 4 || ldx >= ((int64_t)1 << 26) || ldg >= ((int64_t)1 << 26)) return false;
   if ((uintptr_t)X % 16 || (uintptr_t)Gm % 16 || (uintptr_t)partial % 16) return false;
   return (int64_t)(D / 16) * nchunks <= 0x7fffffff;
@@ -855,7 +855,10 @@ static size_t grad_partial_floats(const harp_plan *plan, int64_t n) {   // the m
   // (the segments behind the leading one are among these, or shorter runs with fewer chunks)
   for (const GradSegment &sg : grad_segments(plan, 0))
     if (sg.k > 1) per_row = std::max(per_row, (size_t)grad_sum_chunks_bound(n, plan->d >> sg.k) * 2 * sg.k);
-  return (per_row * (size_t)plan->d + 3) / 4 * 4;
+  size_t most = per_row * (size_t)plan->d;
+  for (int t = 0; t < plan->m; ++t)
+    if (grad_big_stage(plan, t)) most = std::max(most, grad_big_partial_floats(plan, t, n));
+  return (most + 3) / 4 * 4;
 }
 size_t grad_workspace_bytes(const harp_plan *plan, int64_t n) {
   int bbig = 0;
@@ -916,15 +919,17 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   const bool last_run = seg[nseg - 1].k > 1 && !(seg[nseg - 1].pair && ldg >= ((int64_t)1 << 25));
   const bool dx_direct = first_run && dX != nullptr;
   // A stage of radix above 8 at the end passes the gradient back out of place, so with float32 rows
-  // its two matrix-core kernels read the caller's G where it lies (1537 x 11008 float32, last radix
+  // its matrix-core kernels read the caller's G where it lies (1537 x 11008 float32, last radix
   // 43: 348 -> 311 us for the whole call).  Their plain fallbacks take one leading dimension and keep
   // the copy.
-  const ColStage &last = stages[seg[nseg - 1].t0];
+  const int tlast = seg[nseg - 1].t0;
+  const ColStage &last = stages[tlast];
   const bool g_direct =
-      !bf && last.b > 8 && (uintptr_t)G % 16 == 0 && ldg % 4 == 0 &&
-      mfma_pass_supported(plan->grad_mfma[1][seg[nseg - 1].t0], G, ldg, g2, d) &&
-      dk_mfma_supported(last.b, last.s, (int)(d / last.b), act + (size_t)(nseg - 1) * mat, d, G, ldg, partial,
-                        nchunks_big);
+      !bf && last.b > 8 && (uintptr_t)G % 16 == 0 && ldg % 4 == 0 && ldg < ((int64_t)1 << 25) &&
+      (grad_big_stage(plan, tlast) ||
+       (mfma_pass_supported(plan->grad_mfma[1][tlast], G, ldg, g2, d) &&
+        dk_mfma_supported(last.b, last.s, (int)(d / last.b), act + (size_t)(nseg - 1) * mat, d, G, ldg, partial,
+                          nchunks_big)));
   if (n > 0) {
     if (!first_run) {
       if (bf) launch_convert((const uint16_t *)X, ldx, act, d, n, d, st);
@@ -1030,6 +1035,13 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         else HARP_GRAD_BWD_TYPES(2);
 #undef HARP_GRAD_BWD_TYPES
 #undef HARP_GRAD_BWD_RUN
+      } else if (grad_big_stage(plan, seg[i].t0)) {
+        const bool own = g_direct && i == nseg - 1;   // reads the caller's G
+        const harp_status_t rc = launch_grad_big(plan, seg[i].t0, in, own ? (const float *)G : g, own ? ldg : d, g2, n,
+                                                 partial, dK[seg[i].t0], st);
+        if (rc != HARP_OK) return rc;
+        std::swap(g, g2);
+        continue;
       } else if (cs.b > 8) {
         const int D = (int)(d / cs.b);
         const dim3 grid((D + 63) / 64, nchunks_big, (cs.b + 3) / 4);
@@ -1039,14 +1051,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         const int64_t gld = own ? ldg : d;
         const bool mf = mfma_pass_supported(plan->grad_mfma[1][seg[i].t0], gsrc, gld, g2, d);
         const bool dkm = dk_mfma_supported(cs.b, cs.s, D, in, d, gsrc, gld, partial, nchunks_big);
-        if (dkm) {
-          switch ((cs.b + 15) / 16) {
-            case 1: launch_dk_mfma<1>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            case 2: launch_dk_mfma<2>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            case 3: launch_dk_mfma<3>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-            default: launch_dk_mfma<4>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st); break;
-          }
-        }
+        if (dkm) launch_dk_mfma<4>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st);
 #define HARP_GRAD_BIG_BWD(BM)                                                                      \
   if (!dkm)                                                                                        \
     hipLaunchKernelGGL((harp_grad_dk_big_kernel<BM>), grid, dim3(kGradThreads), 0, st, in, g, d, n, \

@@ -249,6 +249,31 @@ def test_pairs_of_passes_behind_the_leading_segment(harp, radices, n, dtype):
     plan.destroy()
 
 
+# A stage of radix 9 .. 48 at a stride that is a multiple of 16: operand tiles one to three, full and not, steps of 16 rows
+# and chunks that are full, short by one and longer by one (one workgroup per compute unit: D / 16 tiles across, so the
+# counts beyond 4096 rows of D = 16 take chunks of more than a step), the stage last, in the middle, and twice.
+@pytest.mark.parametrize("d,radices,kind,counts", [
+    (144, [4, 4, 9], "generic", (1, 15, 16, 17, 4097, 8200)), (256, [8, 2, 16], "orth", (31, 4096)), (272, [4, 4, 17], "orth", (33, 4113)),
+    (1024, [8, 4, 32], "generic", (16, 130)), (528, [2, 8, 33], "orth", (47, 4100)), (688, [4, 4, 43], "generic", (64, 8193)),
+    (768, [8, 2, 48], "orth", (5, 4098)), (11008, [8, 8, 4, 43], "orth", (81, 257)), (1408, [4, 4, 11, 8], "generic", (65,)),
+    (1936, [16, 11, 11], "orth", (40,))])
+def test_large_radix_on_the_matrix_cores(harp, d, radices, kind, counts):
+    rng = np.random.default_rng(d)
+    blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
+    plan = harp.Plan(d, radices, blocks, signs)
+    for n in counts:
+        say("grad large radix", radices, n)
+        X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+        dK, dX = harp.harp_grad_blocks(plan, to_device(X, "f32"), to_device(G, "f32"))
+        rK, rX = ho.grad_blocks(X, G, d, radices, blocks, signs)
+        assert_dk_parity(dK, rK, X, G, f"dK, {n} rows")
+        if kind == "orth":
+            assert_dk_accuracy(dK, rK, X, G, d, radices, blocks, signs, f"dK, {n} rows")
+        mag = summand_magnitude(G, d, radices, blocks, transpose=True) if kind == "generic" else None
+        assert_parity(to_host64(dX), rX, "f32", f"dX, {n} rows", mag=mag)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("n", [1, 65, 130])
 def test_last_stage_of_large_radix_reads_gradient_rows_at_any_pitch(harp, n):
     """float32 rows, a last stage of radix above 8 at a stride that is a multiple of 16: G is read

@@ -52,7 +52,7 @@ def scratch_bytes(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", ["harp_grad_bwd_run_kernel", "harp_grad_fwd_run_kernel", "harp_grad_bwd_kernel", "harp_grad_pair_bwd_kernel", "harp_grad_pair_fwd_kernel",
-                                    "harp_grad_lead_bwd_kernel", "harp_grad_pair_reduce_kernel",
+                                    "harp_grad_lead_bwd_kernel", "harp_grad_big_bwd_kernel", "harp_grad_pair_reduce_kernel",
                                     "harp_colpair_kernel", "harp_colwide_kernel", "harp_col_one_kernel"])
 def test_no_scratch(scratch_bytes, kernel):
     sizes = {k: v for k, v in scratch_bytes.items() if kernel in k}
