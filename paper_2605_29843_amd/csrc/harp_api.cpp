@@ -387,15 +387,16 @@ bool build_program(const harp_plan *plan, const std::vector<const float *> &bloc
             (chunk == 4096 || chunk == 2048 || chunk == 1024 || chunk == 512 || chunk == 256));
   const int dense_t = tied ? m - 2 : ((hp.z16 && plan->radices[tb - 1] == 2) ? tb - 1 : -1);
   std::vector<StageEff> eff;
-  const int dense_both = (top2 && hp.z16) ? m - 1 : -1;
+  // chunk of radices 8, 8, 8, 3..8: its kernel has its own image (build_chain_image)
+  const bool chain = fused && tb == 4 && plan->radices[0] == 8 && plan->radices[1] == 8 && plan->radices[2] == 8 &&
+                     plan->radices[3] >= 3 && plan->radices[3] <= 8;
+  // (going down, a chain's kernel takes a dense radix-2 stage along on the way in)
+  const int dense_both = (top2 && (hp.z16 || (chain && dir == DIR_TRN))) ? m - 1 : -1;
   if (!build_effective(plan, blocks, signs, algo, dir, true, eff, dense_t, dense_both)) {
     if (tied) return false;
     build_effective(plan, blocks, signs, algo, dir, false, eff, dense_t, dense_both);
   }
   auto local = [&](int i) { return eff[i].t < tb; };
-  // chunk of radices 8, 8, 8, 3..8: its kernel has its own image (build_chain_image)
-  const bool chain = fused && tb == 4 && plan->radices[0] == 8 && plan->radices[1] == 8 && plan->radices[2] == 8 &&
-                     plan->radices[3] >= 3 && plan->radices[3] <= 8;
   hp.chunk = (int32_t)chunk;
   hp.n_chunk = 0;
   hp.chunk_first = (dir == DIR_FWD);
@@ -915,6 +916,9 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
   if (dpp_top_supported(plan, hp.dpp, X, ldx, dt_in, Y, ldy, dt_out))
     return launch_dpp_top_kernel(plan, hp.dpp, X, ldx, Y, ldy, n,
                                  choose_pipe_rows(plan, n, plan->d / hp.chunk, hp.chunk), stream);
+  // the same above a chain of radices 8, 8, 8, 3 .. 8
+  if (chain_top_supported(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n))
+    return launch_chain_top(plan, hp, X, ldx, Y, ldy, n, stream);
   const int64_t d = plan->d;
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);

@@ -69,10 +69,11 @@ struct ChainShape {
   static constexpr int64_t TOTAL = OFF_D + (int64_t)4 * ND * 256;
 };
 
-template <typename TI, typename TO, int R4, bool TRN, int HV>
+// TOP: radix of the stage above the chunk, which a transposed program runs first; 0: none, or not here.
+template <typename TI, typename TO, int R4, bool TRN, int HV, int TOP = 0>
 __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kernel(
     const TI *X, int64_t ldx, TO *Y, int64_t ldy, int64_t n, int R, unsigned ntile, unsigned total,
-    const float *__restrict__ image) {
+    const float *__restrict__ image, const float *__restrict__ tparams) {
   using S = ChainShape<R4, HV>;
   constexpr int H = S::H, NW = S::NW, LB = S::LB;
   constexpr bool BI = sizeof(TI) == 2, BO = sizeof(TO) == 2;
@@ -85,13 +86,15 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
   // L2 holds the block values of few chunks.
   const unsigned id = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (id >= total) return;   // the whole workgroup
-  const int kch = (int)(id / ntile);
-  const int64_t r0 = (int64_t)(id % ntile) * R;
+  // (TOP: of the same rows, all chunks one after the other, so that the row is read from memory once)
+  const unsigned nch = TOP > 0 ? total / ntile : 1;
+  const int kch = (int)(TOP > 0 ? id % nch : id / ntile);
+  const int64_t r0 = (int64_t)(TOP > 0 ? id / nch : id % ntile) * R;
   const int nr = (int)((n - r0 < R) ? (n - r0) : R);
   const BlockValues<1024> val = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(image + (int64_t)kch * S::TOTAL), 0,
                                                               (int)(S::TOTAL * 4), 0x00020000),
                            lane * 16};
-  const TI *Xt = X + r0 * ldx + (int64_t)kch * S::CHUNK;
+  const TI *Xt = X + r0 * ldx + (TOP > 0 ? 0 : (int64_t)kch * S::CHUNK);
   TO *Yt = Y + r0 * ldy + (int64_t)kch * S::CHUNK;
 
   // low side: unit u, its groups and coordinates (40 and 48 groups: the fourth wave repeats the last
@@ -266,7 +269,49 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
     }
   } else {
     float y[LB][HV][H];
-    if constexpr (BI) {
+    if constexpr (TOP > 0) {
+      // The stage above the chunk on the way in: coordinate c of the chunk is the sum over the row's TOP chunks of
+      // x[j][c] K_c[j][kch], in the order in which the stage's own kernel adds.  A wave takes the same coordinates of all
+      // rows, so their TOP values of K are read once per tile.  (The row is read once per chunk, the last TOP - 1 times from
+      // the caches.)
+      constexpr int PW = (NR4 + NW - 1) / NW;
+      f4v z[PW][4 * HV];
+      first_pieces(iD, S::ND);
+#pragma unroll
+      for (int k = 0; k < PW; ++k) {
+        const int c = ((w + k * NW < NR4 ? w + k * NW : NR4 - 1) * 64 + lane) * 4;   // (past the end the last ones once more)
+        f4v f[TOP];
+#pragma unroll
+        for (int j = 0; j < TOP; ++j)
+          f[j] = *reinterpret_cast<const f4v *>(tparams + (size_t)(j * TOP + kch) * S::CHUNK + c);
+#pragma unroll
+        for (int r = 0; r < 4 * HV; ++r) {
+          const TI *p = Xt + (int64_t)(r < nr ? r : nr - 1) * ldx + c;
+#pragma unroll
+          for (int j = 0; j < TOP; ++j) {
+            const uint2 q = *reinterpret_cast<const uint2 *>(p + (int64_t)j * S::CHUNK);
+            const float x[4] = {__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u), __uint_as_float(q.y << 16),
+                                __uint_as_float(q.y & 0xffff0000u)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[k][r][e] = j == 0 ? x[e] * f[0][e] : fmaf(x[e], f[j][e], z[k][r][e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < HV; ++h) {
+        if (h) lds_barrier();
+#pragma unroll
+        for (int k = 0; k < PW; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f4v *>(lds + pos4(r, (w + k * NW < NR4 ? w + k * NW : NR4 - 1) * 64 + lane)) = z[k][4 * h + r];
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < LB; ++b)
+#pragma unroll
+          for (int j = 0; j < H; ++j) y[b][h][j] = lds[pos(row, j, (w * LB + b) * 16 + slot)];
+      }
+    } else if constexpr (BI) {
       u4v raw[LB][HV][NR8];   // wave w: rows w (w, w + 2) and the one four further on
 #pragma unroll
       for (int k = 0; k < LB; ++k)
@@ -408,9 +453,9 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
   }
 }
 
-template <typename TI, typename TO, int R4, bool TRN, int HV>
+template <typename TI, typename TO, int R4, bool TRN, int HV, int TOP = 0>
 harp_status_t launch_chain_rows(const harp_plan *plan, const ChainImage &ci, const void *X, int64_t ldx, void *Y,
-                                int64_t ldy, int64_t n, hipStream_t stream) {
+                                int64_t ldy, int64_t n, hipStream_t stream, const float *tparams = nullptr) {
   using S = ChainShape<R4, HV>;
   constexpr size_t lds = (size_t)4 * S::PITCH * 4;
   if (lds > (size_t)plan->lds_bytes) return HARP_ERR_UNSUPPORTED;
@@ -420,7 +465,7 @@ harp_status_t launch_chain_rows(const harp_plan *plan, const ChainImage &ci, con
   const int64_t ntile = (n + R - 1) / R;
   const int64_t total = ntile * nchunk;
   if (total > 0x7ffffff0) return HARP_ERR_UNSUPPORTED;
-  auto kern = harp_chain_kernel<TI, TO, R4, TRN, HV>;
+  auto kern = harp_chain_kernel<TI, TO, R4, TRN, HV, TOP>;
   static thread_local int attr_done_dev = -1;   // per instantiation
   if (attr_done_dev != plan->device) {
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -431,8 +476,13 @@ harp_status_t launch_chain_rows(const harp_plan *plan, const ChainImage &ci, con
     attr_done_dev = plan->device;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(64 * S::NW), lds, stream, (const TI *)X, ldx,
-                     (TO *)Y, ldy, n, R, (unsigned)ntile, (unsigned)total, ci.img);
+                     (TO *)Y, ldy, n, R, (unsigned)ntile, (unsigned)total, ci.img, tparams);
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
+}
+
+bool chain_rows_of_four(const harp_plan *plan, int64_t n, int chunk) {
+  const int64_t cus = plan->num_cu > 0 ? plan->num_cu : 256;
+  return plan->rows_override > 0 ? plan->rows_override <= 4 : (n + 3) / 4 * (plan->d / chunk) <= cus;
 }
 
 template <typename TI, typename TO, int R4, bool TRN>
@@ -443,10 +493,7 @@ harp_status_t launch_chain_inst(const harp_plan *plan, const ChainImage &ci, con
   // uses the block values twice as often.  Eight / four rows, bf16, us: 4096 at 1 row 9.8 / 6.9, 512 rows 10.6 / 8.2,
   // 1024 rows (256 tiles) 12.0 / 9.6, 1030 rows 12.1 / 13.8; 14336 (two launches) at 6 rows 12.5 / 9.9, 256 rows (256 tiles)
   // 17.9 / 15.7, 512 rows 23.0 / 24.0; 2048 at 1024 rows 8.9 / 5.8.
-  const int64_t cus = plan->num_cu > 0 ? plan->num_cu : 256;
-  const bool four = plan->rows_override > 0 ? plan->rows_override <= 4
-                                            : (n + 3) / 4 * (plan->d / ChainShape<R4>::CHUNK) <= cus;
-  return four ? launch_chain_rows<TI, TO, R4, TRN, 1>(plan, ci, X, ldx, Y, ldy, n, stream)
+  return chain_rows_of_four(plan, n, ChainShape<R4>::CHUNK) ? launch_chain_rows<TI, TO, R4, TRN, 1>(plan, ci, X, ldx, Y, ldy, n, stream)
               : launch_chain_rows<TI, TO, R4, TRN, 2>(plan, ci, X, ldx, Y, ldy, n, stream);
 }
 
@@ -541,6 +588,37 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
                                   hipStream_t stream) {
   harp_status_t st = HARP_ERR_UNSUPPORTED;
   HARP_CHAIN_R4(ci.r4, (st = launch_chain_shape<R4>(plan, ci, X, ldx, dt_in, Y, ldy, dt_out, n, stream)));
+  return st;
+}
+
+// Transposed split program of bf16 rows whose one stage above the chain has radix 2 .. 4: one launch, no intermediate (12 bytes
+// per coordinate become 4).  Not in place: a workgroup may store its chunk of a row before another one has read it.  Tiles of
+// eight rows only; few rows keep two launches.  Two launches / one, us: 8192 (8, 8, 8, 8 | 2) at 514 rows 19.3 / 15.0, 2048 rows
+// 51 / 25; 14336 (8, 8, 8, 7 | 4) at 300 rows 19.4 / 17.8, 777 rows 35.4 / 27.0, 2048 rows 82 / 54, 4096 rows 173 / 129.  With a run of tiles
+// of one chunk per XCD, as without the stage, the row came from memory TOP times: 777 rows 30.2, 2048 rows 68.
+bool chain_top_supported(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, harp_dtype_t dt_in,
+                         const void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n) {
+  const PassDesc &pd = hp.prog.pass[0];
+  if (!hp.chain.img || !hp.chain.trn || hp.chunk_first || hp.prog.npass != hp.n_chunk + 1 || X == Y) return false;
+  if (dt_in != HARP_BF16 || dt_out != HARP_BF16 || !radix_supported(plan, hp, 1, hp.n_chunk, hp.chunk, X, ldx, Y, ldy) ||
+      radix_rebuilds_in_kernel(plan, hp.prog, 1, hp.n_chunk, hp.chunk))
+    return false;
+  const bool dense = (pd.kind == PASS_SMALL && (pd.b == 3 || pd.b == 4)) ||
+                     (pd.kind == PASS_POW2_DENSE && pd.k == 1 && pd.P == 2 && pd.V == 4);
+  return dense && !pd.tied && pd.nq == hp.chunk && pd.nqp == hp.chunk && pd.S == hp.chunk && (uintptr_t)pd.params % 16 == 0 &&
+         !chain_rows_of_four(plan, n, hp.chunk);
+}
+
+harp_status_t launch_chain_top(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, void *Y, int64_t ldy,
+                               int64_t n, hipStream_t stream) {
+  const PassDesc &pd = hp.prog.pass[0];
+  harp_status_t st = HARP_ERR_UNSUPPORTED;
+#define HARP_CHAIN_TOP(T) \
+  HARP_CHAIN_R4(hp.chain.r4, (st = launch_chain_rows<uint16_t, uint16_t, R4, true, 2, T>(plan, hp.chain, X, ldx, Y, ldy, n, stream, pd.params)))
+  if (pd.P == 2) HARP_CHAIN_TOP(2)
+  else if (pd.P == 3) HARP_CHAIN_TOP(3)
+  else if (pd.P == 4) HARP_CHAIN_TOP(4)
+#undef HARP_CHAIN_TOP
   return st;
 }
 

@@ -113,3 +113,36 @@ def test_tiles_of_four_and_eight_rows(radices, counts, dtype):
             some = np.unique(np.linspace(0, n - 1, 9).astype(int))
             assert_parity(to_host64(outs[2])[some], oracle(X[some], d, radices, blocks, signs), dtype, f"{fn.__name__} n={n}")
     plan.destroy()
+
+
+# The stage above the chunk on the way in (bf16, transposed, not in place): its radices 2 .. 4 over every last radix of a chain, rows
+# that fill the last tile of eight and rows that do not, pitches; against the oracle, and against the same call in place, which takes
+# two launches (the same sums in the same order: equal bits).
+@pytest.mark.parametrize("top", [2, 3, 4])
+@pytest.mark.parametrize("r4", [3, 4, 5, 6, 7, 8])
+def test_chain_takes_the_stage_above_along(r4, top):
+    import torch
+    from paper_2605_29843_amd import harp
+    radices = [8, 8, 8, r4, top]
+    d = int(np.prod(radices))
+    if d <= 4096:
+        pytest.skip("the whole row is one chunk of other radices")
+    rng = np.random.default_rng(d)
+    kind = "qr" if r4 % 2 else "generic"
+    blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
+    plan = harp.Plan(d, radices, blocks, signs)
+    for n in (1024 // top + 8, 1024 // top + 13):   # more tiles of four rows than compute units
+        print("chain with the stage above", radices, n, file=sys.stderr, flush=True)
+        X = gi.round_to_bf16(rng.standard_normal((n, d)).astype(np.float32))
+        Xd = to_device(X, "bf16")
+        wide = torch.zeros(n, d + 16, dtype=Xd.dtype, device="cuda")
+        got = harp.harp_apply_transpose(plan, Xd, wide[:, 8:8 + d])
+        two = Xd.clone()
+        harp.harp_apply_transpose(plan, two, two)
+        assert torch.equal(got, two)
+        assert bool((wide[:, :8] == 0).all()) and bool((wide[:, 8 + d:] == 0).all())
+        rows = np.r_[0:8, n - 14:n]
+        mag = summand_magnitude(X[rows], d, radices, blocks, True) if kind == "generic" else None
+        assert_parity(to_host64(got)[rows], ho.apply_transpose_staged(X[rows], d, radices, blocks, signs), "bf16",
+                      f"transposed n={n}", mag=mag)
+    plan.destroy()
