@@ -917,8 +917,8 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
     return launch_dpp_top_kernel(plan, hp.dpp, X, ldx, Y, ldy, n,
                                  choose_pipe_rows(plan, n, plan->d / hp.chunk, hp.chunk), stream);
   // the same above a chain of radices 8, 8, 8, 3 .. 8
-  if (chain_top_supported(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n))
-    return launch_chain_top(plan, hp, X, ldx, Y, ldy, n, stream);
+  if (chain_top_supported(plan, hp, X, ldx, dt_in, Y, ldy, dt_out))
+    return launch_chain_top(plan, hp, X, ldx, Y, ldy, dt_in, n, stream);
   const int64_t d = plan->d;
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);
@@ -1720,6 +1720,8 @@ harp_status_t harp_apply_noalloc(const harp_plan_t *plan, const void *X, int64_t
                                  (hipStream_t)stream);
   // the whole batch has to fit the library's own array: no slab loop, a clear refusal instead
   if ((size_t)n > HARP_NOALLOC_SCRATCH_BYTES / ((size_t)plan->d * 4)) return HARP_ERR_UNSUPPORTED;
+  if (chain_top_supported(plan, hp, X, ldx, dt, Y, ldy, dt))   // (within that limit, too)
+    return launch_chain_top(plan, hp, X, ldx, Y, ldy, dt, n, (hipStream_t)stream);
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();

@@ -86,10 +86,12 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
   // L2 holds the block values of few chunks.
   const unsigned id = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (id >= total) return;   // the whole workgroup
-  // (TOP: of the same rows, all chunks one after the other, so that the row is read from memory once)
-  const unsigned nch = TOP > 0 ? total / ntile : 1;
-  const int kch = (int)(TOP > 0 ? id % nch : id / ntile);
-  const int64_t r0 = (int64_t)(TOP > 0 ? id / nch : id % ntile) * R;
+  // (TOP: of the same rows, all chunks one after the other, so that the row is read from memory once; few rows are
+  // less than the block values)
+  constexpr bool ROWS_FIRST = TOP > 0 && HV == 2;
+  const unsigned nch = ROWS_FIRST ? total / ntile : 1;
+  const int kch = (int)(ROWS_FIRST ? id % nch : id / ntile);
+  const int64_t r0 = (int64_t)(ROWS_FIRST ? id / nch : id % ntile) * R;
   const int nr = (int)((n - r0 < R) ? (n - r0) : R);
   const BlockValues<1024> val = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(image + (int64_t)kch * S::TOTAL), 0,
                                                               (int)(S::TOTAL * 4), 0x00020000),
@@ -289,9 +291,18 @@ __global__ __launch_bounds__((64 * ChainShape<R4>::NW), 2) void harp_chain_kerne
           const TI *p = Xt + (int64_t)(r < nr ? r : nr - 1) * ldx + c;
 #pragma unroll
           for (int j = 0; j < TOP; ++j) {
-            const uint2 q = *reinterpret_cast<const uint2 *>(p + (int64_t)j * S::CHUNK);
-            const float x[4] = {__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u), __uint_as_float(q.y << 16),
-                                __uint_as_float(q.y & 0xffff0000u)};
+            float x[4];
+            if constexpr (BI) {
+              const uint2 q = *reinterpret_cast<const uint2 *>(p + (int64_t)j * S::CHUNK);
+              x[0] = __uint_as_float(q.x << 16);
+              x[1] = __uint_as_float(q.x & 0xffff0000u);
+              x[2] = __uint_as_float(q.y << 16);
+              x[3] = __uint_as_float(q.y & 0xffff0000u);
+            } else {
+              const f4v q = *reinterpret_cast<const f4v *>(p + (int64_t)j * S::CHUNK);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = q[e];
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) z[k][r][e] = j == 0 ? x[e] * f[0][e] : fmaf(x[e], f[j][e], z[k][r][e]);
           }
@@ -591,34 +602,40 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
   return st;
 }
 
-// Transposed split program of bf16 rows whose one stage above the chain has radix 2 .. 4: one launch, no intermediate (12 bytes
-// per coordinate become 4).  Not in place: a workgroup may store its chunk of a row before another one has read it.  Tiles of
-// eight rows only; few rows keep two launches.  Two launches / one, us: 8192 (8, 8, 8, 8 | 2) at 514 rows 19.3 / 15.0, 2048 rows
-// 51 / 25; 14336 (8, 8, 8, 7 | 4) at 300 rows 19.4 / 17.8, 777 rows 35.4 / 27.0, 2048 rows 82 / 54, 4096 rows 173 / 129.  With a run of tiles
-// of one chunk per XCD, as without the stage, the row came from memory TOP times: 777 rows 30.2, 2048 rows 68.
+// Transposed split program whose one stage above the chain has radix 2 .. 4: one launch, no intermediate (bf16: 12 bytes per
+// coordinate become 4).  Not in place: a workgroup may store its chunk of a row before another one has read it.  Larger radices are
+// not built: a row would be read that many times.  Two launches / one, us, bf16: 8192 (8, 8, 8, 8 | 2) at 1 row 9.6 / 8.0, 514 rows
+// 19.3 / 15.0, 2048 rows 51 / 25; 14336 (8, 8, 8, 7 | 4) at 8 rows 10.2 / 9.2, 300 rows 19.6 / 17.7, 777 rows 35 / 27, 2048 rows
+// 82 / 57; float32: 5120 (8, 8, 8, 5 | 2) at 3000 rows 58 / 36, 14336 at 777 rows 45 / 33.  Tiles of eight go row by row over an XCD; with a
+// run of tiles of one chunk, as without the stage, the row came from memory TOP times (14336: 777 rows 30, 2048 rows 68).
+// Tiles of four keep that order: few rows are less than the block values (20 rows of 14336 11.3 -> 10.6).
 bool chain_top_supported(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, harp_dtype_t dt_in,
-                         const void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n) {
+                         const void *Y, int64_t ldy, harp_dtype_t dt_out) {
   const PassDesc &pd = hp.prog.pass[0];
   if (!hp.chain.img || !hp.chain.trn || hp.chunk_first || hp.prog.npass != hp.n_chunk + 1 || X == Y) return false;
-  if (dt_in != HARP_BF16 || dt_out != HARP_BF16 || !radix_supported(plan, hp, 1, hp.n_chunk, hp.chunk, X, ldx, Y, ldy) ||
+  if (dt_in != dt_out || !radix_supported(plan, hp, 1, hp.n_chunk, hp.chunk, X, ldx, Y, ldy) ||
       radix_rebuilds_in_kernel(plan, hp.prog, 1, hp.n_chunk, hp.chunk))
     return false;
   const bool dense = (pd.kind == PASS_SMALL && (pd.b == 3 || pd.b == 4)) ||
                      (pd.kind == PASS_POW2_DENSE && pd.k == 1 && pd.P == 2 && pd.V == 4);
-  return dense && !pd.tied && pd.nq == hp.chunk && pd.nqp == hp.chunk && pd.S == hp.chunk && (uintptr_t)pd.params % 16 == 0 &&
-         !chain_rows_of_four(plan, n, hp.chunk);
+  return dense && !pd.tied && pd.nq == hp.chunk && pd.nqp == hp.chunk && pd.S == hp.chunk && (uintptr_t)pd.params % 16 == 0;
 }
 
 harp_status_t launch_chain_top(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, void *Y, int64_t ldy,
-                               int64_t n, hipStream_t stream) {
+                               harp_dtype_t dt, int64_t n, hipStream_t stream) {
   const PassDesc &pd = hp.prog.pass[0];
   harp_status_t st = HARP_ERR_UNSUPPORTED;
-#define HARP_CHAIN_TOP(T) \
-  HARP_CHAIN_R4(hp.chain.r4, (st = launch_chain_rows<uint16_t, uint16_t, R4, true, 2, T>(plan, hp.chain, X, ldx, Y, ldy, n, stream, pd.params)))
+  const bool four = chain_rows_of_four(plan, n, hp.chunk);
+#define HARP_CHAIN_TOP_T(T, TX, HV) \
+  (launch_chain_rows<TX, TX, R4, true, HV, T>(plan, hp.chain, X, ldx, Y, ldy, n, stream, pd.params))
+#define HARP_CHAIN_TOP(T)                                                                                             \
+  HARP_CHAIN_R4(hp.chain.r4, st = dt == HARP_BF16 ? (four ? HARP_CHAIN_TOP_T(T, uint16_t, 1) : HARP_CHAIN_TOP_T(T, uint16_t, 2)) \
+                                                  : (four ? HARP_CHAIN_TOP_T(T, float, 1) : HARP_CHAIN_TOP_T(T, float, 2)))
   if (pd.P == 2) HARP_CHAIN_TOP(2)
   else if (pd.P == 3) HARP_CHAIN_TOP(3)
   else if (pd.P == 4) HARP_CHAIN_TOP(4)
 #undef HARP_CHAIN_TOP
+#undef HARP_CHAIN_TOP_T
   return st;
 }
 

@@ -358,9 +358,9 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
                                   harp_dtype_t dt_in, void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n,
                                   hipStream_t stream);
 bool chain_top_supported(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, harp_dtype_t dt_in,
-                         const void *Y, int64_t ldy, harp_dtype_t dt_out, int64_t n);
+                         const void *Y, int64_t ldy, harp_dtype_t dt_out);
 harp_status_t launch_chain_top(const harp_plan *plan, const HostProgram &hp, const void *X, int64_t ldx, void *Y, int64_t ldy,
-                               int64_t n, hipStream_t stream);
+                               harp_dtype_t dt, int64_t n, hipStream_t stream);
 // column-mode passes (harp_col.hip): group plan->col[dir] into passes; launch one pass on a
 // row-major [nrows, ncols] matrix (nrows == plan->d; may run in place)
 // host_image: the dense blocks on the host; wide: passes of 512 rows are allowed as well

@@ -115,12 +115,13 @@ def test_tiles_of_four_and_eight_rows(radices, counts, dtype):
     plan.destroy()
 
 
-# The stage above the chunk on the way in (bf16, transposed, not in place): its radices 2 .. 4 over every last radix of a chain, rows
-# that fill the last tile of eight and rows that do not, pitches; against the oracle, and against the same call in place, which takes
-# two launches (the same sums in the same order: equal bits).
+# The stage above the chunk on the way in (transposed, not in place): its radices 2 .. 4 over every last radix of a chain, rows
+# that fill the last tile of four or eight and rows that do not, pitches; against the oracle, and against the same call in place, which
+# takes two launches (the same sums in the same order: equal bits).
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("top", [2, 3, 4])
 @pytest.mark.parametrize("r4", [3, 4, 5, 6, 7, 8])
-def test_chain_takes_the_stage_above_along(r4, top):
+def test_chain_takes_the_stage_above_along(r4, top, dtype):
     import torch
     from paper_2605_29843_amd import harp
     radices = [8, 8, 8, r4, top]
@@ -131,18 +132,20 @@ def test_chain_takes_the_stage_above_along(r4, top):
     kind = "qr" if r4 % 2 else "generic"
     blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
     plan = harp.Plan(d, radices, blocks, signs)
-    for n in (1024 // top + 8, 1024 // top + 13):   # more tiles of four rows than compute units
-        print("chain with the stage above", radices, n, file=sys.stderr, flush=True)
-        X = gi.round_to_bf16(rng.standard_normal((n, d)).astype(np.float32))
-        Xd = to_device(X, "bf16")
+    for n in (1, 7, 1024 // top + 8, 1024 // top + 13):   # tiles of four rows; more of them than compute units: of eight
+        print("chain with the stage above", radices, n, dtype, file=sys.stderr, flush=True)
+        X = rng.standard_normal((n, d)).astype(np.float32)
+        if dtype == "bf16":
+            X = gi.round_to_bf16(X)
+        Xd = to_device(X, dtype)
         wide = torch.zeros(n, d + 16, dtype=Xd.dtype, device="cuda")
         got = harp.harp_apply_transpose(plan, Xd, wide[:, 8:8 + d])
         two = Xd.clone()
         harp.harp_apply_transpose(plan, two, two)
         assert torch.equal(got, two)
         assert bool((wide[:, :8] == 0).all()) and bool((wide[:, 8 + d:] == 0).all())
-        rows = np.r_[0:8, n - 14:n]
+        rows = np.unique(np.r_[0:min(8, n), max(n - 14, 0):n])
         mag = summand_magnitude(X[rows], d, radices, blocks, True) if kind == "generic" else None
-        assert_parity(to_host64(got)[rows], ho.apply_transpose_staged(X[rows], d, radices, blocks, signs), "bf16",
+        assert_parity(to_host64(got)[rows], ho.apply_transpose_staged(X[rows], d, radices, blocks, signs), dtype,
                       f"transposed n={n}", mag=mag)
     plan.destroy()
