@@ -780,7 +780,8 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
       (void)hipGetLastError();
-      return HARP_ERR_DEVICE;
+      if (stream != nullptr) return HARP_ERR_DEVICE;
+      cs = hipStreamCaptureStatusNone;   // the default stream beside a capture: if it may not be used, the launches say so
     }
     const bool capturing = cs != hipStreamCaptureStatusNone;
     if (!slot || slot->seen < bytes) {
