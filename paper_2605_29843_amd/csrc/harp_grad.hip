@@ -918,16 +918,16 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   // (rows of a pair are addressed by 32-bit offsets from the first of a few)
   const bool last_run = seg[nseg - 1].k > 1 && !(seg[nseg - 1].pair && ldg >= ((int64_t)1 << 25));
   const bool dx_direct = first_run && dX != nullptr;
-  // A stage of radix above 8 at the end passes the gradient back out of place, so with float32 rows
-  // its matrix-core kernels read the caller's G where it lies (1537 x 11008 float32, last radix
-  // 43: 348 -> 311 us for the whole call).  Their plain fallbacks take one leading dimension and keep
-  // the copy.
+  // A stage of radix above 8 at the end passes the gradient back out of place, so its matrix-core kernels read the caller's G
+  // where it lies (1537 x 11008 float32, last radix 43: 348 -> 311 us for the whole call; 2048 x 11008 bf16 in one launch:
+  // a conversion of 26 us less), radix 49 and up float32 rows only.  Their plain fallbacks take one leading dimension and
+  // keep the copy.
   const int tlast = seg[nseg - 1].t0;
   const ColStage &last = stages[tlast];
   const bool g_direct =
-      !bf && last.b > 8 && (uintptr_t)G % 16 == 0 && ldg % 4 == 0 && ldg < ((int64_t)1 << 25) &&
+      last.b > 8 && (uintptr_t)G % (bf ? 8 : 16) == 0 && ldg % 4 == 0 && ldg < ((int64_t)1 << 25) &&
       (grad_big_stage(plan, tlast) ||
-       (mfma_pass_supported(plan->grad_mfma[1][tlast], G, ldg, g2, d) &&
+       (!bf && mfma_pass_supported(plan->grad_mfma[1][tlast], G, ldg, g2, d) &&
         dk_mfma_supported(last.b, last.s, (int)(d / last.b), act + (size_t)(nseg - 1) * mat, d, G, ldg, partial,
                           nchunks_big)));
   if (n > 0) {
@@ -1037,8 +1037,8 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
 #undef HARP_GRAD_BWD_RUN
       } else if (grad_big_stage(plan, seg[i].t0)) {
         const bool own = g_direct && i == nseg - 1;   // reads the caller's G
-        const harp_status_t rc = launch_grad_big(plan, seg[i].t0, in, own ? (const float *)G : g, own ? ldg : d, g2, n,
-                                                 partial, dK[seg[i].t0], st);
+        const harp_status_t rc = launch_grad_big(plan, seg[i].t0, in, own ? G : (const void *)g, own ? ldg : d, own && bf, g2,
+                                                 n, partial, dK[seg[i].t0], st);
         if (rc != HARP_OK) return rc;
         std::swap(g, g2);
         continue;

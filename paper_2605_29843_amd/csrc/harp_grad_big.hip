@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "harp_internal.h"
 #include "harp_mfma4.h"
@@ -31,9 +32,9 @@ constexpr int kBigThreads = 512, kBigWaves = kBigThreads / 64, kBigRows = 16;
 constexpr int kBigJ = 16 * kBigRows + 4, kBigStep = 4 * kBigRows;
 __device__ __forceinline__ int big_slot(int block) { return (4 * (block & 3) + (block >> 2)) * kBigRows; }
 
-template <int KT>
+template <int KT, typename TG>
 __global__ __launch_bounds__(kBigThreads, 2) void harp_grad_big_bwd_kernel(
-    const float *__restrict__ X, const float *__restrict__ G, int64_t ldg, float *__restrict__ Gout, int64_t d, int64_t n,
+    const float *__restrict__ X, const TG *__restrict__ G, int64_t ldg, float *__restrict__ Gout, int64_t d, int64_t n,
     int rows, int S, int b, int gx, int share, const f4v *__restrict__ operands, float *__restrict__ partial) {
   constexpr int TILE = 16 * KT * kBigJ, MAXG = (kBigRows * 16 * KT * 4 + kBigThreads - 1) / kBigThreads;
   __shared__ __attribute__((aligned(16))) float lds[3 * TILE];
@@ -53,16 +54,19 @@ __global__ __launch_bounds__(kBigThreads, 2) void harp_grad_big_bwd_kernel(
   const int lo4 = tid & 3, row = (tid >> 2) % kBigRows;
   const int col = base + 4 * lo4, place = big_slot(4 * lo4) + row;
   auto value = [&](int u) { return w + kBigWaves * u < b ? w + kBigWaves * u : b - 1; };
-  f4v px[MAXG], pg[MAXG];
+  typedef typename std::conditional<sizeof(TG) == 2, uint2, f4v>::type raw_t;   // four elements of G as loaded
+  f4v px[MAXG];
+  raw_t pg[MAXG];
   auto fetch = [&](int64_t first) {   // rows past the end repeat the last one
     const int64_t r = first < r1 ? first : r1 - 1;
     const int last = (int)(r1 - 1 - r);
     const uint32_t at = (uint32_t)(row < last ? row : last);
-    const float *xr = X + r * d, *gr = G + r * ldg;
+    const float *xr = X + r * d;
+    const TG *gr = G + r * ldg;
 #pragma unroll
     for (int u = 0; u < MAXG; ++u) {
       px[u] = *reinterpret_cast<const f4v *>(xr + value(u) * S + (at * (uint32_t)d + (uint32_t)col));
-      pg[u] = *reinterpret_cast<const f4v *>(gr + value(u) * S + (at * (uint32_t)ldg + (uint32_t)col));
+      pg[u] = *reinterpret_cast<const raw_t *>(gr + value(u) * S + (at * (uint32_t)ldg + (uint32_t)col));
     }
   };
   fetch(r0);
@@ -84,12 +88,19 @@ __global__ __launch_bounds__(kBigThreads, 2) void harp_grad_big_bwd_kernel(
   for (int64_t r = r0; r < r1; r += kBigRows) {
     const int left = (int)(r1 - r < kBigRows ? r1 - r : kBigRows);
 #pragma unroll
-    for (int u = 0; u < MAXG; ++u)
+    for (int u = 0; u < MAXG; ++u) {
+      f4v gv;
+      if constexpr (sizeof(TG) == 2)
+        gv = (f4v){__uint_as_float(pg[u].x << 16), __uint_as_float(pg[u].x & 0xffff0000u), __uint_as_float(pg[u].y << 16),
+                   __uint_as_float(pg[u].y & 0xffff0000u)};
+      else
+        gv = pg[u];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {   // rows past the end enter as zeros
         tx[value(u) * kBigJ + place + k * kBigStep] = row < left ? px[u][k] : 0.f;
-        tg[value(u) * kBigJ + place + k * kBigStep] = row < left ? pg[u][k] : 0.f;
+        tg[value(u) * kBigJ + place + k * kBigStep] = row < left ? gv[k] : 0.f;
       }
+    }
     fetch(r + kBigRows);
     lds_barrier();
 #pragma unroll
@@ -198,7 +209,8 @@ int big_rows(const harp_plan *plan, int64_t n, int64_t gx) {
 
 }  // namespace
 
-// The stage at t runs here (the choice depends on the plan alone; X, G and Gout must then lie on boundaries of 16 bytes).
+// The stage at t runs here (the choice depends on the plan alone; X and Gout must then lie on boundaries of 16 bytes, G on
+// boundaries of four elements).
 bool grad_big_stage(const harp_plan *plan, int t) {
   const int b = plan->radices[t];
   return b >= 9 && b <= 48 && plan->grad_mfma[1].size() > (size_t)t && plan->grad_mfma[1][t].aux != nullptr &&
@@ -211,7 +223,7 @@ size_t grad_big_partial_floats(const harp_plan *plan, int t, int64_t n) {
   return (size_t)std::max<int64_t>(few, (n + 127) / 128) * (size_t)(plan->d * b);
 }
 
-harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, const float *G, int64_t ldg, float *Gout,
+harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf, float *Gout,
                               int64_t n, float *partial, float *dK, hipStream_t st) {
   const PassDesc &pd = plan->grad_mfma[1][t];
   const int b = pd.b, KT = (b + 15) / 16;
@@ -222,13 +234,19 @@ harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, cons
   const int share = gx % 4 == 0 && total % 32 == 0 ? 4 : 1;
   // the float32 operand tiles follow the bf16 ones of all blocks
   const f4v *operands = reinterpret_cast<const f4v *>(static_cast<const uint16_t *>(pd.aux) + (size_t)pd.nqp * KT * KT * 2 * 64 * 4);
-#define HARP_BIG(T)                                                                                                     \
-  hipLaunchKernelGGL((harp_grad_big_bwd_kernel<T>), dim3((unsigned)total), dim3(kBigThreads), 0, st, X, G, ldg, Gout, d, n, \
-                     rows, (int)pd.S, b, (int)gx, share, operands, partial)
+#define HARP_BIG_T(T, TG)                                                                                              \
+  hipLaunchKernelGGL((harp_grad_big_bwd_kernel<T, TG>), dim3((unsigned)total), dim3(kBigThreads), 0, st, X, (const TG *)G, \
+                     ldg, Gout, d, n, rows, (int)pd.S, b, (int)gx, share, operands, partial)
+#define HARP_BIG(T)                     \
+  do {                                  \
+    if (bf) HARP_BIG_T(T, uint16_t);    \
+    else HARP_BIG_T(T, float);          \
+  } while (0)
   if (KT == 1) HARP_BIG(1);
   else if (KT == 2) HARP_BIG(2);
   else HARP_BIG(3);
 #undef HARP_BIG
+#undef HARP_BIG_T
   const size_t quads = (size_t)(d * b / 4);   // D is a multiple of 16
   hipLaunchKernelGGL(harp_grad_big_sum_kernel, dim3((unsigned)((quads + kBigSumThreads - 1) / kBigSumThreads)),
                      dim3(kBigSumThreads), 0, st, reinterpret_cast<const f4v *>(partial), (int)chunks, quads,

@@ -437,11 +437,11 @@ harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X,
                                    float *Gout, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st);
 harp_status_t launch_grad_sums(const GradSums &sums, hipStream_t st);
-// a stage of radix 9 .. 48 on the matrix cores, backward and its reduction (harp_grad_big.hip); X, G, Gout on 16-byte
-// boundaries with leading dimensions that are multiples of four
+// a stage of radix 9 .. 48 on the matrix cores, backward and its reduction (harp_grad_big.hip); X, Gout on boundaries of 16 bytes,
+// G on boundaries of four elements, leading dimensions that are multiples of four
 bool grad_big_stage(const harp_plan *plan, int t);
 size_t grad_big_partial_floats(const harp_plan *plan, int t, int64_t n);
-harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, const float *G, int64_t ldg, float *Gout,
+harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf, float *Gout,
                               int64_t n, float *partial, float *dK, hipStream_t st);
 int choose_pipe_rows(const harp_plan *plan, int64_t n, int64_t nchunk, int chunk);
 const HostProgram *select_program(const harp_plan *plan, Direction dir, int64_t n,

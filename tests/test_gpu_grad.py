@@ -274,25 +274,27 @@ def test_large_radix_on_the_matrix_cores(harp, d, radices, kind, counts):
     plan.destroy()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n", [1, 65, 130])
-def test_last_stage_of_large_radix_reads_gradient_rows_at_any_pitch(harp, n):
-    """float32 rows, a last stage of radix above 8 at a stride that is a multiple of 16: G is read
-    where it lies (pitch and start on 16 bytes) or from a copy (any other); both give the bits of a
+def test_last_stage_of_large_radix_reads_gradient_rows_at_any_pitch(harp, n, dtype):
+    """A last stage of radix above 8 at a stride that is a multiple of 16: G is read
+    where it lies (pitch and start on boundaries of four elements) or from a copy (any other); both give the bits of a
     contiguous G."""
     import torch
     d, radices = 1408, [2] * 4 + [8, 11]
     rng = np.random.default_rng(n)
     blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
     plan = harp.Plan(d, radices, blocks, signs)
-    X = to_device(rng.standard_normal((n, d)).astype(np.float32), "f32")
-    G = to_device(rng.standard_normal((n, d)).astype(np.float32), "f32")
+    Xh, Gh = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    if dtype == "bf16":
+        Xh, Gh = gi.round_to_bf16(Xh), gi.round_to_bf16(Gh)
+    X, G = to_device(Xh, dtype), to_device(Gh, dtype)
     dK0, dX0 = harp.harp_grad_blocks(plan, X, G)
-    ref, ref_dx = ho.grad_blocks(X.cpu().numpy().astype(np.float64), G.cpu().numpy().astype(np.float64),
-                                 d, radices, blocks, signs)
-    assert_dk_parity(dK0, ref, X.cpu().numpy(), G.cpu().numpy(), "contiguous")
-    assert_parity(to_host64(dX0), ref_dx, "f32", "dX")
+    ref, ref_dx = ho.grad_blocks(Xh.astype(np.float64), Gh.astype(np.float64), d, radices, blocks, signs)
+    assert_dk_parity(dK0, ref, Xh, Gh, "contiguous")
+    assert_parity(to_host64(dX0), ref_dx, dtype, "dX")
     for pad, off in ((4, 0), (4, 4), (3, 0), (4, 1)):
-        big = torch.zeros(n, d + pad + off, device="cuda")
+        big = torch.zeros(n, d + pad + off, device="cuda", dtype=G.dtype)
         view = big[:, off:off + d]
         view.copy_(G)
         dK, dX = harp.harp_grad_blocks(plan, X, view)
