@@ -1337,7 +1337,7 @@ harp_status_t harp::plan_create_impl(harp_plan **out, int64_t d, int32_t m, cons
     if (!blocks[t]) return HARP_ERR_INVALID_ARG;
   for (int t = 0; t < m; ++t)
     if (radices[t] > HARP_MAX_RADIX) return HARP_ERR_UNSUPPORTED;
-  if (d > (int64_t)1 << 24) return HARP_ERR_UNSUPPORTED;
+  if (d > kMaxDim) return HARP_ERR_UNSUPPORTED;
 
   harp_plan *plan = new (std::nothrow) harp_plan();
   if (!plan) return HARP_ERR_OOM;

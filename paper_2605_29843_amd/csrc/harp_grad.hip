@@ -809,23 +809,34 @@ struct GradSegment {
   int t0, k;
   bool pair;
 };
-static std::vector<GradSegment> grad_segments(const harp_plan *plan, int lead) {
+static std::vector<GradSegment> grad_segments(const std::vector<int32_t> &radices, int lead) {
   std::vector<GradSegment> seg;
-  const int m = plan->m;
+  const int m = (int)radices.size();
   if (lead > 0) seg.push_back(GradSegment{0, lead, false});
   int t = lead;
   while (t < m) {
-    int k = lead > 0 ? grad_pair_stages(plan, t) : 0;
+    int k = lead > 0 ? grad_pair_stages(radices, t) : 0;
     const bool pair = k > 0;
     if (!pair) {
       k = 1;
-      if (plan->radices[t] == 2)
-        while (k < 3 && t + k < m && plan->radices[t + k] == 2) ++k;
+      if (radices[t] == 2)
+        while (k < 3 && t + k < m && radices[t + k] == 2) ++k;
     }
     seg.push_back(GradSegment{t, k, pair});
     t += k;
   }
   return seg;
+}
+static std::vector<GradSegment> grad_segments(const harp_plan *plan, int lead) { return grad_segments(plan->radices, lead); }
+
+extern "C" int32_t harp_internal_grad_sides(int32_t m, const int32_t *radices, int32_t *room) {
+  const std::vector<int32_t> r(radices, radices + m);
+  const int lead = grad_seg_stages(r);
+  int sides = lead > 0 ? 2 : 0;
+  if (lead > 0)
+    for (const GradSegment &sg : grad_segments(r, lead)) sides += sg.pair ? 2 : 0;
+  *room = kGradMostSides;
+  return sides;
 }
 
 // Stages of radix above 8 take longer row chunks: blockIdx.z already supplies parallelism, and a

@@ -778,18 +778,21 @@ __global__ __launch_bounds__(kRedThreads) void harp_grad_pair_reduce_kernel(Grad
 }
 
 // Stages of one pass at stage t: one of radix up to 8, or as many radix-2 stages as follow, up to three.
-int pass_stages(const harp_plan *plan, int t) {
-  if (t >= plan->m || plan->radices[t] > 8) return 0;
-  if (plan->radices[t] != 2) return 1;
+int pass_stages(const std::vector<int32_t> &radices, int t) {
+  const int m = (int)radices.size();
+  if (t >= m || radices[t] > 8) return 0;
+  if (radices[t] != 2) return 1;
   int k = 1;
-  while (k < 3 && t + k < plan->m && plan->radices[t + k] == 2) ++k;
+  while (k < 3 && t + k < m && radices[t + k] == 2) ++k;
   return k;
 }
-int pass_size(const harp_plan *plan, int t, int k) {
+int pass_size(const std::vector<int32_t> &radices, int t, int k) {
   int B = 1;
-  for (int i = 0; i < k; ++i) B *= plan->radices[t + i];
+  for (int i = 0; i < k; ++i) B *= radices[t + i];
   return B;
 }
+int pass_stages(const harp_plan *plan, int t) { return pass_stages(plan->radices, t); }
+int pass_size(const harp_plan *plan, int t, int k) { return pass_size(plan->radices, t, k); }
 PassBlocks pass_blocks(const harp_plan *plan, int t, int k) {
   PassBlocks pb;
   for (int i = 0; i < 3; ++i) pb.blocks[i] = plan->col[DIR_FWD][t + std::min(i, k - 1)].blocks;
@@ -819,6 +822,7 @@ int64_t pair_slots(const harp_plan *plan) { return num_cu(plan); }
 int64_t lead_slots(const harp_plan *plan) { return 2 * (int64_t)num_cu(plan); }
 
 // the sums of a launch, passes of ka and kb stages from stage t on, for the reduction at the end of the call
+// (callers have seen to it that there is room for two more: sums_room)
 void add_sums(const harp_plan *plan, int t, int ka, int kb, const float *partial_a, const float *partial_b, int64_t chunks,
               float *const *dK, GradSums &sums) {
   for (int i = 0; i < 2; ++i) {
@@ -835,14 +839,16 @@ void add_sums(const harp_plan *plan, int t, int ka, int kb, const float *partial
   }
 }
 
+bool sums_room(const GradSums &sums) { return sums.nsides + 2 <= kGradMostSides; }
+
 }  // namespace
 
 // Stages of the pair of passes that starts at stage t, or 0: eight coordinates first, then 2 .. 8, at a
 // stride of 16 neighbouring groups.
-int grad_pair_stages(const harp_plan *plan, int t) {
-  const int ka = pass_stages(plan, t);
-  if (ka == 0 || pass_size(plan, t, ka) != 8 || plan->strides[t] % 16 != 0) return 0;
-  const int kb = pass_stages(plan, t + ka);
+int grad_pair_stages(const std::vector<int32_t> &radices, int t) {
+  const int ka = pass_stages(radices, t);
+  if (ka == 0 || pass_size(radices, t, ka) != 8 || pass_size(radices, 0, t) % 16 != 0) return 0;
+  const int kb = pass_stages(radices, t + ka);
   return kb == 0 ? 0 : ka + kb;
 }
 
@@ -890,6 +896,7 @@ harp_status_t launch_grad_pair_fwd(const harp_plan *plan, int t, const float *X,
 harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf,
                                    float *Gout, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st) {
+  if (!sums_room(sums)) return HARP_ERR_UNSUPPORTED;
   const int ka = pass_stages(plan, t), kb = pass_stages(plan, t + ka), B = pass_size(plan, t + ka, kb);
   const int64_t d = plan->d, tiles = d / (128 * B);
   const int rows = chunk_rows(n, tiles, pair_slots(plan), 4 * pair_sets(B) * pair_times(B, bf ? 2 : 4), kPairLeast, kPairRows);
@@ -917,6 +924,7 @@ static bool lead_vec(const void *p, int64_t ld, bool bf) { return ld % (bf ? 8 :
 harp_status_t launch_grad_lead_bwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, const float *G,
                                    void *dX, int64_t lddx, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st) {
+  if (!sums_room(sums)) return HARP_ERR_UNSUPPORTED;
   const int64_t d = plan->d, tiles = (d + 127) / 128;
   const int rows = chunk_rows(n, tiles, lead_slots(plan), 4 * kLeadWaves, kLeadLeast, kLeadRows);
   const int64_t chunks = (n + rows - 1) / rows;

@@ -221,12 +221,15 @@ SegBlocks seg_blocks(const harp_plan *plan, int nst) {
 // 52 / 59 / 68 / 86 us at 11008 (8, 8, 4, 43).  At 64 rows and up it is 1.15 - 3.3 times as fast from d = 128
 // (262144 rows: 2811 -> 1220 us radix 2, 3644 -> 1213 us radix 8) to 28672 (64 rows: 126 -> 105, 166 -> 107 us).
 int grad_seg_stages(const harp_plan *plan, int64_t n) {
-  if (!plan->orthogonal || n < 64 || plan->d <= kSegP || plan->d % kSegP) return 0;
+  if (!plan->orthogonal || n < 64) return 0;
   if (n > (int64_t)65535 * 128) return 0;   // (beyond that the grids and the counts of chunks have not been tried)
-  const int b = plan->radices[0], k = b == 2 ? 6 : (b == 8 ? 2 : 0);
-  if (k == 0 || plan->m <= k) return 0;
+  return grad_seg_stages(plan->radices);
+}
+int grad_seg_stages(const std::vector<int32_t> &radices) {
+  const int b = radices[0], k = b == 2 ? 6 : (b == 8 ? 2 : 0);
+  if (k == 0 || (int)radices.size() <= k) return 0;   // (the first k alone: 64 coordinates and nothing behind them)
   for (int t = 1; t < k; ++t)
-    if (plan->radices[t] != b) return 0;
+    if (radices[t] != b) return 0;
   return k;
 }
 

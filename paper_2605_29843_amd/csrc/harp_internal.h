@@ -13,6 +13,8 @@
 
 namespace harp {
 
+constexpr int64_t kMaxDim = (int64_t)1 << 24;   // of a plan
+
 // A *pass* is a run of consecutive stages that one thread executes on a register-resident
 // sub-tensor of the row: the P = prod(radices of the run) coordinates
 //     base + j * S,  j = 0..P-1,   base = hi * P * S + lo,   q = hi * S + lo  (q < d / P)
@@ -408,6 +410,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
                           int64_t lddx, void *ws, hipStream_t st);
 // leading segment of 64 coordinates of the gradient path: rule and forward kernel (harp_grad_seg.hip)
 int grad_seg_stages(const harp_plan *plan, int64_t n);
+int grad_seg_stages(const std::vector<int32_t> &radices);   // of orthogonal blocks and 64 rows or more
 harp_status_t launch_grad_seg_fwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, float *Y,
                                   int64_t n, hipStream_t st);
 // its backward kernel, and pairs of passes at larger strides (harp_grad_pair.hip).  partial: the sums of a
@@ -416,6 +419,11 @@ struct PassBlocks {   // dense image of a pass's stages ([c][b][b] each)
   const float *blocks[3];
   int nst;   // radix-2 stages taken together; 0: one stage as it is
 };
+// Two sums for the first 64 coordinates, two for each pair behind them; a pair has at least 16 coordinates (8, then 2 .. 8).
+constexpr int grad_most_sides(int64_t d) { return d < 16 ? 2 : 2 + grad_most_sides(d / 16); }
+constexpr int kGradMostSides = grad_most_sides(kMaxDim / 64);
+// Sums of a schedule's calls, and how many there is room for (for the tests: the choice of segments needs no device).
+extern "C" int32_t harp_internal_grad_sides(int32_t m, const int32_t *radices, int32_t *room);
 struct GradSums {
   struct Side {
     const float *partial;
@@ -423,14 +431,15 @@ struct GradSums {
     float *dK[3];
     const int8_t *signs;            // the pass's first stage is stage 0
     int B, s, blocks, nchunks;      // size, stride and blocks of the pass, chunks of rows
-  } side[8];                        // two for 64 coordinates, or for 16 or more behind them (d <= 2^24)
+  } side[kGradMostSides];
   int nsides;
 };
+static_assert(kGradMostSides == 10 && sizeof(GradSums) <= 1024, "a kernel argument");
 size_t grad_lead_partial_bytes(const harp_plan *plan, int64_t n);
 harp_status_t launch_grad_lead_bwd(const harp_plan *plan, int nst, const void *X, int64_t ldx, bool bf, const float *G,
                                    void *dX, int64_t lddx, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st);
-int grad_pair_stages(const harp_plan *plan, int t);
+int grad_pair_stages(const std::vector<int32_t> &radices, int t);
 size_t grad_pair_partial_bytes(const harp_plan *plan, int t, int64_t n);
 harp_status_t launch_grad_pair_fwd(const harp_plan *plan, int t, const float *X, float *Y, int64_t n, hipStream_t st);
 harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf,

@@ -156,7 +156,7 @@ harp_status_t harp_plan_create_from_theta(harp_plan_t **out, int64_t d, int32_t 
   if (flags & HARP_BLOCKS_ON_DEVICE) return HARP_ERR_INVALID_ARG;   // Theta is read on the host
   harp_status_t st = check_schedule(d, m, radices);
   if (st != HARP_OK) return st;
-  if (d > (int64_t)1 << 24) return HARP_ERR_UNSUPPORTED;
+  if (d > harp::kMaxDim) return HARP_ERR_UNSUPPORTED;
   try {
     std::vector<std::vector<float>> store((size_t)m);
     std::vector<float *> outp((size_t)m);
@@ -249,7 +249,7 @@ harp_status_t harp_plan_create_from_theta_int8(harp_plan_t **out, int64_t d, int
   flags &= ~(uint32_t)HARP_THETA_IN_KERNEL;
   harp_status_t st = check_schedule(d, m, radices);
   if (st != HARP_OK) return st;
-  if (d > (int64_t)1 << 24) return HARP_ERR_UNSUPPORTED;
+  if (d > harp::kMaxDim) return HARP_ERR_UNSUPPORTED;
   try {
     std::vector<std::vector<float>> store((size_t)m);
     std::vector<float *> outp((size_t)m);
@@ -317,7 +317,7 @@ harp_status_t harp_plan_create_kronecker(harp_plan_t **out, int32_t K, const flo
   if (flags & ~(uint32_t)(HARP_VALIDATE_ORTHO | HARP_F32_INTERMEDIATES)) return HARP_ERR_INVALID_ARG;
   if (K < 2 || n2 < 2 || m2 < 1) return HARP_ERR_INVALID_ARG;
   if (K > HARP_MAX_RADIX || m2 + 1 > HARP_MAX_STAGES) return HARP_ERR_UNSUPPORTED;
-  if (n2 > ((int64_t)1 << 24) / K) return HARP_ERR_UNSUPPORTED;
+  if (n2 > harp::kMaxDim / K) return HARP_ERR_UNSUPPORTED;
   harp_status_t st = check_schedule(n2, m2, radices2);
   if (st != HARP_OK) return st;
   try {

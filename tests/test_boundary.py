@@ -305,3 +305,30 @@ def test_kronecker_blocks_expand_to_the_kronecker_product():
         harp.harp_kronecker_blocks(np.array([[1, 0.5], [1, -1]], np.float32), n2, radices2, blocks2)
     assert e.value.status == harp.HARP_ERR_INVALID_ARG
 
+
+
+def test_sums_of_a_gradient_call_have_room():
+    """The gradient's launches leave two sums for the first 64 coordinates and two for each pair of passes behind
+    them, in an array of fixed size: every schedule up to the largest dimension (2^24) has to fit."""
+    def sides(radices):
+        room = C.c_int32()
+        return harp.lib.harp_internal_grad_sides(len(radices), (C.c_int32 * len(radices))(*radices), C.byref(room)), room.value
+
+    assert sides([2] * 12) == (4, 10) and sides([8, 8, 4, 43]) == (2, 10) and sides([4, 4, 9]) == (0, 10)
+    most = 0
+    for radices in ([8, 8] + [8, 2] * 4, [2] * 6 + [8, 2] * 4, [2] * 9 + [2, 8] * 3, [8, 8, 8, 2, 8, 3, 8, 2, 8, 3],
+                    [8, 8] + [2, 2, 2, 3] * 3, [8] * 8, [2] * 24):
+        n, room = sides(radices)
+        assert int(np.prod(radices)) <= 1 << 24 and n <= room, radices
+        most = max(most, n)
+    assert most == 10
+    rng = np.random.default_rng(1)
+    for _ in range(2000):   # and anything between
+        radices = [8, 8] if rng.random() < 0.5 else [2] * 6
+        while True:
+            b = int(rng.choice([2, 2, 3, 4, 5, 8, 8, 8, 11]))
+            if int(np.prod(radices)) * b > 1 << 24:
+                break
+            radices.append(b)
+        n, room = sides(radices)
+        assert n <= room, radices

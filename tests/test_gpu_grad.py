@@ -408,3 +408,26 @@ def test_dX_may_be_X_or_G(harp, d, radices, n, dtype):
         assert st == 0
         assert torch.equal(out, dX0) and all(torch.equal(a, b) for a, b in zip(dK, dK0)), over
     plan.destroy()
+
+
+def test_four_pairs_of_passes_behind_the_leading_segment(harp):
+    """2^22 coordinates, the smallest row with four pairs (ten sums at the end of the call): 64 rows at once against
+    the same rows 32 at a time, which go stage by stage, block gradients added."""
+    import torch
+    radices, n = [8, 8] + [8, 2] * 4, 64
+    d = int(np.prod(radices))
+    rng = np.random.default_rng(4)
+    blocks = [np.tile(gi.qr_blocks(512, b, rng), (d // b // 512, 1, 1)) for b in radices]
+    plan = harp.Plan(d, radices, blocks, gi.make_signs(d, rng))
+    say("grad", radices, n)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    X = torch.randn(n, d, device="cuda", generator=gen)
+    G = torch.randn(n, d, device="cuda", generator=gen)
+    dK, dX = harp.harp_grad_blocks(plan, X, G)
+    halves = [harp.harp_grad_blocks(plan, X[r:r + 32], G[r:r + 32]) for r in (0, 32)]
+    # float32 both ways, sums of up to 64 terms after up to 10 stages: about 3e-7 of the norm each
+    rel = lambda a, b: float((a.double() - b.double()).norm() / b.double().norm())
+    assert rel(dX, torch.cat([h[1] for h in halves])) < 2e-6
+    for t in range(len(radices)):
+        assert rel(dK[t], halves[0][0][t].double() + halves[1][0][t].double()) < 2e-6, t
+    plan.destroy()
