@@ -754,18 +754,18 @@ float *scratch_alloc(size_t bytes) {
   return nullptr;
 }
 
-// The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= cap = one full
-// slab); `hold` is kept until the call's launches are queued.  Small ones lie in a buffer of the plan's own (8 MB), larger ones
+// The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= most, the call's rows or one
+// full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.  Small ones lie in a buffer of the plan's own (8 MB), larger ones
 // in the stream's shared one: its first use allocates room for three such calls, one that needs more then the most that
 // any plan does.  Nothing is freed and the stream is never waited for.
 // A captured call, too, gets a buffer of the plan's own, kept until the plan is destroyed: a graph holds its address and
 // may be replayed on another stream.  It is allocated inside the capture (this thread's capture mode is relaxed
 // meanwhile), and only if the plan has run on the stream before with as large a batch: `seen` notes, per
-// stream, how much that is taken to be.  The same buffer serves streams that have no shared one: each thread's own default
+// stream, the largest `most` (slabs of one size take less than that: a call of a slab and a little more, two of about half).  The same buffer serves streams that have no shared one: each thread's own default
 // stream, which goes by one handle in all threads, and streams beyond the first eight.
 // Per-call stream-ordered allocation was measured first: it added two stream operations to
 // every call, 29 us per call on a 2-kernel program against 11 us of kernel time.
-harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t bytes, size_t cap,
+harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t bytes, size_t most, size_t cap,
                            std::unique_lock<std::mutex> &hold, float **out) {
   SharedScratch *shared = nullptr;
   {
@@ -784,9 +784,9 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
       cs = hipStreamCaptureStatusNone;   // the default stream beside a capture: if it may not be used, the launches say so
     }
     const bool capturing = cs != hipStreamCaptureStatusNone;
-    if (!slot || slot->seen < bytes) {
+    if (!slot || slot->seen < most) {
       if (capturing) return HARP_ERR_UNSUPPORTED;
-      const size_t seen = std::max(bytes, slot ? cap : std::min(cap, kOwnScratch));
+      const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
       if (!slot) plan->scratch.push_back(harp_plan::Scratch{stream, nullptr, 0, 0});
       slot = slot ? slot : &plan->scratch.back();
       slot->seen = seen;
@@ -932,7 +932,7 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
                               hp.z16 ? (size_t)slab_rows_cap_z16(d) * z16_ld(d) * 2 : (size_t)0);
   float *Z = nullptr;
   std::unique_lock<std::mutex> hold;
-  harp_status_t zst = plan_scratch(plan, stream, (size_t)slab * row_bytes, cap, hold, &Z);
+  harp_status_t zst = plan_scratch(plan, stream, (size_t)slab * row_bytes, (size_t)std::min(n, slab_cap) * row_bytes, cap, hold, &Z);
   if (zst != HARP_OK) return zst;
   return run_split(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n, Z, slab, stream);
 }

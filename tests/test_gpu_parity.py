@@ -771,6 +771,43 @@ def test_graph_capture_and_replay(harp, d, radices, n):
     plan.destroy()
 
 
+def test_a_full_slab_is_captured_after_a_call_of_more_rows(harp):
+    """The eager call may go in slabs of one size, each smaller than a full one; a captured call of as many rows as
+    one slab holds, or fewer, is accepted after it all the same, and one of more rows than the plan has run with is not."""
+    import torch
+    d, radices = 14336, [2] * 11 + [7]
+    full = (128 << 20) // (4 * d) // 256 * 256   # rows of one float32 slab
+    rng = np.random.default_rng(40)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X = torch.randn(full + 1000, d, device="cuda")
+    ref = harp.harp_apply(plan, X)
+    side, few = torch.cuda.Stream(), torch.cuda.Stream()
+    Y = torch.zeros_like(X)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(few):
+        harp.harp_apply(plan, X[:900], Y[:900], few)
+        torch.cuda.synchronize()
+        with pytest.raises(harp.HarpError) as e:
+            with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=few):
+                harp.harp_apply(plan, X[:1800], Y[:1800], few)
+        assert e.value.status == harp.HARP_ERR_UNSUPPORTED
+    with torch.cuda.stream(side):
+        harp.harp_apply(plan, X, Y, side)
+        torch.cuda.synchronize()
+        for n in (full, 1800):
+            say("captured after more rows", n)
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=side):
+                harp.harp_apply(plan, X[:n], Y[:n], side)
+            for _ in range(3):
+                Y.zero_()
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(Y[:n], ref[:n]) and bool((Y[n:] == 0).all())
+    plan.destroy()
+
+
 def test_plans_share_the_intermediate_of_a_stream(harp):
     """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
     stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
