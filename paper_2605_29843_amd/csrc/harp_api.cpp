@@ -684,7 +684,7 @@ int64_t slab_rows_cap_z16(int64_t d) {
 // memory-side cache.  Three plans in turn, bf16, us a call: 2048 x 11008 radix 2 75 -> 60, 4096 x 28672 transposed 211 -> 198,
 // 3000 x 8192 radix 8 72 -> 64.  Calls take turns in three places where these fit: rewriting at once what the
 // last call's kernels have just read costs more than it saves (one place, 1001 x 5120 float32: 19.9 -> 20.9 us).
-// Below 8 MB nothing is gained, and the calls are short enough for the query of the capture to show (9.2 -> 9.5 us a call).
+// Below 8 MB nothing is gained, and the calls are short enough for the lock to show.
 // Bounded (eight streams a device; further ones get buffers of the plan's own) and given back when the device's
 // last plan is destroyed.
 struct SharedScratch {
@@ -747,22 +747,20 @@ SharedScratch *shared_entry(int dev, hipStream_t stream) {
   return g_shared.back().get();
 }
 
-float *scratch_alloc(size_t bytes) {
-  float *p = nullptr;
-  if (hipMalloc((void **)&p, bytes) == hipSuccess) return p;
-  (void)hipGetLastError();
-  return nullptr;
-}
-
 // The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= most, the call's rows or one
-// full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.  Small ones lie in a buffer of the plan's own (8 MB), larger ones
+// full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.
+// Small ones lie in a buffer of the plan's own (8 MB), larger ones
 // in the stream's shared one: its first use allocates room for three such calls, one that needs more then the most that
 // any plan does.  Nothing is freed and the stream is never waited for.
-// A captured call, too, gets a buffer of the plan's own, kept until the plan is destroyed: a graph holds its address and
-// may be replayed on another stream.  It is allocated inside the capture (this thread's capture mode is relaxed
-// meanwhile), and only if the plan has run on the stream before with as large a batch: `seen` notes, per
-// stream, the largest `most` (slabs of one size take less than that: a call of a slab and a little more, two of about half).  The same buffer serves streams that have no shared one: each thread's own default
-// stream, which goes by one handle in all threads, and streams beyond the first eight.
+// Captured calls have a buffer of their own, kept until the plan is destroyed: a graph holds its address and
+// may be replayed on another stream while the plan runs on this one.  (All of a stream's captured calls use that one:
+// a program that captures again and again must not collect buffers.)  It is allocated inside the capture (this thread's
+// capture mode is relaxed meanwhile), and only if the plan has run on the stream before with as large a batch: `seen`
+// notes, per stream, the largest `most` (slabs of one size take less than that: a call of a slab and a little more, two
+// of about half).  Eager calls of any size have a buffer of the plan's own on streams without a shared one: each
+// thread's own default stream, which goes by one handle in all threads, and streams beyond the first eight.
+// The default stream cannot be captured, so a small call there does not ask (on another stream, 14336 radix 2, one row, bound by
+// the host: 7.22 -> 7.35 us a call; where the kernels take longer than the call, nothing).
 // Per-call stream-ordered allocation was measured first: it added two stream operations to
 // every call, 29 us per call on a 2-kernel program against 11 us of kernel time.
 harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t bytes, size_t most, size_t cap,
@@ -773,8 +771,8 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     harp_plan::Scratch *slot = nullptr;
     for (auto &sc : plan->scratch)
       if (sc.stream == stream) slot = &sc;
-    if (slot && bytes <= kOwnScratch && slot->bytes >= bytes) {
-      *out = slot->ptr;
+    if (slot && stream == nullptr && bytes <= kOwnScratch && slot->eager.bytes >= bytes) {
+      *out = slot->eager.ptr;
       return HARP_OK;
     }
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -787,13 +785,14 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     if (!slot || slot->seen < most) {
       if (capturing) return HARP_ERR_UNSUPPORTED;
       const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
-      if (!slot) plan->scratch.push_back(harp_plan::Scratch{stream, nullptr, 0, 0});
+      if (!slot) plan->scratch.push_back(harp_plan::Scratch{stream, {}, {}, 0});
       slot = slot ? slot : &plan->scratch.back();
       slot->seen = seen;
     }
     if (bytes > kOwnScratch && !capturing && stream != hipStreamPerThread) shared = shared_entry(plan->device, stream);
     if (!shared) {
-      if (slot->bytes < bytes) {
+      harp_plan::Buffer &own = capturing ? slot->captured : slot->eager;
+      if (own.bytes < bytes) {
         const size_t want = bytes > kOwnScratch ? slot->seen : std::max(bytes, std::min(cap, kOwnScratch));
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
@@ -805,11 +804,11 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
         if (!ok) (void)hipGetLastError();
         if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (!ok) return HARP_ERR_OOM;
-        if (slot->ptr) plan->retired.push_back(slot->ptr);   // queued launches and graphs still hold its address
-        slot->ptr = p;
-        slot->bytes = want;
+        if (own.ptr) plan->retired.push_back(own.ptr);   // queued launches and graphs still hold its address
+        own.ptr = p;
+        own.bytes = want;
       }
-      *out = slot->ptr;
+      *out = own.ptr;
       return HARP_OK;
     }
   }
@@ -1678,7 +1677,8 @@ harp_status_t harp_plan_destroy(harp_plan_t *plan) {
   for (void *p : plan->dev_allocs)
     if (p && hipFree(p) != hipSuccess) st = HARP_ERR_DEVICE;
   for (auto &sc : plan->scratch)
-    if (sc.ptr && hipFree(sc.ptr) != hipSuccess) st = HARP_ERR_DEVICE;
+    for (float *p : {sc.eager.ptr, sc.captured.ptr})
+      if (p && hipFree(p) != hipSuccess) st = HARP_ERR_DEVICE;
   for (void *p : plan->retired)
     if (p && hipFree(p) != hipSuccess) st = HARP_ERR_DEVICE;
   if (plan->counted) {

@@ -243,16 +243,20 @@ struct harp_plan {
   int device = 0;
   int lds_bytes = 0;   // usable LDS per workgroup
   int num_cu = 0;
-  // Per stream the plan has run on in two launches or more: a buffer for small intermediates and captured calls, and
-  // the size up to which a captured call may ask for one.  Nothing is freed
+  bool counted = false;   // among its device's plans, which keep the shared buffers
+  // Per stream the plan has run on in two launches or more: a buffer for small intermediates, one for captured calls, and
+  // the size up to which a captured call may ask for it.  Nothing is freed
   // before the plan is destroyed: a buffer that a later, larger call outgrows moves to
   // `retired`, because launches already queued and HIP graphs captured earlier still hold
   // its address.
-  bool counted = false;   // among its device's plans, which keep the shared buffers
+  struct Buffer {
+    float *ptr = nullptr;
+    size_t bytes = 0;
+  };
   struct Scratch {
     hipStream_t stream;
-    float *ptr;      // null: none yet
-    size_t bytes, seen;
+    Buffer eager, captured;
+    size_t seen;
   };
   mutable std::mutex scratch_mu;
   mutable std::vector<Scratch> scratch;

@@ -808,6 +808,40 @@ def test_a_full_slab_is_captured_after_a_call_of_more_rows(harp):
     plan.destroy()
 
 
+@pytest.mark.parametrize("n", [24, 600])
+def test_a_graph_runs_beside_eager_calls_of_its_plan(harp, n):
+    """A graph captured on one stream and replayed on another while the plan runs eagerly on the first, with other
+    rows: both give the bits they give alone (24 rows: an intermediate below 8 MB, the plan's own; 600: above)."""
+    import torch
+    d, radices = 14336, [2] * 11 + [7]
+    rng = np.random.default_rng(n)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    A, B = torch.randn(n, d, device="cuda"), torch.randn(n, d, device="cuda")
+    YA, YB = torch.zeros_like(A), torch.zeros_like(B)
+    refA, refB = harp.harp_apply(plan, A), harp.harp_apply(plan, B)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        harp.harp_apply(plan, A, YA, side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            for _ in range(8):
+                harp.harp_apply(plan, A, YA, side)
+    say("graph beside eager calls", n, plan.kernel_name(n))
+    for _ in range(5):
+        YA.zero_(), YB.zero_()
+        torch.cuda.synchronize()
+        for _ in range(10):
+            with torch.cuda.stream(other):
+                g.replay()
+            for _ in range(8):
+                harp.harp_apply(plan, B, YB, side)
+        torch.cuda.synchronize()
+        assert torch.equal(YA, refA) and torch.equal(YB, refB)
+    plan.destroy()
+
+
 def test_plans_share_the_intermediate_of_a_stream(harp):
     """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
     stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
