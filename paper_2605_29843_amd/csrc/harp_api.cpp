@@ -684,7 +684,7 @@ int64_t slab_rows_cap_z16(int64_t d) {
 // memory-side cache.  Three plans in turn, bf16, us a call: 2048 x 11008 radix 2 75 -> 60, 4096 x 28672 transposed 211 -> 198,
 // 3000 x 8192 radix 8 72 -> 64.  Calls take turns in three places where these fit: rewriting at once what the
 // last call's kernels have just read costs more than it saves (one place, 1001 x 5120 float32: 19.9 -> 20.9 us).
-// Below 8 MB nothing is gained, and the calls are short enough for the lock to show.
+// Below 8 MB nothing is gained.
 // Bounded (eight streams a device; further ones get buffers of the plan's own) and given back when the device's
 // last plan is destroyed.
 struct SharedScratch {
@@ -766,6 +766,7 @@ SharedScratch *shared_entry(int dev, hipStream_t stream) {
 harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t bytes, size_t most, size_t cap,
                            std::unique_lock<std::mutex> &hold, float **out) {
   SharedScratch *shared = nullptr;
+  bool beside = false;
   {
     std::lock_guard<std::mutex> lock(plan->scratch_mu);
     harp_plan::Scratch *slot = nullptr;
@@ -775,11 +776,13 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
       *out = slot->eager.ptr;
       return HARP_OK;
     }
+    // The default stream beside another stream's capture: whether it may be used, the launches say; nothing is allocated.
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+    beside = hipStreamIsCapturing(stream, &cs) != hipSuccess;
+    if (beside) {
       (void)hipGetLastError();
-      if (stream != nullptr) return HARP_ERR_DEVICE;
-      cs = hipStreamCaptureStatusNone;   // the default stream beside a capture: if it may not be used, the launches say so
+      if (stream != nullptr || !slot || slot->seen < most) return HARP_ERR_DEVICE;
+      cs = hipStreamCaptureStatusNone;
     }
     const bool capturing = cs != hipStreamCaptureStatusNone;
     if (!slot || slot->seen < most) {
@@ -793,6 +796,7 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     if (!shared) {
       harp_plan::Buffer &own = capturing ? slot->captured : slot->eager;
       if (own.bytes < bytes) {
+        if (beside) return HARP_ERR_DEVICE;
         const size_t want = bytes > kOwnScratch ? slot->seen : std::max(bytes, std::min(cap, kOwnScratch));
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
@@ -815,6 +819,7 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
   hold = std::unique_lock<std::mutex>(shared->mu);
   const size_t place = (bytes + 4095) / 4096 * 4096;
   if (shared->bytes < bytes) {
+    if (beside) return HARP_ERR_DEVICE;
     const size_t want = std::max(bytes, shared->ptr ? kSharedMost : std::min(kSharedMost, kSharedTurns * place));
     float *p = nullptr;
     if (hipMalloc((void **)&p, want) != hipSuccess) {

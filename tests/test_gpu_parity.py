@@ -842,6 +842,35 @@ def test_a_graph_runs_beside_eager_calls_of_its_plan(harp, n):
     plan.destroy()
 
 
+@pytest.mark.parametrize("n", [24, 600])
+def test_default_stream_beside_a_capture(harp, n):
+    """While a blocking stream is being captured the default stream may not be used: a plan's first call there is a
+    device error before anything is allocated, and the plan works once the capture is over."""
+    import ctypes
+    import torch
+    d, radices = 14336, [2] * 11 + [7]
+    rng = np.random.default_rng(n)
+    X = torch.randn(n, d, device="cuda")
+    Y = torch.zeros_like(X)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    torch.cuda.synchronize()
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)   # the runtime that is loaded
+    stream, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(stream)) == 0
+    say("default stream beside a capture", n)
+    assert hip.hipStreamBeginCapture(stream, 0) == 0
+    status = harp.lib.harp_apply(plan.handle, X.data_ptr(), d, Y.data_ptr(), d, n, harp.HARP_F32, None)
+    hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+    if graph.value:
+        hip.hipGraphDestroy(graph)
+    hip.hipGetLastError()
+    assert hip.hipStreamDestroy(stream) == 0
+    assert status == harp.HARP_ERR_DEVICE
+    assert torch.equal(harp.harp_apply(plan, X), harp.harp_apply(plan, X)) and bool((Y == 0).all())
+    plan.destroy()
+
+
 def test_plans_share_the_intermediate_of_a_stream(harp):
     """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
     stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
