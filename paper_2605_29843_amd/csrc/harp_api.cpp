@@ -747,6 +747,29 @@ SharedScratch *shared_entry(int dev, hipStream_t stream) {
   return g_shared.back().get();
 }
 
+// The plan runs `most` bytes of rows on `stream`, outside a capture (scratch_mu is held; slot: the stream's, if it has one).
+harp_plan::Scratch *scratch_seen(const harp_plan_t *plan, hipStream_t stream, harp_plan::Scratch *slot, size_t most, size_t cap) {
+  const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
+  if (!slot) {
+    plan->scratch.push_back(harp_plan::Scratch{stream, {}, {}, 0});
+    slot = &plan->scratch.back();
+  }
+  slot->seen = seen;
+  return slot;
+}
+// The same for a call that goes without an intermediate where another of its size would not (a transposed call in
+// place takes two launches, one out of place one): a captured call is then accepted after either.
+void scratch_not_needed(const harp_plan_t *plan, hipStream_t stream, size_t most, size_t cap) {
+  std::lock_guard<std::mutex> lock(plan->scratch_mu);
+  harp_plan::Scratch *slot = nullptr;
+  for (auto &sc : plan->scratch)
+    if (sc.stream == stream) slot = &sc;
+  if (slot && slot->seen >= most) return;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+  else if (cs == hipStreamCaptureStatusNone) scratch_seen(plan, stream, slot, most, cap);
+}
+
 // The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= most, the call's rows or one
 // full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.
 // Small ones lie in a buffer of the plan's own (8 MB), larger ones
@@ -787,10 +810,7 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     const bool capturing = cs != hipStreamCaptureStatusNone;
     if (!slot || slot->seen < most) {
       if (capturing) return HARP_ERR_UNSUPPORTED;
-      const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
-      if (!slot) plan->scratch.push_back(harp_plan::Scratch{stream, {}, {}, 0});
-      slot = slot ? slot : &plan->scratch.back();
-      slot->seen = seen;
+      slot = scratch_seen(plan, stream, slot, most, cap);
     }
     if (bytes > kOwnScratch && !capturing && stream != hipStreamPerThread) shared = shared_entry(plan->device, stream);
     if (!shared) {
@@ -922,9 +942,12 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
     return launch_dpp_top_kernel(plan, hp.dpp, X, ldx, Y, ldy, n,
                                  choose_pipe_rows(plan, n, plan->d / hp.chunk, hp.chunk), stream);
   // the same above a chain of radices 8, 8, 8, 3 .. 8
-  if (chain_top_supported(plan, hp, X, ldx, dt_in, Y, ldy, dt_out))
-    return launch_chain_top(plan, hp, X, ldx, Y, ldy, dt_in, n, stream);
   const int64_t d = plan->d;
+  if (chain_top_supported(plan, hp, X, ldx, dt_in, Y, ldy, dt_out)) {
+    const int64_t full = slab_rows_cap(d);
+    scratch_not_needed(plan, stream, (size_t)std::min(n, full) * d * 4, (size_t)full * d * 4);
+    return launch_chain_top(plan, hp, X, ldx, Y, ldy, dt_in, n, stream);
+  }
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);
   // slabs of one size: the last one would otherwise be a launch with little to do

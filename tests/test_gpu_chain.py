@@ -149,3 +149,30 @@ def test_chain_takes_the_stage_above_along(r4, top, dtype):
         assert_parity(to_host64(got)[rows], ho.apply_transpose_staged(X[rows], d, radices, blocks, signs), dtype,
                       f"transposed n={n}", mag=mag)
     plan.destroy()
+
+
+def test_in_place_call_is_captured_after_one_out_of_place():
+    """Out of place a transposed call with a stage above the chain needs no intermediate; in place it does.  Running the
+    plan once either way is enough for a captured call in place."""
+    import torch
+    from paper_2605_29843_amd import harp
+    d, radices, n = 8192, [8, 8, 8, 8, 2], 70
+    rng = np.random.default_rng(9)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X = torch.randn(n, d, device="cuda")
+    Y, Z = torch.zeros_like(X), X.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        harp.harp_apply_transpose(plan, X, Y, side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            harp.harp_apply_transpose(plan, Z, Z, side)
+    for _ in range(3):
+        Z.copy_(X)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Z, Y)
+    plan.destroy()
