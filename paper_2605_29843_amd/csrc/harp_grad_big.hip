@@ -182,8 +182,9 @@ __global__ __launch_bounds__(kBigThreads, 2) void harp_grad_big_bwd_kernel(
 
 // dK = the chunks' sums in ascending order within each eight, then the eights in ascending order.
 constexpr int kBigSumThreads = 256;
+// (dK is the caller's: four stores where it is not on a boundary of 16 bytes.)
 __global__ __launch_bounds__(kBigSumThreads) void harp_grad_big_sum_kernel(const f4v *__restrict__ partial, int nchunks,
-                                                                           size_t total, f4v *__restrict__ dK) {
+                                                                           size_t total, int aligned, float *__restrict__ dK) {
   const size_t e = (size_t)blockIdx.x * kBigSumThreads + threadIdx.x;
   if (e >= total) return;
   f4v s = {0.f, 0.f, 0.f, 0.f};
@@ -197,7 +198,12 @@ __global__ __launch_bounds__(kBigSumThreads) void harp_grad_big_sum_kernel(const
       if (k + u < nchunks) part += v[u];
     s += part;
   }
-  dK[e] = s;
+  if (aligned) {
+    *reinterpret_cast<f4v *>(dK + 4 * e) = s;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dK[4 * e + i] = s[i];
+  }
 }
 
 // Rows of a workgroup: one workgroup per compute unit, in whole steps, 128 rows at most.
@@ -250,7 +256,7 @@ harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, cons
   const size_t quads = (size_t)(d * b / 4);   // D is a multiple of 16
   hipLaunchKernelGGL(harp_grad_big_sum_kernel, dim3((unsigned)((quads + kBigSumThreads - 1) / kBigSumThreads)),
                      dim3(kBigSumThreads), 0, st, reinterpret_cast<const f4v *>(partial), (int)chunks, quads,
-                     reinterpret_cast<f4v *>(dK));
+                     (uintptr_t)dK % 16 == 0 ? 1 : 0, dK);
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 

@@ -379,6 +379,38 @@ def test_bits_do_not_depend_on_where_the_matrices_lie(harp, d, radices, n, dtype
     plan.destroy()
 
 
+# One stage of each way in which block gradients are written: the matrix cores' (9, 16 with one operand tile, 43 with three), the
+# pairs' and the first 64 coordinates', a run of radix-2 stages, a single stage, a stride that is no multiple of 16
+@pytest.mark.parametrize("d,radices,n", [(144, [4, 4, 9], 20), (256, [8, 2, 16], 33), (688, [4, 4, 43], 65), (512, [8, 8, 8], 64),
+                                         (4096, [8, 8, 8, 8], 70), (4096, [2] * 12, 64), (240, [5, 6, 8], 37), (44, [4, 11], 9)])
+def test_block_gradients_may_lie_at_any_float(harp, d, radices, n):
+    import ctypes
+    import torch
+    rng = np.random.default_rng(d + n)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X, G = torch.randn(n, d, device="cuda"), torch.randn(n, d, device="cuda")
+    dK0, dX0 = harp.harp_grad_blocks(plan, X, G)
+    need = harp.harp_grad_blocks_workspace_size(plan, n)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for shift in (1, 2, 3):   # one array for all stages, each `shift` floats behind a boundary of 16 bytes
+        sizes = [(a.numel() + 7) // 4 * 4 for a in dK0]
+        flat = torch.full((sum(sizes) + 4,), 7.0, device="cuda")
+        at = [sum(sizes[:t]) + shift for t in range(len(sizes))]
+        ptrs = (ctypes.c_void_p * len(dK0))(*[flat.data_ptr() + 4 * a for a in at])
+        dX = torch.empty_like(X)
+        say("block gradients at", shift, radices, n)
+        st = harp.lib.harp_grad_blocks(plan.handle, X.data_ptr(), d, G.data_ptr(), d, n, harp.HARP_F32, ptrs, dX.data_ptr(), d,
+                                       ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert st == 0 and torch.equal(dX, dX0)
+        beside = torch.ones_like(flat, dtype=torch.bool)
+        for a, ref in zip(at, dK0):
+            assert torch.equal(flat[a:a + ref.numel()], ref.reshape(-1)), shift
+            beside[a:a + ref.numel()] = False
+        assert bool((flat[beside] == 7.0).all())
+    plan.destroy()
+
+
 # dX written over X or G: a leading segment (radix 2, radix 8), a run of radix-2 stages, a single
 # stage at either end, one run and nothing else
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
