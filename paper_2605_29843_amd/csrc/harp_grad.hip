@@ -926,8 +926,8 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
   // at the end reads the caller's G, and the first run writes dX: no separate conversion pass.
   const bool bf = (dt == HARP_BF16);
   const bool first_run = seg[0].k > 1;
-  // (rows of a pair are addressed by 32-bit offsets from the first of a few)
-  const bool last_run = seg[nseg - 1].k > 1 && !(seg[nseg - 1].pair && ldg >= ((int64_t)1 << 25));
+  const GradSegment &behind = seg[nseg - 1];
+  const bool last_run = behind.k > 1 && (!behind.pair || grad_pair_reads(plan, behind.t0, ldg, bf));
   const bool dx_direct = first_run && dX != nullptr;
   // A stage of radix above 8 at the end passes the gradient back out of place, so its matrix-core kernels read the caller's G
   // where it lies (1537 x 11008 float32, last radix 43: 348 -> 311 us for the whole call; 2048 x 11008 bf16 in one launch:

@@ -228,10 +228,10 @@ __device__ __forceinline__ void sums_add(f4v (&to)[NH][NH], const f4v (&from)[NH
     for (int b = 0; b < NH; ++b) to[a][b] += from[a][b];
 }
 
-// Byte offset from a scalar row address (rows of fewer than 2^25 elements, a few rows at a time).
-template <typename T>
-__device__ __forceinline__ T pair_at(const T *p, uint32_t i) {
-  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + i * (uint32_t)sizeof(T));
+// Byte offset from a scalar row address: 32 bits for rows of fewer than 2^25 elements, a few rows at a time.
+template <typename T, typename I>
+__device__ __forceinline__ T pair_at(const T *p, I i) {
+  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + i * (I)sizeof(T));
 }
 
 constexpr int kPairWaves = 8;
@@ -248,7 +248,8 @@ constexpr int pair_room(int B, int sets) { return 32 * ((B + 3) / 4) * 64 * sets
 // w S + 8 S i, i < B, of every set.  What a wave hands over lies in LDS as [coordinate][set][group][row], the row's place
 // exchanged by the coordinate's low bits so that both layouts read without conflicts.  Gout may be Gin: all
 // of a step's rows have arrived, in every wave, before its second barrier, and are written behind it.
-template <int B, typename TG>
+// I: of the offsets of gradient rows.
+template <int B, typename TG, typename I = uint32_t>
 __global__ __launch_bounds__(64 * kPairWaves, 2) void harp_grad_pair_bwd_kernel(
     const float *__restrict__ X, const TG *Gin, int64_t ldg, float *Gout, int64_t d, int64_t n, int rows,
     PassBlocks pa, PassBlocks pb, int S, int tiles, int share, float *__restrict__ partial_a,
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void harp_grad_pair_bwd_kernel(
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int row = 4 * s + q < last ? 4 * s + q : last;
-      const uint32_t o = (uint32_t)row * (uint32_t)ldg + (uint32_t)at_b;
+      const I o = (I)row * (I)ldg + (I)at_b;
 #pragma unroll
       for (int i = 0; i < B; ++i) ng[s][i] = pair_at(gr + 8 * i * S, o);
     }
@@ -893,6 +894,14 @@ harp_status_t launch_grad_pair_fwd(const harp_plan *plan, int t, const float *X,
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
+// Gradient rows further apart than 32-bit offsets reach are copied to float32 first, but for bf16 rows of eight and eight
+// coordinates, whose sums float32 rows would not give (fewer rows a step): their kernel exists with 64-bit offsets, too.
+constexpr int64_t kPairPitch = (int64_t)1 << 25;
+bool grad_pair_reads(const harp_plan *plan, int t, int64_t ldg, bool bf) {
+  const int ka = pass_stages(plan, t), kb = pass_stages(plan, t + ka);
+  return ldg < kPairPitch || (bf && pass_size(plan, t + ka, kb) == 8);
+}
+
 harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf,
                                    float *Gout, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st) {
@@ -905,13 +914,14 @@ harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X,
   const int S = (int)plan->strides[t], share = pair_share(tiles, total, bf);
   const int64_t tiles16 = d / 128;
   float *partial_b = partial + (size_t)chunks * (size_t)tiles16 * 1024;
-#define HARP_PAIR_BWD_T(BB, T)                                                                                   \
-  hipLaunchKernelGGL((harp_grad_pair_bwd_kernel<BB, T>), dim3((unsigned)total), dim3(64 * kPairWaves), 0, st, X, \
+#define HARP_PAIR_BWD_T(BB, T, I)                                                                                \
+  hipLaunchKernelGGL((harp_grad_pair_bwd_kernel<BB, T, I>), dim3((unsigned)total), dim3(64 * kPairWaves), 0, st, X, \
                      (const T *)G, ldg, Gout, d, n, rows, pa, pb, S, (int)tiles, share, partial, partial_b)
-#define HARP_PAIR_BWD(BB)                  \
-  if (bf) HARP_PAIR_BWD_T(BB, uint16_t);   \
-  else HARP_PAIR_BWD_T(BB, float)
-  HARP_PAIR_SIZE(B, HARP_PAIR_BWD)
+#define HARP_PAIR_BWD(BB)                          \
+  if (bf) HARP_PAIR_BWD_T(BB, uint16_t, uint32_t); \
+  else HARP_PAIR_BWD_T(BB, float, uint32_t)
+  if (ldg >= kPairPitch) HARP_PAIR_BWD_T(8, uint16_t, uint64_t);
+  else HARP_PAIR_SIZE(B, HARP_PAIR_BWD)
 #undef HARP_PAIR_BWD
 #undef HARP_PAIR_BWD_T
   add_sums(plan, t, ka, kb, partial, partial_b, chunks, dK, sums);

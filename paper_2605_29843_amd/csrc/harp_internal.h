@@ -446,6 +446,7 @@ harp_status_t launch_grad_lead_bwd(const harp_plan *plan, int nst, const void *X
 int grad_pair_stages(const std::vector<int32_t> &radices, int t);
 size_t grad_pair_partial_bytes(const harp_plan *plan, int t, int64_t n);
 harp_status_t launch_grad_pair_fwd(const harp_plan *plan, int t, const float *X, float *Y, int64_t n, hipStream_t st);
+bool grad_pair_reads(const harp_plan *plan, int t, int64_t ldg, bool bf);   // the caller's G where it lies
 harp_status_t launch_grad_pair_bwd(const harp_plan *plan, int t, const float *X, const void *G, int64_t ldg, bool bf,
                                    float *Gout, int64_t n, float *partial, float *const *dK, GradSums &sums,
                                    hipStream_t st);

@@ -379,6 +379,28 @@ def test_bits_do_not_depend_on_where_the_matrices_lie(harp, d, radices, n, dtype
     plan.destroy()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("radices", [[2] * 12, [8, 8, 8, 4]])
+def test_bits_do_not_depend_on_a_pitch_beyond_32_bit_offsets(harp, radices, dtype):
+    """Gradient rows 2^25 elements apart and more: read with 64-bit offsets, or copied first."""
+    import torch
+    d, n = int(np.prod(radices)), 67
+    rng = np.random.default_rng(d)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X, G = torch.randn(n, d, device="cuda"), torch.randn(n, d, device="cuda")
+    if dtype == "bf16":
+        X, G = X.bfloat16(), G.bfloat16()
+    dK0, dX0 = harp.harp_grad_blocks(plan, X, G)
+    big = torch.empty(n, (1 << 25) + 8, device="cuda", dtype=G.dtype)
+    view = big[:, :d]
+    view.copy_(G)
+    say("gradient rows far apart", radices, dtype)
+    dK, dX = harp.harp_grad_blocks(plan, X, view)
+    torch.cuda.synchronize()
+    assert torch.equal(dX, dX0) and all(torch.equal(a, b) for a, b in zip(dK, dK0))
+    plan.destroy()
+
+
 # One stage of each way in which block gradients are written: the matrix cores' (9, 16 with one operand tile, 43 with three), the
 # pairs' and the first 64 coordinates', a run of radix-2 stages, a single stage, a stride that is no multiple of 16
 @pytest.mark.parametrize("d,radices,n", [(144, [4, 4, 9], 20), (256, [8, 2, 16], 33), (688, [4, 4, 43], 65), (512, [8, 8, 8], 64),
