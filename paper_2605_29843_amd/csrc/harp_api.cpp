@@ -677,6 +677,42 @@ int64_t slab_rows_cap_z16(int64_t d) {
   return slab;
 }
 
+// Rows of a slab for n > cap rows: full slabs and a rest, or as many slabs of one size (a multiple of 128 rows).  The rest of
+// a call is a pair of launches with little to do, and smaller slabs stay in the memory-side cache; but a slab of one size
+// may take as many rounds of workgroups as a full one.  Measured at 700 row counts of 5120 .. 28672 (1.02 to 4.9 slabs; time with
+// a rest / in equal slabs, so above 1 equal ones win):
+//   - float32 rows at either end: 0.985 - 1.16 whatever the rest; where a radix above 8 runs first (11008 transposed)
+//     0.95 - 1.02 with less than a quarter of a slab left, 0.98 - 1.06 beyond;
+//   - bf16 rows: 0.95 - 1.05 with less than a quarter left, 0.985 - 1.09 beyond; transposed, and with an intermediate of halves, the
+//     line is three eighths (0.93 - 1.02, 0.987 - 1.04);
+//   - three streamed stages with an intermediate of halves (13824 radix 2): 0.88 - 1.007, never;
+//   - chains with one tile of eight rows per compute unit at a time (chunks above 2048 coordinates) are paced by rounds of tiles: 0.89 -
+//     1.07 where equal slabs take more rounds, 0.97 - 1.13 where they take fewer; with as many, float32 rows gain from a quarter or with
+//     three slabs (0.98 - 1.12, else 0.93 - 1.07), bf16 rows do not (0.91 - 1.04).
+int64_t slab_rows(const harp_plan_t *plan, const HostProgram &hp, bool float32, bool z16, int64_t n, int64_t cap) {
+  const int64_t slabs = (n + cap - 1) / cap, rest = n % cap;
+  if (slabs == 1) return n;
+  const int64_t even = std::min(cap, ((n + slabs - 1) / slabs + 127) / 128 * 128);
+  const int nstream = hp.prog.npass - hp.n_chunk, p0 = hp.chunk_first ? hp.n_chunk : 0;
+  const bool large = 8 * rest >= (float32 || (hp.chunk_first && !z16) ? 2 : 3) * cap, chain = hp.chain.img != nullptr;
+  if (z16 && nstream > 1) return cap;
+  if (chain && hp.chunk > 2048) {
+    const int64_t cus = plan->num_cu > 0 ? plan->num_cu : 256;
+    auto rounds = [&](int64_t slab) {
+      int64_t r = 0;
+      for (int64_t r0 = 0; r0 < n; r0 += slab) r += ((std::min(slab, n - r0) + 7) / 8 * (plan->d / hp.chunk) + cus - 1) / cus;
+      return r;
+    };
+    const int64_t more = rounds(even) - rounds(cap);
+    if (more != 0) return more < 0 && (float32 || 8 * rest >= cap) ? even : cap;
+    return float32 && (large || slabs > 2) ? even : cap;
+  }
+  bool big_first = false;
+  for (int k = 0; k < nstream; ++k) big_first = big_first || (!hp.chunk_first && hp.prog.pass[p0 + k].b > 8);
+  if (float32 && !chain && !big_first) return even;
+  return large || (float32 && chain && slabs > 2) ? even : cap;
+}
+
 // Intermediates of split programs from 8 MB on, which plans share: one buffer per device and stream.  Work on one stream
 // is ordered, so the calls that are queued on it can use the same memory one after the other; `mu` is held while a
 // call's launches are queued, so that two host threads cannot interleave theirs.  With a buffer of its own
@@ -950,9 +986,7 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
   }
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);
-  // slabs of one size: the last one would otherwise be a launch with little to do
-  const int64_t nslab = (n + slab_cap - 1) / slab_cap;
-  const int64_t slab = nslab == 1 ? n : std::min(slab_cap, ((n + nslab - 1) / nslab + 127) / 128 * 128);
+  const int64_t slab = slab_rows(plan, hp, dt_in == HARP_F32 || dt_out == HARP_F32, z16, n, slab_cap);
   const size_t row_bytes = z16 ? (size_t)z16_ld(d) * 2 : (size_t)d * 4;
   // one buffer per stream serves both forms: its full size is the larger of the two slabs
   const size_t cap = std::max((size_t)slab_rows_cap(d) * d * 4,

@@ -871,6 +871,27 @@ def test_default_stream_beside_a_capture(harp, n):
     plan.destroy()
 
 
+# Calls of more rows than a slab holds, on both sides of each line of the rule that cuts them (full slabs and a rest, or
+# slabs of one size): a chain that equal slabs would cost rounds of tiles and one that they save some, halves with one streamed stage and
+# with three, a large radix first, plain float32 rows.
+@pytest.mark.parametrize("d,radices,dtype", [(28672, [8, 8, 8, 8, 7], "bf16"), (14336, [8, 8, 8, 7, 4], "f32"),
+                                             (28672, [2] * 12 + [7], "bf16"), (13824, [2] * 9 + [3, 3, 3], "bf16"),
+                                             (11008, [2] * 8 + [43], "f32"), (11008, [8, 8, 4, 43], "bf16")])
+def test_results_do_not_depend_on_how_rows_are_cut(harp, d, radices, dtype):
+    import torch
+    full = (128 << 20) // (4 * d) // 256 * 256
+    rng = np.random.default_rng(d)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X = torch.randn(full * 29 // 10, d, device="cuda")
+    X = X.bfloat16() if dtype == "bf16" else X
+    for fn in (harp.harp_apply, harp.harp_apply_transpose):
+        pieces = torch.cat([fn(plan, X[r:r + 700]) for r in range(0, X.shape[0], 700)])
+        for n in (full + 40, full * 5 // 4, full * 3 // 2, full * 2 + 300, full * 29 // 10):
+            say("rows cut into slabs", radices, n, dtype, fn.__name__)
+            assert torch.equal(fn(plan, X[:n]), pieces[:n]), n
+    plan.destroy()
+
+
 def test_plans_share_the_intermediate_of_a_stream(harp):
     """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
     stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
