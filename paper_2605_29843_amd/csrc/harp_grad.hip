@@ -329,11 +329,11 @@ constexpr int kDkRows = 8;                  // rows per step (16 measured 1 % fa
 constexpr int kDkLS = kDkRows + 1;          // LDS stride between consecutive blocks
 constexpr int kDkJS = 16 * kDkLS + 4;       // LDS stride between consecutive r
 
-template <int KT>
 __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
     const float *__restrict__ X, int64_t ldx, const float *__restrict__ Gm, int64_t ldg, int64_t n, int rows,
     int D, int s, int b, int gx, int paired, float *__restrict__ partial) {
   typedef float f4v __attribute__((ext_vector_type(4)));
+  constexpr int KT = 4;   // operand tiles of 16: radix 49 .. 64
   constexpr int MAXG = (kDkRows * 16 * KT * 4 + 1023) / 1024;
   constexpr int TILE = 16 * KT * kDkJS;
   __shared__ float lds[2 * TILE];
@@ -445,13 +445,12 @@ __global__ __launch_bounds__(1024) void harp_grad_dk_mfma_kernel(
     }
 }
 
-template <int KT>
 static void launch_dk_mfma(const float *X, int64_t ldx, const float *Gm, int64_t ldg, int64_t n, int rows, int nchunks,
                            int D, int s, int b, float *partial, hipStream_t st) {
   const int gx = D / 16;
   const int64_t total = (int64_t)gx * nchunks;
   const int paired = (gx % 2 == 0) && (total % 16 == 0);
-  hipLaunchKernelGGL((harp_grad_dk_mfma_kernel<KT>), dim3((unsigned)total), dim3(1024), 0, st, X, ldx, Gm, ldg, n,
+  hipLaunchKernelGGL(harp_grad_dk_mfma_kernel, dim3((unsigned)total), dim3(1024), 0, st, X, ldx, Gm, ldg, n,
                      rows, D, s, b, gx, paired, partial);
 }
 
@@ -1062,7 +1061,7 @@ harp_status_t launch_grad(const harp_plan *plan, const void *X, int64_t ldx, con
         const int64_t gld = own ? ldg : d;
         const bool mf = mfma_pass_supported(plan->grad_mfma[1][seg[i].t0], gsrc, gld, g2, d);
         const bool dkm = dk_mfma_supported(cs.b, cs.s, D, in, d, gsrc, gld, partial, nchunks_big);
-        if (dkm) launch_dk_mfma<4>(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st);
+        if (dkm) launch_dk_mfma(in, d, gsrc, gld, n, rows_big, nchunks_big, D, cs.s, cs.b, partial, st);
 #define HARP_GRAD_BIG_BWD(BM)                                                                      \
   if (!dkm)                                                                                        \
     hipLaunchKernelGGL((harp_grad_dk_big_kernel<BM>), grid, dim3(kGradThreads), 0, st, in, g, d, n, \
