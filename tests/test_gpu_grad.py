@@ -224,14 +224,17 @@ def test_leading_segment_and_stage_by_stage_agree_with_the_oracle(harp, d, radic
 # Two passes of one launch behind the leading segment: eight coordinates (one stage, or three of radix 2), then
 # 2 .. 8 (one stage, or one, two, three of radix 2), at the end of the plan and with a stage behind them; rows that
 # fill a workgroup's chunk, leave a set of four with one row, and leave whole sets empty; tiles of 16 groups that share
-# lines with neighbours and that do not.
+# lines with neighbours and that do not.  The last nine: chunks of 48 rows (the fewest rounds on 256 compute units), three steps of
+# 16 rows for second passes of two, three and four coordinates, the last chunk's with a step that is not full.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("radices,n", [
     ([8, 8, 8, 2], 64), ([8, 8, 8, 3], 81), ([8, 8, 8, 4], 65), ([8, 8, 8, 5], 97), ([8, 8, 8, 6], 70),
     ([8, 8, 8, 7], 67), ([8, 8, 8, 8], 145), ([2] * 6 + [8, 3], 131), ([2] * 6 + [8, 2, 2], 66), ([2] * 6 + [8, 2], 79),
     ([2] * 10, 96), ([2] * 11, 161), ([2] * 12, 73), ([2] * 9 + [5], 64), ([8, 8] + [2] * 6, 99), ([8, 8, 2, 2, 2, 7], 77),
     ([8, 8, 8, 2, 3], 66), ([2] * 12 + [3], 65), ([8, 8, 8, 5, 2], 83), ([8, 8, 8, 3, 3], 70), ([2] * 6 + [8, 4, 2], 69),
-    ([8, 8, 8, 6, 2], 64), ([8, 8, 8, 7, 2], 64)])
+    ([8, 8, 8, 6, 2], 64), ([8, 8, 8, 7, 2], 64),
+    ([8, 8, 8, 2], 3001), ([8, 8, 8, 3], 3001), ([8, 8, 8, 4], 3001), ([8, 8, 8, 2, 3], 1501), ([8, 8, 8, 3, 2], 1501),
+    ([8, 8, 8, 4, 2], 1501), ([2] * 10 + [5], 1001), ([2] * 9 + [3, 3, 3], 601), ([2] * 11 + [7], 333)])
 def test_pairs_of_passes_behind_the_leading_segment(harp, radices, n, dtype):
     d = int(np.prod(radices))
     rng = np.random.default_rng(d + n)
@@ -252,25 +255,28 @@ def test_pairs_of_passes_behind_the_leading_segment(harp, radices, n, dtype):
 # A stage of radix 9 .. 48 at a stride that is a multiple of 16: operand tiles one to three, full and not, steps of 16 rows
 # and chunks that are full, short by one and longer by one (one workgroup per compute unit: D / 16 tiles across, so the
 # counts beyond 4096 rows of D = 16 take chunks of more than a step), the stage last, in the middle, and twice.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,radices,kind,counts", [
     (144, [4, 4, 9], "generic", (1, 15, 16, 17, 4097, 8200)), (256, [8, 2, 16], "orth", (31, 4096)), (272, [4, 4, 17], "orth", (33, 4113)),
     (1024, [8, 4, 32], "generic", (16, 130)), (528, [2, 8, 33], "orth", (47, 4100)), (688, [4, 4, 43], "generic", (64, 8193)),
     (768, [8, 2, 48], "orth", (5, 4098)), (11008, [8, 8, 4, 43], "orth", (81, 257)), (1408, [4, 4, 11, 8], "generic", (65,)),
     (1936, [16, 11, 11], "orth", (40,))])
-def test_large_radix_on_the_matrix_cores(harp, d, radices, kind, counts):
+def test_large_radix_on_the_matrix_cores(harp, d, radices, kind, counts, dtype):
     rng = np.random.default_rng(d)
     blocks, signs = gi.make_blocks(d, radices, kind, rng), gi.make_signs(d, rng)
     plan = harp.Plan(d, radices, blocks, signs)
     for n in counts:
-        say("grad large radix", radices, n)
+        say("grad large radix", radices, n, dtype)
         X, G = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
-        dK, dX = harp.harp_grad_blocks(plan, to_device(X, "f32"), to_device(G, "f32"))
+        if dtype == "bf16":
+            X, G = gi.round_to_bf16(X), gi.round_to_bf16(G)
+        dK, dX = harp.harp_grad_blocks(plan, to_device(X, dtype), to_device(G, dtype))
         rK, rX = ho.grad_blocks(X, G, d, radices, blocks, signs)
         assert_dk_parity(dK, rK, X, G, f"dK, {n} rows")
         if kind == "orth":
             assert_dk_accuracy(dK, rK, X, G, d, radices, blocks, signs, f"dK, {n} rows")
         mag = summand_magnitude(G, d, radices, blocks, transpose=True) if kind == "generic" else None
-        assert_parity(to_host64(dX), rX, "f32", f"dX, {n} rows", mag=mag)
+        assert_parity(to_host64(dX), rX, dtype, f"dX, {n} rows", mag=mag)
     plan.destroy()
 
 

@@ -896,15 +896,12 @@ def test_plans_share_the_intermediate_of_a_stream(harp):
     """Plans of two launches take turns in one buffer per stream: two host threads queue calls of two plans on one
     stream, a graph of a third plan is replayed on another stream at the same time, and every result has the
     bits of the plan alone; more streams than there are shared buffers; the memory of many plans is
-    that of one buffer and goes with the last plan."""
+    that of one buffer."""
     import threading
     import torch
     d, radices, n = 14336, [2] * 11 + [7], 600
     rng = np.random.default_rng(31)
-    torch.cuda.synchronize()
-    free0 = torch.cuda.mem_get_info()[0]
     plans = [harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)) for _ in range(6)]
-    plan_bytes = free0 - torch.cuda.mem_get_info()[0]
     X = to_device(gi.round_to_bf16(rng.standard_normal((n, d)).astype(np.float32)), "bf16")
     out = [torch.zeros_like(X) for _ in plans]
     ref = [torch.zeros_like(X) for _ in plans]
@@ -954,12 +951,54 @@ def test_plans_share_the_intermediate_of_a_stream(harp):
     torch.cuda.synchronize()
     assert all(torch.equal(y, ref[3]) for y in ys)
     del g
-    held = torch.cuda.mem_get_info()[0]
     for p in plans:
         p.destroy()
+
+
+def test_buffers_go_with_the_last_plan():
+    """In a process of its own, where no other plan is alive: the shared intermediate stays while one plan is left, and
+    with the last one everything that plans hold has been given back."""
+    import os
+    import subprocess
+    child = """
+import numpy as np, torch
+from paper_2605_29843_amd import harp, inputs as gi
+d, radices, n = 14336, [2] * 11 + [7], 2300
+rng = np.random.default_rng(1)
+X = torch.randn(n, d, device="cuda")
+Y = torch.zeros_like(X)
+blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
+def plan_of(rows):
+    p = harp.Plan(d, radices, blocks, signs)
+    harp.harp_apply(p, X[:rows], Y[:rows])
     torch.cuda.synchronize()
-    # every plan's own memory and at least one buffer came back (plans of other tests may be alive and keep theirs)
-    assert torch.cuda.mem_get_info()[0] - held >= plan_bytes // 2
+    return p
+def free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+plan_of(40).destroy()                       # kernels and the runtime's own memory are there
+base = free()
+one, two = plan_of(n), plan_of(n)
+side = torch.cuda.Stream()
+with torch.cuda.stream(side):
+    harp.harp_apply(two, X, Y, side)
+    harp.harp_apply(two, X[:40], Y[:40], side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        harp.harp_apply(two, X, Y, side)
+assert base - free() >= 3 * (120 << 20)     # two streams' shared buffers, a captured call's
+del g
+two.destroy()
+assert base - free() >= 2 * (120 << 20)     # the shared ones are still there
+one.destroy()
+assert base - free() < 8 << 20, base - free()
+print("given back", flush=True)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    say("buffers go with the last plan")
+    done = subprocess.run([sys.executable, "-u", "-c", child], cwd=root, capture_output=True, text=True, timeout=100)
+    assert done.returncode == 0 and "given back" in done.stdout, done.stdout + done.stderr
 
 
 def test_one_plan_on_two_streams_and_two_host_threads(harp):

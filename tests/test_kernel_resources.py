@@ -58,3 +58,20 @@ def test_no_scratch(scratch_bytes, kernel):
     sizes = {k: v for k, v in scratch_bytes.items() if kernel in k}
     assert sizes
     assert not {k: v for k, v in sizes.items() if v}
+
+
+def test_scratch_of_the_chain_kernels(scratch_bytes):
+    """Tiles of eight rows of a chain with a last radix of 4 hold two blocks of 16 coordinates per wave and may spill a few
+    registers, and so may float32 rows of a last radix of 7 with a radix-4 stage above; no other instance does."""
+    sizes = {k: v for k, v in scratch_bytes.items() if "harp_chain_kernel" in k}
+    assert len(sizes) > 100
+    for name, size in sizes.items():   # <in, out, last radix, transposed, four rows each, stage above>
+        arg = re.search(r"harp_chain_kernelI[ft](?:[ft]|S\w*_)Li(\d)ELb(\d)ELi(\d)ELi(\d)EE", name)
+        assert arg, name
+        r4, trn, four, top = (int(a) for a in arg.groups())
+        most = 0
+        if four == 2 and r4 == 4:
+            most = 160 if trn else 64
+        elif four == 2 and r4 == 7 and top == 4 and "kernelIff" in name:
+            most = 16
+        assert size <= most, (name, size)
