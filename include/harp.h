@@ -140,8 +140,8 @@ harp_status_t harp_plan_destroy(harp_plan_t *plan);
  * value within 2^-12 of itself or 2^-25 of the largest of its 16 neighbours: an eighth of the
  * rounding of the bf16 result); HARP_F32_INTERMEDIATES at plan creation keeps float32.  A
  * transposed call whose one stage above a 4096-chunk has radix 2, 3 or 5 (d = 8192, 12288,
- * 20480), or radix 2, 3 or 4 above stages 8, 8, 8, 3..8 (more than a few rows), runs in one
- * launch without any intermediate when Y is not X.
+ * 20480), or radix 2, 3 or 4 above stages 8, 8, 8, 3..8, runs in one launch without any
+ * intermediate when Y is not X.
  */
 harp_status_t harp_apply(const harp_plan_t *plan, const void *X, int64_t ldx, void *Y,
                          int64_t ldy, int64_t n, harp_dtype_t dt, void *stream);

@@ -57,7 +57,9 @@ struct ChainShape {
   // aligned quads while the inputs they replace are spread over other quads, so a stage of two rows per lane
   // needs up to 64 registers more than its coordinates: with a ring of 16 most shapes spilled (2048 x 4096 bf16
   // 15.3 us against 14.6, six rows of 14336 13.6 against 12.5).  Radix 4 has smaller batches: eight pieces are as
-  // many ahead; its waves hold two blocks of 16 lo, and five of its seven instances still spill 8 to 35 registers.
+  // many ahead; its waves hold two blocks of 16 lo, and five of its seven instances still spill 7 to 35 registers, with the stage above on the way
+  // in all six of them 33 to 39 (and radix 7 under a stage of radix 4 with float32 rows, 4); those are ahead of two launches all the same
+  // (8, 8, 8, 4, 4 transposed, bf16, us: 300 rows 17.6 -> 14.5, 3000 rows 70 -> 63, 8000 rows 189 -> 149; float32 18.9 -> 14.2, 84 -> 83, 262 -> 199).
   // One row per lane has room: one row of 4096 bf16 7.1 us with a ring of 12, 6.9 with 16, 7.0 with 24, 7.3 with 48.
   static constexpr int RING = HV == 1 ? 16 : R4 == 4 ? 8 : 12;
   static constexpr int NA = 32;                       // pieces per unit, stages at strides 1 and 8
@@ -604,7 +606,7 @@ harp_status_t launch_chain_kernel(const harp_plan *plan, const ChainImage &ci, c
 
 // Transposed split program whose one stage above the chain has radix 2 .. 4: one launch, no intermediate (bf16: 12 bytes per
 // coordinate become 4).  Not in place: a workgroup may store its chunk of a row before another one has read it.  Larger radices are
-// not built: a row would be read that many times.  Two launches / one, us, bf16: 8192 (8, 8, 8, 8 | 2) at 1 row 9.6 / 8.0, 514 rows
+// neither built nor measured: a row would be read that many times.  Two launches / one, us, bf16: 8192 (8, 8, 8, 8 | 2) at 1 row 9.6 / 8.0, 514 rows
 // 19.3 / 15.0, 2048 rows 51 / 25; 14336 (8, 8, 8, 7 | 4) at 8 rows 10.2 / 9.2, 300 rows 19.6 / 17.7, 777 rows 35 / 27, 2048 rows
 // 82 / 57; float32: 5120 (8, 8, 8, 5 | 2) at 3000 rows 58 / 36, 14336 at 777 rows 45 / 33.  Tiles of eight go row by row over an XCD; with a
 // run of tiles of one chunk, as without the stage, the row came from memory TOP times (14336: 777 rows 30, 2048 rows 68).

@@ -211,8 +211,10 @@ __device__ __forceinline__ void pass_sums(const float (&x)[NH][4], const float (
 #pragma unroll
       for (int b = 0; b < NH; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[a][r], g[b][r], acc[a][b], 0, 0, 0);
 }
-// Sums of eight rows are made from zero and then added to those of the chunk: one sum over all of the chunk's rows (up to
-// 64) left dK of 333 rows 5 - 28 % further from the exact one than sums of eight do.
+// Sums of a few rows are made from zero and then added to those of the chunk: one sum over all of the chunk's rows (up to
+// 64) left dK of 333 rows 5 - 28 % further from the exact one than sums of eight do.  Eight rows are two sets of
+// four; four are summed in pass a where a step has one set for each wave (second passes of two, and of eight with float32
+// gradient rows) and in pass b of the latter.
 template <int NH>
 __device__ __forceinline__ void sums_clear(f4v (&acc)[NH][NH]) {
 #pragma unroll
