@@ -180,24 +180,38 @@ __global__ __launch_bounds__(kBigThreads, 2) void harp_grad_big_bwd_kernel(
   }
 }
 
-// dK = the chunks' sums in ascending order within each eight, then the eights in ascending order.
+// dK = the chunks' sums in ascending order within each eight, then the eights in ascending order; with SL slices of the
+// chunks, the slices in ascending order behind that.  A thread's eights follow one another, so few blocks with many chunks
+// want slices: 144 x 9 values leave two workgroups a serial walk over 250 chunks (4000 x 144 float32 (4, 4, 9), whole call 65 -> 49 us;
+// 100000 x 528 (4, 4, 33), 782 chunks, 1628 -> 1572).  (dK is the caller's: four stores where it is not on a boundary of 16 bytes.)
 constexpr int kBigSumThreads = 256;
-// (dK is the caller's: four stores where it is not on a boundary of 16 bytes.)
+template <int SL>
 __global__ __launch_bounds__(kBigSumThreads) void harp_grad_big_sum_kernel(const f4v *__restrict__ partial, int nchunks,
                                                                            size_t total, int aligned, float *__restrict__ dK) {
-  const size_t e = (size_t)blockIdx.x * kBigSumThreads + threadIdx.x;
-  if (e >= total) return;
+  constexpr int Q = kBigSumThreads / SL;   // quads of a workgroup
+  const int slice = (int)threadIdx.x / Q;
+  const size_t own = (size_t)blockIdx.x * Q + threadIdx.x % Q, e = own < total ? own : total - 1;
+  const int per = ((nchunks + SL - 1) / SL + 7) / 8 * 8, k0 = slice * per, k1 = k0 + per < nchunks ? k0 + per : nchunks;
   f4v s = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < nchunks; k += 8) {
+  for (int k = k0; k < k1; k += 8) {
     f4v v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(k + u < nchunks ? k + u : k) * total + e];
+    for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(k + u < k1 ? k + u : k) * total + e];
     f4v part = v[0];
 #pragma unroll
     for (int u = 1; u < 8; ++u)
-      if (k + u < nchunks) part += v[u];
+      if (k + u < k1) part += v[u];
     s += part;
   }
+  if constexpr (SL > 1) {
+    __shared__ f4v sums[kBigSumThreads];
+    sums[threadIdx.x] = s;
+    __syncthreads();
+    if (slice > 0) return;
+#pragma unroll
+    for (int i = 1; i < SL; ++i) s += sums[i * Q + threadIdx.x];
+  }
+  if (own >= total) return;
   if (aligned) {
     *reinterpret_cast<f4v *>(dK + 4 * e) = s;
   } else {
@@ -254,9 +268,15 @@ harp_status_t launch_grad_big(const harp_plan *plan, int t, const float *X, cons
 #undef HARP_BIG
 #undef HARP_BIG_T
   const size_t quads = (size_t)(d * b / 4);   // D is a multiple of 16
-  hipLaunchKernelGGL(harp_grad_big_sum_kernel, dim3((unsigned)((quads + kBigSumThreads - 1) / kBigSumThreads)),
-                     dim3(kBigSumThreads), 0, st, reinterpret_cast<const f4v *>(partial), (int)chunks, quads,
-                     (uintptr_t)dK % 16 == 0 ? 1 : 0, dK);
+#define HARP_BIG_SUM(SL)                                                                                                   \
+  hipLaunchKernelGGL((harp_grad_big_sum_kernel<SL>), dim3((unsigned)((quads * SL + kBigSumThreads - 1) / kBigSumThreads)), \
+                     dim3(kBigSumThreads), 0, st, reinterpret_cast<const f4v *>(partial), (int)chunks, quads,              \
+                     (uintptr_t)dK % 16 == 0 ? 1 : 0, dK)
+  // (16 chunks are two steps of a thread, and 65536 quads a workgroup per compute unit)
+  if (chunks <= 16 || quads >= 65536) HARP_BIG_SUM(1);
+  else if (chunks <= 64) HARP_BIG_SUM(4);
+  else HARP_BIG_SUM(16);
+#undef HARP_BIG_SUM
   return hipGetLastError() == hipSuccess ? HARP_OK : HARP_ERR_DEVICE;
 }
 
