@@ -255,10 +255,10 @@ def test_pairs_of_passes_behind_the_leading_segment(harp, radices, n, dtype):
 # A stage of radix 9 .. 48 at a stride that is a multiple of 16: operand tiles one to three, full and not, steps of 16 rows
 # and chunks that are full, short by one and longer by one (one workgroup per compute unit: D / 16 tiles across, so the
 # counts beyond 4096 rows of D = 16 take chunks of more than a step), the stage last, in the middle, and twice; chunks added by one
-# thread, by four (25 and 33 chunks: the last of them one or none) and by sixteen.
+# thread, by four (25 and 33 chunks: the last of them one or none) and by sixteen; chunks that fill the chip twice.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,radices,kind,counts", [
-    (144, [4, 4, 9], "generic", (1, 15, 16, 17, 400, 520, 4097, 8200)), (256, [8, 2, 16], "orth", (31, 4096)), (272, [4, 4, 17], "orth", (33, 4113)),
+    (144, [4, 4, 9], "generic", (1, 15, 16, 17, 400, 520, 4097, 8200, 33000)), (256, [8, 2, 16], "orth", (31, 4096)), (272, [4, 4, 17], "orth", (33, 4113)),
     (1024, [8, 4, 32], "generic", (16, 130)), (528, [2, 8, 33], "orth", (47, 4100)), (688, [4, 4, 43], "generic", (64, 8193)),
     (768, [8, 2, 48], "orth", (5, 4098)), (11008, [8, 8, 4, 43], "orth", (81, 257)), (1408, [4, 4, 11, 8], "generic", (65,)),
     (1936, [16, 11, 11], "orth", (40,))])
