@@ -681,21 +681,32 @@ int64_t slab_rows_cap_z16(int64_t d) {
 // a call is a pair of launches with little to do, and smaller slabs stay in the memory-side cache; but a slab of one size
 // may take as many rounds of workgroups as a full one.  Measured at 700 row counts of 5120 .. 28672 (1.02 to 4.9 slabs; time with
 // a rest / in equal slabs, so above 1 equal ones win):
-//   - float32 rows at either end: 0.985 - 1.16 whatever the rest; where a radix above 8 runs first (11008 transposed)
-//     0.95 - 1.02 with less than a quarter of a slab left, 0.98 - 1.06 beyond;
-//   - bf16 rows: 0.95 - 1.05 with less than a quarter left, 0.985 - 1.09 beyond; transposed, and with an intermediate of halves, the
-//     line is three eighths (0.93 - 1.02, 0.987 - 1.04);
+//   - chunks of radix 2, float32 rows at either end: 0.985 - 1.16 whatever the rest; where a radix above 8 runs first (11008
+//     transposed) 0.95 - 1.02 with less than a quarter of a slab left, 0.98 - 1.06 beyond;
+//   - the same, bf16 rows: 0.95 - 1.04 with less than a quarter left, 0.985 - 1.04 beyond; transposed, and with an intermediate of halves,
+//     the line is three eighths (0.93 - 1.02, 0.987 - 1.04);
 //   - three streamed stages with an intermediate of halves (13824 radix 2): 0.88 - 1.007, never;
 //   - chains with one tile of eight rows per compute unit at a time (chunks above 2048 coordinates) are paced by rounds of tiles: 0.89 -
 //     1.07 where equal slabs take more rounds, 0.97 - 1.13 where they take fewer; with as many, float32 rows gain from a quarter or with
-//     three slabs (0.98 - 1.12, else 0.93 - 1.07), bf16 rows do not (0.91 - 1.04).
-int64_t slab_rows(const harp_plan_t *plan, const HostProgram &hp, bool float32, bool z16, int64_t n, int64_t cap) {
+//     three slabs (0.98 - 1.12, else 0.93 - 1.07), bf16 rows do not (0.91 - 1.04); shorter chains as radix 2, or with three slabs
+//     (13824: 1.02 - 1.1);
+//   - chunks of other radices with a kernel (8, 8, 4; equal ones): float32 rows forward 0.99 - 1.06, the others 0.94 - 1.02;
+//   - chunks on the tile kernels (15625 x 3): 0.90 - 1.0, never.
+int64_t slab_rows(const harp_plan_t *plan, const HostProgram &hp, const void *X, int64_t ldx, const void *Y, int64_t ldy,
+                  bool float32, bool z16, int64_t n, int64_t cap) {
   const int64_t slabs = (n + cap - 1) / cap, rest = n % cap;
   if (slabs == 1) return n;
   const int64_t even = std::min(cap, ((n + slabs - 1) / slabs + 127) / 128 * 128);
   const int nstream = hp.prog.npass - hp.n_chunk, p0 = hp.chunk_first ? hp.n_chunk : 0;
-  const bool large = 8 * rest >= (float32 || (hp.chunk_first && !z16) ? 2 : 3) * cap, chain = hp.chain.img != nullptr;
+  const bool large = 8 * rest >= (float32 || (hp.chunk_first && !z16) ? 2 : 3) * cap;
   if (z16 && nstream > 1) return cap;
+  const int pc = hp.chunk_first ? 0 : nstream;
+  const void *cx = hp.chunk_first ? X : nullptr, *cy = hp.chunk_first ? nullptr : Y;   // (the intermediate is aligned)
+  const int64_t clx = hp.chunk_first ? ldx : plan->d, cly = hp.chunk_first ? plan->d : ldy;
+  const bool radix = radix_supported(plan, hp, pc, hp.n_chunk, hp.chunk, cx, clx, cy, cly), chain = radix && hp.chain.img;
+  if (!z16 && !chain && !pipe_supported(plan, hp.prog, pc, hp.n_chunk, hp.chunk, cx, clx, cy, cly) &&
+      !wave_supported(plan, hp.prog, pc, hp.n_chunk, hp.chunk, cx, clx, cy, cly))
+    return radix && float32 && hp.chunk_first ? even : cap;
   if (chain && hp.chunk > 2048) {
     const int64_t cus = plan->num_cu > 0 ? plan->num_cu : 256;
     auto rounds = [&](int64_t slab) {
@@ -986,7 +997,7 @@ harp_status_t apply_dir(const harp_plan_t *plan, Direction dir, const void *X, i
   }
   const bool z16 = split_uses_z16(plan, hp, X, ldx, dt_in, Y, ldy, dt_out, n);
   const int64_t slab_cap = z16 ? slab_rows_cap_z16(d) : slab_rows_cap(d);
-  const int64_t slab = slab_rows(plan, hp, dt_in == HARP_F32 || dt_out == HARP_F32, z16, n, slab_cap);
+  const int64_t slab = slab_rows(plan, hp, X, ldx, Y, ldy, dt_in == HARP_F32 || dt_out == HARP_F32, z16, n, slab_cap);
   const size_t row_bytes = z16 ? (size_t)z16_ld(d) * 2 : (size_t)d * 4;
   // one buffer per stream serves both forms: its full size is the larger of the two slabs
   const size_t cap = std::max((size_t)slab_rows_cap(d) * d * 4,

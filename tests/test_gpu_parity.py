@@ -873,10 +873,11 @@ def test_default_stream_beside_a_capture(harp, n):
 
 # Calls of more rows than a slab holds, on both sides of each line of the rule that cuts them (full slabs and a rest, or
 # slabs of one size): a chain that equal slabs would cost rounds of tiles and one that they save some, halves with one streamed stage and
-# with three, a large radix first, plain float32 rows.
+# with three, a large radix first, plain float32 rows, chunks on the tile kernels.
 @pytest.mark.parametrize("d,radices,dtype", [(28672, [8, 8, 8, 8, 7], "bf16"), (14336, [8, 8, 8, 7, 4], "f32"),
                                              (28672, [2] * 12 + [7], "bf16"), (13824, [2] * 9 + [3, 3, 3], "bf16"),
-                                             (11008, [2] * 8 + [43], "f32"), (11008, [8, 8, 4, 43], "bf16")])
+                                             (11008, [2] * 8 + [43], "f32"), (11008, [8, 8, 4, 43], "bf16"),
+                                             (9375, [5] * 5 + [3], "f32")])
 def test_results_do_not_depend_on_how_rows_are_cut(harp, d, radices, dtype):
     import torch
     full = (128 << 20) // (4 * d) // 256 * 256
