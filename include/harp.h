@@ -120,13 +120,13 @@ harp_status_t harp_plan_destroy(harp_plan_t *plan);
  * radix-2 stages followed by one radix-3 stage, run in two or more launches through a
  * float32 intermediate of at most 128 MB.  It is allocated (hipMalloc) the first time a stream sees
  * a call that needs it, so that call may block: up to 8 MB by the plan, which keeps it until
- * harp_plan_destroy; larger ones are shared by all plans of the device on that stream (eight
- * streams; beyond them each plan has its own) until the last plan is destroyed.  Captured calls use
- * another buffer, one per plan and stream, kept until harp_plan_destroy: a graph may be replayed on any
- * stream beside the plan's eager calls, but graphs captured from one plan on one stream must not run at
- * the same time as each other.  If the plan has not run on the stream before with as many rows, a captured
- * call returns HARP_ERR_UNSUPPORTED (run the plan once on the stream before capturing).  HARP_ERR_OOM
- * if the memory cannot be had.
+ * harp_plan_destroy; larger ones are shared by all plans of the device on that stream, whose calls take
+ * turns in up to three (eight streams; beyond them each plan has its own), until the last plan is
+ * destroyed.  Captured calls use another buffer, one per plan and stream, kept until harp_plan_destroy:
+ * a graph may be replayed on any stream beside the plan's eager calls, but graphs captured from one plan
+ * on one stream must not run at the same time as each other.  If the plan has not run on the stream
+ * before with as many rows, a captured call returns HARP_ERR_UNSUPPORTED (run the plan once on the
+ * stream before capturing).  HARP_ERR_OOM if the memory cannot be had.
  * Arithmetic is float32 with one rounding at a bf16 store, with one exception: when dt is
  * HARP_BF16, a stage of radix 9..64 of such a plan runs on the matrix cores with every float32
  * operand split into two bf16 terms (x_hi K_hi + x_lo K_hi + x_hi K_lo accumulated in float32,

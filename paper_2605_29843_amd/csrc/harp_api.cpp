@@ -724,26 +724,31 @@ int64_t slab_rows(const harp_plan_t *plan, const HostProgram &hp, const void *X,
   return large || (float32 && chain && slabs > 2) ? even : cap;
 }
 
-// Intermediates of split programs from 8 MB on, which plans share: one buffer per device and stream.  Work on one stream
+// Intermediates of split programs from 8 MB on, which plans share, by device and stream.  Work on one stream
 // is ordered, so the calls that are queued on it can use the same memory one after the other; `mu` is held while a
 // call's launches are queued, so that two host threads cannot interleave theirs.  With a buffer of its own
 // each, the plans of a model (one per layer) held up to 128 MB each and evicted each other's from the 256 MB
 // memory-side cache.  Three plans in turn, bf16, us a call: 2048 x 11008 radix 2 75 -> 60, 4096 x 28672 transposed 211 -> 198,
-// 3000 x 8192 radix 8 72 -> 64.  Calls take turns in three places where these fit: rewriting at once what the
+// 3000 x 8192 radix 8 72 -> 64.  Calls take turns in as many places of up to three as make 128 MB: rewriting at once what the
 // last call's kernels have just read costs more than it saves (one place, 1001 x 5120 float32: 19.9 -> 20.9 us).
+// Each place is an allocation of its own, as large as its first call: three side by side in one allocation were slower, for no
+// reason seen in the addresses (438 x 14336 bf16 radix 2 transposed 19.3 against 20.1 us in a process of its own; after other plans have come
+// and gone 640 x 8192 bf16 radix 8 20.2 against 24.6, 972 x 5120 float32 19.7 against 20.8).
 // Below 8 MB nothing is gained.
-// Bounded (eight streams a device; further ones get buffers of the plan's own) and given back when the device's
-// last plan is destroyed.
+// Bounded (128, 64 and 43 MB a stream, and what these have outgrown; eight streams a device, further ones get buffers of the
+// plan's own) and given back when the device's last plan is destroyed.
+constexpr unsigned kSharedTurns = 3;
 struct SharedScratch {
   int device = -1;
   hipStream_t stream = nullptr;
   std::mutex mu;
-  float *ptr = nullptr;
-  size_t bytes = 0;
+  struct Place {
+    float *ptr = nullptr;
+    size_t bytes = 0;
+    void *outgrown = nullptr;   // launches already queued may still use it
+  } place[kSharedTurns];
   unsigned turn = 0;
-  void *outgrown = nullptr;   // launches already queued may still use it
 };
-constexpr unsigned kSharedTurns = 3;
 constexpr size_t kOwnScratch = (size_t)8 << 20;     // least size of a plan's own buffer; larger intermediates are shared
 constexpr size_t kSharedMost = (size_t)128 << 20;   // at least every plan's cap
 constexpr int kSharedStreams = 8;
@@ -763,10 +768,11 @@ harp_status_t shared_plan_destroyed(int dev) {
   harp_status_t st = HARP_OK;
   if (--g_plans[dev] > 0) return st;
   for (auto &s : g_shared)
-    if (s->device == dev) {
-      if (s->ptr && hipFree(s->ptr) != hipSuccess) st = HARP_ERR_DEVICE;
-      if (s->outgrown && hipFree(s->outgrown) != hipSuccess) st = HARP_ERR_DEVICE;
-    }
+    if (s->device == dev)
+      for (auto &pl : s->place) {
+        if (pl.ptr && hipFree(pl.ptr) != hipSuccess) st = HARP_ERR_DEVICE;
+        if (pl.outgrown && hipFree(pl.outgrown) != hipSuccess) st = HARP_ERR_DEVICE;
+      }
   g_shared.erase(std::remove_if(g_shared.begin(), g_shared.end(),
                                 [&](const std::unique_ptr<SharedScratch> &s) { return s->device == dev; }),
                  g_shared.end());
@@ -820,8 +826,8 @@ void scratch_not_needed(const harp_plan_t *plan, hipStream_t stream, size_t most
 // The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= most, the call's rows or one
 // full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.
 // Small ones lie in a buffer of the plan's own (8 MB), larger ones
-// in the stream's shared one: its first use allocates room for three such calls, one that needs more then the most that
-// any plan does.  Nothing is freed and the stream is never waited for.
+// in a place that the stream's calls share: its first use allocates what the call needs, one that needs more then the most that
+// comes there.  Nothing is freed and the stream is never waited for.
 // Captured calls have a buffer of their own, kept until the plan is destroyed: a graph holds its address and
 // may be replayed on another stream while the plan runs on this one.  (All of a stream's captured calls use that one:
 // a program that captures again and again must not collect buffers.)  It is allocated inside the capture (this thread's
@@ -884,21 +890,23 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     }
   }
   hold = std::unique_lock<std::mutex>(shared->mu);
-  const size_t place = (bytes + 4095) / 4096 * 4096;
-  if (shared->bytes < bytes) {
+  const unsigned turns = (unsigned)std::max<size_t>(1, std::min<size_t>(kSharedTurns, kSharedMost / bytes));
+  const unsigned turn = (shared->turn + 1) % turns;
+  SharedScratch::Place &pl = shared->place[turn];
+  if (pl.bytes < bytes) {
     if (beside) return HARP_ERR_DEVICE;
-    const size_t want = std::max(bytes, shared->ptr ? kSharedMost : std::min(kSharedMost, kSharedTurns * place));
+    const size_t want = std::max(bytes, pl.ptr ? kSharedMost / (turn + 1) : (size_t)0);
     float *p = nullptr;
     if (hipMalloc((void **)&p, want) != hipSuccess) {
       (void)hipGetLastError();
       return HARP_ERR_OOM;
     }
-    shared->outgrown = shared->ptr;   // (at most once: want is then the most there is)
-    shared->ptr = p;
-    shared->bytes = want;
+    pl.outgrown = pl.ptr;   // (at most once: want is then the most that comes here)
+    pl.ptr = p;
+    pl.bytes = want;
   }
-  shared->turn = (shared->turn + 1) % (unsigned)std::max<size_t>(1, std::min<size_t>(kSharedTurns, shared->bytes / place));
-  *out = shared->ptr + shared->turn * (place / sizeof(float));
+  shared->turn = turn;
+  *out = pl.ptr;
   return HARP_OK;
 }
 
