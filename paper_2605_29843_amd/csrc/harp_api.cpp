@@ -731,7 +731,7 @@ int64_t slab_rows(const harp_plan_t *plan, const HostProgram &hp, const void *X,
 // memory-side cache.  Three plans in turn, bf16, us a call: 2048 x 11008 radix 2 75 -> 60, 4096 x 28672 transposed 211 -> 198,
 // 3000 x 8192 radix 8 72 -> 64.  Calls take turns in as many places of up to three as make 128 MB: rewriting at once what the
 // last call's kernels have just read costs more than it saves (one place, 1001 x 5120 float32: 19.9 -> 20.9 us).
-// Each place is an allocation of its own, as large as its first call: three side by side in one allocation were slower, for no
+// Each place is an allocation of its own: three side by side in one allocation were slower, for no
 // reason seen in the addresses (438 x 14336 bf16 radix 2 transposed 19.3 against 20.1 us in a process of its own; after other plans have come
 // and gone 640 x 8192 bf16 radix 8 20.2 against 24.6, 972 x 5120 float32 19.7 against 20.8).
 // Below 8 MB nothing is gained.
@@ -804,7 +804,7 @@ SharedScratch *shared_entry(int dev, hipStream_t stream) {
 harp_plan::Scratch *scratch_seen(const harp_plan_t *plan, hipStream_t stream, harp_plan::Scratch *slot, size_t most, size_t cap) {
   const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
   if (!slot) {
-    plan->scratch.push_back(harp_plan::Scratch{stream, {}, {}, 0});
+    plan->scratch.push_back(harp_plan::Scratch{stream, {}, {}, 0, 0});
     slot = &plan->scratch.back();
   }
   slot->seen = seen;
@@ -826,8 +826,10 @@ void scratch_not_needed(const harp_plan_t *plan, hipStream_t stream, size_t most
 // The float32 intermediate for a call of `plan` on `stream`, at least `bytes` long (bytes <= most, the call's rows or one
 // full slab where they are more, <= cap, one full slab of either form); `hold` is kept until the call's launches are queued.
 // Small ones lie in a buffer of the plan's own (8 MB), larger ones
-// in a place that the stream's calls share: its first use allocates what the call needs, one that needs more then the most that
-// comes there.  Nothing is freed and the stream is never waited for.
+// in a place that the stream's calls share.  A plan's first call of so many rows allocates the places that it will take turns in, with
+// room in the first for any call of as many rows; a place that is too small is replaced by one for the most that comes there.  Later
+// calls of as many rows or fewer make do with the places there are, so a plan that has been warmed up neither waits for an
+// allocation nor makes one beside another thread's capture.  Nothing is freed and the stream is never waited for.
 // Captured calls have a buffer of their own, kept until the plan is destroyed: a graph holds its address and
 // may be replayed on another stream while the plan runs on this one.  (All of a stream's captured calls use that one:
 // a program that captures again and again must not collect buffers.)  It is allocated inside the capture (this thread's
@@ -843,6 +845,7 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
                            std::unique_lock<std::mutex> &hold, float **out) {
   SharedScratch *shared = nullptr;
   bool beside = false;
+  size_t fresh = 0;   // what a plan's first call of so many rows is to find room for
   {
     std::lock_guard<std::mutex> lock(plan->scratch_mu);
     harp_plan::Scratch *slot = nullptr;
@@ -866,6 +869,7 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
       slot = scratch_seen(plan, stream, slot, most, cap);
     }
     if (bytes > kOwnScratch && !capturing && stream != hipStreamPerThread) shared = shared_entry(plan->device, stream);
+    if (shared && !beside && slot->room < most) fresh = slot->room = slot->seen;
     if (!shared) {
       harp_plan::Buffer &own = capturing ? slot->captured : slot->eager;
       if (own.bytes < bytes) {
@@ -891,22 +895,34 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
   }
   hold = std::unique_lock<std::mutex>(shared->mu);
   const unsigned turns = (unsigned)std::max<size_t>(1, std::min<size_t>(kSharedTurns, kSharedMost / bytes));
-  const unsigned turn = (shared->turn + 1) % turns;
-  SharedScratch::Place &pl = shared->place[turn];
-  if (pl.bytes < bytes) {
-    if (beside) return HARP_ERR_DEVICE;
-    const size_t want = std::max(bytes, pl.ptr ? kSharedMost / (turn + 1) : (size_t)0);
+  auto grow = [&](unsigned k, size_t need) {
+    SharedScratch::Place &pl = shared->place[k];
+    if (pl.bytes >= need) return true;
+    const size_t want = std::max(need, pl.ptr ? kSharedMost / (k + 1) : (size_t)0);
     float *p = nullptr;
     if (hipMalloc((void **)&p, want) != hipSuccess) {
       (void)hipGetLastError();
-      return HARP_ERR_OOM;
+      return false;
     }
     pl.outgrown = pl.ptr;   // (at most once: want is then the most that comes here)
     pl.ptr = p;
     pl.bytes = want;
+    return true;
+  };
+  if (fresh > 0) {
+    grow(0, fresh);
+    for (unsigned k = 1; k < turns; ++k) grow(k, bytes);
+  }
+  unsigned turn = turns;
+  for (unsigned i = 1; i <= turns && turn == turns; ++i)
+    if (shared->place[(shared->turn + i) % turns].bytes >= bytes) turn = (shared->turn + i) % turns;
+  if (turn == turns) {   // no place yet (or no memory for more than this call)
+    if (beside) return HARP_ERR_DEVICE;
+    turn = 0;
+    if (!grow(turn, bytes)) return HARP_ERR_OOM;
   }
   shared->turn = turn;
-  *out = pl.ptr;
+  *out = shared->place[turn].ptr;
   return HARP_OK;
 }
 

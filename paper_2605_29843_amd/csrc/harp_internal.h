@@ -245,7 +245,7 @@ struct harp_plan {
   int num_cu = 0;
   bool counted = false;   // among its device's plans, which keep the shared buffers
   // Per stream the plan has run on in two launches or more: a buffer for small intermediates, one for captured calls, and
-  // the size up to which a captured call may ask for it.  Nothing is freed
+  // the sizes up to which a captured call may ask for it (`seen`) and up to which the shared buffers were asked for (`room`).  Nothing is freed
   // before the plan is destroyed: a buffer that a later, larger call outgrows moves to
   // `retired`, because launches already queued and HIP graphs captured earlier still hold
   // its address.
@@ -256,7 +256,7 @@ struct harp_plan {
   struct Scratch {
     hipStream_t stream;
     Buffer eager, captured;
-    size_t seen;
+    size_t seen, room;
   };
   mutable std::mutex scratch_mu;
   mutable std::vector<Scratch> scratch;

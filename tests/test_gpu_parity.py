@@ -1002,6 +1002,47 @@ print("given back", flush=True)
     assert done.returncode == 0 and "given back" in done.stdout, done.stdout + done.stderr
 
 
+def test_only_the_first_call_of_its_size_allocates():
+    """In a process of its own: a plan's first call on a stream takes all the memory that calls of as many rows or fewer
+    (down to 8 MB of intermediate) will need, so that a plan that has been warmed up never waits for an allocation, and
+    never makes one beside another thread's capture."""
+    import os
+    import subprocess
+    child = """
+import numpy as np, torch
+from paper_2605_29843_amd import harp, inputs as gi
+d, radices = 14336, [2] * 11 + [7]
+full = (128 << 20) // (4 * d) // 256 * 256   # rows of one float32 slab
+rng = np.random.default_rng(1)
+X = torch.randn(full + 1000, d, device="cuda")
+Y = torch.zeros_like(X)
+blocks, signs = gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng)
+def call(p, rows):
+    harp.harp_apply(p, X[:rows], Y[:rows])
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+warm = harp.Plan(d, radices, blocks, signs)
+call(warm, 40)
+warm.destroy()
+for first, then in [((300,), (300, 300, 300, 200, 200, 200)), ((full + 40,), (full, full, 900, 900, 300, 300, 300)),
+                    ((200, 400), (700, 1000, full, 300, 300, 300))]:
+    one, two = (harp.Plan(d, radices, blocks, signs) for _ in range(2))
+    for rows in first:
+        held = call(one, rows)
+    for rows in then:
+        assert call(one, rows) == held, (first, rows)
+    held = call(two, 500)
+    for rows in (500, 500, 400, 400, 250, 250, 250):
+        assert call(two, rows) == held, (first, "another plan", rows)
+    one.destroy(), two.destroy()
+print("no more than that", flush=True)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    say("only first calls allocate")
+    done = subprocess.run([sys.executable, "-u", "-c", child], cwd=root, capture_output=True, text=True, timeout=100)
+    assert done.returncode == 0 and "no more than that" in done.stdout, done.stdout + done.stderr
+
+
 def test_one_plan_on_two_streams_and_two_host_threads(harp):
     """A plan is immutable after create: two host threads drive it on two streams at the same
     time (a split program, whose float32 intermediate is kept per stream) and both reproduce the
