@@ -800,6 +800,23 @@ SharedScratch *shared_entry(int dev, hipStream_t stream) {
   return g_shared.back().get();
 }
 
+// Memory for an intermediate, or null.  In the thread's relaxed capture mode: inside a capture it may be had, and beside
+// another thread's the request would end that capture and fail (a plan that has run with many rows takes its own small
+// buffer at its first call of few, so a program that has warmed up may still come here).
+float *scratch_alloc(size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  float *p = nullptr;
+  bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (ok) {
+    ok = hipMalloc((void **)&p, bytes) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  } else {
+    (void)hipGetLastError();
+  }
+  return ok ? p : nullptr;
+}
+
 // The plan runs `most` bytes of rows on `stream`, outside a capture (scratch_mu is held; slot: the stream's, if it has one).
 harp_plan::Scratch *scratch_seen(const harp_plan_t *plan, hipStream_t stream, harp_plan::Scratch *slot, size_t most, size_t cap) {
   const size_t seen = std::max(most, slot ? cap : std::min(cap, kOwnScratch));
@@ -828,13 +845,12 @@ void scratch_not_needed(const harp_plan_t *plan, hipStream_t stream, size_t most
 // Small ones lie in a buffer of the plan's own (8 MB), larger ones
 // in a place that the stream's calls share.  A plan's first call of so many rows allocates the places that it will take turns in, with
 // room in the first for any call of as many rows; a place that is too small is replaced by one for the most that comes there.  Later
-// calls of as many rows or fewer make do with the places there are, so a plan that has been warmed up neither waits for an
-// allocation nor makes one beside another thread's capture.  Nothing is freed and the stream is never waited for.
+// calls of as many rows or fewer make do with the places there are, so a plan that has been warmed up does not wait for an
+// allocation.  Nothing is freed and the stream is never waited for.
 // Captured calls have a buffer of their own, kept until the plan is destroyed: a graph holds its address and
 // may be replayed on another stream while the plan runs on this one.  (All of a stream's captured calls use that one:
-// a program that captures again and again must not collect buffers.)  It is allocated inside the capture (this thread's
-// capture mode is relaxed meanwhile), and only if the plan has run on the stream before with as large a batch: `seen`
-// notes, per stream, the largest `most` (slabs of one size take less than that: a call of a slab and a little more, two
+// a program that captures again and again must not collect buffers.)  It is allocated inside the capture, and only if
+// the plan has run on the stream before with as large a batch: `seen` notes, per stream, the largest `most` (slabs of one size take less than that: a call of a slab and a little more, two
 // of about half).  Eager calls of any size have a buffer of the plan's own on streams without a shared one: each
 // thread's own default stream, which goes by one handle in all threads, and streams beyond the first eight.
 // The default stream cannot be captured, so a small call there does not ask (on another stream, 14336 radix 2, one row, bound by
@@ -875,16 +891,8 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
       if (own.bytes < bytes) {
         if (beside) return HARP_ERR_DEVICE;
         const size_t want = bytes > kOwnScratch ? slot->seen : std::max(bytes, std::min(cap, kOwnScratch));
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
-          (void)hipGetLastError();
-          return HARP_ERR_UNSUPPORTED;
-        }
-        float *p = nullptr;
-        const bool ok = hipMalloc((void **)&p, want) == hipSuccess;
-        if (!ok) (void)hipGetLastError();
-        if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (!ok) return HARP_ERR_OOM;
+        float *p = scratch_alloc(want);
+        if (!p) return HARP_ERR_OOM;
         if (own.ptr) plan->retired.push_back(own.ptr);   // queued launches and graphs still hold its address
         own.ptr = p;
         own.bytes = want;
@@ -899,11 +907,8 @@ harp_status_t plan_scratch(const harp_plan_t *plan, hipStream_t stream, size_t b
     SharedScratch::Place &pl = shared->place[k];
     if (pl.bytes >= need) return true;
     const size_t want = std::max(need, pl.ptr ? kSharedMost / (k + 1) : (size_t)0);
-    float *p = nullptr;
-    if (hipMalloc((void **)&p, want) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
+    float *p = scratch_alloc(want);
+    if (!p) return false;
     pl.outgrown = pl.ptr;   // (at most once: want is then the most that comes here)
     pl.ptr = p;
     pl.bytes = want;

@@ -871,6 +871,49 @@ def test_default_stream_beside_a_capture(harp, n):
     plan.destroy()
 
 
+def test_few_rows_after_many_beside_another_threads_capture(harp):
+    """A plan that has run with many rows, whose intermediate is shared, takes its own buffer at the first call of few: that call
+    is accepted while another thread captures a stream, and the capture goes on."""
+    import threading
+    import torch
+    d, radices, n = 14336, [2] * 11 + [7], 600
+    rng = np.random.default_rng(77)
+    plan = harp.Plan(d, radices, gi.make_blocks(d, radices, "orth", rng), gi.make_signs(d, rng))
+    X = torch.randn(n, d, device="cuda")
+    ref = harp.harp_apply(plan, X)
+    Y, A, B = torch.zeros_like(X), torch.ones(1000, device="cuda"), torch.zeros(1000, device="cuda")
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    harp.harp_apply(plan, X, Y, side)
+    torch.cuda.synchronize()
+    Y.zero_()
+    torch.cuda.synchronize()
+    say("few rows beside a capture", n)
+    failed = []
+
+    def few():
+        try:
+            harp.harp_apply(plan, X[:24], Y[:24], side)
+        except Exception as e:   # noqa: BLE001
+            failed.append(e)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=other):   # (captures in the global mode)
+        torch.add(A, 2.0, out=B)
+        t = threading.Thread(target=few)
+        t.start()
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    assert torch.equal(Y[:24], ref[:24]) and bool((Y[24:] == 0).all())
+    for _ in range(3):
+        B.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((B == 3.0).all())
+    plan.destroy()
+
+
 # Calls of more rows than a slab holds, on both sides of each line of the rule that cuts them (full slabs and a rest, or
 # slabs of one size): a chain that equal slabs would cost rounds of tiles and one that they save some, halves with one streamed stage and
 # with three, a large radix first, plain float32 rows, chunks on the tile kernels.
@@ -1004,8 +1047,7 @@ print("given back", flush=True)
 
 def test_only_the_first_call_of_its_size_allocates():
     """In a process of its own: a plan's first call on a stream takes all the memory that calls of as many rows or fewer
-    (down to 8 MB of intermediate) will need, so that a plan that has been warmed up never waits for an allocation, and
-    never makes one beside another thread's capture."""
+    (down to 8 MB of intermediate) will need, so that a plan that has been warmed up does not wait for an allocation."""
     import os
     import subprocess
     child = """
