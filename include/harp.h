@@ -118,10 +118,10 @@ harp_status_t harp_plan_destroy(harp_plan_t *plan);
  * follows stages of radix <= 8 with a product that is a multiple of 16 and at least 64 (a
  * leftover prime at the end of the schedule), and -- for forward calls with n >= 512 -- plans of
  * radix-2 stages followed by one radix-3 stage, run in two or more launches through a
- * float32 intermediate of at most 128 MB.  It is allocated (hipMalloc) by a plan's first call on a stream
- * that needs it for so many rows, so that call may block: up to 8 MB by the plan (few rows after many: their first call, too),
- * which keeps it until
- * harp_plan_destroy; larger ones are shared by all plans of the device on that stream, whose calls take
+ * float32 intermediate of at most 128 MB.  It is allocated (hipMalloc) by a plan's first call on a
+ * stream that needs it for so many rows, so that call may block: up to 8 MB by the plan, which keeps it
+ * until harp_plan_destroy (the first call of few rows after many allocates it, too); larger ones are
+ * shared by all plans of the device on that stream, whose calls take
  * turns in up to three (eight streams; beyond them each plan has its own), until the last plan is
  * destroyed.  Captured calls use another buffer, one per plan and stream, kept until harp_plan_destroy:
  * a graph may be replayed on any stream beside the plan's eager calls, but graphs captured from one plan
