@@ -1,6 +1,6 @@
 """CPU float64 oracle for the HARP structured-rotation path.  TEST INFRASTRUCTURE ONLY.
 
-This module is the checker, not the product: only ``tests/``, the smoke entry and
+This module is the oracle, not the product: only ``tests/``, the smoke entry and
 the ``cpu_baseline`` leg of the benchmark may import it.  It shares no code with
 the HIP library and never imports it.
 
